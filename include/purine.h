@@ -101,8 +101,10 @@ int purine_conv_out_shape(const purine_conv_desc* desc, const int64_t x_dim[4],
 
 /* Bytes of device scratch the given pass needs (0 when none). Returns 0 for illegal shapes: the
  * operator call itself reports the error. Forward and backward-data keep a repacked, zero-padded
- * copy of the filter there (none for a forward pass with fewer than 16 input channels);
- * backward-weight keeps its split-reduction partial sums there. */
+ * copy of the filter there (none for a forward pass with fewer than 16 input channels), F32 layers
+ * with several taps also a copy of the gathered tensor (6 bytes per element, channels rounded up to
+ * a multiple of 16) and the partial outputs of a split reduction; backward-weight keeps its
+ * split-reduction partial sums there. */
 size_t purine_conv_workspace_bytes(int pass, const purine_conv_desc* desc, const int64_t x_dim[4],
                                    const int64_t w_dim[4], int32_t dtype);
 size_t purine_bias_bwd_workspace_bytes(const int64_t dy_dim[4], int32_t dtype);
@@ -433,7 +435,8 @@ void purine_set_kernel_probe(void* start_event, void* stop_event);
 /* Tuning hook (host only, process-wide, not thread safe): forces the (rows, pixels) tile of the
  * forward / backward-data kernels to one of 128x128, 96x256, 96x128, 64x256, 128x64, 64x128, 32x256,
  * 64x64, 32x128; any other pair (e.g. 0, 0) restores the automatic choice. Results are bit-identical
- * for every shape: the reduction order per output element does not depend on it.
+ * for every shape: the reduction order per output element does not depend on it. (The automatic
+ * choice may be another kernel, whose sums are ordered differently: F32 layers with several taps.)
  * (48|16, 256|128) does the same for the 16-row-granular tiles of GEMMs with at most 16 or 33..48
  * rows, (192, 128) selects an uncalibrated tile.
  * For 1x1 / stride-1 / unpadded layers, which run the streaming GEMM kernel instead: (32|64|96, 2),

@@ -61,6 +61,16 @@ struct ConvGeom {
     int x_ns, y_ns;
 };
 
+// Part of the plan below: the fp32 kernel on packed bf16 parts (conv_packets.hip).
+struct PacketPlan {
+    bool use;
+    int bm, bn, tiles_i, tiles_pix;
+    int steps, splits, steps_per_split;    // reduction steps (16 channels of one tap each), split over workgroups
+    int Cb;                                // packed channel groups of 8 per image
+    size_t a_bytes, b_offset, b_bytes, part_offset, ws_bytes;   // scratch: filter, activations, partial outputs
+    double us;                             // expected time
+};
+
 // Launch plan of the forward / backward-data implicit GEMM: same answer for the workspace query and
 // for the launch.
 struct PixPlan {
@@ -81,6 +91,7 @@ struct PixPlan {
     // fully-connected backward-data shape: few rows, few pixels, a long reduction)
     int gemm_splits, gemm_split_ci;
     size_t gemm_part_offset;   // byte offset of the fp32 partial tiles inside the scratch
+    PacketPlan pk;
 };
 PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, bool accumulate = false);
 void force_pix_tile(int bm, int bn);

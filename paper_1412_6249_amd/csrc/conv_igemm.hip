@@ -723,6 +723,19 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
         pl.blk_offset = (pl.ws_bytes + 255) / 256 * 256;
         pl.ws_bytes = pl.blk_offset + gathered * elem;
     }
+    if (dtype == PURINE_F32 && !pl.flat && g_force_bm == 0 && g_no_buffer_loads == 0) {
+        // fp32 layers with several taps: the kernel on packed bf16 parts (conv_packets.hip), where it is
+        // expected to be faster than this file's. Those run at about 0.78 of the fp32 MFMA rate on a
+        // full chip, plus the filter repack; the packed kernel at 1.6 - 1.8 times that once its operands
+        // are laid out (layers of 38 - 115 GFLOP: 0.35 -> 0.20, 0.52 -> 0.31, 1.00 -> 0.60 ms; 2 images at
+        // 13x13, 384 -> 384: 140 -> 29 us). It loses where the layout pass is most of the work: 16 or
+        // fewer rows (5x5, 32 -> 16 at 28x28: 53.5 against 55 us), the strided first layers' depth-to-space
+        // output (11x11 / 4, 3 channels: 349 against 384 us), launches of a few microseconds.
+        const double old_us = best * 2.0 * Ci * pl.Rt * pl.St / (157.3e6 / 256.0 * 0.78) + 6.0;
+        pl.pk = plan_packets(make_pix_params(dtype, g, pl), pl.mode == 2);
+        pl.pk.use = pl.pk.use && Co > 16 && pl.pk.us * 1.05 < old_us;
+        if (pl.pk.use) { if (pl.pk.ws_bytes > pl.ws_bytes) pl.ws_bytes = pl.pk.ws_bytes; return pl; }
+    }
     // identity gather: the streaming GEMM applies
     const long long HW = (long long)g.H * g.W;
     const bool forced = (g_force_bn == 1 || g_force_bn == 2 || g_force_bn == 4) && g_force_bm >= 32 &&
@@ -787,6 +800,7 @@ hipError_t launch_conv_pix(int dtype, const ConvGeom& g, const PixPlan& pl, cons
     p.bias = epi.bias; p.relu = epi.relu; p.mask = epi.mask;
     p.beta = beta;
 
+    if (pl.pk.use) return launch_packets(p, pl.pk, pl.mode, wt, g.K, g.C, ws, st);
     if (pl.gemm1x1) {
         const uintptr_t align = (uintptr_t)pl.gemm_tn * (dtype == PURINE_BF16 ? 2 : 4) - 1;
         if ((((uintptr_t)in | (uintptr_t)out | (uintptr_t)epi.mask) & align) == 0) {

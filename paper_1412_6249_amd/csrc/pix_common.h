@@ -615,5 +615,10 @@ hipError_t dispatch_flat_bf16(PixParams& p, int bm, int bn, hipStream_t st);
 // streaming GEMM for 1x1 / stride 1 / unpadded layers (conv_gemm1x1.hip); p.wt is the KCRS filter
 hipError_t dispatch_gemm1x1(const PixParams& p, int dtype, bool trans, int tm, int tn, hipStream_t st);
 
+// fp32 layers on packed bf16 parts (conv_packets.hip). mode: 0 forward, 1 backward-data with unit
+// stride, 2 backward-data phase-folded; w: the KCRS filter.
+PacketPlan plan_packets(const PixParams& p, bool d2s);
+hipError_t launch_packets(PixParams p, const PacketPlan& k, int mode, const void* w, int K, int C, void* ws, hipStream_t st);
+
 }  // namespace pix
 }  // namespace purine

@@ -1,0 +1,117 @@
+"""The fp32 convolutions that run on packed bf16 parts (three per operand, six products): at the edges
+of their tiles, reduction steps and splits, in every form the operators have, against the oracle and
+against the general fp32 kernels (reached by switching raw buffer loads off, which the packed kernels
+need). The split must not cost precision: its error against fp64 may not exceed the general kernels'."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+# N, C, H, W, K, R, S, stride, pad. What is at an edge: one row past a 16- / 32- / 128-row tile, channel
+# counts on either side of a 16-channel step, pixel counts on either side of a tile, a long reduction
+# over few pixels (split over workgroups), unequal filter and image sides, strides (phase-folded
+# backward-data) and filters that fit inside one stride step
+CASES = [(8, 64, 28, 28, 33, 3, 3, 1, 1), (4, 33, 9, 11, 45, 3, 3, 1, 1), (3, 17, 16, 8, 129, 2, 3, 1, (1, 0)),
+         (1, 256, 6, 6, 40, 3, 3, 1, 1), (1, 130, 5, 23, 64, 1, 5, 1, (0, 2)), (2, 31, 13, 15, 24, 3, 3, 2, 1),
+         (2, 24, 14, 11, 33, 5, 4, (3, 2), (2, 1)), (5, 96, 13, 13, 97, 3, 3, 1, 1), (2, 64, 32, 32, 64, 3, 3, 1, 1)]
+
+
+def _general(pa, on):
+    pa.purine_debug_force_tile(0, -1 if on else 0)
+
+
+def _run(pa, case, x, w, b, dy, act, prev):
+    """y (bias + ReLU), y (plain), dx, dx accumulated onto prev, dx through the mask; and the scratch sizes."""
+    import torch
+    from gpu_util import to_dev, workspace, to_host, DEV
+    desc = pa.conv_desc(case[7], case[8])
+    need = [pa.purine_conv_workspace_bytes(k, desc, x.shape, w.shape, pa.PURINE_F32) for k in (0, 1)]
+    wf, wd = (workspace(n) for n in need)
+    tx, tw, tb, tdy, tact = (to_dev(a) for a in (x, w, b, dy, act))
+    y, yp = (torch.full(dy.shape, float("nan"), device=DEV) for _ in range(2))
+    dx, dm = (torch.full(x.shape, float("nan"), device=DEV) for _ in range(2))
+    da = to_dev(prev)
+    pa.purine_conv_fwd_bias_relu(desc, tx, tw, tb, y, relu=True, ws=wf)
+    pa.purine_conv_fwd(desc, tx, tw, yp, ws=wf)
+    pa.purine_conv_bwd_data(desc, tdy, tw, dx, ws=wd)
+    pa.purine_conv_bwd_data(desc, tdy, tw, da, beta=1.0, ws=wd)
+    pa.purine_conv_bwd_data_relu(desc, tdy, tw, tact, dm, ws=wd)
+    torch.cuda.synchronize()
+    return [to_host(t) for t in (y, yp, dx, da, dm)], need
+
+
+def _inputs(case, seed=5):
+    N, C, H, W, K, R, S, stride, pad = case
+    rs = np.random.default_rng(seed)
+    f = lambda *s: rs.standard_normal(s).astype(np.float32)
+    P, Q = oracle.out_shape((N, C, H, W), (K, C, R, S), stride, pad)[2:]
+    return f(N, C, H, W), f(K, C, R, S), f(K), f(N, K, P, Q), f(N, C, H, W), f(N, C, H, W)
+
+
+@pytest.mark.parametrize("case", CASES, ids=str)
+def test_packed_parts_against_the_oracle_and_the_general_kernels(case):
+    import paper_1412_6249_amd as pa
+    from gpu_util import rel_l2
+    x, w, b, dy, act, prev = _inputs(case)
+    stride, pad = case[7], case[8]
+    got, _ = _run(pa, case, x, w, b, dy, act, prev)
+    _general(pa, True)
+    try:
+        base, _ = _run(pa, case, x, w, b, dy, act, prev)
+    finally:
+        _general(pa, False)
+    assert any(not np.array_equal(g, o) for g, o in zip(got, base))     # at least one pass took the packed kernels
+    y = oracle.conv_fwd(x, w, stride, pad)
+    dx = oracle.conv_bwd_data(dy, w, x.shape, stride, pad)
+    refs = (np.maximum(oracle.bias_fwd(y, b), 0), y, dx, dx + prev, np.where(act > 0, dx, 0.0))
+    for name, g, o, r in zip(("y fused", "y", "dx", "dx accumulated", "dx masked"), got, base, refs):
+        # both round the result once (0.3 * 2^-24 on average); beyond that the split's sums may be no
+        # further off than the fp32 MFMA's
+        assert rel_l2(g, r) <= max(rel_l2(o, r), 1.0e-7), (name, rel_l2(g, r), rel_l2(o, r))
+        assert rel_l2(g, r) <= 1e-5, name
+
+
+def test_infinities_nans_and_values_at_the_ends_of_the_range():
+    """An infinity times the zero low parts of the other operand is a NaN in the split products, and a
+    value above the largest bf16 has no rounded high part: outputs that come out infinite or NaN are
+    computed again the way the fp32 kernel would. Same infinities, same NaNs as the general kernel."""
+    import paper_1412_6249_amd as pa
+    from gpu_util import rel_l2
+    case = (2, 40, 12, 12, 48, 3, 3, 1, 1)
+    x, w, b, dy, act, prev = _inputs(case)
+    big = np.float32(3.4028234e38)
+    x[0, 3, 2, 2], x[0, 5, 9, 9], x[1, 0, 0, 0], x[1, 7, 6, 6] = np.inf, np.nan, -np.inf, big
+    dy[0, 1, 3, 3], dy[1, 2, 8, 8], dy[1, 40, 1, 10] = -np.inf, np.nan, big
+    w *= np.float32(0.1)                        # so that no finite partial sum overflows, whatever the order
+    w[4, 4, 0, 0] = np.inf
+    x[0, :, 5, 5] *= np.float32(1e-30)          # and small ones: exact down to the parts' smallest subnormal
+    got, need = _run(pa, case, x, w, b, dy, act, prev)
+    _general(pa, True)
+    try:
+        base, need0 = _run(pa, case, x, w, b, dy, act, prev)
+    finally:
+        _general(pa, False)
+    assert need[0] != need0[0] and need[1] != need0[1]      # both passes take the packed kernels (more scratch)
+    for name, g, o in zip(("y fused", "y", "dx", "dx accumulated", "dx masked"), got, base):
+        assert np.array_equal(np.isnan(g), np.isnan(o)), name
+        inf = np.isinf(o)
+        assert np.array_equal(np.isinf(g), inf) and np.array_equal(g[inf], o[inf]), name
+        ok = np.isfinite(o) & (np.abs(o) < 1e30)
+        assert ok.mean() > 0.5 and rel_l2(g[ok], o[ok]) <= 1e-6, name
+
+
+@pytest.mark.parametrize("amax", [2, 1000])
+def test_integers_are_exact(amax):
+    """Integers whose partial sums stay below 2^24 come out exactly, also those that need two parts."""
+    import paper_1412_6249_amd as pa
+    case = (2, 64, 8, 9, 72, 3, 3, 1, 1)
+    rs = np.random.default_rng(3)
+    x, w, b, dy, act, prev = (np.zeros_like(a) for a in _inputs(case))
+    x[:] = rs.integers(-amax, amax + 1, x.shape)
+    dy[:] = rs.integers(-amax, amax + 1, dy.shape)
+    w[:] = rs.integers(-2, 3, w.shape)
+    got, _ = _run(pa, case, x, w, b, dy, act, prev)
+    assert np.array_equal(got[1], oracle.conv_fwd(x, w, 1, 1).astype(np.float32))
+    assert np.array_equal(got[2], oracle.conv_bwd_data(dy, w, x.shape, 1, 1).astype(np.float32))
