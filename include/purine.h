@@ -101,10 +101,12 @@ int purine_conv_out_shape(const purine_conv_desc* desc, const int64_t x_dim[4],
 
 /* Bytes of device scratch the given pass needs (0 when none). Returns 0 for illegal shapes: the
  * operator call itself reports the error. Forward and backward-data keep a repacked, zero-padded
- * copy of the filter there (none for a forward pass with fewer than 16 input channels), F32 layers
- * with several taps also a copy of the gathered tensor (6 bytes per element, channels rounded up to
- * a multiple of 16) and the partial outputs of a split reduction; backward-weight keeps its
- * split-reduction partial sums there. */
+ * copy of the filter there (none for a forward pass with fewer than 16 input channels); F32 layers
+ * with several taps and a strided gather or few output tiles also a copy of the gathered tensor (6
+ * bytes per element, channels rounded up to a multiple of 16) and the partial outputs of a split
+ * reduction. Backward-weight keeps its split-reduction partial sums there, F32 layers bound by the
+ * matrix cores also copies of x and dy (6 bytes per element; the size is a whole number of copies of
+ * dw, and of K sums for the fused bias gradient). */
 size_t purine_conv_workspace_bytes(int pass, const purine_conv_desc* desc, const int64_t x_dim[4],
                                    const int64_t w_dim[4], int32_t dtype);
 size_t purine_bias_bwd_workspace_bytes(const int64_t dy_dim[4], int32_t dtype);
@@ -153,8 +155,9 @@ int purine_conv_bwd_weight(const purine_conv_desc* desc, const purine_tensor* x,
  * sums go to a fixed array inside the library's device image (purine_static_scratch_bytes() bytes,
  * 64 MiB, held by every GPU the library runs on until the process ends). The call allocates
  * nothing: no hipMalloc / hipFree and no allocating library routine. A layer whose
- * purine_conv_workspace_bytes(PURINE_CONV_BWD_WEIGHT, ...) exceeds that size is refused with
- * PURINE_E_STATIC_SCRATCH before anything is launched. The first call on a device looks up that
+ * split-reduction partial sums exceed that size is refused with PURINE_E_STATIC_SCRATCH before
+ * anything is launched (copies of x and dy that purine_conv_workspace_bytes counts as well need not
+ * fit at once: the call then works through the splits a few at a time). The first call on a device looks up that
  * device's address of the array (once; the device current at the call is the one used). Every
  * call on a GPU shares that GPU's array: calls that overlap in time on one GPU (different streams
  * with no ordering between them, or different host threads) race on it and must be ordered by the

@@ -298,7 +298,6 @@ namespace {
 // library, so every GPU that loads the library holds its own copy until the process ends. In host
 // code the name `scratch` is only a handle for hipGetSymbolAddress: the address a kernel may use
 // is looked up once per device (with that device current) and kept in g_scratch_ptr.
-constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 void* g_scratch_ptr[kMaxDevices];
@@ -340,16 +339,17 @@ int conv_bwd_weight_impl(const purine_conv_desc* desc, const purine_tensor* x, c
     if (overlaps(dw, x) || overlaps(dw, dy)) return PURINE_E_LAYOUT;
     if (db && (overlaps(db, x) || overlaps(db, dy) || overlaps(db, dw))) return PURINE_E_LAYOUT;
     const WgradPlan plan = plan_wgrad(g, x->dtype);
-    const size_t need = db ? wgrad_db_offset(plan) + plan.db_ws_bytes : plan.ws_bytes;
+    size_t need = db ? wgrad_db_offset(plan) + plan.db_ws_bytes : plan.ws_bytes;
     if (static_ws) {
-        if (need > kStaticScratchBytes) return PURINE_E_STATIC_SCRATCH;
+        if (plan.static_bytes > kStaticScratchBytes) return PURINE_E_STATIC_SCRATCH;
+        need = plan.static_bytes;
         if ((rc = static_scratch_of_current_device(&ws))) return rc;
         ws_bytes = kStaticScratchBytes;
     }
     if (!ws || ws_bytes < need) return PURINE_E_WORKSPACE;
     if (((uintptr_t)ws) & 15u) return PURINE_E_LAYOUT;
     hipError_t e = launch_conv_wgrad(x->dtype, g, plan, x->data, dy->data, (float*)dw->data,
-                                     db ? (float*)db->data : nullptr, beta, ws, (hipStream_t)hip_stream);
+                                     db ? (float*)db->data : nullptr, beta, ws, ws_bytes, (hipStream_t)hip_stream);
     return hip_status(e);
 }
 }  // namespace

@@ -101,7 +101,27 @@ bool buffer_loads_disabled();   // tuning hook: (anything, -1) given to force_pi
 
 // Split of the pixel reduction of the weight gradient: same answer for the workspace query and
 // for the launch.
+// Part of the plan below: the fp32 kernel on packed bf16 parts (conv_wgrad_packets.hip).
+struct WgradPacketPlan {
+    bool use;
+    int bands, PB, groups;                 // bands of PB output rows per image; groups of 8 bands
+    int real, PD, pairs, WB, XD;           // output positions of a band, padded to whole pairs; x positions (rows of WB)
+    int bm, bn, tiles_i, tiles_j, steps, splits, steps_per_split;
+    int db_rows;                           // rows of the bias gradient's partial sums
+    size_t dy_group, x_group;              // bytes of a packed group and plane
+    size_t part_bytes, ws_bytes;           // scratch: partial sums of dw, then the packed operands,
+    size_t db_offset, copies;              // then the bias sums; all of it in whole copies of dw
+    double us;                             // expected time
+};
+WgradPacketPlan plan_wgrad_packets(const ConvGeom& g, size_t limit);
+hipError_t launch_wgrad_packets(const ConvGeom& g, const WgradPacketPlan& k, const void* x, const void* dy, float* dw, float* db, float beta, void* ws,
+                                size_t ws_bytes, hipStream_t st);
+// scratch of purine_conv_bwd_weight_static
+constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
+
 struct WgradPlan {
+    WgradPacketPlan pk;
+    size_t static_bytes;  // what the layer has to fit into kStaticScratchBytes with: the general kernels' partial sums
     bool rows;         // bf16 3x3 layers: the row-staging kernel (one partial tile per persistent workgroup)
     bool cols;         // bf16 layers with C*R*S <= 160: whole-filter tiles per wavefront (conv_wgrad_cols_bf16.hip)
     bool taps;         // bf16 layers with C*R <= 32 and a known filter row shape: one tile per column tap (conv_wgrad_taps_bf16.hip)
@@ -159,7 +179,7 @@ hipError_t launch_conv_pix(int dtype, const ConvGeom& g, const PixPlan& plan, co
                            hipStream_t st);
 // db != null: also db = beta*db + sum of dy over pixels (fused BiasBwd), scratch behind dw's partials
 hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const WgradPlan& plan, const void* x,
-                             const void* dy, float* dw, float* db, float beta, void* ws, hipStream_t st);
+                             const void* dy, float* dw, float* db, float beta, void* ws, size_t ws_bytes, hipStream_t st);
 hipError_t launch_bias_fwd(int dtype, const void* b, void* y, int N, int K, int PQ, hipStream_t st);
 hipError_t launch_bias_bwd(int dtype, const void* dy, float* db, float beta, int N, int K, int PQ,
                            const BiasBwdPlan& plan, void* ws, hipStream_t st);

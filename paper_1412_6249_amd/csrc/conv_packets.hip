@@ -20,43 +20,14 @@
 // an offset outside the buffer, which loads zeros) and every MFMA fragment is one conflict-free 16-byte
 // LDS read. The extra pass over the activations (4 bytes read, 6 written per element) is paid
 // back where the gathered elements are used by several taps and row tiles.
+#include "packets.h"
 #include "pix_common.h"
 
 namespace purine {
 namespace pix {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int PLANES = 3;
-
-// x = p0 + p1 + p2 exactly (as long as the parts stay above the smallest bf16 subnormal). Values that
-// round up past the largest bf16 are truncated instead; infinities and NaNs go into p0 alone.
-__device__ __forceinline__ void split3(float x, __bf16& p0, __bf16& p1, __bf16& p2) {
-    const uint32_t u = __float_as_uint(x);
-    p0 = (__bf16)x;
-    if ((u & 0x7fffffffu) >= 0x7f7f8000u) {                    // would round to infinity, or is not finite
-        const bool nan = (u & 0x7fffffffu) > 0x7f800000u;
-        p0 = __builtin_bit_cast(__bf16, (uint16_t)(nan ? 0x7fc0u : (u >> 16)));
-        if ((u & 0x7f800000u) == 0x7f800000u) { p1 = (__bf16)0.0f; p2 = (__bf16)0.0f; return; }
-    }
-    const float r1 = x - (float)p0;
-    p1 = (__bf16)r1;
-    p2 = (__bf16)(r1 - (float)p1);
-}
-
-__device__ __forceinline__ void store_split8(const float (&v)[8], unsigned char* base, size_t plane_bytes) {
-    bf16x8 q[PLANES];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        __bf16 a, b, c;
-        split3(v[e], a, b, c);
-        q[0][e] = a; q[1][e] = b; q[2][e] = c;
-    }
-#pragma unroll
-    for (int pl = 0; pl < PLANES; ++pl) *reinterpret_cast<bf16x8*>(base + pl * plane_bytes) = q[pl];
-}
+using namespace packets;
 
 // One launch lays out both operands: workgroups below `x_blocks` take the activations (a thread per
 // packet, lanes along positions: 8 coalesced 4-byte loads, three coalesced 16-byte stores), the others
@@ -112,21 +83,6 @@ __global__ __launch_bounds__(256) void pack_operands_kernel(const PackParams q) 
     // [row tile][step][plane][half][row]
     store_split8(v, q.wp + ((size_t)ts * PLANES * 2 + half) * q.bm * 16 + (size_t)row * 16, (size_t)2 * q.bm * 16);
 }
-
-template <int TM, int TN, int WM, int WN>
-struct Tile {
-    static constexpr int BM = TM * WM * 32, BN = TN * WN * 32, NW = WM * WN;
-    static constexpr int A_BYTES = PLANES * 2 * BM * 16, B_BYTES = PLANES * 2 * BN * 16;
-    static constexpr int STAGE = A_BYTES + B_BYTES;
-    static constexpr int NS = STAGE * 3 + 2048 <= 80 * 1024 ? 3 : 2;      // ring of step buffers; two workgroups per CU
-    static constexpr int LDS = NS * STAGE + 1024 + BM * 4;                // + spare KB + bias
-    static constexpr int LA = A_BYTES / 1024;                             // direct-to-LDS loads of a wavefront: 64 packets each
-    static constexpr int RA = (LA + NW - 1) / NW;
-    static constexpr int PG = BN / 64, WPG = NW / PG;                     // pixel groups of 64; wavefronts per group
-    static constexpr int RB = (2 * PLANES + WPG - 1) / WPG;
-    static constexpr int LOADS = RA + RB;                                 // per wavefront and step, whatever happens
-    static_assert(NW % PG == 0 && LOADS * (NS - 1) <= 60, "");
-};
 
 struct PacketParams {
     const void* a; const void* b;       // packed filter, packed activations
@@ -232,37 +188,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void igemm_packets_kernel(const Pi
     const int b_off = T::A_BYTES + (khalf * T::BN + wn * TN * 32 + (lane & 31)) * 16;
     int slot = 0;
     for (int s = s0; s < s1; ++s) {
-        // step s has landed (everything this wavefront requested but the younger steps), and every
-        // wavefront is done with the step before it, whose slot the next request overwrites. A bare
-        // barrier: a fence would wait for the loads in flight as well.
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt((0x0070 | ((T::LOADS * (T::NS - 2)) & 15) | (((T::LOADS * (T::NS - 2)) >> 4) << 14)));
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        const int next = slot == 0 ? T::NS - 1 : slot - 1;
-        request(s + T::NS - 1, next);
-        const unsigned char* st = smem + slot * T::STAGE;
-        bf16x8 av[PLANES][TM], bv[PLANES][TN];
-#pragma unroll
-        for (int pl = 0; pl < PLANES; ++pl) {
-#pragma unroll
-            for (int a = 0; a < TM; ++a) av[pl][a] = *reinterpret_cast<const bf16x8*>(st + a_off + (pl * 2 * T::BM + a * 32) * 16);
-#pragma unroll
-            for (int b = 0; b < TN; ++b) bv[pl][b] = *reinterpret_cast<const bf16x8*>(st + b_off + (pl * 2 * T::BN + b * 32) * 16);
-        }
-        auto mul = [&](int i, int j, floatx16 (&acc)[TM][TN]) {
-#pragma unroll
-            for (int a = 0; a < TM; ++a)
-#pragma unroll
-                for (int b = 0; b < TN; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i][a], bv[j][b], acc[a][b], 0, 0, 0);
-        };
-        mul(0, 0, hi);
-        mul(0, 1, lo);
-        mul(1, 0, lo);
-        mul(1, 1, lo);
-        mul(0, 2, lo);
-        mul(2, 0, lo);
+        // step s is in LDS, and every wavefront is done with the step before it, whose slot the next
+        // request overwrites
+        packets_landed<T::LOADS * (T::NS - 2)>();
+        request(s + T::NS - 1, slot == 0 ? T::NS - 1 : slot - 1);
+        multiply_step<T, TM, TN>(smem + slot * T::STAGE, a_off, b_off, hi, lo);
         slot = slot + 1 == T::NS ? 0 : slot + 1;
     }
     // the last requests must not outlive the workgroup's LDS
@@ -270,17 +200,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void igemm_packets_kernel(const Pi
 
     // The sum of the two sets; infinities and NaNs that the split products make of infinite or
     // overflowing operands (an infinity times a zero part) are computed again as the fp32 kernel would.
-    unsigned long long bad = 0;
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                hi[a][b][e] += lo[a][b][e];
-                if (!(__builtin_fabsf(hi[a][b][e]) <= 3.402823466e38f)) bad |= 1ull << ((a * TN + b) * 16 + e);
-            }
-    static_assert(TM * TN * 16 <= 64, "");
+    unsigned long long bad = join_sets<TM, TN>(hi, lo);
     if (__builtin_expect(__any(bad != 0), 0)) {
         while (bad) {
             const int idx = __ffsll((long long)bad) - 1;
@@ -302,23 +222,12 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void igemm_packets_kernel(const Pi
                     for (int half = 0; half < 2; ++half) {
                         const unsigned char* pa = (const unsigned char*)q.a + (size_t)(rt * q.steps + s) * T::A_BYTES + (half * T::BM + row) * 16;
                         const unsigned char* pb = (const unsigned char*)q.b + ((size_t)(n * q.Cb + g * 2 + half) * p.HiWi + (inside ? h * p.Wi + w : 0)) * 16;
-                        for (int c = 0; c < 8; ++c) {
-                            float x[2] = {0.0f, 0.0f};
-                            for (int pl = PLANES - 1; pl >= 0; --pl) {       // small parts first: every sum is exact
-                                x[0] += (float)*reinterpret_cast<const __bf16*>(pa + pl * 2 * T::BM * 16 + c * 2);
-                                x[1] += inside ? (float)*reinterpret_cast<const __bf16*>(pb + (size_t)pl * q.plane_bytes + c * 2) : 0.0f;
-                            }
-                            sum = __builtin_fmaf(x[0], x[1], sum);
-                        }
+                        for (int c = 0; c < 8; ++c)
+                            sum = __builtin_fmaf(join_parts(pa + c * 2, 2 * T::BM * 16), inside ? join_parts(pb + c * 2, q.plane_bytes) : 0.0f, sum);
                     }
                 }
             }
-#pragma unroll
-            for (int a = 0; a < TM; ++a)
-#pragma unroll
-                for (int b = 0; b < TN; ++b)
-#pragma unroll
-                    for (int k = 0; k < 16; ++k) hi[a][b][k] = (a * TN + b) * 16 + k == idx ? sum : hi[a][b][k];
+            replace_element<TM, TN>(hi, idx, sum);
         }
     }
     store_tile<float, D2S, FUSED, TM, TN, !MINUS>(p, (float*)p.out + (size_t)split * q.split_stride, hi, i0 + wm * TM * 32,
@@ -364,21 +273,6 @@ hipError_t launch_main(const PixParams& p, const PacketParams& q, hipStream_t st
     return hipGetLastError();
 }
 
-// cycles: MFMA time of a step on one SIMD (TM * TN * 6 * 32); eff: the share of it that the tile reaches
-// (256 -> 384 channels at 13x13, N = 128, main kernel alone: 168 us with 64x256, 187 with 128x128, 195
-// with 64x128, 200 with 96x128 and its padding, 215 with 32x256).
-struct PacketTile { int bm, bn, cycles; float eff; };
-#define PACKET_TILES(CALL)                                              \
-    switch (bm * 1000 + bn) {                                           \
-        case 128128: return CALL(2, 2, 2, 2);                           \
-        case 96128:  return CALL(3, 1, 1, 4);                           \
-        case 64256:  return CALL(2, 2, 1, 4);                           \
-        case 64128:  return CALL(1, 2, 2, 2);                           \
-        case 32256:  return CALL(1, 2, 1, 4);                           \
-        default: return hipErrorInvalidValue;                           \
-    }
-constexpr PacketTile kPacketTiles[] = {{128, 128, 768, 0.68f}, {64, 256, 768, 0.74f}, {96, 128, 576, 0.70f}, {64, 128, 384, 0.64f}, {32, 256, 384, 0.58f}};
-
 template <bool MINUS, bool D2S, bool FUSED>
 hipError_t by_tile(const PixParams& p, const PacketParams& q, int bm, int bn, hipStream_t st) {
 #define CALL(TM, TN, WM, WN) launch_main<MINUS, D2S, FUSED, TM, TN, WM, WN>(p, q, st)
@@ -404,23 +298,32 @@ PacketPlan plan_packets(const PixParams& p, bool d2s) {
     const long long cb = (p.Ci + 15) / 16 * 2;
     const long long b_bytes = (long long)p.N * cb * p.HiWi * 16 * PLANES;
     if (p.Rt * p.St < 2 || p.Ci < 8 || b_bytes >= 0x7fffffffLL || p.in_bytes == 0) return k;
+    // a copy of the gathered tensor in the scratch: only for strided gathers and for launches too small to
+    // fill the chip without a split reduction
+    const bool strided = p.g_mul_h > 1 || p.g_mul_w > 1;
+    if (!strided && ((p.Co + 127) / 128) * (((long long)p.M + 255) / 256) >= 128) return k;
     const double ghz = 2.2e3;                             // cycles per microsecond
     const double out_bytes = (double)p.M * p.Co * 4.0;
-    for (const PacketTile& t : kPacketTiles) {
+    for (const PacketTile& t : kTiles) {
         const long long ti = (p.Co + t.bm - 1) / t.bm, tp = ((long long)p.M + t.bn - 1) / t.bn, tiles = ti * tp;
         const long long a_bytes = ti * steps * PLANES * 2 * t.bm * 16;
         if (a_bytes >= 0x7fffffffLL) continue;
         // laying out the operands: 10 bytes per packed element, and a launch
         const double pack_us = 5.0 + ((double)b_bytes + (double)a_bytes) / 6.0 * 10.0 / 4.5e6;
+        // no split, or split counts that fill the chip to 1/2, 1, 3/2 .. 4 workgroups per CU
         long long last = -1;
-        for (long long sp = 1; sp <= 64 && sp <= steps; ++sp) {
+        for (int half_fill = 0; half_fill <= 8; ++half_fill) {
+            long long sp = half_fill * 128 / tiles;
+            if (sp < 1) sp = 1;
+            if (sp > 64) sp = 64;
             const long long per = (steps + sp - 1) / sp;
-            if ((steps + per - 1) / per != sp || per == last) continue;
+            sp = (steps + per - 1) / per;
+            if (per == last) continue;
             last = per;
-            if (sp > 1 && (tiles * sp > 1024 || sp * out_bytes >= 128.0 * (1 << 20))) break;
+            if (sp > 1 && sp * out_bytes >= 128.0 * (1 << 20)) break;
             const double x = (double)(tiles * sp) / 256.0;
             const double load = x <= 1.0 ? 1.45 : 0.5 * (x + (double)((tiles * sp + 255) / 256));
-            double us = load * ((double)per * t.cycles / t.eff + (d2s && sp == 1 ? 40000.0 : 4000.0)) / ghz + pack_us;
+            double us = load * ((double)per * t.cycles / t.eff + (d2s && sp == 1 ? 40000.0 : 4000.0)) / ghz + 4.0 + pack_us;
             if (sp > 1) us += 6.0 + 2.0 * sp * out_bytes / 8e6;
             if (!k.use || us < k.us) {
                 k.use = true; k.us = us;

@@ -749,8 +749,9 @@ hipError_t dispatch_f32(WgradParams& p, const WgradPlan& plan, hipStream_t st) {
 
 }  // namespace
 
-WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
+static WgradPlan plan_wgrad_general(const ConvGeom& g, int dtype, double* us) {
     WgradPlan pl{};
+    *us = 0.0;
     {
         // bf16 3x3 / stride 1 / pad 1 layers with rows of whole 16-byte packets: operands staged in
         // LDS row by row, persistent workgroups (conv_wgrad_rows_bf16.hip); one partial tile per worker
@@ -853,11 +854,30 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
     pl.chunk = (int)chunk;
     pl.ws_bytes = (size_t)splits * (size_t)g.K * (size_t)CRS * sizeof(float);
     pl.db_ws_bytes = (size_t)splits * (size_t)g.K * sizeof(float);
+    *us = best_time * 1e6 + 8.0;
+    return pl;
+}
+
+WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
+    double us;
+    WgradPlan pl = plan_wgrad_general(g, dtype, &us);
+    pl.static_bytes = pl.ws_bytes;
+    if (dtype != PURINE_F32 || buffer_loads_disabled()) return pl;
+    // fp32: the kernel on packed bf16 parts where it is expected to be faster. The layout pass costs 10
+    // bytes per element of x and dy, so 1x1 layers and layers of few channels stay on the general
+    // kernels (96 -> 96 channels 1x1 at 54x54, N = 64: 65 us there, 90 us for the layout pass alone);
+    // MFMA-bound ones gain what the forward pass gains. A layer that the static-scratch entry point
+    // takes has to go through its scratch on the same splits (the results are the same bits).
+    const WgradPacketPlan pk = plan_wgrad_packets(g, pl.ws_bytes <= kStaticScratchBytes ? kStaticScratchBytes : 0);
+    if (!pk.use || pk.us * 1.05 >= us) return pl;
+    pl.pk = pk;
+    pl.ws_bytes = pk.copies * (size_t)g.K * g.C * g.R * g.S * sizeof(float);
+    pl.db_ws_bytes = pk.copies * (size_t)g.K * sizeof(float);
     return pl;
 }
 
 hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const WgradPlan& plan, const void* x,
-                             const void* dy, float* dw, float* db, float beta, void* ws, hipStream_t st) {
+                             const void* dy, float* dw, float* db, float beta, void* ws, size_t ws_bytes, hipStream_t st) {
     WgradParams p{};
     p.x = x; p.dy = dy;
     // bias-gradient partials [split][K] sit behind the weight-gradient partials
@@ -882,6 +902,8 @@ hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const WgradPlan& plan
     }
     hipError_t e;
     const bool vec = p.PQ % 32 == 0 && (((uintptr_t)dy) & 15u) == 0;
+    if (plan.pk.use)
+        return launch_wgrad_packets(g, plan.pk, x, dy, dw, db, beta, ws, ws_bytes < plan.pk.ws_bytes ? ws_bytes : plan.pk.ws_bytes, st);
     if (plan.rows) e = launch_wgrad_rows_bf16(g, plan.splits, x, dy, (float*)ws, p.db_out, st);
     else if (plan.taps) e = launch_wgrad_taps_bf16(g, x, dy, (float*)ws, p.db_out, st);
     else if (plan.cols) e = launch_wgrad_cols_bf16(g, x, dy, (float*)ws, p.db_out, st);

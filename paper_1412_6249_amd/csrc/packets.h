@@ -1,0 +1,150 @@
+// What the two kernels on packed bf16 parts share (conv_packets.hip: forward and backward-data,
+// conv_wgrad_packets.hip: weight gradient): the split of an fp32 number, the tile shapes, the
+// multiplication of one step.
+#pragma once
+#include "common.h"
+
+namespace purine {
+namespace packets {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+constexpr int PLANES = 3;
+
+// x = p0 + p1 + p2 exactly (as long as the parts stay above the smallest bf16 subnormal). Values that
+// round up past the largest bf16 are truncated instead; infinities and NaNs go into p0 alone.
+__device__ __forceinline__ void split3(float x, __bf16& p0, __bf16& p1, __bf16& p2) {
+    const uint32_t u = __float_as_uint(x);
+    p0 = (__bf16)x;
+    if ((u & 0x7fffffffu) >= 0x7f7f8000u) {                    // would round to infinity, or is not finite
+        const bool nan = (u & 0x7fffffffu) > 0x7f800000u;
+        p0 = __builtin_bit_cast(__bf16, (uint16_t)(nan ? 0x7fc0u : (u >> 16)));
+        if ((u & 0x7f800000u) == 0x7f800000u) { p1 = (__bf16)0.0f; p2 = (__bf16)0.0f; return; }
+    }
+    const float r1 = x - (float)p0;
+    p1 = (__bf16)r1;
+    p2 = (__bf16)(r1 - (float)p1);
+}
+
+__device__ __forceinline__ void store_split8(const float (&v)[8], unsigned char* base, size_t plane_bytes) {
+    bf16x8 q[PLANES];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        __bf16 a, b, c;
+        split3(v[e], a, b, c);
+        q[0][e] = a; q[1][e] = b; q[2][e] = c;
+    }
+#pragma unroll
+    for (int pl = 0; pl < PLANES; ++pl) *reinterpret_cast<bf16x8*>(base + pl * plane_bytes) = q[pl];
+}
+
+template <int TM, int TN, int WM, int WN>
+struct Tile {
+    static constexpr int BM = TM * WM * 32, BN = TN * WN * 32, NW = WM * WN;
+    static constexpr int A_BYTES = PLANES * 2 * BM * 16, B_BYTES = PLANES * 2 * BN * 16;
+    static constexpr int STAGE = A_BYTES + B_BYTES;
+    static constexpr int NS = STAGE * 3 + 2048 <= 80 * 1024 ? 3 : 2;      // ring of step buffers; two workgroups per CU
+    static constexpr int LDS = NS * STAGE + 1024 + BM * 4;                // + spare KB + bias
+    static constexpr int LA = A_BYTES / 1024;                             // direct-to-LDS loads of a wavefront: 64 packets each
+    static constexpr int RA = (LA + NW - 1) / NW;
+    static constexpr int LB = B_BYTES / 1024;
+    static constexpr int RBL = (LB + NW - 1) / NW;
+    static constexpr int PG = BN / 64, WPG = NW / PG;                     // pixel groups of 64; wavefronts per group
+    static constexpr int RB = (2 * PLANES + WPG - 1) / WPG;
+    static constexpr int LOADS = RA + RB;                                 // per wavefront and step, whatever happens
+    static_assert(NW % PG == 0 && LOADS * (NS - 1) <= 60, "");
+};
+
+// cycles: MFMA time of a step on one SIMD (TM * TN * 6 * 32); eff / eff_w: the share of it that the tile
+// reaches in the forward / backward-data and in the weight-gradient kernel (256 -> 384 channels 3x3 at
+// 13x13, N = 128, whole operators less the layout pass: forward 168 us with 64x256, 187 with 128x128, 195
+// with 64x128, 200 with 96x128, 215 with 32x256; weight gradient 180 with 128x128, 194 with 64x256, 193 with
+// 96x128, 218 with 64x128: there the filter columns share no packets, so the squarer tile moves less).
+struct PacketTile { int bm, bn, cycles; float eff, eff_w; };
+#define PACKET_TILES(CALL)                                              \
+    switch (bm * 1000 + bn) {                                           \
+        case 128128: return CALL(2, 2, 2, 2);                           \
+        case 96128:  return CALL(3, 1, 1, 4);                           \
+        case 64256:  return CALL(2, 2, 1, 4);                           \
+        case 64128:  return CALL(1, 2, 2, 2);                           \
+        case 32256:  return CALL(1, 2, 1, 4);                           \
+        default: return hipErrorInvalidValue;                           \
+    }
+constexpr PacketTile kTiles[] = {{128, 128, 768, 0.68f, 0.74f}, {64, 256, 768, 0.74f, 0.69f}, {96, 128, 576, 0.70f, 0.69f},
+                                 {64, 128, 384, 0.64f, 0.63f}, {32, 256, 384, 0.58f, 0.60f}};
+
+// The MFMAs of one reduction step, from the step's LDS buffer: the largest of the six products into
+// `hi`, the five corrections into `lo`.
+template <typename T, int TM, int TN>
+__device__ __forceinline__ void multiply_step(const unsigned char* st, int a_off, int b_off, floatx16 (&hi)[TM][TN], floatx16 (&lo)[TM][TN]) {
+    bf16x8 av[PLANES][TM], bv[PLANES][TN];
+#pragma unroll
+    for (int pl = 0; pl < PLANES; ++pl) {
+#pragma unroll
+        for (int a = 0; a < TM; ++a) av[pl][a] = *reinterpret_cast<const bf16x8*>(st + a_off + (pl * 2 * T::BM + a * 32) * 16);
+#pragma unroll
+        for (int b = 0; b < TN; ++b) bv[pl][b] = *reinterpret_cast<const bf16x8*>(st + b_off + (pl * 2 * T::BN + b * 32) * 16);
+    }
+    auto mul = [&](int i, int j, floatx16 (&acc)[TM][TN]) {
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+            for (int b = 0; b < TN; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i][a], bv[j][b], acc[a][b], 0, 0, 0);
+    };
+    mul(0, 0, hi);
+    mul(0, 1, lo);
+    mul(1, 0, lo);
+    mul(1, 1, lo);
+    mul(0, 2, lo);
+    mul(2, 0, lo);
+}
+
+// Every load of this wavefront but the `YOUNGER` youngest has written its LDS packets; then all
+// wavefronts meet. A bare barrier: a fence would wait for the loads in flight as well. The empty asm
+// statements keep the compiler from moving LDS accesses across.
+template <int YOUNGER>
+__device__ __forceinline__ void packets_landed() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070 | (YOUNGER & 15) | ((YOUNGER >> 4) << 14));      // vmcnt(YOUNGER), lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Adds the two accumulator sets (into hi) and returns a bit per element that is infinite or NaN.
+template <int TM, int TN>
+__device__ __forceinline__ unsigned long long join_sets(floatx16 (&hi)[TM][TN], const floatx16 (&lo)[TM][TN]) {
+    static_assert(TM * TN * 16 <= 64, "");
+    unsigned long long bad = 0;
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                hi[a][b][e] += lo[a][b][e];
+                if (!(__builtin_fabsf(hi[a][b][e]) <= 3.402823466e38f)) bad |= 1ull << ((a * TN + b) * 16 + e);
+            }
+    return bad;
+}
+
+template <int TM, int TN>
+__device__ __forceinline__ void replace_element(floatx16 (&hi)[TM][TN], int idx, float v) {
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int k = 0; k < 16; ++k) hi[a][b][k] = (a * TN + b) * 16 + k == idx ? v : hi[a][b][k];
+}
+
+// The fp32 number whose parts sit `plane` bytes apart (the small parts first: every sum is exact).
+__device__ __forceinline__ float join_parts(const unsigned char* p, size_t plane) {
+    float v = 0.0f;
+    for (int pl = PLANES - 1; pl >= 0; --pl) v += (float)*reinterpret_cast<const __bf16*>(p + pl * plane);
+    return v;
+}
+
+}  // namespace packets
+}  // namespace purine

@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 # counts on either side of a 16-channel step, pixel counts on either side of a tile, a long reduction
 # over few pixels (split over workgroups), unequal filter and image sides, strides (phase-folded
 # backward-data) and filters that fit inside one stride step
-CASES = [(8, 64, 28, 28, 33, 3, 3, 1, 1), (4, 33, 9, 11, 45, 3, 3, 1, 1), (3, 17, 16, 8, 129, 2, 3, 1, (1, 0)),
-         (1, 256, 6, 6, 40, 3, 3, 1, 1), (1, 130, 5, 23, 64, 1, 5, 1, (0, 2)), (2, 31, 13, 15, 24, 3, 3, 2, 1),
+CASES = [(8, 64, 28, 28, 33, 3, 3, 1, 1), (2, 233, 9, 11, 45, 3, 3, 1, 1), (3, 17, 16, 8, 129, 2, 3, 1, (1, 0)),
+         (1, 256, 6, 6, 40, 3, 3, 1, 1), (1, 130, 5, 23, 64, 1, 5, 1, (0, 2)), (4, 161, 27, 29, 96, 3, 3, 2, 1),
          (2, 24, 14, 11, 33, 5, 4, (3, 2), (2, 1)), (5, 96, 13, 13, 97, 3, 3, 1, 1), (2, 64, 32, 32, 64, 3, 3, 1, 1)]
 
 
@@ -79,7 +79,7 @@ def test_infinities_nans_and_values_at_the_ends_of_the_range():
     computed again the way the fp32 kernel would. Same infinities, same NaNs as the general kernel."""
     import paper_1412_6249_amd as pa
     from gpu_util import rel_l2
-    case = (2, 40, 12, 12, 48, 3, 3, 1, 1)
+    case = (2, 200, 12, 12, 208, 3, 3, 1, 1)
     x, w, b, dy, act, prev = _inputs(case)
     big = np.float32(3.4028234e38)
     x[0, 3, 2, 2], x[0, 5, 9, 9], x[1, 0, 0, 0], x[1, 7, 6, 6] = np.inf, np.nan, -np.inf, big
@@ -115,3 +115,101 @@ def test_integers_are_exact(amax):
     got, _ = _run(pa, case, x, w, b, dy, act, prev)
     assert np.array_equal(got[1], oracle.conv_fwd(x, w, 1, 1).astype(np.float32))
     assert np.array_equal(got[2], oracle.conv_bwd_data(dy, w, x.shape, 1, 1).astype(np.float32))
+
+
+# ---- weight gradient (conv_wgrad_packets.hip): eight images, or bands of eight images' rows, per packet
+# N below, at and past a group of eight; odd planes (a padded position); bands with a ragged last one;
+# channel counts around the 16-channel tiles of the layout pass; strides, unequal sides, columns past a tile
+WCASES = [(8, 32, 9, 9, 48, 3, 3, 1, 1), (1, 64, 16, 14, 96, 3, 3, 1, 1), (3, 70, 13, 11, 33, 3, 3, 1, 1), (2, 33, 24, 17, 40, 5, 3, 1, (2, 1)),
+          (17, 40, 12, 13, 65, 3, 3, 2, 1), (12, 72, 31, 30, 130, 5, 4, (3, 2), (2, 1)), (9, 130, 8, 8, 70, 2, 2, 1, 0), (29, 41, 25, 19, 95, 3, 5, 1, (0, 2))]
+
+
+def _wgrad(pa, case, x, dy, prev_w, prev_b, beta):
+    import torch
+    from gpu_util import to_dev, workspace, to_host
+    desc = pa.conv_desc(case[7], case[8])
+    need = pa.purine_conv_workspace_bytes(pa.PURINE_CONV_BWD_WEIGHT_BIAS, desc, x.shape, prev_w.shape, pa.PURINE_F32)
+    tx, tdy, dw, db, alone = to_dev(x), to_dev(dy), to_dev(prev_w), to_dev(prev_b), to_dev(prev_w)
+    ws = workspace(need)
+    ws.fill_(0xff)                   # NaN patterns: nothing may be read that was not written
+    pa.purine_conv_bwd_weight_bias(desc, tx, tdy, dw, db, beta=beta, ws=ws)
+    ws.fill_(0xff)
+    pa.purine_conv_bwd_weight(desc, tx, tdy, alone, beta=beta, ws=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(dw.view(torch.int32), alone.view(torch.int32))       # the same bits (NaNs too)
+    return to_host(dw), to_host(db), need
+
+
+@pytest.mark.parametrize("beta", [0.0, 1.0])
+@pytest.mark.parametrize("case", WCASES, ids=str)
+def test_weight_gradient_on_packed_parts(case, beta):
+    import paper_1412_6249_amd as pa
+    from gpu_util import rel_l2
+    x, w, b, dy, _, _ = _inputs(case)
+    got_w, got_b, need = _wgrad(pa, case, x, dy, w, b, beta)
+    _general(pa, True)
+    try:
+        base_w, _, need0 = _wgrad(pa, case, x, dy, w, b, beta)
+    finally:
+        _general(pa, False)
+    assert need != need0                 # the layer takes the packed kernel: its scratch holds the packed operands
+    ref = oracle.conv_bwd_weight(x, dy, w.shape, case[7], case[8]) + beta * w
+    ref_b = oracle.bias_bwd(dy) + beta * b
+    # the result's own rounding is 0.3 * 2^-24; the sums beyond it may be no further off than the general kernel's
+    assert rel_l2(got_w, ref) <= max(rel_l2(base_w, ref), 1.0e-7), (rel_l2(got_w, ref), rel_l2(base_w, ref))
+    assert rel_l2(got_b, ref_b) <= 1e-6
+
+
+def test_weight_gradient_route_and_nonfinite_values():
+    """The layer takes the packed kernel (its scratch holds the packed operands), and infinities and NaNs
+    come out where the general kernel has them: also next to padding, in the last band's missing rows and
+    in the images a partial group lacks, where the other operand's zeros must not meet them."""
+    import paper_1412_6249_amd as pa
+    from gpu_util import rel_l2
+    case = (5, 160, 15, 15, 192, 3, 3, 1, 1)
+    x, w, b, dy, _, _ = _inputs(case)
+    x[0, 3, 0, 0], x[4, 9, 14, 14], x[2, 20, 7, 7] = np.inf, -np.inf, np.nan
+    x[1, 30, 3, 3] = np.float32(3.4028234e38)
+    dy *= np.float32(1e-3)
+    dy[4, 5, 14, 14], dy[3, 8, 0, 7], dy[0, 63, 10, 10] = np.inf, np.nan, -np.inf
+    got_w, got_b, need = _wgrad(pa, case, x, dy, w, b, 0.0)
+    _general(pa, True)
+    try:
+        base_w, base_b, need0 = _wgrad(pa, case, x, dy, w, b, 0.0)
+    finally:
+        _general(pa, False)
+    assert need != need0
+    for g, o in ((got_w, base_w), (got_b, base_b)):
+        assert np.array_equal(np.isnan(g), np.isnan(o))
+        inf = np.isinf(o)
+        assert np.array_equal(np.isinf(g), inf) and np.array_equal(g[inf], o[inf])
+        ok = np.isfinite(o) & (np.abs(o) < 1e30)
+        assert ok.any() and rel_l2(g[ok], o[ok]) <= 1e-6
+
+
+def test_weight_gradient_in_the_static_scratch_takes_the_splits_in_turn():
+    """The packed operands of this layer do not fit the static scratch at once; the entry point packs and
+    multiplies a few splits at a time and gives the same bits as the call with a workspace."""
+    import torch
+    import paper_1412_6249_amd as pa
+    from gpu_util import workspace, rel_l2, to_host, DEV
+    N, C, H, W, K = 24, 128, 56, 56, 128
+    g = torch.Generator(device=DEV)
+    g.manual_seed(7)
+    x = torch.randn((N, C, H, W), generator=g, device=DEV)
+    dy = torch.randn((N, K, H, W), generator=g, device=DEV)
+    desc = pa.conv_desc(1, 1)
+    need = pa.purine_conv_workspace_bytes(pa.PURINE_CONV_BWD_WEIGHT, desc, x.shape, (K, C, 3, 3), pa.PURINE_F32)
+    assert need > pa.purine_static_scratch_bytes()
+    want, got, base = (torch.full((K, C, 3, 3), float("nan"), device=DEV) for _ in range(3))
+    pa.purine_conv_bwd_weight(desc, x, dy, want, ws=workspace(need))
+    for _ in range(2):
+        pa.purine_conv_bwd_weight_static(desc, x, dy, got)
+    _general(pa, True)
+    try:
+        pa.purine_conv_bwd_weight_static(desc, x, dy, base)
+    finally:
+        _general(pa, False)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    assert rel_l2(to_host(got), to_host(base)) <= 2e-6        # two fp32 sums of 75264 products each
