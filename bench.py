@@ -25,6 +25,22 @@ sys.path.insert(0, ROOT)
 
 PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}     # MI355X dense MFMA peaks
 HBM_PEAK_GBS = 8000.0
+# Most passes of fp32 layers with several taps and at least 16 input channels multiply on the bf16 matrix
+# cores: three exact bf16 parts per operand, six bf16 products per fp32 product. Their matrix roof is the
+# bf16 peak, and what the units execute is six times the layer's flops.
+SPLIT_PRODUCTS = 6
+FORWARD_KINDS = (0, 13)
+
+
+def products(L, kind):
+    if L.dtype != "f32" or L.R * L.S == 1 or L.C < 16:
+        return 1
+    return 1 if kind in FORWARD_KINDS and L.C * L.R * L.S > 2048 else SPLIT_PRODUCTS
+
+
+def mfma_peak(L, kind):
+    """Peak of the matrix units for this pass, in TFLOP/s of the layer's own flops."""
+    return PEAK_TFLOPS["bf16"] / SPLIT_PRODUCTS if products(L, kind) > 1 else PEAK_TFLOPS[L.dtype]
 
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "hbm_traffic_dominant_kernels.md")
 
@@ -220,16 +236,17 @@ def run_config(cfg, args, secondary_figures):
     if kind in (3, 15):
         sizes["w"] = sizes["w"] // elem * 4          # the weight gradient is fp32
     algo_bytes = sizes["x"] + sizes["w"] + sizes["y"] + (sizes["x"] if kind == 14 else 0)
-    ridge = PEAK_TFLOPS[dtype] * 1e12 / (HBM_PEAK_GBS * 1e9)
+    ridge = mfma_peak(L, kind) * 1e12 / (HBM_PEAK_GBS * 1e9)
     if L.flop_per_pass / algo_bytes >= ridge:
-        achieved = L.flop_per_pass / (avg_ms * 1e-3) / 1e12
-        bound, peak, unit = "mfma", PEAK_TFLOPS[dtype], "TFLOP/s"
+        achieved = products(L, kind) * L.flop_per_pass / (avg_ms * 1e-3) / 1e12       # executed by the matrix units
+        bound, peak, unit = "mfma", mfma_peak(L, kind) * products(L, kind), "TFLOP/s"
     else:
         achieved = algo_bytes / (avg_ms * 1e-3) / 1e9
         bound, peak, unit = "hbm", HBM_PEAK_GBS, "GB/s"
     roofline = {"bound": bound, "kernel": kname, "achieved": round(achieved, 3),
                 "peak": peak, "unit": unit,
                 "frac": round(achieved / peak, 4),
+                "products_per_multiply": products(L, kind),
                 "avg_kernel_ms": round(avg_ms, 4),
                 "bracket_overhead_ms": round(bracket_ms, 4),
                 "algorithmic_bytes": algo_bytes,
@@ -280,7 +297,8 @@ def run_config(cfg, args, secondary_figures):
     value = flop / (ms_per_step * 1e-3) / 1e12
     return {"workload": WORKLOAD_NAMES[cfg], "ms_per_step": round(ms_per_step, 4), "value": round(value, 3),
             "dtype": dtype, "conv_gflop_per_step": round(flop / 1e9, 2),
-            "frac_of_mfma_peak": round(value / PEAK_TFLOPS[dtype], 4),
+            # matrix-unit time of the step at peak / its time
+            "frac_of_mfma_peak": round(sum(l.flop_per_pass / mfma_peak(l, k) for l in CONV_LAYERS[cfg] for k in (0, 2, 3)) / 1e12 / (ms_per_step * 1e-3), 4),
             "roofline": roofline, "secondary": secondary, "merge": merge, "streams": n_streams}
 
 

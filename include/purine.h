@@ -445,6 +445,9 @@ void purine_set_kernel_probe(void* start_event, void* stop_event);
  * For 1x1 / stride-1 / unpadded layers, which run the streaming GEMM kernel instead: (32|64|96, 2),
  * (64|96, 1) or (32|64, 4) force its rows per workgroup and pixels per lane, and (-1, anything) sends
  * those layers through the general kernel.
+ * F32 layers with several taps that the kernels on bf16 parts can take: (-6, anything) sends forward and
+ * backward-data through the one that splits in LDS, (-7, anything) all three passes through the ones
+ * on packed parts, whatever the automatic choice.
  * (anything, -1) makes every kernel take ordinary global loads with explicit zero fill instead of
  * range-checked raw buffer loads (the path tensors of 2 GiB and more take anyway). */
 void purine_debug_force_tile(int bm, int bn);

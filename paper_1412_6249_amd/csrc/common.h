@@ -71,6 +71,16 @@ struct PacketPlan {
     double us;                             // expected time
 };
 
+// ... and the one that splits a patch of the gathered tensor in LDS (conv_patch_f32.hip).
+struct PatchF32Plan {
+    bool use;
+    int bm, tiles_i, tiles_pix;
+    int bands, Wb, PW;          // images are cut into bands of Wb columns; patch rows of PW positions
+    int cgs;                    // groups of 16 gathered channels
+    size_t a_bytes;
+    double us;
+};
+
 // Launch plan of the forward / backward-data implicit GEMM: same answer for the workspace query and
 // for the launch.
 struct PixPlan {
@@ -92,9 +102,12 @@ struct PixPlan {
     int gemm_splits, gemm_split_ci;
     size_t gemm_part_offset;   // byte offset of the fp32 partial tiles inside the scratch
     PacketPlan pk;
+    PatchF32Plan pf;
 };
 PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, bool accumulate = false);
 void force_pix_tile(int bm, int bn);
+bool split_patch_forced();           // test hook: (-6, anything): fp32 layers run the kernel that splits a patch in LDS wherever it applies
+bool split_packets_forced();         // test hook: (-7, anything): ... the kernels on packed bf16 parts (forward, backward-data, weight gradient)
 bool patch_split_roles_forced();     // test hook: (-5, anything) gives it layers of few tiles too
 bool patch_split_roles_disabled();   // tuning hook: (-4, anything) keeps the bf16 patch kernel on its one-role form
 bool buffer_loads_disabled();   // tuning hook: (anything, -1) given to force_pix_tile

@@ -557,6 +557,8 @@ static int g_force_bm = 0, g_force_bn = 0;   // tuning hook, see purine_debug_fo
 static int g_no_buffer_loads = 0;            // tuning hook: bn == -1 in purine_debug_force_tile
 bool buffer_loads_disabled() { return g_no_buffer_loads != 0; }
 bool patch_split_roles_disabled() { return g_force_bm == -4; }   // tuning hook: force_pix_tile(-4, x)
+bool split_patch_forced() { return g_force_bm == -6; }           // test hooks: fp32 layers run the kernel that splits in LDS
+bool split_packets_forced() { return g_force_bm == -7; }         // / the ones on packed parts wherever they apply
 bool patch_split_roles_forced() { return g_force_bm == -5; }     // test hook: force_pix_tile(-5, x), also for layers of few tiles
 void force_pix_tile(int bm, int bn) {
     g_no_buffer_loads = (bn == -1 && bm != -2) ? 1 : 0;
@@ -723,18 +725,37 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
         pl.blk_offset = (pl.ws_bytes + 255) / 256 * 256;
         pl.ws_bytes = pl.blk_offset + gathered * elem;
     }
-    if (dtype == PURINE_F32 && !pl.flat && g_force_bm == 0 && g_no_buffer_loads == 0) {
-        // fp32 layers with several taps: the kernel on packed bf16 parts (conv_packets.hip), where it is
-        // expected to be faster than this file's. Those run at about 0.78 of the fp32 MFMA rate on a
-        // full chip, plus the filter repack; the packed kernel at 1.6 - 1.8 times that once its operands
-        // are laid out (layers of 38 - 115 GFLOP: 0.35 -> 0.20, 0.52 -> 0.31, 1.00 -> 0.60 ms; 2 images at
-        // 13x13, 384 -> 384: 140 -> 29 us). It loses where the layout pass is most of the work: 16 or
-        // fewer rows (5x5, 32 -> 16 at 28x28: 53.5 against 55 us), the strided first layers' depth-to-space
-        // output (11x11 / 4, 3 channels: 349 against 384 us), launches of a few microseconds.
+    if (dtype == PURINE_F32 && !pl.flat && g_no_buffer_loads == 0 && (g_force_bm == 0 || split_patch_forced() || split_packets_forced())) {
+        // fp32 layers with several taps: the kernels on bf16 parts, where they are expected to be faster. The
+        // fp32 MFMA kernels run at about 0.78 of the matrix rate on a full chip, plus the filter repack; the
+        // split kernels at 1.6 - 1.9 times that (N = 128, before -> after: 5x5 256 <- 96 at 27x27
+        // backward-data 1.01 -> 0.69 ms, 3x3 384 <- 384 at 13x13 0.50 -> 0.28, forward 3x3 96 -> 128 at 28x28
+        // 0.236 -> 0.140; 2 images at 13x13, 384 -> 384 forward: 140 -> 29 us). They lose where 16 or fewer
+        // rows leave half a tile empty (5x5, 32 -> 16 at 28x28: 53.5 against 55 us), on the strided first
+        // layers' depth-to-space output (11x11 / 4, 3 channels: 349 against 384 us) and in launches of a
+        // few microseconds. A patch in LDS (conv_patch_f32.hip) needs no copy of the activations; strided
+        // gathers and launches that need a split reduction to fill the chip take packed operands
+        // (conv_packets.hip).
+        // A forward pass over more than 2048 products per output stays on the fp32 kernels (unless it is a
+        // small launch, where the split reduction gains 3 - 5 times): what it computes decides ReLU signs and
+        // pooling winners, the rounding error of such long fp32 chains is 6 - 7e-7, and a kernel with another
+        // one, exact or not, decides enough near-ties differently to move the gradients of the five-layer
+        // stack by 1.5 - 2.7e-3 in norm (0 - 0.7e-3 on the inception module's shorter sums).
         const double old_us = best * 2.0 * Ci * pl.Rt * pl.St / (157.3e6 / 256.0 * 0.78) + 6.0;
-        pl.pk = plan_packets(make_pix_params(dtype, g, pl), pl.mode == 2);
-        pl.pk.use = pl.pk.use && Co > 16 && pl.pk.us * 1.05 < old_us;
+        const PixParams pp = make_pix_params(dtype, g, pl);
+        pl.pf = plan_patch_f32(pp, pl.mode == 2);
+        pl.pk = plan_packets(pp, pl.mode == 2);
+        if (pl.pf.use && pl.pf.a_bytes > pl.ws_bytes) pl.pf.use = false;
+        const bool small = ((long long)Co + 127) / 128 * ((M + 255) / 256) < 32;       // at most an eighth of the CUs get a tile
+        if (pl.mode == 0 && g_force_bm == 0 && (long long)Ci * g.R * g.S > 2048 && !small) pl.pk.use = pl.pf.use = false;
+        if (g_force_bm == 0) {
+            pl.pk.use = pl.pk.use && Co > 16 && pl.pk.us * 1.05 < old_us && !(pl.pf.use && pl.pf.us < pl.pk.us);
+            pl.pf.use = pl.pf.use && !pl.pk.use && Co > 16 && pl.pf.us * 1.05 < old_us;
+        } else {
+            if (split_patch_forced()) pl.pk.use = false; else pl.pf.use = false;
+        }
         if (pl.pk.use) { if (pl.pk.ws_bytes > pl.ws_bytes) pl.ws_bytes = pl.pk.ws_bytes; return pl; }
+        if (pl.pf.use) return pl;
     }
     // identity gather: the streaming GEMM applies
     const long long HW = (long long)g.H * g.W;
@@ -800,6 +821,7 @@ hipError_t launch_conv_pix(int dtype, const ConvGeom& g, const PixPlan& pl, cons
     p.bias = epi.bias; p.relu = epi.relu; p.mask = epi.mask;
     p.beta = beta;
 
+    if (pl.pf.use) return launch_patch_f32(p, pl.pf, pl.mode, wt, g.K, g.C, ws, st);
     if (pl.pk.use) return launch_packets(p, pl.pk, pl.mode, wt, g.K, g.C, ws, st);
     if (pl.gemm1x1) {
         const uintptr_t align = (uintptr_t)pl.gemm_tn * (dtype == PURINE_BF16 ? 2 : 4) - 1;

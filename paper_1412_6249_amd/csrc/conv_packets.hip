@@ -301,7 +301,7 @@ PacketPlan plan_packets(const PixParams& p, bool d2s) {
     // a copy of the gathered tensor in the scratch: only for strided gathers and for launches too small to
     // fill the chip without a split reduction
     const bool strided = p.g_mul_h > 1 || p.g_mul_w > 1;
-    if (!strided && ((p.Co + 127) / 128) * (((long long)p.M + 255) / 256) >= 128) return k;
+    if (!strided && !split_packets_forced() && ((p.Co + 127) / 128) * (((long long)p.M + 255) / 256) >= 128) return k;
     const double ghz = 2.2e3;                             // cycles per microsecond
     const double out_bytes = (double)p.M * p.Co * 4.0;
     for (const PacketTile& t : kTiles) {

@@ -1,0 +1,403 @@
+// fp32 forward / backward-data layers with several taps and a unit-stride gather (forward with stride 1,
+// backward-data with any stride after phase folding) on the bf16 matrix cores: the arithmetic of
+// conv_packets.hip (three exact bf16 parts, six products, two accumulator sets), with the parts made
+// in LDS instead of in scratch memory.
+//
+// Bound: MFMA, in practice the power limit (bf16 MFMAs on random data run at 1.9 - 2.0 GHz; the same
+// launch on zeros is a quarter faster). A workgroup of eight wavefronts owns BM rows x 256 consecutive
+// pixels, one workgroup per CU. All positions that the taps of those pixels touch form a patch of a few
+// haloed rows (possibly of several images); per group of 16 gathered channels the patch is loaded
+// once from NCHW (a lane takes 8 channels of one position: coalesced 4-byte loads), split in registers
+// and stored to LDS as packets [part][channel half][position][8], and every tap reads its B fragments
+// there at an offset of its own: an element is split once per row tile and not once per tap, and
+// nothing is copied in HBM. Two patch buffers: the next group's loads are issued after its
+// predecessor's first tap and split after the last. The filter is repacked (fp32, [row tile][group]
+// [tap][row][16]) and a step's tile is split on its way into a two-slot ring, four elements per thread.
+// One barrier per tap.
+//
+// Measured at N = 128 (whole operator, fp32 MFMA kernel before): 384 <- 384 channels 3x3 at 13x13
+// backward-data 0.50 -> 0.28 ms (204 TFLOP/s; 0.31 with the operands packed in scratch), 96 -> 128 3x3 at
+// 28x28 forward 0.236 -> 0.140, 96 <- 256 5x5 at 27x27 backward-data 1.01 -> 0.69 (365 tiles on 256 CUs).
+#include "packets.h"
+#include "pix_common.h"
+
+namespace purine {
+namespace pix {
+namespace {
+
+using namespace packets;
+
+constexpr int BN = 256, POS = 704, NT = 512;      // pixels, patch positions, threads of a workgroup
+constexpr int TASKS = (2 * POS + NT - 1) / NT;    // fill tasks (position, channel half) per thread
+
+struct PatchF32Params {
+    const float* a;             // repacked filter
+    unsigned a_bytes;
+    int taps, cgs;
+    int bands, Wb, PW, Mv;      // Mv: pixels counted over bands of Wb columns
+    int h_base, w_base;         // input row / column of patch row / column 0, relative to the output row / column
+    int img_rows;               // patch rows of a whole image: Ho + Rt - 1
+    FastDiv div_ho, div_wb, div_bands, div_pw, div_img, div_st;
+};
+
+// Filter repack, one thread per four channels: [row tile][group][tap][row][16], zero past the last row
+// or channel; modes as in the filter repack of the tap kernels.
+struct FilterPack {
+    const float* w; float* a;
+    int mode, K, C, R, S, sh, sw, St, Co, bm, taps, cgs, total;
+    FastDiv div_bm, div_taps, div_cgs, div_st, div_phases, div_sw;
+};
+__global__ __launch_bounds__(256) void pack_filter_f32_kernel(const FilterPack q) {
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= q.total) return;
+    const int quad = t & 3;
+    int rest = t >> 2;
+    int u = fastdiv(rest, q.div_bm);
+    const int row = rest - u * q.bm;
+    rest = u;
+    u = fastdiv(rest, q.div_taps);
+    const int tap = rest - u * q.taps;
+    const int rt = fastdiv(u, q.div_cgs), cg = u - rt * q.cgs;
+    const int tr = fastdiv(tap, q.div_st), tc = tap - tr * q.St;
+    const int i = rt * q.bm + row, ci0 = cg * 16 + quad * 4;
+    int fixed = 0, stride = 0, lim = 0;          // channel ci sits at w[fixed + ci * stride], ci < lim
+    if (i < q.Co) {
+        if (q.mode == 0) { fixed = (i * q.C * q.R + tr) * q.S + tc; stride = q.R * q.S; lim = q.C; }
+        else if (q.mode == 1) { fixed = (i * q.R + tr) * q.S + tc; stride = q.C * q.R * q.S; lim = q.K; }
+        else {
+            const int c = fastdiv(i, q.div_phases), ab = i - c * q.sh * q.sw;
+            const int pa = fastdiv(ab, q.div_sw), pb = ab - pa * q.sw;
+            const int r = pa + q.sh * tr, s = pb + q.sw * tc;
+            fixed = (c * q.R + r) * q.S + s; stride = q.C * q.R * q.S;
+            lim = (r < q.R && s < q.S) ? q.K : 0;
+        }
+    }
+    floatx4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = ci0 + e < lim ? q.w[(size_t)fixed + (size_t)(ci0 + e) * stride] : 0.0f;
+    *reinterpret_cast<floatx4*>(q.a + (size_t)t * 4) = v;
+}
+
+template <int TM, int WM>
+struct PatchTile {
+    static constexpr int BM = TM * WM * 32, WN = 8 / WM, TN = BN / (WN * 32);
+    static constexpr int A_BYTES = PLANES * 2 * BM * 16, P_BYTES = PLANES * 2 * POS * 16;
+    static constexpr int LDS = 2 * A_BYTES + 2 * P_BYTES + 512 + BM * 4;       // + spare half KB + bias
+};
+
+template <bool MINUS, bool D2S, bool FUSED, int TM, int WM>
+__global__ __launch_bounds__(NT, 2) void igemm_patch_f32_kernel(const PixParams p, const PatchF32Params q) {
+    typedef PatchTile<TM, WM> T;
+    constexpr int TN = T::TN, WN = T::WN;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    unsigned char* patch = smem + 2 * T::A_BYTES;
+    unsigned char* spare = patch + 2 * T::P_BYTES;
+    float* bias_s = reinterpret_cast<float*>(spare + 512);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int khalf = lane >> 5;
+    const int wm = wave / WN, wn = wave % WN;
+    // row tiles innermost: they read the same patch and share an XCD's L2
+    const int id = xcd_tile(blockIdx.x, gridDim.x);
+    const int pt = id / p.tiles_i, rt = id - pt * p.tiles_i;
+    const int i0 = rt * T::BM, p0 = pt * BN;
+
+    if (FUSED && !MINUS) stage_bias<float, T::BM, NT>(bias_s, p, i0, tid);
+
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(q.a), (short)0, (int)q.a_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.in), (short)0, (int)p.in_bytes, 0x00020000);
+
+    // the tile's output rows, counted over (image, band, row)
+    const int rho0 = fastdiv(p0, q.div_wb), rho1 = fastdiv(min(p0 + BN, q.Mv) - 1, q.div_wb);
+    const int v0 = fastdiv(rho0, q.div_ho), ho0 = rho0 - v0 * p.Ho;
+    const int v1 = fastdiv(rho1, q.div_ho);
+    const int npos = (rho1 - rho0 + (v1 - v0) * (p.Rt - 1) + p.Rt) * q.PW;
+    const int first_rows = p.Ho - ho0 + p.Rt - 1;         // patch rows that belong to image v0
+
+    // fill tasks of this thread: byte offset of (channel half's first channel, position) and LDS offset
+    int src[TASKS], dst[TASKS], half[TASKS];
+#pragma unroll
+    for (int j = 0; j < TASKS; ++j) {
+        const int t = tid + j * NT;
+        half[j] = t >= npos ? 1 : 0;
+        const int pos = t - half[j] * npos;
+        const bool task = t < 2 * npos;
+        const int prow = fastdiv(task ? pos : 0, q.div_pw), pcol = (task ? pos : 0) - prow * q.PW;
+        int v = v0, h = ho0 + q.h_base + prow;
+        if (prow >= first_rows) {
+            const int u = prow - first_rows, k = fastdiv(u, q.div_img);
+            v = v0 + 1 + k;
+            h = q.h_base + u - k * q.img_rows;
+        }
+        const int n = fastdiv(v, q.div_bands), w = (v - n * q.bands) * q.Wb + q.w_base + pcol;
+        const bool ok = task && n < p.N && (unsigned)h < (unsigned)p.Hi && (unsigned)w < (unsigned)p.Wi;
+        src[j] = ok ? (n * p.in_ns + half[j] * 8 * p.HiWi + h * p.Wi + w) * 4 : -1;
+        dst[j] = task ? (half[j] * POS + pos) * 16 : -1;
+    }
+    // the pixels this lane multiplies: patch position at tap offset 0, and its place in the output
+    int pbase[TN], opix[TN];
+#pragma unroll
+    for (int b = 0; b < TN; ++b) {
+        const int px = p0 + wn * TN * 32 + b * 32 + (lane & 31);
+        const bool live = px < q.Mv;
+        const int rho = fastdiv(live ? px : p0, q.div_wb), wb = (live ? px : p0) - rho * q.Wb;
+        const int v = fastdiv(rho, q.div_ho), ho = rho - v * p.Ho;
+        pbase[b] = ((rho - rho0 + (v - v0) * (p.Rt - 1)) * q.PW + wb + khalf * POS) * 16;
+        const int n = fastdiv(v, q.div_bands), wo = (v - n * q.bands) * q.Wb + wb;
+        opix[b] = live && wo < p.Wo ? n * p.HoWo + ho * p.Wo + wo : 0x7fffffff;
+    }
+
+    float breg[TASKS][8];
+    auto load_patch = [&](int cg) {               // cg == cgs: every offset lies outside, nothing is fetched
+#pragma unroll
+        for (int j = 0; j < TASKS; ++j) {
+            const int lim = p.Ci - cg * 16 - half[j] * 8;      // channels left for this task
+            const int soff = cg < q.cgs ? cg * 16 * p.HiWi * 4 : 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                unsigned v = src[j] >= 0 && e < lim ? (unsigned)src[j] + (unsigned)(e * p.HiWi * 4) : 0x80000000u;
+                breg[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, v, soff, 0));
+            }
+        }
+    };
+    auto store_patch = [&](int buf) {
+#pragma unroll
+        for (int j = 0; j < TASKS; ++j)
+            if (dst[j] >= 0) {
+                typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+                u32x4 pk[PLANES];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    uint32_t part[PLANES];
+                    split_pair(breg[j][2 * e], breg[j][2 * e + 1], part);
+#pragma unroll
+                    for (int pl = 0; pl < PLANES; ++pl) pk[pl][e] = part[pl];
+                }
+#pragma unroll
+                for (int pl = 0; pl < PLANES; ++pl)
+                    *reinterpret_cast<u32x4*>(patch + buf * T::P_BYTES + dst[j] + pl * 2 * POS * 16) = pk[pl];
+            }
+    };
+    // filter tile of a step: four channels of one row per thread
+    const bool a_lane = tid < T::BM * 4;
+    const unsigned a_voff = a_lane ? (unsigned)(tid * 16) : 0x80000000u;
+    const int a_dst = ((tid >> 1) & 1) * T::BM * 16 + (tid >> 2) * 16 + (tid & 1) * 8;
+    auto load_a = [&](int step) {
+        return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(ra, a_voff, (rt * q.cgs * q.taps + step) * T::BM * 64, 0));
+    };
+    auto store_a = [&](const floatx4& f, int slot) {
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        uint32_t p01[PLANES], p23[PLANES];
+        split_pair(f[0], f[1], p01);
+        split_pair(f[2], f[3], p23);
+        unsigned char* base = a_lane ? smem + slot * T::A_BYTES + a_dst : spare + lane * 8;
+#pragma unroll
+        for (int pl = 0; pl < PLANES; ++pl)
+            *reinterpret_cast<u32x2*>(base + (a_lane ? pl * 2 * T::BM * 16 : 0)) = u32x2{p01[pl], p23[pl]};
+    };
+
+    floatx16 hi[TM][TN], lo[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) { hi[a][b][e] = 0.0f; lo[a][b][e] = 0.0f; }
+
+    const int a_off = (khalf * T::BM + wm * TM * 32 + (lane & 31)) * 16;
+    // A wavefront's LDS traffic is done, then all wavefronts meet; loads in flight stay in flight.
+    auto meet = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xc07f);        // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    auto multiply = [&](int step, int buf, int tap_off) {
+        const unsigned char* sa = smem + (step & 1) * T::A_BYTES + a_off;
+        const unsigned char* sb = patch + buf * T::P_BYTES + tap_off;
+        bf16x8 av[PLANES][TM], bv[PLANES][TN];
+#pragma unroll
+        for (int pl = 0; pl < PLANES; ++pl) {
+#pragma unroll
+            for (int a = 0; a < TM; ++a) av[pl][a] = *reinterpret_cast<const bf16x8*>(sa + (pl * 2 * T::BM + a * 32) * 16);
+#pragma unroll
+            for (int b = 0; b < TN; ++b) bv[pl][b] = *reinterpret_cast<const bf16x8*>(sb + pbase[b] + pl * 2 * POS * 16);
+        }
+        auto mul = [&](int i, int j, floatx16 (&acc)[TM][TN]) {
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i][a], bv[j][b], acc[a][b], 0, 0, 0);
+        };
+        mul(0, 0, hi);
+        mul(0, 1, lo);
+        mul(1, 0, lo);
+        mul(1, 1, lo);
+        mul(0, 2, lo);
+        mul(2, 0, lo);
+    };
+
+    const int n_steps = q.cgs * q.taps;
+    load_patch(0);
+    store_a(load_a(0), 0);
+    store_patch(0);
+    int step = 0;
+    for (int cg = 0; cg < q.cgs; ++cg) {
+        const int buf = cg & 1;
+        int tr = 0, tc = 0;
+        auto tap_offset = [&]() { return MINUS ? ((p.Rt - 1 - tr) * q.PW + (p.St - 1 - tc)) * 16 : (tr * q.PW + tc) * 16; };
+        // first tap: the next group's patch is requested behind the next step's filter tile, so that
+        // waiting for the latter does not wait for the former
+        meet();
+        {
+            const floatx4 f = load_a(step + 1);      // (one past the last step: still inside the buffer's range check)
+            load_patch(cg + 1);
+            __builtin_amdgcn_sched_barrier(0);       // requests first: they have the whole step to arrive
+            multiply(step, buf, tap_offset());
+            store_a(f, (step + 1) & 1);
+            ++step;
+        }
+        for (int tap = 1; tap < q.taps; ++tap) {
+            if (++tc == p.St) { tc = 0; ++tr; }
+            meet();
+            const floatx4 f = load_a(step + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(step, buf, tap_offset());
+            store_a(f, (step + 1) & 1);
+            ++step;
+        }
+        if (cg + 1 < q.cgs) store_patch(buf ^ 1);
+    }
+
+    // infinities and NaNs: again, as plain fp32 sums (conv_packets.hip)
+    unsigned long long bad = join_sets<TM, TN>(hi, lo);
+    if (__builtin_expect(__any(bad != 0), 0)) {
+        while (bad) {
+            const int idx = __ffsll((long long)bad) - 1;
+            bad &= bad - 1;
+            const int ab = idx >> 4, e = idx & 15;
+            const int row = wm * TM * 32 + (ab / TN) * 32 + (e >> 2) * 8 + khalf * 4 + (e & 3);
+            int px = opix[0];
+#pragma unroll
+            for (int b = 1; b < TN; ++b) px = ab % TN == b ? opix[b] : px;
+            float sum = 0.0f;
+            if (px < p.M && i0 + row < p.Co) {
+                const int n = fastdiv(px, p.div_howo), rem = px - n * p.HoWo;
+                const int ho = fastdiv(rem, p.div_wo), wo = rem - ho * p.Wo;
+                for (int s = 0; s < n_steps && sum == sum; ++s) {
+                    const int g = s / q.taps, tap = s - g * q.taps;
+                    const int r = fastdiv(tap, q.div_st), t = tap - r * p.St;
+                    const int h = MINUS ? ho + p.g_add_h - r : ho + p.g_add_h + r, w = MINUS ? wo + p.g_add_w - t : wo + p.g_add_w + t;
+                    const bool inside = (unsigned)h < (unsigned)p.Hi && (unsigned)w < (unsigned)p.Wi;
+                    const float* pa = q.a + ((size_t)(rt * n_steps + s) * T::BM + row) * 16;
+                    const float* pb = (const float*)p.in + (size_t)n * p.in_ns + (size_t)g * 16 * p.HiWi + (inside ? h * p.Wi + w : 0);
+                    for (int c = 0; c < 16 && g * 16 + c < p.Ci; ++c)
+                        sum = __builtin_fmaf(pa[c], inside ? pb[(size_t)c * p.HiWi] : 0.0f, sum);
+                }
+            }
+            replace_element<TM, TN>(hi, idx, sum);
+        }
+    }
+    store_tile_at<float, D2S, FUSED, TM, TN, !MINUS>(p, (float*)p.out, hi, i0 + wm * TM * 32, [&](int b) { return opix[b]; }, khalf,
+                                                     bias_s, i0, 0x7fffffff);
+}
+
+template <bool MINUS, bool D2S, bool FUSED, int TM, int WM>
+hipError_t launch_main(const PixParams& p, const PatchF32Params& q, hipStream_t st) {
+    typedef PatchTile<TM, WM> T;
+    const long long total = (long long)p.tiles_i * p.tiles_pix;
+    if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&igemm_patch_f32_kernel<MINUS, D2S, FUSED, TM, WM>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS);
+    if (e != hipSuccess) return e;
+    ProbeScope probe(st);
+    (void)hipGetLastError();   // drop stale status left by earlier, unrelated runtime calls
+    hipLaunchKernelGGL((igemm_patch_f32_kernel<MINUS, D2S, FUSED, TM, WM>), dim3((unsigned)total), dim3(NT), T::LDS, st, p, q);
+    return hipGetLastError();
+}
+
+template <bool MINUS, bool D2S, bool FUSED>
+hipError_t by_tile(const PixParams& p, const PatchF32Params& q, int bm, hipStream_t st) {
+    switch (bm) {
+        case 128: return launch_main<MINUS, D2S, FUSED, 2, 2>(p, q, st);
+        case 96:  return launch_main<MINUS, D2S, FUSED, 3, 1>(p, q, st);
+        case 64:  return launch_main<MINUS, D2S, FUSED, 2, 1>(p, q, st);
+        case 32:  return launch_main<MINUS, D2S, FUSED, 1, 1>(p, q, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+// cycles: MFMA time of a step on a SIMD, two wavefronts; eff: the share of it that the tile reaches
+struct RowTile { int bm, cycles; float eff; };
+constexpr RowTile kRowTiles[] = {{128, 1536, 0.72f}, {96, 1152, 0.66f}, {64, 768, 0.58f}, {32, 384, 0.45f}};
+
+}  // namespace
+
+// How the layer would run here and the expected time (conv_igemm.hip compares). Pure host arithmetic.
+PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s) {
+    PatchF32Plan k{};
+    if (p.Rt * p.St < 2 || p.Ci < 8 || p.in_bytes == 0 || p.g_mul_h != 1 || p.g_mul_w != 1) return k;
+    // bands of columns: as few as keep the worst tile's patch within the LDS buffers
+    for (int bands = 1; bands <= 32; ++bands) {
+        const int wb = (p.Wo + bands - 1) / bands, pw = wb + p.St - 1;
+        if (bands > 1 && (wb < 8 || (long long)(bands - 1) * wb >= p.Wo)) break;
+        const long long rows = (BN + wb - 2) / wb + 1;                       // output rows that 256 pixels can touch
+        const long long crossings = (rows - 1 + p.Ho - 1) / p.Ho;            // image (or band) boundaries among them
+        if ((rows + crossings * (p.Rt - 1) + p.Rt - 1) * pw > POS) continue;
+        k.bands = bands; k.Wb = wb; k.PW = pw;
+        break;
+    }
+    const long long mv = (long long)p.N * k.bands * p.Ho * k.Wb;
+    if (!k.bands || mv > 0x7fffff00LL) return k;
+    k.cgs = (p.Ci + 15) / 16;
+    const long long tp = (mv + BN - 1) / BN;
+    for (const RowTile& t : kRowTiles) {
+        const long long ti = (p.Co + t.bm - 1) / t.bm;
+        const long long a_bytes = ti * k.cgs * p.Rt * p.St * t.bm * 64;
+        if (a_bytes >= 0x7fffffffLL || ti * tp > 0x7fffffffLL) continue;
+        const double x = (double)(ti * tp) / 256.0;
+        const double load = 0.3 * x + 0.7 * (double)((ti * tp + 255) / 256);         // one workgroup per CU
+        const double us = 10.0 + load * (k.cgs * (p.Rt * p.St * t.cycles / t.eff + 1000.0) + (d2s ? 50000.0 : 10000.0)) / 2.2e3;
+        if (!k.use || us < k.us) {
+            k.use = true; k.us = us;
+            k.bm = t.bm; k.tiles_i = (int)ti; k.tiles_pix = (int)tp;
+            k.a_bytes = (size_t)a_bytes;
+        }
+    }
+    return k;
+}
+
+hipError_t launch_patch_f32(PixParams p, const PatchF32Plan& k, int mode, const void* w, int K, int C, void* ws, hipStream_t st) {
+    if (!ws) return hipErrorInvalidValue;
+    FilterPack f{};
+    f.w = (const float*)w; f.a = (float*)ws;
+    f.mode = mode; f.K = K; f.C = C; f.R = p.R; f.S = p.S; f.sh = p.sh; f.sw = p.sw; f.St = p.St; f.Co = p.Co;
+    f.bm = k.bm; f.taps = p.Rt * p.St; f.cgs = k.cgs;
+    f.total = (int)(k.a_bytes / 16);
+    f.div_bm = make_fastdiv(k.bm); f.div_taps = make_fastdiv(f.taps); f.div_cgs = make_fastdiv(k.cgs); f.div_st = make_fastdiv(p.St);
+    f.div_phases = make_fastdiv(p.sh * p.sw); f.div_sw = make_fastdiv(p.sw);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(pack_filter_f32_kernel, dim3((unsigned)((f.total + 255) / 256)), dim3(256), 0, st, f);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+
+    PatchF32Params q{};
+    q.a = (const float*)ws; q.a_bytes = (unsigned)k.a_bytes;
+    q.taps = f.taps; q.cgs = k.cgs;
+    q.bands = k.bands; q.Wb = k.Wb; q.PW = k.PW; q.Mv = p.N * k.bands * p.Ho * k.Wb;
+    q.h_base = mode == 0 ? p.g_add_h : p.g_add_h - (p.Rt - 1);
+    q.w_base = mode == 0 ? p.g_add_w : p.g_add_w - (p.St - 1);
+    q.img_rows = p.Ho + p.Rt - 1;
+    q.div_ho = make_fastdiv(p.Ho); q.div_wb = make_fastdiv(k.Wb); q.div_bands = make_fastdiv(k.bands); q.div_pw = make_fastdiv(k.PW);
+    q.div_img = make_fastdiv(q.img_rows); q.div_st = make_fastdiv(p.St);
+    p.tiles_i = k.tiles_i; p.tiles_pix = k.tiles_pix;
+    const bool fused = p.bias || p.relu || p.mask;
+    if (mode == 0) return fused ? by_tile<false, false, true>(p, q, k.bm, st) : by_tile<false, false, false>(p, q, k.bm, st);
+    if (mode == 1) return fused ? by_tile<true, false, true>(p, q, k.bm, st) : by_tile<true, false, false>(p, q, k.bm, st);
+    return fused ? by_tile<true, true, true>(p, q, k.bm, st) : by_tile<true, true, false>(p, q, k.bm, st);
+}
+
+}  // namespace pix
+}  // namespace purine

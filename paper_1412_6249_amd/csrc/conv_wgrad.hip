@@ -869,7 +869,7 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
     // MFMA-bound ones gain what the forward pass gains. A layer that the static-scratch entry point
     // takes has to go through its scratch on the same splits (the results are the same bits).
     const WgradPacketPlan pk = plan_wgrad_packets(g, pl.ws_bytes <= kStaticScratchBytes ? kStaticScratchBytes : 0);
-    if (!pk.use || pk.us * 1.05 >= us) return pl;
+    if (!pk.use || (pk.us * 1.05 >= us && !split_packets_forced())) return pl;
     pl.pk = pk;
     pl.ws_bytes = pk.copies * (size_t)g.K * g.C * g.R * g.S * sizeof(float);
     pl.db_ws_bytes = pk.copies * (size_t)g.K * sizeof(float);

@@ -39,6 +39,21 @@ __device__ __forceinline__ void store_split8(const float (&v)[8], unsigned char*
     for (int pl = 0; pl < PLANES; ++pl) *reinterpret_cast<bf16x8*>(base + pl * plane_bytes) = q[pl];
 }
 
+// The parts of two numbers, for kernels that have the fp32 numbers at hand when an output comes out
+// infinite or NaN: no special values (an infinity, or a value that rounds to one, leaves NaNs in the
+// lower parts). Eleven instructions.
+__device__ __forceinline__ void split_pair(float x, float y, uint32_t (&part)[PLANES]) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int pl = 0; pl < PLANES; ++pl) {
+        const floatx2 f = {x, y};
+        part[pl] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
+        x -= __uint_as_float(part[pl] << 16);
+        y -= __uint_as_float(part[pl] & 0xffff0000u);
+    }
+}
+
 template <int TM, int TN, int WM, int WN>
 struct Tile {
     static constexpr int BM = TM * WM * 32, BN = TN * WN * 32, NW = WM * WN;

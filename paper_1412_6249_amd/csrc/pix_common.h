@@ -153,11 +153,11 @@ struct TileAddr {
 // FWD: the forward pass (bias / ReLU may be fused, never a mask or an accumulate); otherwise
 // backward-data (mask and accumulate possible, never bias / ReLU). Knowing the pass at compile time
 // keeps the other pass's options out of the per-element code.
-template <typename T, bool D2S, bool FUSED, int TM, int TN, bool FWD>
-__device__ __forceinline__ void store_tile(const PixParams& p, T* __restrict__ out,
-                                           floatx16 (&acc)[TM][TN], int i_base, int pix_base,
-                                           int khalf, const float* bias_lds, int i_tile0,
-                                           int pix_limit = 0x7fffffff, int bstep = 32) {
+// pix_of(b): the lane's pixel in column tile b (p.M or more: none).
+template <typename T, bool D2S, bool FUSED, int TM, int TN, bool FWD, typename PixOf>
+__device__ __forceinline__ void store_tile_at(const PixParams& p, T* __restrict__ out,
+                                              floatx16 (&acc)[TM][TN], int i_base, PixOf pix_of,
+                                              int khalf, const float* bias_lds, int i_tile0, int pix_limit) {
     if ((!FUSED || FWD) && !D2S && p.out_bytes != 0) {
         // NCHW output through raw buffer stores: a lane's pixel (and its half's four rows) is one
         // offset register per column tile, set up once; a row's part of the address is a scalar; a
@@ -171,7 +171,7 @@ __device__ __forceinline__ void store_tile(const PixParams& p, T* __restrict__ o
         unsigned voff[TN];
 #pragma unroll
         for (int b = 0; b < TN; ++b) {
-            const int pix = pix_base + b * bstep;
+            const int pix = pix_of(b);
             const bool live = pix < p.M && pix < pix_limit;
             const int n = fastdiv(live ? pix : 0, p.div_howo);
             voff[b] = live ? (unsigned)(n * p.out_ns + (pix - n * p.HoWo) + khalf * 4 * p.HoWo) * (unsigned)sizeof(T) : 0x80000000u;
@@ -226,7 +226,7 @@ __device__ __forceinline__ void store_tile(const PixParams& p, T* __restrict__ o
         constexpr bool QUAD = sizeof(T) == 2;   // bf16: bias of four consecutive rows as one 16-byte LDS read
 #pragma unroll
         for (int b = 0; b < TN; ++b) {
-            const int pix = pix_base + b * bstep;
+            const int pix = pix_of(b);
             if (pix >= p.M || pix >= pix_limit) continue;
             const int n = fastdiv(pix, p.div_howo);
             const TileAddr<T, D2S> addr(p, n, pix - n * p.HoWo);
@@ -268,7 +268,7 @@ __device__ __forceinline__ void store_tile(const PixParams& p, T* __restrict__ o
     constexpr bool QUAD_BIAS = sizeof(T) == 2;
 #pragma unroll
     for (int b = 0; b < TN; ++b) {
-        const int pix = pix_base + b * bstep;
+        const int pix = pix_of(b);
         if (pix >= p.M || pix >= pix_limit) continue;
         const int n = fastdiv(pix, p.div_howo);
         const TileAddr<T, D2S> addr(p, n, pix - n * p.HoWo);
@@ -314,6 +314,14 @@ __device__ __forceinline__ void store_tile(const PixParams& p, T* __restrict__ o
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+}
+
+template <typename T, bool D2S, bool FUSED, int TM, int TN, bool FWD>
+__device__ __forceinline__ void store_tile(const PixParams& p, T* __restrict__ out,
+                                           floatx16 (&acc)[TM][TN], int i_base, int pix_base,
+                                           int khalf, const float* bias_lds, int i_tile0,
+                                           int pix_limit = 0x7fffffff, int bstep = 32) {
+    store_tile_at<T, D2S, FUSED, TM, TN, FWD>(p, out, acc, i_base, [=](int b) { return pix_base + b * bstep; }, khalf, bias_lds, i_tile0, pix_limit);
 }
 
 // Same epilogue for 16x16 MFMA tiles: accumulator register e holds row (lane/16)*4 + e, column
@@ -614,6 +622,11 @@ hipError_t launch_rows_bf16(const PixParams& p, const RowsGeom& q, const void* w
 hipError_t dispatch_flat_bf16(PixParams& p, int bm, int bn, hipStream_t st);
 // streaming GEMM for 1x1 / stride 1 / unpadded layers (conv_gemm1x1.hip); p.wt is the KCRS filter
 hipError_t dispatch_gemm1x1(const PixParams& p, int dtype, bool trans, int tm, int tn, hipStream_t st);
+
+// fp32 layers with a unit-stride gather on bf16 parts split in LDS (conv_patch_f32.hip); mode and w as
+// below. launch_patch_f32 repacks the filter (fp32) into ws.
+PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s);
+hipError_t launch_patch_f32(PixParams p, const PatchF32Plan& k, int mode, const void* w, int K, int C, void* ws, hipStream_t st);
 
 // fp32 layers on packed bf16 parts (conv_packets.hip). mode: 0 forward, 1 backward-data with unit
 // stride, 2 backward-data phase-folded; w: the KCRS filter.

@@ -1,5 +1,4 @@
-"""The fp32 convolutions that run on packed bf16 parts (three per operand, six products): at the edges
-of their tiles, reduction steps and splits, in every form the operators have, against the oracle and
+"""The fp32 convolutions that run on bf16 parts (three per operand, six products): at the edges of their tiles, reduction steps and splits, in every form the operators have, against the oracle and
 against the general fp32 kernels (reached by switching raw buffer loads off, which the packed kernels
 need). The split must not cost precision: its error against fp64 may not exceed the general kernels'."""
 import numpy as np
@@ -9,17 +8,25 @@ import oracle
 
 pytestmark = pytest.mark.gpu
 
-# N, C, H, W, K, R, S, stride, pad. What is at an edge: one row past a 16- / 32- / 128-row tile, channel
-# counts on either side of a 16-channel step, pixel counts on either side of a tile, a long reduction
-# over few pixels (split over workgroups), unequal filter and image sides, strides (phase-folded
-# backward-data) and filters that fit inside one stride step
-CASES = [(8, 64, 28, 28, 33, 3, 3, 1, 1), (2, 233, 9, 11, 45, 3, 3, 1, 1), (3, 17, 16, 8, 129, 2, 3, 1, (1, 0)),
-         (1, 256, 6, 6, 40, 3, 3, 1, 1), (1, 130, 5, 23, 64, 1, 5, 1, (0, 2)), (4, 161, 27, 29, 96, 3, 3, 2, 1),
-         (2, 24, 14, 11, 33, 5, 4, (3, 2), (2, 1)), (5, 96, 13, 13, 97, 3, 3, 1, 1), (2, 64, 32, 32, 64, 3, 3, 1, 1)]
+# N, C, H, W, K, R, S, stride, pad. What is at an edge: one row past a 16- / 32- / 96- / 128-row tile,
+# channel counts on either side of a 16-channel step, pixel counts on either side of a tile, tiles that
+# cross several images, rows so wide that the LDS patch is cut into bands (a ragged last one), a long
+# reduction over few pixels (split over workgroups), unequal filter and image sides, strides
+# (phase-folded backward-data) and filters that fit inside one stride step
+CASES = [(2, 16, 9, 9, 17, 3, 3, 1, 1), (2, 233, 9, 11, 45, 3, 3, 1, 1), (3, 17, 16, 8, 129, 2, 3, 1, (1, 0)),
+         (1, 256, 6, 6, 40, 3, 3, 1, 1), (1, 130, 5, 23, 64, 1, 5, 1, (0, 2)), (4, 31, 27, 29, 96, 3, 3, 2, 1),
+         (2, 24, 14, 11, 33, 5, 4, (3, 2), (2, 1)), (5, 96, 13, 13, 97, 3, 3, 1, 1), (8, 64, 28, 28, 33, 3, 3, 1, 1),
+         (60, 17, 4, 3, 20, 3, 3, 1, 1), (1, 24, 33, 141, 40, 3, 3, 1, 1), (1, 16, 9, 300, 18, 1, 2, 1, 0),
+         (3, 40, 29, 31, 70, 5, 5, 1, 2), (2, 48, 15, 15, 32, 2, 2, 2, 0), (1, 16, 70, 70, 24, 7, 7, 1, 3)]
 
 
 def _general(pa, on):
     pa.purine_debug_force_tile(0, -1 if on else 0)
+
+
+def _forced(pa, route):
+    """route: "auto", "patch" (split in LDS), "packets" (packed parts) or "general" (fp32 MFMA kernels)."""
+    pa.purine_debug_force_tile(*{"auto": (0, 0), "patch": (-6, 0), "packets": (-7, 0), "general": (0, -1)}[route])
 
 
 def _run(pa, case, x, w, b, dy, act, prev):
@@ -51,29 +58,41 @@ def _inputs(case, seed=5):
 
 
 @pytest.mark.parametrize("case", CASES, ids=str)
-def test_packed_parts_against_the_oracle_and_the_general_kernels(case):
+def test_split_products_against_the_oracle_and_the_general_kernels(case):
+    """All three routes over the same layers. The general kernels' result is what the split ones may not be
+    further off the exact one than."""
     import paper_1412_6249_amd as pa
     from gpu_util import rel_l2
     x, w, b, dy, act, prev = _inputs(case)
     stride, pad = case[7], case[8]
-    got, _ = _run(pa, case, x, w, b, dy, act, prev)
-    _general(pa, True)
+    got = {}
     try:
-        base, _ = _run(pa, case, x, w, b, dy, act, prev)
+        for route in ("general", "patch", "packets", "auto"):
+            _forced(pa, route)
+            got[route], _ = _run(pa, case, x, w, b, dy, act, prev)
     finally:
-        _general(pa, False)
-    assert any(not np.array_equal(g, o) for g, o in zip(got, base))     # at least one pass took the packed kernels
+        _forced(pa, "auto")
     y = oracle.conv_fwd(x, w, stride, pad)
     dx = oracle.conv_bwd_data(dy, w, x.shape, stride, pad)
     refs = (np.maximum(oracle.bias_fwd(y, b), 0), y, dx, dx + prev, np.where(act > 0, dx, 0.0))
-    for name, g, o, r in zip(("y fused", "y", "dx", "dx accumulated", "dx masked"), got, base, refs):
-        # both round the result once (0.3 * 2^-24 on average); beyond that the split's sums may be no
-        # further off than the fp32 MFMA's
-        assert rel_l2(g, r) <= max(rel_l2(o, r), 1.0e-7), (name, rel_l2(g, r), rel_l2(o, r))
-        assert rel_l2(g, r) <= 1e-5, name
+    unit = stride == 1
+    sh, sw = (stride, stride) if isinstance(stride, int) else stride
+    taps_b = -(-case[5] // sh) * -(-case[6] // sw)           # taps of the phase-folded backward pass; one: not for these kernels
+    for route in ("patch", "packets", "auto"):
+        differs = [not np.array_equal(g, o) for g, o in zip(got[route], got["general"])]
+        if route == "patch":             # a strided forward gather is not for this one
+            assert (differs[1] or not unit) and (differs[2] or taps_b == 1), case
+        elif route == "packets":
+            assert differs[1] and (differs[2] or taps_b == 1), case
+        for name, g, o, r in zip(("y fused", "y", "dx", "dx accumulated", "dx masked"), got[route], got["general"], refs):
+            # both round the result once (0.3 * 2^-24 on average); beyond that the split's sums may be no
+            # further off than the fp32 MFMA's
+            assert rel_l2(g, r) <= max(rel_l2(o, r), 1.0e-7), (route, name, rel_l2(g, r), rel_l2(o, r))
+            assert rel_l2(g, r) <= 1e-5, (route, name)
 
 
-def test_infinities_nans_and_values_at_the_ends_of_the_range():
+@pytest.mark.parametrize("route", ["patch", "packets"])
+def test_infinities_nans_and_values_at_the_ends_of_the_range(route):
     """An infinity times the zero low parts of the other operand is a NaN in the split products, and a
     value above the largest bf16 has no rounded high part: outputs that come out infinite or NaN are
     computed again the way the fp32 kernel would. Same infinities, same NaNs as the general kernel."""
@@ -87,23 +106,25 @@ def test_infinities_nans_and_values_at_the_ends_of_the_range():
     w *= np.float32(0.1)                        # so that no finite partial sum overflows, whatever the order
     w[4, 4, 0, 0] = np.inf
     x[0, :, 5, 5] *= np.float32(1e-30)          # and small ones: exact down to the parts' smallest subnormal
-    got, need = _run(pa, case, x, w, b, dy, act, prev)
-    _general(pa, True)
     try:
-        base, need0 = _run(pa, case, x, w, b, dy, act, prev)
+        _forced(pa, route)
+        got, _ = _run(pa, case, x, w, b, dy, act, prev)
+        _forced(pa, "general")
+        base, _ = _run(pa, case, x, w, b, dy, act, prev)
     finally:
-        _general(pa, False)
-    assert need[0] != need0[0] and need[1] != need0[1]      # both passes take the packed kernels (more scratch)
+        _forced(pa, "auto")
+    assert not np.array_equal(got[1], base[1], equal_nan=True) and not np.array_equal(got[2], base[2], equal_nan=True)
     for name, g, o in zip(("y fused", "y", "dx", "dx accumulated", "dx masked"), got, base):
         assert np.array_equal(np.isnan(g), np.isnan(o)), name
         inf = np.isinf(o)
         assert np.array_equal(np.isinf(g), inf) and np.array_equal(g[inf], o[inf]), name
         ok = np.isfinite(o) & (np.abs(o) < 1e30)
-        assert ok.mean() > 0.5 and rel_l2(g[ok], o[ok]) <= 1e-6, name
+        assert ok.mean() > 0.4 and rel_l2(g[ok], o[ok]) <= 1e-6, name
 
 
+@pytest.mark.parametrize("route", ["patch", "packets"])
 @pytest.mark.parametrize("amax", [2, 1000])
-def test_integers_are_exact(amax):
+def test_integers_are_exact(amax, route):
     """Integers whose partial sums stay below 2^24 come out exactly, also those that need two parts."""
     import paper_1412_6249_amd as pa
     case = (2, 64, 8, 9, 72, 3, 3, 1, 1)
@@ -112,7 +133,11 @@ def test_integers_are_exact(amax):
     x[:] = rs.integers(-amax, amax + 1, x.shape)
     dy[:] = rs.integers(-amax, amax + 1, dy.shape)
     w[:] = rs.integers(-2, 3, w.shape)
-    got, _ = _run(pa, case, x, w, b, dy, act, prev)
+    try:
+        _forced(pa, route)
+        got, _ = _run(pa, case, x, w, b, dy, act, prev)
+    finally:
+        _forced(pa, "auto")
     assert np.array_equal(got[1], oracle.conv_fwd(x, w, 1, 1).astype(np.float32))
     assert np.array_equal(got[2], oracle.conv_bwd_data(dy, w, x.shape, 1, 1).astype(np.float32))
 
@@ -120,7 +145,7 @@ def test_integers_are_exact(amax):
 # ---- weight gradient (conv_wgrad_packets.hip): eight images, or bands of eight images' rows, per packet
 # N below, at and past a group of eight; odd planes (a padded position); bands with a ragged last one;
 # channel counts around the 16-channel tiles of the layout pass; strides, unequal sides, columns past a tile
-WCASES = [(8, 32, 9, 9, 48, 3, 3, 1, 1), (1, 64, 16, 14, 96, 3, 3, 1, 1), (3, 70, 13, 11, 33, 3, 3, 1, 1), (2, 33, 24, 17, 40, 5, 3, 1, (2, 1)),
+WCASES = [(8, 32, 9, 9, 48, 3, 3, 1, 1), (1, 16, 7, 5, 17, 3, 3, 1, 1), (5, 40, 9, 9, 24, 1, 1, 1, 0), (2, 3, 31, 29, 20, 7, 7, 2, 3), (1, 64, 16, 14, 96, 3, 3, 1, 1), (3, 70, 13, 11, 33, 3, 3, 1, 1), (2, 33, 24, 17, 40, 5, 3, 1, (2, 1)),
           (17, 40, 12, 13, 65, 3, 3, 2, 1), (12, 72, 31, 30, 130, 5, 4, (3, 2), (2, 1)), (9, 130, 8, 8, 70, 2, 2, 1, 0), (29, 41, 25, 19, 95, 3, 5, 1, (0, 2))]
 
 
@@ -146,12 +171,13 @@ def test_weight_gradient_on_packed_parts(case, beta):
     import paper_1412_6249_amd as pa
     from gpu_util import rel_l2
     x, w, b, dy, _, _ = _inputs(case)
-    got_w, got_b, need = _wgrad(pa, case, x, dy, w, b, beta)
-    _general(pa, True)
     try:
+        _forced(pa, "packets")
+        got_w, got_b, need = _wgrad(pa, case, x, dy, w, b, beta)
+        _forced(pa, "general")
         base_w, _, need0 = _wgrad(pa, case, x, dy, w, b, beta)
     finally:
-        _general(pa, False)
+        _forced(pa, "auto")
     assert need != need0                 # the layer takes the packed kernel: its scratch holds the packed operands
     ref = oracle.conv_bwd_weight(x, dy, w.shape, case[7], case[8]) + beta * w
     ref_b = oracle.bias_bwd(dy) + beta * b
