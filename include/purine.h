@@ -447,7 +447,8 @@ void purine_set_kernel_probe(void* start_event, void* stop_event);
  * those layers through the general kernel.
  * F32 layers with several taps that the kernels on bf16 parts can take: (-6, anything) sends forward and
  * backward-data through the one that splits in LDS, (-7, anything) all three passes through the ones
- * on packed parts, whatever the automatic choice.
+ * on packed parts, (-8, anything) the forward pass through the LDS kernel with fp32 products, whatever
+ * the automatic choice.
  * (anything, -1) makes every kernel take ordinary global loads with explicit zero fill instead of
  * range-checked raw buffer loads (the path tensors of 2 GiB and more take anyway). */
 void purine_debug_force_tile(int bm, int bn);

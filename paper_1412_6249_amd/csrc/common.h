@@ -73,7 +73,7 @@ struct PacketPlan {
 
 // ... and the one that splits a patch of the gathered tensor in LDS (conv_patch_f32.hip).
 struct PatchF32Plan {
-    bool use;
+    bool use, split;            // split: bf16 parts; else fp32 products in the tap kernel's order
     int bm, tiles_i, tiles_pix;
     int bands, Wb, PW;          // images are cut into bands of Wb columns; patch rows of PW positions
     int cgs;                    // groups of 16 gathered channels

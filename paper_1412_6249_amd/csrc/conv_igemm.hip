@@ -558,6 +558,7 @@ static int g_no_buffer_loads = 0;            // tuning hook: bn == -1 in purine_
 bool buffer_loads_disabled() { return g_no_buffer_loads != 0; }
 bool patch_split_roles_disabled() { return g_force_bm == -4; }   // tuning hook: force_pix_tile(-4, x)
 bool split_patch_forced() { return g_force_bm == -6; }           // test hooks: fp32 layers run the kernel that splits in LDS
+bool f32_patch_forced() { return g_force_bm == -8; }             // / forward passes the fp32 patch kernel
 bool split_packets_forced() { return g_force_bm == -7; }         // / the ones on packed parts wherever they apply
 bool patch_split_roles_forced() { return g_force_bm == -5; }     // test hook: force_pix_tile(-5, x), also for layers of few tiles
 void force_pix_tile(int bm, int bn) {
@@ -725,7 +726,7 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
         pl.blk_offset = (pl.ws_bytes + 255) / 256 * 256;
         pl.ws_bytes = pl.blk_offset + gathered * elem;
     }
-    if (dtype == PURINE_F32 && !pl.flat && g_no_buffer_loads == 0 && (g_force_bm == 0 || split_patch_forced() || split_packets_forced())) {
+    if (dtype == PURINE_F32 && !pl.flat && g_no_buffer_loads == 0 && (g_force_bm == 0 || split_patch_forced() || split_packets_forced() || f32_patch_forced())) {
         // fp32 layers with several taps: the kernels on bf16 parts, where they are expected to be faster. The
         // fp32 MFMA kernels run at about 0.78 of the matrix rate on a full chip, plus the filter repack; the
         // split kernels at 1.6 - 1.9 times that (N = 128, before -> after: 5x5 256 <- 96 at 27x27
@@ -740,19 +741,23 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
         // small launch, where the split reduction gains 3 - 5 times): what it computes decides ReLU signs and
         // pooling winners, the rounding error of such long fp32 chains is 6 - 7e-7, and a kernel with another
         // one, exact or not, decides enough near-ties differently to move the gradients of the five-layer
-        // stack by 1.5 - 2.7e-3 in norm (0 - 0.7e-3 on the inception module's shorter sums).
+        // stack by 1.5 - 2.7e-3 in norm (0 - 0.7e-3 on the inception module's shorter sums). Such a pass takes
+        // the patch kernel with fp32 products instead, which adds in the tap kernel's order.
         const double old_us = best * 2.0 * Ci * pl.Rt * pl.St / (157.3e6 / 256.0 * 0.78) + 6.0;
         const PixParams pp = make_pix_params(dtype, g, pl);
-        pl.pf = plan_patch_f32(pp, pl.mode == 2);
+        const bool small = ((long long)Co + 127) / 128 * ((M + 255) / 256) < 32;       // at most an eighth of the CUs get a tile
+        const bool keep_bits = pl.mode == 0 && (long long)Ci * g.R * g.S > 2048 && !small;
+        pl.pf = plan_patch_f32(pp, pl.mode == 2, !(keep_bits && g_force_bm == 0) && !f32_patch_forced());
         pl.pk = plan_packets(pp, pl.mode == 2);
         if (pl.pf.use && pl.pf.a_bytes > pl.ws_bytes) pl.pf.use = false;
-        const bool small = ((long long)Co + 127) / 128 * ((M + 255) / 256) < 32;       // at most an eighth of the CUs get a tile
-        if (pl.mode == 0 && g_force_bm == 0 && (long long)Ci * g.R * g.S > 2048 && !small) pl.pk.use = pl.pf.use = false;
+        if (f32_patch_forced() && pl.mode != 0) pl.pf.use = false;
+        // (GEMMs whose tiles are 16x16x4 MFMAs add in another order than the patch kernel's 32x32x2)
+        if (keep_bits && g_force_bm == 0) { pl.pk.use = false; if (rows16) pl.pf.use = false; }
         if (g_force_bm == 0) {
             pl.pk.use = pl.pk.use && Co > 16 && pl.pk.us * 1.05 < old_us && !(pl.pf.use && pl.pf.us < pl.pk.us);
             pl.pf.use = pl.pf.use && !pl.pk.use && Co > 16 && pl.pf.us * 1.05 < old_us;
         } else {
-            if (split_patch_forced()) pl.pk.use = false; else pl.pf.use = false;
+            if (split_packets_forced()) pl.pf.use = false; else pl.pk.use = false;
         }
         if (pl.pk.use) { if (pl.pk.ws_bytes > pl.ws_bytes) pl.ws_bytes = pl.pk.ws_bytes; return pl; }
         if (pl.pf.use) return pl;

@@ -15,6 +15,11 @@
 // [tap][row][16]) and a step's tile is split on its way into a two-slot ring, four elements per thread.
 // One barrier per tap.
 //
+// The same kernel with fp32 parts and MFMAs (SPLIT = false) serves the forward passes whose bits have to
+// stay those of the fp32 tap kernel: each output's products are added in that kernel's order. There the
+// matrix units are the bound (32x32x2: 8/3 of the time), and what it gains is the tap kernel's gather per
+// tap and its waits.
+//
 // Measured at N = 128 (whole operator, fp32 MFMA kernel before): 384 <- 384 channels 3x3 at 13x13
 // backward-data 0.50 -> 0.28 ms (204 TFLOP/s; 0.31 with the operands packed in scratch), 96 -> 128 3x3 at
 // 28x28 forward 0.236 -> 0.140, 96 <- 256 5x5 at 27x27 backward-data 1.01 -> 0.69 (365 tiles on 256 CUs).
@@ -27,8 +32,11 @@ namespace {
 
 using namespace packets;
 
-constexpr int BN = 256, POS = 704, NT = 512;      // pixels, patch positions, threads of a workgroup
-constexpr int TASKS = (2 * POS + NT - 1) / NT;    // fill tasks (position, channel half) per thread
+// Pixels of a workgroup's tile and positions its patch may have. Split: one workgroup of eight wavefronts on
+// a CU; fp32: two of four wavefronts, whose waits and epilogues fall into each other's MFMAs (384 <- 256
+// channels 3x3 at 13x13, N = 128 forward: 0.309 ms with one of eight, 0.301 with two of four).
+constexpr int pixels_of(bool split) { return split ? 256 : 128; }
+constexpr int positions_of(bool split) { return split ? 704 : 504; }
 
 struct PatchF32Params {
     const float* a;             // repacked filter
@@ -78,17 +86,23 @@ __global__ __launch_bounds__(256) void pack_filter_f32_kernel(const FilterPack q
     *reinterpret_cast<floatx4*>(q.a + (size_t)t * 4) = v;
 }
 
-template <int TM, int WM>
+// SPLIT: three bf16 parts x two channel halves per row / position; else fp32: (groups of four MFMA steps)
+// x (lane halves). 16-byte packets either way.
+template <bool SPLIT, int TM, int WM>
 struct PatchTile {
-    static constexpr int BM = TM * WM * 32, WN = 8 / WM, TN = BN / (WN * 32);
-    static constexpr int A_BYTES = PLANES * 2 * BM * 16, P_BYTES = PLANES * 2 * POS * 16;
+    static constexpr int BN = pixels_of(SPLIT), POS = positions_of(SPLIT), WAVES = SPLIT ? 8 : 4, NT = WAVES * 64;
+    static constexpr int TASKS = (2 * POS + NT - 1) / NT;                      // fill tasks (position, channel half) per thread
+    static constexpr int BM = TM * WM * 32, WN = WAVES / WM, TN = BN / (WN * 32);
+    static constexpr int AL = (BM * 4 + NT - 1) / NT;                          // filter loads (four channels of a row) per thread and step
+    static constexpr int PACKETS = SPLIT ? PLANES * 2 : 4;
+    static constexpr int A_BYTES = PACKETS * BM * 16, P_BYTES = PACKETS * POS * 16;
     static constexpr int LDS = 2 * A_BYTES + 2 * P_BYTES + 512 + BM * 4;       // + spare half KB + bias
 };
 
-template <bool MINUS, bool D2S, bool FUSED, int TM, int WM>
-__global__ __launch_bounds__(NT, 2) void igemm_patch_f32_kernel(const PixParams p, const PatchF32Params q) {
-    typedef PatchTile<TM, WM> T;
-    constexpr int TN = T::TN, WN = T::WN;
+template <bool SPLIT, bool MINUS, bool D2S, bool FUSED, int TM, int WM>
+__global__ __launch_bounds__(SPLIT ? 512 : 256, 2) void igemm_patch_f32_kernel(const PixParams p, const PatchF32Params q) {
+    typedef PatchTile<SPLIT, TM, WM> T;
+    constexpr int TN = T::TN, WN = T::WN, BN = T::BN, POS = T::POS, NT = T::NT, TASKS = T::TASKS;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned char* patch = smem + 2 * T::A_BYTES;
     unsigned char* spare = patch + 2 * T::P_BYTES;
@@ -133,7 +147,7 @@ __global__ __launch_bounds__(NT, 2) void igemm_patch_f32_kernel(const PixParams 
         const int n = fastdiv(v, q.div_bands), w = (v - n * q.bands) * q.Wb + q.w_base + pcol;
         const bool ok = task && n < p.N && (unsigned)h < (unsigned)p.Hi && (unsigned)w < (unsigned)p.Wi;
         src[j] = ok ? (n * p.in_ns + half[j] * 8 * p.HiWi + h * p.Wi + w) * 4 : -1;
-        dst[j] = task ? (half[j] * POS + pos) * 16 : -1;
+        dst[j] = task ? (half[j] * (SPLIT ? POS : 2 * POS) + pos) * 16 : -1;
     }
     // the pixels this lane multiplies: patch position at tap offset 0, and its place in the output
     int pbase[TN], opix[TN];
@@ -164,7 +178,12 @@ __global__ __launch_bounds__(NT, 2) void igemm_patch_f32_kernel(const PixParams 
     auto store_patch = [&](int buf) {
 #pragma unroll
         for (int j = 0; j < TASKS; ++j)
-            if (dst[j] >= 0) {
+            if (!SPLIT && dst[j] >= 0) {
+                // channel 8 * half + e is reduction index 2 * ks + l of the group: step group `half`, lane half l = e & 1
+                const floatx4 even = {breg[j][0], breg[j][2], breg[j][4], breg[j][6]}, odd = {breg[j][1], breg[j][3], breg[j][5], breg[j][7]};
+                *reinterpret_cast<floatx4*>(patch + buf * T::P_BYTES + dst[j]) = even;
+                *reinterpret_cast<floatx4*>(patch + buf * T::P_BYTES + dst[j] + POS * 16) = odd;
+            } else if (SPLIT && dst[j] >= 0) {
                 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
                 u32x4 pk[PLANES];
 #pragma unroll
@@ -179,22 +198,39 @@ __global__ __launch_bounds__(NT, 2) void igemm_patch_f32_kernel(const PixParams 
                     *reinterpret_cast<u32x4*>(patch + buf * T::P_BYTES + dst[j] + pl * 2 * POS * 16) = pk[pl];
             }
     };
-    // filter tile of a step: four channels of one row per thread
-    const bool a_lane = tid < T::BM * 4;
-    const unsigned a_voff = a_lane ? (unsigned)(tid * 16) : 0x80000000u;
-    const int a_dst = ((tid >> 1) & 1) * T::BM * 16 + (tid >> 2) * 16 + (tid & 1) * 8;
+    // filter tile of a step: four channels of T::AL rows per thread
+    struct FilterRegs { floatx4 f[T::AL]; };
     auto load_a = [&](int step) {
-        return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(ra, a_voff, (rt * q.cgs * q.taps + step) * T::BM * 64, 0));
-    };
-    auto store_a = [&](const floatx4& f, int slot) {
-        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-        uint32_t p01[PLANES], p23[PLANES];
-        split_pair(f[0], f[1], p01);
-        split_pair(f[2], f[3], p23);
-        unsigned char* base = a_lane ? smem + slot * T::A_BYTES + a_dst : spare + lane * 8;
+        FilterRegs r;
 #pragma unroll
-        for (int pl = 0; pl < PLANES; ++pl)
-            *reinterpret_cast<u32x2*>(base + (a_lane ? pl * 2 * T::BM * 16 : 0)) = u32x2{p01[pl], p23[pl]};
+        for (int j = 0; j < T::AL; ++j) {
+            const int t = tid + j * NT;
+            r.f[j] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(ra, t < T::BM * 4 ? (unsigned)(t * 16) : 0x80000000u,
+                                                                                    (rt * q.cgs * q.taps + step) * T::BM * 64, 0));
+        }
+        return r;
+    };
+    auto store_a = [&](const FilterRegs& r, int slot) {
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        typedef float floatx2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int j = 0; j < T::AL; ++j) {
+            const int t = tid + j * NT;
+            const bool mine = (T::BM * 4) % NT == 0 || t < T::BM * 4;       // the others write to the spare half KB
+            const int a_dst = ((t >> 1) & 1) * (SPLIT ? 1 : 2) * T::BM * 16 + (t >> 2) * 16 + (t & 1) * 8;
+            unsigned char* base = mine ? smem + slot * T::A_BYTES + a_dst : spare + lane * 8;
+            if constexpr (!SPLIT) {
+                *reinterpret_cast<floatx2*>(base) = floatx2{r.f[j][0], r.f[j][2]};
+                *reinterpret_cast<floatx2*>(base + (mine ? T::BM * 16 : 0)) = floatx2{r.f[j][1], r.f[j][3]};
+            } else {
+                uint32_t p01[PLANES], p23[PLANES];
+                split_pair(r.f[j][0], r.f[j][1], p01);
+                split_pair(r.f[j][2], r.f[j][3], p23);
+#pragma unroll
+                for (int pl = 0; pl < PLANES; ++pl)
+                    *reinterpret_cast<u32x2*>(base + (mine ? pl * 2 * T::BM * 16 : 0)) = u32x2{p01[pl], p23[pl]};
+            }
+        }
     };
 
     floatx16 hi[TM][TN], lo[TM][TN];
@@ -216,6 +252,25 @@ __global__ __launch_bounds__(NT, 2) void igemm_patch_f32_kernel(const PixParams 
     auto multiply = [&](int step, int buf, int tap_off) {
         const unsigned char* sa = smem + (step & 1) * T::A_BYTES + a_off;
         const unsigned char* sb = patch + buf * T::P_BYTES + tap_off;
+        if constexpr (!SPLIT) {
+            // the fp32 MFMAs of the tap kernel, in its order: an output's sum has the same bits
+#pragma unroll
+            for (int kg = 0; kg < 2; ++kg) {
+                floatx4 af[TM], bf[TN];
+#pragma unroll
+                for (int a = 0; a < TM; ++a) af[a] = *reinterpret_cast<const floatx4*>(sa + (kg * 2 * T::BM + a * 32) * 16);
+#pragma unroll
+                for (int b = 0; b < TN; ++b) bf[b] = *reinterpret_cast<const floatx4*>(sb + pbase[b] + kg * 2 * POS * 16);
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int a = 0; a < TM; ++a)
+#pragma unroll
+                        for (int b = 0; b < TN; ++b)
+                            hi[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[a][ks], bf[b][ks], hi[a][b], 0, 0, 0);
+            }
+            return;
+        } else {
         bf16x8 av[PLANES][TM], bv[PLANES][TN];
 #pragma unroll
         for (int pl = 0; pl < PLANES; ++pl) {
@@ -237,6 +292,7 @@ __global__ __launch_bounds__(NT, 2) void igemm_patch_f32_kernel(const PixParams 
         mul(1, 1, lo);
         mul(0, 2, lo);
         mul(2, 0, lo);
+        }
     };
 
     const int n_steps = q.cgs * q.taps;
@@ -252,7 +308,7 @@ __global__ __launch_bounds__(NT, 2) void igemm_patch_f32_kernel(const PixParams 
         // waiting for the latter does not wait for the former
         meet();
         {
-            const floatx4 f = load_a(step + 1);      // (one past the last step: still inside the buffer's range check)
+            const FilterRegs f = load_a(step + 1);      // (one past the last step: still inside the buffer's range check)
             load_patch(cg + 1);
             __builtin_amdgcn_sched_barrier(0);       // requests first: they have the whole step to arrive
             multiply(step, buf, tap_offset());
@@ -262,7 +318,7 @@ __global__ __launch_bounds__(NT, 2) void igemm_patch_f32_kernel(const PixParams 
         for (int tap = 1; tap < q.taps; ++tap) {
             if (++tc == p.St) { tc = 0; ++tr; }
             meet();
-            const floatx4 f = load_a(step + 1);
+            const FilterRegs f = load_a(step + 1);
             __builtin_amdgcn_sched_barrier(0);
             multiply(step, buf, tap_offset());
             store_a(f, (step + 1) & 1);
@@ -272,8 +328,8 @@ __global__ __launch_bounds__(NT, 2) void igemm_patch_f32_kernel(const PixParams 
     }
 
     // infinities and NaNs: again, as plain fp32 sums (conv_packets.hip)
-    unsigned long long bad = join_sets<TM, TN>(hi, lo);
-    if (__builtin_expect(__any(bad != 0), 0)) {
+    unsigned long long bad = SPLIT ? join_sets<TM, TN>(hi, lo) : 0ull;
+    if (SPLIT && __builtin_expect(__any(bad != 0), 0)) {
         while (bad) {
             const int idx = __ffsll((long long)bad) - 1;
             bad &= bad - 1;
@@ -304,46 +360,50 @@ __global__ __launch_bounds__(NT, 2) void igemm_patch_f32_kernel(const PixParams 
                                                      bias_s, i0, 0x7fffffff);
 }
 
-template <bool MINUS, bool D2S, bool FUSED, int TM, int WM>
+template <bool SPLIT, bool MINUS, bool D2S, bool FUSED, int TM, int WM>
 hipError_t launch_main(const PixParams& p, const PatchF32Params& q, hipStream_t st) {
-    typedef PatchTile<TM, WM> T;
+    typedef PatchTile<SPLIT, TM, WM> T;
     const long long total = (long long)p.tiles_i * p.tiles_pix;
     if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&igemm_patch_f32_kernel<MINUS, D2S, FUSED, TM, WM>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&igemm_patch_f32_kernel<SPLIT, MINUS, D2S, FUSED, TM, WM>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS);
     if (e != hipSuccess) return e;
     ProbeScope probe(st);
     (void)hipGetLastError();   // drop stale status left by earlier, unrelated runtime calls
-    hipLaunchKernelGGL((igemm_patch_f32_kernel<MINUS, D2S, FUSED, TM, WM>), dim3((unsigned)total), dim3(NT), T::LDS, st, p, q);
+    hipLaunchKernelGGL((igemm_patch_f32_kernel<SPLIT, MINUS, D2S, FUSED, TM, WM>), dim3((unsigned)total), dim3(T::NT), T::LDS, st, p, q);
     return hipGetLastError();
 }
 
-template <bool MINUS, bool D2S, bool FUSED>
+template <bool SPLIT, bool MINUS, bool D2S, bool FUSED>
 hipError_t by_tile(const PixParams& p, const PatchF32Params& q, int bm, hipStream_t st) {
     switch (bm) {
-        case 128: return launch_main<MINUS, D2S, FUSED, 2, 2>(p, q, st);
-        case 96:  return launch_main<MINUS, D2S, FUSED, 3, 1>(p, q, st);
-        case 64:  return launch_main<MINUS, D2S, FUSED, 2, 1>(p, q, st);
-        case 32:  return launch_main<MINUS, D2S, FUSED, 1, 1>(p, q, st);
+        case 128: return launch_main<SPLIT, MINUS, D2S, FUSED, 2, 2>(p, q, st);
+        case 96:  return launch_main<SPLIT, MINUS, D2S, FUSED, 3, 1>(p, q, st);
+        case 64:  return launch_main<SPLIT, MINUS, D2S, FUSED, 2, 1>(p, q, st);
+        case 32:  return launch_main<SPLIT, MINUS, D2S, FUSED, 1, 1>(p, q, st);
         default: return hipErrorInvalidValue;
     }
 }
 
-// cycles: MFMA time of a step on a SIMD, two wavefronts; eff: the share of it that the tile reaches
+// cycles: MFMA time of a step on a SIMD; eff: the share of it that the tile reaches (split: six bf16 products,
+// two wavefronts per SIMD; fp32: one, and half the pixels)
 struct RowTile { int bm, cycles; float eff; };
-constexpr RowTile kRowTiles[] = {{128, 1536, 0.72f}, {96, 1152, 0.66f}, {64, 768, 0.58f}, {32, 384, 0.45f}};
+constexpr RowTile kSplitTiles[] = {{128, 1536, 0.72f}, {96, 1152, 0.66f}, {64, 768, 0.58f}, {32, 384, 0.45f}};
+constexpr RowTile kF32Tiles[] = {{128, 2048, 0.90f}, {96, 1536, 0.88f}, {64, 1024, 0.84f}, {32, 512, 0.75f}};
 
 }  // namespace
 
 // How the layer would run here and the expected time (conv_igemm.hip compares). Pure host arithmetic.
-PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s) {
+PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s, bool split) {
     PatchF32Plan k{};
+    k.split = split;
     if (p.Rt * p.St < 2 || p.Ci < 8 || p.in_bytes == 0 || p.g_mul_h != 1 || p.g_mul_w != 1) return k;
+    const int BN = pixels_of(split), POS = positions_of(split);
     // bands of columns: as few as keep the worst tile's patch within the LDS buffers
     for (int bands = 1; bands <= 32; ++bands) {
         const int wb = (p.Wo + bands - 1) / bands, pw = wb + p.St - 1;
         if (bands > 1 && (wb < 8 || (long long)(bands - 1) * wb >= p.Wo)) break;
-        const long long rows = (BN + wb - 2) / wb + 1;                       // output rows that 256 pixels can touch
+        const long long rows = (BN + wb - 2) / wb + 1;                       // output rows that a tile can touch
         const long long crossings = (rows - 1 + p.Ho - 1) / p.Ho;            // image (or band) boundaries among them
         if ((rows + crossings * (p.Rt - 1) + p.Rt - 1) * pw > POS) continue;
         k.bands = bands; k.Wb = wb; k.PW = pw;
@@ -353,13 +413,15 @@ PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s) {
     if (!k.bands || mv > 0x7fffff00LL) return k;
     k.cgs = (p.Ci + 15) / 16;
     const long long tp = (mv + BN - 1) / BN;
-    for (const RowTile& t : kRowTiles) {
+    for (int i = 0; i < 4; ++i) {
+        const RowTile& t = split ? kSplitTiles[i] : kF32Tiles[i];
         const long long ti = (p.Co + t.bm - 1) / t.bm;
         const long long a_bytes = ti * k.cgs * p.Rt * p.St * t.bm * 64;
         if (a_bytes >= 0x7fffffffLL || ti * tp > 0x7fffffffLL) continue;
-        const double x = (double)(ti * tp) / 256.0;
-        const double load = 0.3 * x + 0.7 * (double)((ti * tp + 255) / 256);         // one workgroup per CU
-        const double us = 10.0 + load * (k.cgs * (p.Rt * p.St * t.cycles / t.eff + 1000.0) + (d2s ? 50000.0 : 10000.0)) / 2.2e3;
+        const double x = (double)(ti * tp) / 256.0, ceil_x = (double)((ti * tp + 255) / 256);
+        // one workgroup per CU at a time (the clock rises a little as CUs run dry), or two
+        const double load = split ? 0.3 * x + 0.7 * ceil_x : x <= 1.0 ? 1.3 : 0.3 * x + 0.7 * ceil_x;
+        const double us = 10.0 + load * (k.cgs * (p.Rt * p.St * t.cycles / t.eff + 1000.0) + (d2s ? 50000.0 : 10000.0)) / (split ? 2.2e3 : 2.4e3);
         if (!k.use || us < k.us) {
             k.use = true; k.us = us;
             k.bm = t.bm; k.tiles_i = (int)ti; k.tiles_pix = (int)tp;
@@ -394,9 +456,13 @@ hipError_t launch_patch_f32(PixParams p, const PatchF32Plan& k, int mode, const 
     q.div_img = make_fastdiv(q.img_rows); q.div_st = make_fastdiv(p.St);
     p.tiles_i = k.tiles_i; p.tiles_pix = k.tiles_pix;
     const bool fused = p.bias || p.relu || p.mask;
-    if (mode == 0) return fused ? by_tile<false, false, true>(p, q, k.bm, st) : by_tile<false, false, false>(p, q, k.bm, st);
-    if (mode == 1) return fused ? by_tile<true, false, true>(p, q, k.bm, st) : by_tile<true, false, false>(p, q, k.bm, st);
-    return fused ? by_tile<true, true, true>(p, q, k.bm, st) : by_tile<true, true, false>(p, q, k.bm, st);
+    if (!k.split) {
+        if (mode != 0) return hipErrorInvalidValue;
+        return fused ? by_tile<false, false, false, true>(p, q, k.bm, st) : by_tile<false, false, false, false>(p, q, k.bm, st);
+    }
+    if (mode == 0) return fused ? by_tile<true, false, false, true>(p, q, k.bm, st) : by_tile<true, false, false, false>(p, q, k.bm, st);
+    if (mode == 1) return fused ? by_tile<true, true, false, true>(p, q, k.bm, st) : by_tile<true, true, false, false>(p, q, k.bm, st);
+    return fused ? by_tile<true, true, true, true>(p, q, k.bm, st) : by_tile<true, true, true, false>(p, q, k.bm, st);
 }
 
 }  // namespace pix

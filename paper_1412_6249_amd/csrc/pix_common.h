@@ -625,7 +625,7 @@ hipError_t dispatch_gemm1x1(const PixParams& p, int dtype, bool trans, int tm, i
 
 // fp32 layers with a unit-stride gather on bf16 parts split in LDS (conv_patch_f32.hip); mode and w as
 // below. launch_patch_f32 repacks the filter (fp32) into ws.
-PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s);
+PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s, bool split);
 hipError_t launch_patch_f32(PixParams p, const PatchF32Plan& k, int mode, const void* w, int K, int C, void* ws, hipStream_t st);
 
 // fp32 layers on packed bf16 parts (conv_packets.hip). mode: 0 forward, 1 backward-data with unit

@@ -25,8 +25,9 @@ def _general(pa, on):
 
 
 def _forced(pa, route):
-    """route: "auto", "patch" (split in LDS), "packets" (packed parts) or "general" (fp32 MFMA kernels)."""
-    pa.purine_debug_force_tile(*{"auto": (0, 0), "patch": (-6, 0), "packets": (-7, 0), "general": (0, -1)}[route])
+    """route: "auto", "patch" (split in LDS), "packets" (packed parts), "patch_f32" (forward: the LDS kernel
+    with fp32 products) or "general" (fp32 MFMA kernels)."""
+    pa.purine_debug_force_tile(*{"auto": (0, 0), "patch": (-6, 0), "packets": (-7, 0), "patch_f32": (-8, 0), "general": (0, -1)}[route])
 
 
 def _run(pa, case, x, w, b, dy, act, prev):
@@ -67,7 +68,7 @@ def test_split_products_against_the_oracle_and_the_general_kernels(case):
     stride, pad = case[7], case[8]
     got = {}
     try:
-        for route in ("general", "patch", "packets", "auto"):
+        for route in ("general", "patch", "packets", "patch_f32", "auto"):
             _forced(pa, route)
             got[route], _ = _run(pa, case, x, w, b, dy, act, prev)
     finally:
@@ -78,7 +79,12 @@ def test_split_products_against_the_oracle_and_the_general_kernels(case):
     unit = stride == 1
     sh, sw = (stride, stride) if isinstance(stride, int) else stride
     taps_b = -(-case[5] // sh) * -(-case[6] // sw)           # taps of the phase-folded backward pass; one: not for these kernels
-    for route in ("patch", "packets", "auto"):
+    # the fp32 patch kernel adds in the order of the tap kernel's 32x32x2 tiles: the same bits (16-row tiles,
+    # which GEMMs of 33 .. 48 and 81 .. 96 rows take, add in another one)
+    K = case[4]
+    if unit and not (K <= 16 or 33 <= K <= 48 or 81 <= K <= 96):
+        assert all(np.array_equal(g, o) for g, o in zip(got["patch_f32"][:2], got["general"][:2])), case
+    for route in ("patch", "packets", "patch_f32", "auto"):
         differs = [not np.array_equal(g, o) for g, o in zip(got[route], got["general"])]
         if route == "patch":             # a strided forward gather is not for this one
             assert (differs[1] or not unit) and (differs[2] or taps_b == 1), case
