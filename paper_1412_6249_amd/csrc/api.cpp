@@ -664,6 +664,36 @@ int check_fc(const purine_tensor* x, const purine_tensor* w, const purine_tensor
 }
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
+// The fp32 passes run as one streaming GEMM each (operands below 2^31 bytes); pass: PURINE_CONV_FWD
+// y[n][k] over c, PURINE_CONV_BWD_DATA dx[n][c] over k, PURINE_CONV_BWD_WEIGHT dw[k][c] over n.
+StreamPlan fc_stream_plan(int pass, int64_t N, int64_t C, int64_t K) {
+    StreamPlan none{};
+    if (buffer_loads_disabled() || N * C * 4 >= 0x7fffffffll || K * C * 4 >= 0x7fffffffll || N * K * 4 >= 0x7fffffffll) return none;
+    if (pass == PURINE_CONV_FWD) return pix::plan_stream(N, K, C, true);
+    if (pass == PURINE_CONV_BWD_DATA) return pix::plan_stream(N, C, K, true);
+    // A short reduction leaves nothing but the write of dw, which the general kernel does as well or better
+    // (9216 x 4096: N = 1 153 against 37 us, N = 16 40 against 37, N = 32 46 either way, N = 64 56 against 66).
+    return N > 32 ? pix::plan_stream(K, C, N, true) : none;
+}
+// The weight gradient's operands are small against its result, and every one of their elements is needed by
+// dozens of tiles: laid out as bf16 parts first, the kernel that copies packets straight into LDS takes 79 us
+// (+ 6 for the layout) where the streaming one splits the same elements again and again in 90 (9216 x 4096, N = 128).
+PacketPlan fc_packet_plan(int64_t N, int64_t C, int64_t K, const StreamPlan& k) {
+    PacketPlan pk = pix::plan_packets_matrix(K, C, N);
+    pk.use = pk.use && N * 8 <= K && N * 8 <= C && pk.us < k.us;
+    return pk;
+}
+size_t fc_general_workspace_bytes(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype);
+// aliasing and scratch of such a pass: what the general composition asks for
+int fc_stream_checks(int pass, const purine_tensor* out, const purine_tensor* a, const purine_tensor* b, int64_t N, int64_t C, int64_t K,
+                     const void* ws, size_t ws_bytes) {
+    if (overlaps(out, a) || overlaps(out, b)) return PURINE_E_LAYOUT;
+    const size_t need = purine_fc_workspace_bytes(pass, N, C, K, PURINE_F32);
+    if (need && (!ws || ws_bytes < need)) return PURINE_E_WORKSPACE;
+    if (need && (((uintptr_t)ws) & 15u)) return PURINE_E_LAYOUT;
+    return PURINE_OK;
+}
+
 }  // namespace
 
 size_t purine_grouped_conv_workspace_bytes(int pass, const purine_conv_desc* desc, int groups,
@@ -724,6 +754,22 @@ int purine_grouped_conv_bwd_weight(const purine_conv_desc* desc, int groups, con
 }
 
 size_t purine_fc_workspace_bytes(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype) {
+    const size_t general = fc_general_workspace_bytes(pass, N, C, K, dtype);
+    if (dtype != PURINE_F32 || N < 1 || C < 1 || K < 1 || N >= (1ll << 31) || C >= (1ll << 31) || K >= (1ll << 31) || pass < PURINE_CONV_FWD ||
+        pass > PURINE_CONV_BWD_WEIGHT_BIAS)
+        return general;
+    const StreamPlan k = fc_stream_plan(pass, N, C, K);
+    if (!k.use) return general;
+    size_t need = k.part_bytes > general ? k.part_bytes : general;
+    if (pass >= PURINE_CONV_BWD_WEIGHT) {
+        const PacketPlan pk = fc_packet_plan(N, C, K, k);
+        if (pk.use && pk.ws_bytes > need) need = pk.ws_bytes;
+    }
+    return need;
+}
+
+namespace {
+size_t fc_general_workspace_bytes(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype) {
     if (N < 1 || C < 1 || K < 1 || !is_float_dtype(dtype)) return 0;
     // one convolution geometry serves the three fp32 passes: a 1x1 filter bank [N, K] over the plane [1, K, 1, C]
     const int64_t xd[4] = {1, K, 1, C}, wd[4] = {N, K, 1, 1};
@@ -750,6 +796,7 @@ size_t purine_fc_workspace_bytes(int pass, int64_t N, int64_t C, int64_t K, int3
         default: return 0;
     }
 }
+}  // namespace
 
 int purine_fc_fwd(const purine_tensor* x, const purine_tensor* w, const purine_tensor* b, purine_tensor* y,
                   void* ws, size_t ws_bytes, void* hip_stream) {
@@ -779,6 +826,16 @@ int purine_fc_fwd(const purine_tensor* x, const purine_tensor* w, const purine_t
         return hip_status(launch_fc_finish_bf16((const float*)acc.data, b ? b->data : nullptr, y->data, (int)N, (int)K,
                                                 (hipStream_t)hip_stream));
     }
+    const StreamPlan k = fc_stream_plan(PURINE_CONV_FWD, x->dim[0], x->dim[1], w->dim[0]);
+    if (k.use) {
+        if ((rc = fc_stream_checks(PURINE_CONV_FWD, y, x, w, x->dim[0], x->dim[1], w->dim[0], ws, ws_bytes))) return rc;
+        const bool second = k.splits > 1;              // the pass that adds the splits also adds the bias
+        hipError_t e = pix::launch_stream_gemm(k, x->data, true, w->data, true, y->data, second && b ? b->data : nullptr, 0.0f, x->dim[0], w->dim[0],
+                                               x->dim[1], ws, (hipStream_t)hip_stream);
+        if (e == hipSuccess && b && !second)
+            e = launch_bias_rows((const float*)b->data, (float*)y->data, (int)y->dim[0], (int)y->dim[1], (hipStream_t)hip_stream);
+        return hip_status(e);
+    }
     if ((rc = conv_bwd_weight_impl(&kUnitConv, &wp, &xp, &yf, nullptr, 0.0f, ws, ws_bytes, hip_stream))) return rc;
     if (b)
         return hip_status(launch_bias_rows((const float*)b->data, (float*)y->data, (int)y->dim[0], (int)y->dim[1],
@@ -802,6 +859,12 @@ int purine_fc_bwd_data(const purine_tensor* dy, const purine_tensor* w, purine_t
             return hip_status(launch_fc_dgrad_bf16(dy->data, w->data, dx->data, (int)dy->dim[0], (int)w->dim[0],
                                                    (int)w->dim[1], ws, (hipStream_t)hip_stream));
         }
+    }
+    const StreamPlan k = dy->dtype == PURINE_F32 ? fc_stream_plan(PURINE_CONV_BWD_DATA, dy->dim[0], w->dim[1], w->dim[0]) : StreamPlan{};
+    if (k.use) {
+        if ((rc = fc_stream_checks(PURINE_CONV_BWD_DATA, dx, dy, w, dy->dim[0], w->dim[1], w->dim[0], ws, ws_bytes))) return rc;
+        return hip_status(pix::launch_stream_gemm(k, dy->data, true, w->data, false, dx->data, nullptr, 0.0f, dy->dim[0], w->dim[1], w->dim[0], ws,
+                                                  (hipStream_t)hip_stream));
     }
     const purine_tensor wp = as_plane(w), dyf = as_filter(dy);
     purine_tensor dxp = as_plane(dx);
@@ -850,9 +913,16 @@ int purine_fc_bwd_weight(const purine_tensor* x, const purine_tensor* dy, purine
     } else {
         // dw[k][c] = sum_n dy[n][k] x[n][c]: the backward-data contraction with dy := x (plane of N
         // channels) and w := dy (filter bank [N x K])
+        const StreamPlan k = fc_stream_plan(PURINE_CONV_BWD_WEIGHT, N, C, K);
         const purine_tensor xp = as_plane(x);
         purine_tensor dwp = as_plane(dw);
-        if ((rc = conv_bwd_data_impl(&kUnitConv, &xp, &dy4, nullptr, &dwp, beta, ws, ws_bytes, hip_stream))) return rc;
+        if (k.use) {
+            if ((rc = fc_stream_checks(PURINE_CONV_BWD_WEIGHT, dw, x, dy, N, C, K, ws, ws_bytes))) return rc;
+            const PacketPlan pk = fc_packet_plan(N, C, K, k);
+            hipError_t e = pk.use ? pix::launch_packets_matrix(pk, dy->data, x->data, dw->data, beta, K, C, N, ws, (hipStream_t)hip_stream)
+                                  : pix::launch_stream_gemm(k, dy->data, false, x->data, false, dw->data, nullptr, beta, K, C, N, ws, (hipStream_t)hip_stream);
+            if (e != hipSuccess) return hip_status(e);
+        } else if ((rc = conv_bwd_data_impl(&kUnitConv, &xp, &dy4, nullptr, &dwp, beta, ws, ws_bytes, hip_stream))) return rc;
     }
     if (db)   // column sums of dy
         return hip_status(launch_fc_bias_bwd(dy->dtype, dy->data, (float*)db->data, (int)N, (int)K, beta,

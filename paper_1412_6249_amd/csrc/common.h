@@ -81,6 +81,23 @@ struct PatchF32Plan {
     double us;
 };
 
+// Plan of the streaming fp32 GEMM on bf16 parts (gemm_stream_f32.hip): rows x columns of the output over a
+// reduction, split over workgroups where scratch for partial outputs is at hand.
+struct StreamPlan {
+    bool use;
+    int bm, tiles_i, tiles_pix, steps, splits, steps_per_split;
+    size_t part_bytes;          // partial outputs (0 without a split)
+    double us;                  // expected time
+};
+namespace pix {
+StreamPlan plan_stream(long long rows, long long cols, long long K, bool may_split);
+PacketPlan plan_packets_matrix(long long rows, long long cols, long long K);
+hipError_t launch_packets_matrix(const PacketPlan& k, const void* a, const void* b, void* out, float beta, long long rows, long long cols, long long K,
+                                 void* ws, hipStream_t st);
+hipError_t launch_stream_gemm(const StreamPlan& k, const void* a, bool a_in, const void* b, bool b_in, void* out, const void* bias, float beta,
+                              long long rows, long long cols, long long K, void* ws, hipStream_t st);
+}
+
 // Launch plan of the forward / backward-data implicit GEMM: same answer for the workspace query and
 // for the launch.
 struct PixPlan {

@@ -292,16 +292,16 @@ hipError_t by_tile(const PixParams& p, const PacketParams& q, int bm, int bn, hi
 // the last-level cache, and costs a launch; the depth-to-space epilogue scatters single elements.
 // Against sweeps of all tiles and split counts on twelve layers the choice is within 5 % of the best
 // on most and 10 % on the worst.
-PacketPlan plan_packets(const PixParams& p, bool d2s) {
+PacketPlan plan_packets(const PixParams& p, bool d2s, bool any_taps) {
     PacketPlan k{};
     const long long steps = (long long)((p.Ci + 15) / 16) * p.Rt * p.St;
     const long long cb = (p.Ci + 15) / 16 * 2;
     const long long b_bytes = (long long)p.N * cb * p.HiWi * 16 * PLANES;
-    if (p.Rt * p.St < 2 || p.Ci < 8 || b_bytes >= 0x7fffffffLL || p.in_bytes == 0) return k;
+    if ((p.Rt * p.St < 2 && !any_taps) || p.Ci < 8 || b_bytes >= 0x7fffffffLL || p.in_bytes == 0) return k;
     // a copy of the gathered tensor in the scratch: only for strided gathers and for launches too small to
     // fill the chip without a split reduction
     const bool strided = p.g_mul_h > 1 || p.g_mul_w > 1;
-    if (!strided && !split_packets_forced() && ((p.Co + 127) / 128) * (((long long)p.M + 255) / 256) >= 128) return k;
+    if (!strided && !any_taps && !split_packets_forced() && ((p.Co + 127) / 128) * (((long long)p.M + 255) / 256) >= 128) return k;
     const double ghz = 2.2e3;                             // cycles per microsecond
     const double out_bytes = (double)p.M * p.Co * 4.0;
     for (const PacketTile& t : kTiles) {
@@ -387,6 +387,25 @@ hipError_t launch_packets(PixParams p, const PacketPlan& k, int mode, const void
     if (mode == 0) return fused ? by_tile<false, false, true>(p, q, k.bm, k.bn, st) : by_tile<false, false, false>(p, q, k.bm, k.bn, st);
     if (mode == 1) return fused ? by_tile<true, false, true>(p, q, k.bm, k.bn, st) : by_tile<true, false, false>(p, q, k.bm, k.bn, st);
     return fused ? by_tile<true, true, true>(p, q, k.bm, k.bn, st) : by_tile<true, true, false>(p, q, k.bm, k.bn, st);
+}
+
+// out[rows][cols] = beta * out + sum over k of a[k][row] * b[k][col], dense (the fully-connected weight
+// gradient: k runs over the batch): the single-tap backward-data pass over one image of K channels.
+static PixParams matrix_params(long long rows, long long cols, long long K) {
+    PixParams p{};
+    p.N = 1; p.Ci = (int)K; p.Hi = 1; p.Wi = p.HiWi = (int)cols; p.Co = (int)rows; p.Ho = 1; p.Wo = p.HoWo = p.M = (int)cols;
+    p.Rt = p.St = p.R = p.S = p.sh = p.sw = p.g_mul_h = p.g_mul_w = p.phases = 1;
+    p.div_howo = p.div_wo = make_fastdiv((uint32_t)cols); p.div_phases = p.div_sw = make_fastdiv(1);
+    p.in_ns = (int)(K * cols); p.out_ns = (int)(rows * cols);
+    p.in_bytes = (unsigned)(K * cols * 4); p.out_bytes = (unsigned)(rows * cols * 4);      // both below 2^31 (the caller's check)
+    return p;
+}
+PacketPlan plan_packets_matrix(long long rows, long long cols, long long K) { return plan_packets(matrix_params(rows, cols, K), false, true); }
+hipError_t launch_packets_matrix(const PacketPlan& k, const void* a, const void* b, void* out, float beta, long long rows, long long cols, long long K,
+                                 void* ws, hipStream_t st) {
+    PixParams p = matrix_params(rows, cols, K);
+    p.in = b; p.out = out; p.beta = beta;
+    return launch_packets(p, k, 1, a, (int)K, (int)rows, ws, st);
 }
 
 }  // namespace pix

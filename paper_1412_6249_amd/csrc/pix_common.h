@@ -630,7 +630,7 @@ hipError_t launch_patch_f32(PixParams p, const PatchF32Plan& k, int mode, const 
 
 // fp32 layers on packed bf16 parts (conv_packets.hip). mode: 0 forward, 1 backward-data with unit
 // stride, 2 backward-data phase-folded; w: the KCRS filter.
-PacketPlan plan_packets(const PixParams& p, bool d2s);
+PacketPlan plan_packets(const PixParams& p, bool d2s, bool any_taps = false);
 hipError_t launch_packets(PixParams p, const PacketPlan& k, int mode, const void* w, int K, int C, void* ws, hipStream_t st);
 
 }  // namespace pix

@@ -245,3 +245,57 @@ def test_weight_gradient_in_the_static_scratch_takes_the_splits_in_turn():
     torch.cuda.synchronize()
     assert torch.equal(got, want)
     assert rel_l2(to_host(got), to_host(base)) <= 2e-6        # two fp32 sums of 75264 products each
+
+
+# N, C, K of a fully-connected layer: rows and columns one past a tile, reductions that are no whole step (and no
+# whole 16-byte packet), reductions split over workgroups, batches on either side of the weight gradient's rule,
+# operands laid out first (dw of the wide ones)
+FC_CASES = [(1, 4, 4), (33, 129, 65), (32, 130, 1001), (129, 1023, 257), (65, 2049, 1000), (40, 1026, 1030), (97, 640, 33), (128, 3000, 4100)]
+
+
+@pytest.mark.parametrize("case", FC_CASES)
+def test_fc_f32(case):
+    """The three passes against fp64, no less exact than the general kernels; twice the same bits; onto a previous
+    gradient; whole numbers exactly; infinities and NaN as a plain sum has them."""
+    import torch
+    import paper_1412_6249_amd as pa
+    from gpu_util import workspace
+    N, C, K = case
+    g = torch.Generator().manual_seed(N + C)
+    f = lambda *s: torch.randn(*s, generator=g)
+    x, w, b, dy, prev = f(N, C), f(K, C), f(K), f(N, K), f(K, C)
+
+    def run(x, w, b, dy, prev):
+        x, w, b, dy, acc = (t.cuda() for t in (x, w, b, dy, prev))
+        nan = lambda *s: torch.full(s, float("nan"), device="cuda")
+        ws = [workspace(pa.purine_fc_workspace_bytes(p, N, C, K)) for p in (0, 1, 2)]
+        y, dx, dw, db = nan(N, K), nan(N, C), nan(K, C), nan(K)
+        pa.purine_fc_fwd(x, w, b, y, ws=ws[0])
+        pa.purine_fc_bwd_data(dy, w, dx, ws=ws[1])
+        pa.purine_fc_bwd_weight(x, dy, dw, db, ws=ws[2])
+        pa.purine_fc_bwd_weight(x, dy, acc, None, beta=1.0, ws=ws[2])
+        torch.cuda.synchronize()
+        return [t.cpu() for t in (y, dx, dw, db, acc)]
+
+    def want(x, w, b, dy, prev):
+        x, w, b, dy, prev = (t.double() for t in (x, w, b, dy, prev))
+        return [x @ w.t() + b, dy @ w, dy.t() @ x, dy.sum(0), dy.t() @ x + prev]
+
+    err = lambda got, ref: [float((a.double() - r).norm() / r.norm()) for a, r in zip(got, ref)]
+    got, again, ref = run(x, w, b, dy, prev), run(x, w, b, dy, prev), want(x, w, b, dy, prev)
+    assert all(torch.equal(a, c) for a, c in zip(got, again))
+    _general(pa, True)
+    try:
+        plain = run(x, w, b, dy, prev)
+    finally:
+        _general(pa, False)
+    # 2^-24 per output is one rounding of the result, which either may have more of
+    assert all(e <= p + 2.0 ** -24 for e, p in zip(err(got, ref), err(plain, ref))), (err(got, ref), err(plain, ref))
+
+    ints = [t.mul(3).round() for t in (x, w, b, dy, prev)]       # sums far below 2^24: exact in any order
+    assert all(torch.equal(a.double(), r) for a, r in zip(run(*ints), want(*ints)))
+
+    bad = [t.clone() for t in (x, w, b, dy, prev)]
+    bad[0][N // 2, C - 1], bad[1][K - 1, 0], bad[3][0, K - 1] = float("inf"), float("nan"), float("-inf")
+    for a, r in zip(run(*bad), want(*bad)):
+        assert torch.equal(a.isnan(), r.isnan()) and torch.equal(a.isposinf(), r.isposinf()) and torch.equal(a.isneginf(), r.isneginf())
