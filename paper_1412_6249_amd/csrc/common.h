@@ -138,6 +138,7 @@ struct WgradPacketPlan {
     int real, PD, pairs, WB, XD;           // output positions of a band, padded to whole pairs; x positions (rows of WB)
     int bm, bn, tiles_i, tiles_j, steps, splits, steps_per_split;
     int db_rows;                           // rows of the bias gradient's partial sums
+    bool reduce_lanes;                     // second pass: wgrad_reduce_kernel, splits over lanes (few channels, many splits)
     size_t dy_group, x_group;              // bytes of a packed group and plane
     size_t part_bytes, ws_bytes;           // scratch: partial sums of dw, then the packed operands,
     size_t db_offset, copies;              // then the bias sums; all of it in whole copies of dw
@@ -146,6 +147,10 @@ struct WgradPacketPlan {
 WgradPacketPlan plan_wgrad_packets(const ConvGeom& g, size_t limit);
 hipError_t launch_wgrad_packets(const ConvGeom& g, const WgradPacketPlan& k, const void* x, const void* dy, float* dw, float* db, float beta, void* ws,
                                 size_t ws_bytes, hipStream_t st);
+// Second pass of a split weight gradient: partial sums [split][k][c][tap], or [split][tap][k][c] (tap_major), into
+// dw, and db_rows rows of K sums into db (db may be null). Reads in the partials' own order.
+hipError_t launch_wgrad_reduce(const float* partial, float* dw, int splits, float beta, bool tap_major, int K, int C, int RS,
+                               const float* db_partial, float* db, int db_rows, hipStream_t st);
 // scratch of purine_conv_bwd_weight_static
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 

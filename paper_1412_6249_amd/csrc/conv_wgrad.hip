@@ -601,19 +601,19 @@ hipError_t dispatch_bf16(WgradParams& p, const WgradPlan& plan, hipStream_t st) 
 // 16 consecutive elements; each of its 16 "split lanes" adds the partials s = lane, lane+16, ... in
 // order (independent loads, so many are in flight), and the 16 lane sums are then added in lane
 // order through LDS. The order never depends on timing, so the result is bit-identical run to run.
-// Workgroups past dw_blocks do the same for the fused bias gradient: partials [split][K] into db[K].
+// Workgroups past dw_blocks do the same for the fused bias gradient: db_rows rows of K partials into db[K].
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restrict__ partial,
                                                            float* __restrict__ dw, int n,
                                                            int splits, float beta, int tap_major,
                                                            int K, int C, int RS, int dw_blocks,
                                                            const float* __restrict__ db_partial,
-                                                           float* __restrict__ db) {
+                                                           float* __restrict__ db, int db_rows) {
     __shared__ float red[16][17];
     const int e = threadIdx.x & 15, sl = threadIdx.x >> 4;
     int blk = blockIdx.x;
     if (blk >= dw_blocks) {   // uniform over the workgroup
         blk -= dw_blocks;
-        partial = db_partial; dw = db; n = K; tap_major = 0;
+        partial = db_partial; dw = db; n = K; tap_major = 0; splits = db_rows;
     }
     const int i = blk * 16 + e;      // index in the partials' own order (coalesced reads)
     float acc = 0.0f;
@@ -654,13 +654,13 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float* __re
                                                                int splits, float beta, int tap_major,
                                                                int K, int C, int RS, int dw_blocks,
                                                                const float* __restrict__ db_partial,
-                                                               float* __restrict__ db) {
+                                                               float* __restrict__ db, int db_rows) {
     __shared__ float red[32][33];
     const int e4 = threadIdx.x & 7, sl = threadIdx.x >> 3;
     int blk = blockIdx.x;
     if (blk >= dw_blocks) {   // uniform over the workgroup: the fused bias gradient's partials
         blk -= dw_blocks;
-        partial = db_partial; dw = db; n = K; tap_major = 0;
+        partial = db_partial; dw = db; n = K; tap_major = 0; splits = db_rows;
     }
     if (n & 3) {
         // bias-gradient partials of a layer whose K is not a multiple of 4 (rows not 16-byte aligned):
@@ -911,20 +911,23 @@ hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const WgradPlan& plan
     else if (plan.tap) e = vec ? dispatch_bf16<true, true>(p, plan, st) : dispatch_bf16<false, true>(p, plan, st);
     else e = vec ? dispatch_bf16<true, false>(p, plan, st) : dispatch_bf16<false, false>(p, plan, st);
     if (e != hipSuccess) return e;
-    const int n = g.K * p.CRS;
+    return launch_wgrad_reduce((const float*)ws, dw, plan.splits, beta, plan.tap, g.K, g.C, p.RS, (const float*)p.db_out, db, plan.splits, st);
+}
+
+hipError_t launch_wgrad_reduce(const float* partial, float* dw, int splits, float beta, bool tap_major, int K, int C, int RS,
+                               const float* db_partial, float* db, int db_rows, hipStream_t st) {
+    const int n = K * C * RS;
     // 16-byte packets need aligned rows in both sets of partials (the scratch itself is aligned)
     const bool vec4 = n % 4 == 0;   // (the bias-gradient partials take an element-wise path when K % 4 != 0)
     if (vec4) {
-        const int dw_blocks = (n + 31) / 32, db_blocks = db ? (g.K + 31) / 32 : 0;
+        const int dw_blocks = (n + 31) / 32, db_blocks = db ? (K + 31) / 32 : 0;
         hipLaunchKernelGGL(wgrad_reduce_vec_kernel, dim3(dw_blocks + db_blocks), dim3(256), 0, st,
-                           (const float*)ws, dw, n, plan.splits, beta, plan.tap ? 1 : 0, g.K, g.C, p.RS,
-                           dw_blocks, (const float*)p.db_out, db);
+                           partial, dw, n, splits, beta, tap_major ? 1 : 0, K, C, RS, dw_blocks, db_partial, db, db_rows);
         return hipGetLastError();
     }
-    const int dw_blocks = (n + 15) / 16, db_blocks = db ? (g.K + 15) / 16 : 0;
+    const int dw_blocks = (n + 15) / 16, db_blocks = db ? (K + 15) / 16 : 0;
     hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(dw_blocks + db_blocks), dim3(256), 0, st,
-                       (const float*)ws, dw, n, plan.splits, beta, plan.tap ? 1 : 0, g.K, g.C, p.RS,
-                       dw_blocks, (const float*)p.db_out, db);
+                       partial, dw, n, splits, beta, tap_major ? 1 : 0, K, C, RS, dw_blocks, db_partial, db, db_rows);
     return hipGetLastError();
 }
 

@@ -328,6 +328,20 @@ hipError_t by_tile(const WgradPacketParams& q, int bm, int bn, int splits, hipSt
 
 size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 
+// Expected times (us) of the two second passes. reduce_taps_kernel reads whole lines only where there are channels
+// enough, and a thread walks ceil(taps / 4) * splits dependent-free but serial loads; wgrad_reduce_kernel (splits
+// over lanes, elements in the partials' order) scatters single floats into dw. Measured, us, taps / lanes: 55 x 3 x
+// 11x11 with 64 splits 155 / 5, 256 x 48 x 5x5 with 64 40 / 16, 128 x 96 x 3x3 with 16 4.1 / 5.4, 384 x 256 x 3x3
+// with 1 4.5 / 13.4 and with 64 34 / 45.
+double reduce_taps_us(double dw_bytes, long long splits, int taps) {
+    const double chain = 0.07 * ((taps + 3) / 4) * (double)splits, mem = (double)splits * dw_bytes / 6e6;
+    return 2.6 + (chain > mem ? chain : mem);
+}
+double reduce_lanes_us(double dw_bytes, long long splits) {
+    const double scatter = dw_bytes / 4.0 * 1e-5, mem = (double)splits * dw_bytes / ((long long)(dw_bytes / 4.0) % 4 == 0 ? 6e6 : 2.5e6);
+    return 4.8 + (scatter > mem ? scatter : mem);
+}
+
 }  // namespace
 
 // How the layer would run on this kernel and the time expected for it; `limit` (0: none): the scratch
@@ -378,11 +392,16 @@ WgradPacketPlan plan_wgrad_packets(const ConvGeom& g, size_t limit) {
                 if (limit && one > limit) continue;
                 const double x = (double)(tiles * sp) / 256.0;
                 const double load = x <= 1.0 ? 1.45 : 0.5 * (x + (double)((tiles * sp + 255) / 256));
-                const double us = load * ((double)per * t.cycles / t.eff_w + 5000.0) / 2.2e3 + 4.0 + pack_us + 6.0 + 2.0 * sp * dw_bytes / 5e6;
+                // the partial sums written, then the second pass
+                double red = reduce_taps_us(dw_bytes, sp, g.R * g.S);
+                const bool lanes = reduce_lanes_us(dw_bytes, sp) < red;
+                if (lanes) red = reduce_lanes_us(dw_bytes, sp);
+                const double part_us = sp * dw_bytes / 5e6;
+                const double us = load * ((double)per * t.cycles / t.eff_w + 5000.0) / 2.2e3 + 4.0 + pack_us + 6.0 + part_us + (red > part_us ? red : part_us);
                 if (!best.use || us < best.us) {
                     k.use = true; k.us = us;
                     k.bm = t.bm; k.bn = t.bn; k.tiles_i = (int)ti; k.tiles_j = (int)tj;
-                    k.splits = (int)sp; k.steps_per_split = (int)per;
+                    k.splits = (int)sp; k.steps_per_split = (int)per; k.reduce_lanes = lanes;
                     best = k;
                 }
             }
@@ -465,6 +484,8 @@ hipError_t launch_wgrad_packets(const ConvGeom& g, const WgradPacketPlan& k, con
         if (e != hipSuccess) return e;
         split = end;
     }
+    if (k.reduce_lanes)
+        return launch_wgrad_reduce((const float*)ws, dw, k.splits, beta, true, g.K, g.C, g.R * g.S, (const float*)db_sums, db, k.db_rows, st);
     const int c_blocks = (g.C + RC - 1) / RC, db_blocks = db ? (g.K + DB_COLS - 1) / DB_COLS : 0;
     const long long dw_blocks = (long long)g.K * c_blocks;
     if (dw_blocks + db_blocks > 0x7fffffffLL) return hipErrorInvalidValue;

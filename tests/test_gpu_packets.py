@@ -247,6 +247,44 @@ def test_weight_gradient_in_the_static_scratch_takes_the_splits_in_turn():
     assert rel_l2(to_host(got), to_host(base)) <= 2e-6        # two fp32 sums of 75264 products each
 
 
+def _time_of(f, calls=30):
+    """Least time of one call over a few rounds of `calls`, in seconds."""
+    import time
+    import torch
+    best = float("inf")
+    for _ in range(6):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(calls):
+            f()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t) / calls)
+    return best
+
+
+# few images of a first layer: three channels, many taps, many splits of the pixel reduction
+@pytest.mark.parametrize("case", [(4, 3, 100, 102, 55, 11, 11, 2, 5), (23, 3, 68, 70, 107, 11, 11, 4, 0), (7, 3, 184, 185, 124, 7, 7, 4, 3),
+                                  (1, 16, 38, 38, 56, 3, 3, 1, 0), (2, 8, 20, 20, 176, 5, 5, 1, 2)], ids=str)
+def test_weight_gradient_takes_no_longer_than_on_the_general_kernel(case):
+    """The automatic route against the general kernels over the same layer. A quarter more is what these calls of
+    15 - 40 us vary by; the second pass that walked taps times splits one by one took 2 - 8 times as long."""
+    import paper_1412_6249_amd as pa
+    from gpu_util import to_dev, workspace
+    x, w, b, dy, _, _ = _inputs(case)
+    desc, tx, tdy, dw, db = pa.conv_desc(case[7], case[8]), to_dev(x), to_dev(dy), to_dev(w), to_dev(b)
+
+    def once():
+        ws = workspace(pa.purine_conv_workspace_bytes(pa.PURINE_CONV_BWD_WEIGHT_BIAS, desc, x.shape, w.shape, pa.PURINE_F32))
+        return _time_of(lambda: pa.purine_conv_bwd_weight_bias(desc, tx, tdy, dw, db, ws=ws))
+    auto = once()
+    _general(pa, True)
+    try:
+        general = once()
+    finally:
+        _general(pa, False)
+    assert auto <= 1.25 * general, (auto, general)
+
+
 # N, C, K of a fully-connected layer: rows and columns one past a tile, reductions that are no whole step (and no
 # whole 16-byte packet), reductions split over workgroups, batches on either side of the weight gradient's rule,
 # operands laid out first (dw of the wide ones)
