@@ -258,9 +258,10 @@ int purine_grouped_conv_bwd_weight(const purine_conv_desc* desc, int groups, con
  * BF16; dw and db are F32.
  *   fwd:        y = x w^T (+ b)          dx = dy w          dw = beta*dw + dy^T x,  db = beta*db + column sums of dy
  * F32 (matrices below 2 GiB): a streaming matrix product on the bf16 matrix cores, three exact bf16 parts per
- * operand and fp32 sums (no less exact than fp32 products), the reduction split over workgroups where tiles alone
- * would leave most of the chip idle (partial outputs in ws, added in a fixed order); the weight gradient of more
- * than 32 images may lay its operands out as such parts in ws first. Every other pass is one of the convolution
+ * operand and fp32 sums, the reduction split over workgroups where tiles alone would leave most of the chip idle
+ * (partial outputs in ws, added in a fixed order): every forward pass, backward-data but for short sums, and the weight
+ * gradient where dw is large (or the batch is whole steps of 16), which may lay its operands out as such parts in ws
+ * first. Every other pass is one of the convolution
  * GEMM kernels on reinterpreted descriptors (a matrix [rows, features] is one image of `rows` channels whose pixel
  * plane is the feature axis, or a 1x1 filter bank): forward runs the weight-gradient kernel (split reduction over
  * C, fixed-order second pass; BF16: its fp32 result gets the bias added and is rounded once), backward-data the

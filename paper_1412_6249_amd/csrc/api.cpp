@@ -669,18 +669,39 @@ size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 StreamPlan fc_stream_plan(int pass, int64_t N, int64_t C, int64_t K) {
     StreamPlan none{};
     if (buffer_loads_disabled() || N * C * 4 >= 0x7fffffffll || K * C * 4 >= 0x7fffffffll || N * K * 4 >= 0x7fffffffll) return none;
-    if (pass == PURINE_CONV_FWD) return pix::plan_stream(N, K, C, true);
-    if (pass == PURINE_CONV_BWD_DATA) return pix::plan_stream(N, C, K, true);
-    // A short reduction leaves nothing but the write of dw, which the general kernel does as well or better
-    // (9216 x 4096: N = 1 153 against 37 us, N = 16 40 against 37, N = 32 46 either way, N = 64 56 against 66).
-    return N > 32 ? pix::plan_stream(K, C, N, true) : none;
+    if (pass == PURINE_CONV_FWD) return pix::plan_stream(N, K, C, true, true);       // (no size found at which the composition is faster)
+    if (pass == PURINE_CONV_BWD_DATA) {
+        // The composition walks the reduction in one workgroup, which a short one leaves soon (us, composition /
+        // streaming, 128 images: 64 x 10 3.8 / 5.9, 3384 x 46 6.8 / 7.4, 9000 x 64 9.0 / 8.7, 1000 x 200 11.4 / 9, 4096 x 1000
+        // 36 / 27; 16 terms are one pass there). Its time, on the scale of the streaming kernel's
+        // expected one, which counts 3 us too many for the second pass of a sum this short.
+        StreamPlan k = pix::plan_stream(N, C, K, true, false);
+        const double composition_us = K <= 16 ? 6.3 : K <= 48 ? 9.2 : K <= 96 ? 10.6 : 12.4 + 0.024 * (double)(K - 96);
+        if (K < 1000) k.use = k.use && k.us - (k.splits > 1 ? 3.0 : 0.0) < composition_us;
+        return k;
+    }
+    // The weight gradient writes K x C sums of N products. Where that write is most of the time, the general kernel
+    // does it as well or better; what decides is how large dw is (us, general / this, at N = 33, 48, 64, 128, 250):
+    //     9216 x 4096   48 / 46   51 / 48   60 / 53   97 / 77   170 / 124
+    //     3140 x 1780   17 / 16   17 / 15   19 / 17   28 / 22
+    //     4096 x 1000   13 / 13   12 / 13   13 / 13   18 / 18   30 / 28
+    //     1185 x 1168    9 / 10    9 / 10   10 / 10   14 / 14   21 / 22
+    //     1000 x 200     7 / 8     9 / 8    10 / 8    15 / 11   13 / 18
+    // (N <= 32: 37 / 153 at 9216 x 4096 and N = 1). On small ones the general kernel is the slower one only where the
+    // batch is whole steps of 16 and the rows whole packets, for which it takes wider tiles than there is work for
+    const int64_t area = K * C;
+    // (and where 32 or fewer rows leave it one row tile: 250 images, 64 x 10, 13 / 9).
+    const bool packets = C % 4 == 0;
+    const bool take = area >= 5ll << 20 ? N > 32 : area >= 2ll << 20 ? N >= 128 && packets
+                    : area <= 1ll << 20 && ((N >= 48 && N % 16 == 0 && packets) || (N >= 192 && K <= 32));
+    return take ? pix::plan_stream(K, C, N, false, false) : none;
 }
 // The weight gradient's operands are small against its result, and every one of their elements is needed by
 // dozens of tiles: laid out as bf16 parts first, the kernel that copies packets straight into LDS takes 79 us
 // (+ 6 for the layout) where the streaming one splits the same elements again and again in 90 (9216 x 4096, N = 128).
 PacketPlan fc_packet_plan(int64_t N, int64_t C, int64_t K, const StreamPlan& k) {
     PacketPlan pk = pix::plan_packets_matrix(K, C, N);
-    pk.use = pk.use && N * 8 <= K && N * 8 <= C && pk.us < k.us;
+    pk.use = pk.use && N * 4 <= K && N * 4 <= C && pk.us < k.us;
     return pk;
 }
 size_t fc_general_workspace_bytes(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype);

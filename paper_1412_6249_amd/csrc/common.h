@@ -90,7 +90,7 @@ struct StreamPlan {
     double us;                  // expected time
 };
 namespace pix {
-StreamPlan plan_stream(long long rows, long long cols, long long K, bool may_split);
+StreamPlan plan_stream(long long rows, long long cols, long long K, bool a_in, bool b_in);
 PacketPlan plan_packets_matrix(long long rows, long long cols, long long K);
 hipError_t launch_packets_matrix(const PacketPlan& k, const void* a, const void* b, void* out, float beta, long long rows, long long cols, long long K,
                                  void* ws, hipStream_t st);

@@ -228,11 +228,17 @@ hipError_t launch_main(const PixParams& p, const StreamParams& q, hipStream_t st
     return hipGetLastError();
 }
 
+// Row tiles of a form. Eight 4-byte loads per packet need more registers than two 16-byte ones: with both operands
+// read along their outer axis 128 rows spill 208 registers and 96 rows 52, with one of them 96 rows spill 32 (weight
+// gradient 3140 x 1780 of 33 images, 128 rows: 49 us, the general kernel 17; backward-data 9216 x 4096 of 131
+// images, 96 rows: 175 us, the general kernel 121).
+constexpr bool has_tile(bool a_in, bool b_in, int bm) { return bm <= 64 || (a_in && (b_in || bm == 128)); }
+
 template <bool A_IN, bool B_IN>
 hipError_t by_tile(const PixParams& p, const StreamParams& q, int bm, hipStream_t st) {
     switch (bm) {
-        case 128: return launch_main<A_IN, B_IN, 2, 2, 2, 2>(p, q, st);
-        case 96:  return launch_main<A_IN, B_IN, 3, 1, 1, 4>(p, q, st);
+        case 128: if constexpr (has_tile(A_IN, B_IN, 128)) return launch_main<A_IN, B_IN, 2, 2, 2, 2>(p, q, st); return hipErrorInvalidValue;
+        case 96:  if constexpr (has_tile(A_IN, B_IN, 96)) return launch_main<A_IN, B_IN, 3, 1, 1, 4>(p, q, st); return hipErrorInvalidValue;
         case 64:  return launch_main<A_IN, B_IN, 1, 2, 2, 2>(p, q, st);
         case 32:  return launch_main<A_IN, B_IN, 1, 1, 1, 4>(p, q, st);
         default: return hipErrorInvalidValue;
@@ -244,18 +250,21 @@ constexpr RowTile kTilesS[] = {{128, 768, 0.62f}, {96, 576, 0.58f}, {64, 384, 0.
 
 }  // namespace
 
-// rows x cols over K; may_split: scratch for partial outputs is at hand. Model as in plan_packets, with the
-// memory's time as a second floor: operands and output once, partial outputs twice.
-StreamPlan plan_stream(long long rows, long long cols, long long K, bool may_split) {
+// rows x cols over K; a_in, b_in as in launch_stream_gemm. Model as in plan_packets, with the memory's time as a
+// second floor: operands and output once, partial outputs twice.
+StreamPlan plan_stream(long long rows, long long cols, long long K, bool a_in, bool b_in) {
     StreamPlan k{};
     const long long steps = (K + 15) / 16;
     if (rows < 1 || cols < 1 || K < 1 || steps > (1 << 26)) return k;
     const double mem_us = 4.0 * ((double)rows * K + (double)cols * K + (double)rows * cols) / 4.5e6;
     for (const RowTile& t : kTilesS) {
         const long long ti = (rows + t.bm - 1) / t.bm, tp = (cols + COLS - 1) / COLS, tiles = ti * tp;
-        if (tiles > 0x7fffffffLL) continue;
+        if (tiles > 0x7fffffffLL || !has_tile(a_in, b_in, t.bm)) continue;
+        // B along its outer axis, read again by every row tile: 9216 x 4096, 131 images on three tiles of 64 rows 153 us,
+        // 200 images on two of 128 rows 115
+        const double eff = a_in && !b_in && t.bm == 64 && ti > 2 ? 0.40 : t.eff;
         long long last = -1;
-        for (int half_fill = 0; half_fill <= (may_split ? 8 : 0); ++half_fill) {
+        for (int half_fill = 0; half_fill <= 8; ++half_fill) {
             long long sp = half_fill * 128 / tiles;
             if (sp < 1) sp = 1;
             if (sp > 64) sp = 64;
@@ -272,7 +281,12 @@ StreamPlan plan_stream(long long rows, long long cols, long long K, bool may_spl
             const double rounds = (double)((tiles * sp + 256 * resident - 1) / (256 * resident));
             const double ragged = x > resident ? 0.5 + 0.5 * rounds * resident / x : 1.0;
             const double load = x <= 1.0 ? 1.45 : x <= 2.0 ? 0.5 * (x + 2.0) : x * ragged;
-            const double mma_us = load * ((double)per * t.cycles / t.eff + 3000.0) / 2.2e3;
+            // B along its outer axis, one workgroup for the whole sum: a step takes its time however little there is to
+            // multiply, 16 loads, their split and a barrier (247 x 169, 128 images, backward-data: 16 steps 16.2 us, split
+            // one by one 8.6 with the second pass; weight gradient 64 x 10 of 128: 8 steps of 32 rows 10 us, of 64 12)
+            const double chain_us = b_in || sp > 1 ? 0.0 : (t.bm == 32 ? 0.8 : 1.05) * (double)per;
+            double mma_us = load * ((double)per * t.cycles / eff + 3000.0) / 2.2e3;
+            if (mma_us < chain_us) mma_us = chain_us;
             // fewer than two workgroups per CU (of the smallest tile three) do not keep enough loads in flight
             const double mem = mem_us * ragged / (x >= (t.bm == 32 ? 2.6 : 1.9) ? 1.0 : x >= 1.0 ? 0.8 : 0.8 * x);
             const double us = (mma_us > mem ? mma_us + 0.3 * mem : mem + 0.3 * mma_us) + 6.0 + (sp > 1 ? 6.0 + 2.0 * part / 7e6 : 0.0);

@@ -337,3 +337,53 @@ def test_fc_f32(case):
     bad[0][N // 2, C - 1], bad[1][K - 1, 0], bad[3][0, K - 1] = float("inf"), float("nan"), float("-inf")
     for a, r in zip(run(*bad), want(*bad)):
         assert torch.equal(a.isnan(), r.isnan()) and torch.equal(a.isposinf(), r.isposinf()) and torch.equal(a.isneginf(), r.isneginf())
+
+
+def _graph_time_of(f, calls=20):
+    """Least time of one call among `calls` captured into a graph, in seconds: the GPU's alone."""
+    import time
+    import torch
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        f()
+        st.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            for _ in range(calls):
+                f()
+        best = float("inf")
+        for _ in range(6):
+            st.synchronize()
+            t = time.perf_counter()
+            g.replay()
+            st.synchronize()
+            best = min(best, (time.perf_counter() - t) / calls)
+    return best
+
+
+# dw on 128-row tiles that spilled their accumulators; dx of a batch one past a tile on 96-row ones; sums of one
+# step; a short weight gradient whose batch is no whole step
+@pytest.mark.parametrize("which, case", [("dw", (48, 3140, 1780)), ("dw", (131, 1000, 200)), ("dw", (200, 9000, 64)),
+                                         ("dx", (131, 9216, 4096)), ("dx", (100, 256, 10)), ("dx", (128, 169, 247))])
+def test_fc_f32_takes_no_longer_than_the_composition(which, case):
+    """The automatic route against the composition of convolution kernels. A quarter more is allowed; these calls took
+    1.3 - 3 times as long before the route weighed both."""
+    import torch
+    import paper_1412_6249_amd as pa
+    from gpu_util import workspace
+    N, C, K = case
+    x, w, dy = (torch.randn(s, device="cuda") for s in ((N, C), (K, C), (N, K)))
+    out = torch.empty_like(w if which == "dw" else x)
+
+    def once():
+        ws = workspace(pa.purine_fc_workspace_bytes(pa.PURINE_CONV_BWD_WEIGHT if which == "dw" else pa.PURINE_CONV_BWD_DATA, N, C, K))
+        if which == "dw":
+            return _graph_time_of(lambda: pa.purine_fc_bwd_weight(x, dy, out, None, ws=ws))
+        return _graph_time_of(lambda: pa.purine_fc_bwd_data(dy, w, out, ws=ws))
+    auto = once()
+    _general(pa, True)
+    try:
+        general = once()
+    finally:
+        _general(pa, False)
+    assert auto <= 1.25 * general, (auto, general)
