@@ -668,7 +668,7 @@ size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 // y[n][k] over c, PURINE_CONV_BWD_DATA dx[n][c] over k, PURINE_CONV_BWD_WEIGHT dw[k][c] over n.
 StreamPlan fc_stream_plan(int pass, int64_t N, int64_t C, int64_t K) {
     StreamPlan none{};
-    if (buffer_loads_disabled() || N * C * 4 >= 0x7fffffffll || K * C * 4 >= 0x7fffffffll || N * K * 4 >= 0x7fffffffll) return none;
+    if (buffer_loads_disabled() || N * C >= (1ll << 29) || K * C >= (1ll << 29) || N * K >= (1ll << 29)) return none;
     if (pass == PURINE_CONV_FWD) return pix::plan_stream(N, K, C, true, true);       // (no size found at which the composition is faster)
     if (pass == PURINE_CONV_BWD_DATA) {
         // The composition walks the reduction in one workgroup, which a short one leaves soon (us, composition /
@@ -699,19 +699,27 @@ StreamPlan fc_stream_plan(int pass, int64_t N, int64_t C, int64_t K) {
 // The weight gradient's operands are small against its result, and every one of their elements is needed by
 // dozens of tiles: laid out as bf16 parts first, the kernel that copies packets straight into LDS takes 79 us
 // (+ 6 for the layout) where the streaming one splits the same elements again and again in 90 (9216 x 4096, N = 128).
-PacketPlan fc_packet_plan(int64_t N, int64_t C, int64_t K, const StreamPlan& k) {
-    PacketPlan pk = pix::plan_packets_matrix(K, C, N);
-    pk.use = pk.use && N * 4 <= K && N * 4 <= C && pk.us < k.us;
-    return pk;
-}
 size_t fc_general_workspace_bytes(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype);
-// aliasing and scratch of such a pass: what the general composition asks for
-int fc_stream_checks(int pass, const purine_tensor* out, const purine_tensor* a, const purine_tensor* b, int64_t N, int64_t C, int64_t K,
-                     const void* ws, size_t ws_bytes) {
+// One plan per call, which also says what scratch the call asks for: at least the composition's.
+struct FcPlan { StreamPlan k; PacketPlan pk; size_t need; };
+FcPlan fc_plan(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype) {
+    FcPlan f{};
+    if (dtype == PURINE_F32) f.k = fc_stream_plan(pass, N, C, K);
+    f.need = fc_general_workspace_bytes(pass, N, C, K, dtype);
+    if (!f.k.use) return f;
+    if (f.k.part_bytes > f.need) f.need = f.k.part_bytes;
+    if (pass >= PURINE_CONV_BWD_WEIGHT) {
+        f.pk = pix::plan_packets_matrix(K, C, N);
+        f.pk.use = f.pk.use && N * 4 <= K && N * 4 <= C && f.pk.us < f.k.us;
+        if (f.pk.use && f.pk.ws_bytes > f.need) f.need = f.pk.ws_bytes;
+    }
+    return f;
+}
+// aliasing and scratch of a streaming pass
+int fc_stream_checks(const FcPlan& f, const purine_tensor* out, const purine_tensor* a, const purine_tensor* b, const void* ws, size_t ws_bytes) {
     if (overlaps(out, a) || overlaps(out, b)) return PURINE_E_LAYOUT;
-    const size_t need = purine_fc_workspace_bytes(pass, N, C, K, PURINE_F32);
-    if (need && (!ws || ws_bytes < need)) return PURINE_E_WORKSPACE;
-    if (need && (((uintptr_t)ws) & 15u)) return PURINE_E_LAYOUT;
+    if (f.need && (!ws || ws_bytes < f.need)) return PURINE_E_WORKSPACE;
+    if (f.need && (((uintptr_t)ws) & 15u)) return PURINE_E_LAYOUT;
     return PURINE_OK;
 }
 
@@ -775,18 +783,9 @@ int purine_grouped_conv_bwd_weight(const purine_conv_desc* desc, int groups, con
 }
 
 size_t purine_fc_workspace_bytes(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype) {
-    const size_t general = fc_general_workspace_bytes(pass, N, C, K, dtype);
-    if (dtype != PURINE_F32 || N < 1 || C < 1 || K < 1 || N >= (1ll << 31) || C >= (1ll << 31) || K >= (1ll << 31) || pass < PURINE_CONV_FWD ||
-        pass > PURINE_CONV_BWD_WEIGHT_BIAS)
-        return general;
-    const StreamPlan k = fc_stream_plan(pass, N, C, K);
-    if (!k.use) return general;
-    size_t need = k.part_bytes > general ? k.part_bytes : general;
-    if (pass >= PURINE_CONV_BWD_WEIGHT) {
-        const PacketPlan pk = fc_packet_plan(N, C, K, k);
-        if (pk.use && pk.ws_bytes > need) need = pk.ws_bytes;
-    }
-    return need;
+    if (N < 1 || C < 1 || K < 1 || N >= (1ll << 31) || C >= (1ll << 31) || K >= (1ll << 31) || pass < PURINE_CONV_FWD || pass > PURINE_CONV_BWD_WEIGHT_BIAS)
+        return fc_general_workspace_bytes(pass, N, C, K, dtype);
+    return fc_plan(pass, N, C, K, dtype).need;
 }
 
 namespace {
@@ -847,9 +846,10 @@ int purine_fc_fwd(const purine_tensor* x, const purine_tensor* w, const purine_t
         return hip_status(launch_fc_finish_bf16((const float*)acc.data, b ? b->data : nullptr, y->data, (int)N, (int)K,
                                                 (hipStream_t)hip_stream));
     }
-    const StreamPlan k = fc_stream_plan(PURINE_CONV_FWD, x->dim[0], x->dim[1], w->dim[0]);
+    const FcPlan plan = fc_plan(PURINE_CONV_FWD, x->dim[0], x->dim[1], w->dim[0], x->dtype);
+    const StreamPlan& k = plan.k;
     if (k.use) {
-        if ((rc = fc_stream_checks(PURINE_CONV_FWD, y, x, w, x->dim[0], x->dim[1], w->dim[0], ws, ws_bytes))) return rc;
+        if ((rc = fc_stream_checks(plan, y, x, w, ws, ws_bytes))) return rc;
         const bool second = k.splits > 1;              // the pass that adds the splits also adds the bias
         hipError_t e = pix::launch_stream_gemm(k, x->data, true, w->data, true, y->data, second && b ? b->data : nullptr, 0.0f, x->dim[0], w->dim[0],
                                                x->dim[1], ws, (hipStream_t)hip_stream);
@@ -881,9 +881,10 @@ int purine_fc_bwd_data(const purine_tensor* dy, const purine_tensor* w, purine_t
                                                    (int)w->dim[1], ws, (hipStream_t)hip_stream));
         }
     }
-    const StreamPlan k = dy->dtype == PURINE_F32 ? fc_stream_plan(PURINE_CONV_BWD_DATA, dy->dim[0], w->dim[1], w->dim[0]) : StreamPlan{};
+    const FcPlan plan = dy->dtype == PURINE_F32 ? fc_plan(PURINE_CONV_BWD_DATA, dy->dim[0], w->dim[1], w->dim[0], dy->dtype) : FcPlan{};
+    const StreamPlan& k = plan.k;
     if (k.use) {
-        if ((rc = fc_stream_checks(PURINE_CONV_BWD_DATA, dx, dy, w, dy->dim[0], w->dim[1], w->dim[0], ws, ws_bytes))) return rc;
+        if ((rc = fc_stream_checks(plan, dx, dy, w, ws, ws_bytes))) return rc;
         return hip_status(pix::launch_stream_gemm(k, dy->data, true, w->data, false, dx->data, nullptr, 0.0f, dy->dim[0], w->dim[1], w->dim[0], ws,
                                                   (hipStream_t)hip_stream));
     }
@@ -934,12 +935,13 @@ int purine_fc_bwd_weight(const purine_tensor* x, const purine_tensor* dy, purine
     } else {
         // dw[k][c] = sum_n dy[n][k] x[n][c]: the backward-data contraction with dy := x (plane of N
         // channels) and w := dy (filter bank [N x K])
-        const StreamPlan k = fc_stream_plan(PURINE_CONV_BWD_WEIGHT, N, C, K);
+        const FcPlan plan = fc_plan(PURINE_CONV_BWD_WEIGHT, N, C, K, PURINE_F32);
+        const StreamPlan& k = plan.k;
+        const PacketPlan& pk = plan.pk;
         const purine_tensor xp = as_plane(x);
         purine_tensor dwp = as_plane(dw);
         if (k.use) {
-            if ((rc = fc_stream_checks(PURINE_CONV_BWD_WEIGHT, dw, x, dy, N, C, K, ws, ws_bytes))) return rc;
-            const PacketPlan pk = fc_packet_plan(N, C, K, k);
+            if ((rc = fc_stream_checks(plan, dw, x, dy, ws, ws_bytes))) return rc;
             hipError_t e = pk.use ? pix::launch_packets_matrix(pk, dy->data, x->data, dw->data, beta, K, C, N, ws, (hipStream_t)hip_stream)
                                   : pix::launch_stream_gemm(k, dy->data, false, x->data, false, dw->data, nullptr, beta, K, C, N, ws, (hipStream_t)hip_stream);
             if (e != hipSuccess) return hip_status(e);

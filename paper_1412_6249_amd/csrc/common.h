@@ -144,7 +144,7 @@ struct WgradPacketPlan {
     size_t db_offset, copies;              // then the bias sums; all of it in whole copies of dw
     double us;                             // expected time
 };
-WgradPacketPlan plan_wgrad_packets(const ConvGeom& g, size_t limit);
+WgradPacketPlan plan_wgrad_packets(const ConvGeom& g, size_t limit, double budget_us);
 hipError_t launch_wgrad_packets(const ConvGeom& g, const WgradPacketPlan& k, const void* x, const void* dy, float* dw, float* db, float beta, void* ws,
                                 size_t ws_bytes, hipStream_t st);
 // Second pass of a split weight gradient: partial sums [split][k][c][tap], or [split][tap][k][c] (tap_major), into

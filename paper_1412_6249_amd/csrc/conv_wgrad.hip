@@ -868,8 +868,9 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
     // kernels (96 -> 96 channels 1x1 at 54x54, N = 64: 65 us there, 90 us for the layout pass alone);
     // MFMA-bound ones gain what the forward pass gains. A layer that the static-scratch entry point
     // takes has to go through its scratch on the same splits (the results are the same bits).
-    const WgradPacketPlan pk = plan_wgrad_packets(g, pl.ws_bytes <= kStaticScratchBytes ? kStaticScratchBytes : 0);
-    if (!pk.use || (pk.us * 1.05 >= us && !split_packets_forced())) return pl;
+    const WgradPacketPlan pk = plan_wgrad_packets(g, pl.ws_bytes <= kStaticScratchBytes ? kStaticScratchBytes : 0,
+                                                  split_packets_forced() ? 1e30 : us / 1.05);
+    if (!pk.use) return pl;
     pl.pk = pk;
     pl.ws_bytes = pk.copies * (size_t)g.K * g.C * g.R * g.S * sizeof(float);
     pl.db_ws_bytes = pk.copies * (size_t)g.K * sizeof(float);
