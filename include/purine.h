@@ -113,6 +113,12 @@ size_t purine_bias_bwd_workspace_bytes(const int64_t dy_dim[4], int32_t dtype);
 
 /* ---- the five operators of the convolution layer (paper Figure 1(b)) ---------------------- */
 
+/* F32 arithmetic. Products are fp32 MFMAs, or six bf16 MFMAs over three bf16 parts of either operand (which route a
+ * pass takes depends on its shape); sums are fp32 either way. The parts hold any operand below 2^112 = 5.2e33 exactly,
+ * and the error of the sum against exact arithmetic is no larger than the fp32 MFMAs' (products of two numbers that are
+ * both subnormal aside). Outputs that involve operands of that size, infinities or NaNs, or that reach 2^96 = 7.9e28, are
+ * computed again as a plain fp32 sum: the result is the fp32 one, at a small fraction of the speed. */
+
 /* Conv: y[n,k,p,q] = sum_{c,r,s} x[n,c,p*sh-ph+r,q*sw-pw+s] * w[k,c,r,s], taps outside x are 0.
  * x, w, y share one dtype (F32 or BF16). The patch matrix is never written to memory.
  * ws: scratch of at least purine_conv_workspace_bytes(PURINE_CONV_FWD, ...) bytes (may be NULL when
@@ -258,7 +264,7 @@ int purine_grouped_conv_bwd_weight(const purine_conv_desc* desc, int groups, con
  * BF16; dw and db are F32.
  *   fwd:        y = x w^T (+ b)          dx = dy w          dw = beta*dw + dy^T x,  db = beta*db + column sums of dy
  * F32 (matrices below 2 GiB): a streaming matrix product on the bf16 matrix cores, three exact bf16 parts per
- * operand and fp32 sums, the reduction split over workgroups where tiles alone would leave most of the chip idle
+ * operand and fp32 sums (as for convolutions, see purine_conv_fwd), the reduction split over workgroups where tiles alone would leave most of the chip idle
  * (partial outputs in ws, added in a fixed order): every forward pass, backward-data but for short sums, and the weight
  * gradient where dw is large (or the batch is whole steps of 16), which may lay its operands out as such parts in ws
  * first. Every other pass is one of the convolution

@@ -43,6 +43,20 @@ struct PackParams {
     FastDiv div_bm, div_steps, div_taps, div_st, div_phases, div_sw;
 };
 
+// Where the filter values of GEMM row i and tap (tr, tc) lie: channel ci's at w[fixed + ci * stride], for ci < lim.
+// mode: 0 forward (row = output channel), 1 backward-data with unit stride (row = input channel), 2 phase-folded
+// (row = (c, a, b), taps a + sh * r', b + sw * s'). Ci: reduction channels.
+struct FilterRun { int fixed, stride, lim; };
+__device__ __forceinline__ FilterRun filter_run(int mode, int i, int tr, int tc, int C, int R, int S, int sh, int sw, int Ci, const FastDiv& div_phases,
+                                                const FastDiv& div_sw) {
+    if (mode == 0) return {(i * C * R + tr) * S + tc, R * S, Ci};
+    if (mode == 1) return {(i * R + tr) * S + tc, C * R * S, Ci};
+    const int c = fastdiv(i, div_phases), ab = i - c * sh * sw;
+    const int pa = fastdiv(ab, div_sw), pb = ab - pa * sw;
+    const int r = pa + sh * tr, s = pb + sw * tc;
+    return {(c * R + r) * S + s, C * R * S, r < R && s < S ? Ci : 0};
+}
+
 __global__ __launch_bounds__(256) void pack_operands_kernel(const PackParams q) {
     float v[8];
     if ((int)blockIdx.x < q.x_blocks) {
@@ -64,22 +78,10 @@ __global__ __launch_bounds__(256) void pack_operands_kernel(const PackParams q) 
     const int cg = fastdiv(step, q.div_taps), tap = step - cg * q.taps;
     const int tr = fastdiv(tap, q.div_st), tc = tap - tr * q.St;
     const int i = rt * q.bm + row, ci0 = cg * 16 + half * 8;
-    int fixed = 0, stride = 0, lim = 0;          // element e sits at w[fixed + (ci0 + e) * stride] when ci0 + e < lim
-    if (i < q.Co) {
-        if (q.mode == 0) {                       // forward: row = k, reduction channel = c
-            fixed = (i * q.C * q.R + tr) * q.S + tc; stride = q.R * q.S; lim = q.C;
-        } else if (q.mode == 1) {                // backward-data, unit stride: row = c, reduction channel = k
-            fixed = (i * q.R + tr) * q.S + tc; stride = q.C * q.R * q.S; lim = q.K;
-        } else {                                 // phase-folded: row = (c, a, b), taps a + sh*r', b + sw*s'
-            const int c = fastdiv(i, q.div_phases), ab = i - c * q.sh * q.sw;
-            const int pa = fastdiv(ab, q.div_sw), pb = ab - pa * q.sw;
-            const int r = pa + q.sh * tr, s = pb + q.sw * tc;
-            fixed = (c * q.R + r) * q.S + s; stride = q.C * q.R * q.S;
-            lim = (r < q.R && s < q.S) ? q.K : 0;
-        }
-    }
+    FilterRun f{0, 0, 0};
+    if (i < q.Co) f = filter_run(q.mode, i, tr, tc, q.C, q.R, q.S, q.sh, q.sw, q.mode == 0 ? q.C : q.K, q.div_phases, q.div_sw);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = ci0 + e < lim ? q.w[(size_t)fixed + (size_t)(ci0 + e) * stride] : 0.0f;
+    for (int e = 0; e < 8; ++e) v[e] = ci0 + e < f.lim ? q.w[(size_t)f.fixed + (size_t)(ci0 + e) * f.stride] : 0.0f;
     // [row tile][step][plane][half][row]
     store_split8(v, q.wp + ((size_t)ts * PLANES * 2 + half) * q.bm * 16 + (size_t)row * 16, (size_t)2 * q.bm * 16);
 }
@@ -89,6 +91,7 @@ struct PacketParams {
     unsigned a_bytes, b_bytes;
     int plane_bytes;                    // of the activations
     int Cb, taps, steps, splits, steps_per_split;
+    int mode;                           // of the filter (filter_run), for outputs that are computed again
     FastDiv div_taps, div_st;
     size_t split_stride;                // elements between the splits' partial outputs
 };
@@ -198,18 +201,18 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void igemm_packets_kernel(const Pi
     // the last requests must not outlive the workgroup's LDS
     __builtin_amdgcn_s_waitcnt(0x0070);
 
-    // The sum of the two sets; infinities and NaNs that the split products make of infinite or
-    // overflowing operands (an infinity times a zero part) are computed again as the fp32 kernel would.
+    // The sum of the two sets; what comes out infinite or NaN (such operands, or ones too large for the split) is
+    // computed again from the fp32 operands as the fp32 kernel would.
     unsigned long long bad = join_sets<TM, TN>(hi, lo);
     if (__builtin_expect(__any(bad != 0), 0)) {
         while (bad) {
             const int idx = __ffsll((long long)bad) - 1;
             bad &= bad - 1;
             const int ab = idx >> 4, e = idx & 15;
-            const int row = wm * TM * 32 + (ab / TN) * 32 + (e >> 2) * 8 + khalf * 4 + (e & 3);
+            const int row = i0 + wm * TM * 32 + (ab / TN) * 32 + (e >> 2) * 8 + khalf * 4 + (e & 3);
             const int pix = j0 + wn * TN * 32 + (ab % TN) * 32 + (lane & 31);
             float sum = 0.0f;
-            if (pix < p.M && i0 + row < p.Co) {
+            if (pix < p.M && row < p.Co) {
                 const int n = fastdiv(pix, p.div_howo), rem = pix - n * p.HoWo;
                 const int ho = fastdiv(rem, p.div_wo), wo = rem - ho * p.Wo;
                 const int hb = ho * p.g_mul_h + p.g_add_h, wb = wo * p.g_mul_w + p.g_add_w;
@@ -217,14 +220,14 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void igemm_packets_kernel(const Pi
                     const int g = fastdiv(s, q.div_taps), tap = s - g * q.taps;
                     const int r = fastdiv(tap, q.div_st), t = tap - r * p.St;
                     const int h = MINUS ? hb - r : hb + r, w = MINUS ? wb - t : wb + t;
-                    // a tap outside the image is a zero that takes part: an infinite filter value times it is NaN
+                    // a tap outside the image, or past the filter in a folded phase, is a zero that takes part: an
+                    // infinite factor times it is NaN
                     const bool inside = (unsigned)h < (unsigned)p.Hi && (unsigned)w < (unsigned)p.Wi;
-                    for (int half = 0; half < 2; ++half) {
-                        const unsigned char* pa = (const unsigned char*)q.a + (size_t)(rt * q.steps + s) * T::A_BYTES + (half * T::BM + row) * 16;
-                        const unsigned char* pb = (const unsigned char*)q.b + ((size_t)(n * q.Cb + g * 2 + half) * p.HiWi + (inside ? h * p.Wi + w : 0)) * 16;
-                        for (int c = 0; c < 8; ++c)
-                            sum = __builtin_fmaf(join_parts(pa + c * 2, 2 * T::BM * 16), inside ? join_parts(pb + c * 2, q.plane_bytes) : 0.0f, sum);
-                    }
+                    const FilterRun f = filter_run(q.mode, row, r, t, p.C, p.R, p.S, p.sh, p.sw, p.Ci, p.div_phases, p.div_sw);
+                    const float* pb = (const float*)p.in + (size_t)n * p.in_ns + (inside ? h * p.Wi + w : 0);
+                    for (int ci = g * 16; ci < g * 16 + 16 && ci < p.Ci; ++ci)
+                        sum = __builtin_fmaf(ci < f.lim ? ((const float*)p.wt)[(size_t)f.fixed + (size_t)ci * f.stride] : 0.0f,
+                                             inside ? pb[(size_t)ci * p.HiWi] : 0.0f, sum);
                 }
             }
             replace_element<TM, TN>(hi, idx, sum);
@@ -366,7 +369,8 @@ hipError_t launch_packets(PixParams p, const PacketPlan& k, int mode, const void
     q.a = base; q.b = base + k.b_offset;
     q.a_bytes = (unsigned)k.a_bytes; q.b_bytes = (unsigned)k.b_bytes; q.plane_bytes = (int)(k.b_bytes / PLANES);
     q.Cb = k.Cb; q.taps = a.taps; q.steps = k.steps; q.splits = k.splits; q.steps_per_split = k.steps_per_split;
-    q.div_taps = a.div_taps; q.div_st = a.div_st;
+    q.mode = mode; q.div_taps = a.div_taps; q.div_st = a.div_st;
+    p.wt = w; p.C = C;
     p.tiles_i = k.tiles_i; p.tiles_pix = k.tiles_pix;
     const bool fused = p.bias || p.relu || p.mask;
     if (k.splits > 1) {

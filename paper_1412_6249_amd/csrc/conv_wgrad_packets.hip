@@ -156,6 +156,9 @@ struct WgradPacketParams {
     int Q, WB, sh, sw;
     int tiles_i, tiles_j, split0, steps, steps_per_split, groups0;
     int bands, N, P, PB;
+    // the fp32 operands, for outputs that are computed again
+    const float* dy_src; const float* x_src;
+    int dy_ns, x_ns, H, W, ph, pw;
     FastDiv div_pairs, div_q, div_c, div_s;
 };
 
@@ -254,7 +257,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void wgrad_packets_kernel(const Wg
     // the last requests must not outlive the workgroup's LDS
     __builtin_amdgcn_s_waitcnt(0x0070);
 
-    // infinities and NaNs: again, as plain fp32 sums over the positions that exist (conv_packets.hip)
+    // infinities and NaNs: again, as plain fp32 sums of the fp32 operands over the positions that exist
     unsigned long long bad = join_sets<TM, TN>(hi, lo);
     if (__builtin_expect(__any(bad != 0), 0)) {
         while (bad) {
@@ -268,17 +271,20 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void wgrad_packets_kernel(const Wg
                 const int tap = fastdiv(col, q.div_c), c = col - tap * q.C;
                 const int r = fastdiv(tap, q.div_s), s = tap - r * q.S;
                 for (int st = s0; st < s1 && sum == sum; ++st) {
-                    const int grp = fastdiv(st, q.div_pairs), lg = grp - q.groups0;
+                    const int grp = fastdiv(st, q.div_pairs);
                     for (int half = 0; half < 2; ++half) {
                         const int m = (st - grp * q.pairs) * 2 + half;
                         if (m >= q.real) continue;
                         const int pr = fastdiv(m, q.div_q), pc = m - pr * q.Q;
-                        const unsigned char* pa = (const unsigned char*)q.dy + ((size_t)(lg * q.PD + m) * q.K + k) * 16;
-                        const unsigned char* pb = (const unsigned char*)q.x + ((size_t)(lg * q.XD + (pr * q.sh + r) * q.WB + pc * q.sw + s) * q.C + c) * 16;
+                        const float* pa = q.dy_src + (size_t)k * q.P * q.Q + pc;
+                        const float* pb = q.x_src + (size_t)c * q.H * q.W;
+                        const int w = pc * q.sw - q.pw + s;
                         for (int im = 0; im < 8; ++im) {
-                            const int v = grp * 8 + im, n = v / q.bands, band = v - n * q.bands;
-                            if (n >= q.N || band * q.PB + pr >= q.P) continue;
-                            sum = __builtin_fmaf(join_parts(pa + im * 2, q.dy_plane), join_parts(pb + im * 2, q.x_plane), sum);
+                            const int v = grp * 8 + im, n = v / q.bands, band = v - n * q.bands, p = band * q.PB + pr;
+                            if (n >= q.N || p >= q.P) continue;
+                            const int h = p * q.sh - q.ph + r;
+                            const bool inside = (unsigned)h < (unsigned)q.H && (unsigned)w < (unsigned)q.W;
+                            sum = __builtin_fmaf(pa[(size_t)n * q.dy_ns + (size_t)p * q.Q], inside ? pb[(size_t)n * q.x_ns + (size_t)h * q.W + w] : 0.0f, sum);
                         }
                     }
                 }
@@ -440,6 +446,7 @@ hipError_t launch_wgrad_packets(const ConvGeom& g, const WgradPacketPlan& k, con
     q.pairs = k.pairs; q.real = k.real; q.PD = k.PD; q.XD = k.XD; q.Q = g.Q; q.WB = k.WB; q.sh = g.sh; q.sw = g.sw;
     q.tiles_i = k.tiles_i; q.tiles_j = k.tiles_j; q.steps = k.steps; q.steps_per_split = k.steps_per_split;
     q.bands = k.bands; q.N = g.N; q.P = g.P; q.PB = k.PB;
+    q.dy_src = (const float*)dy; q.x_src = (const float*)x; q.dy_ns = g.y_ns; q.x_ns = g.x_ns; q.H = g.H; q.W = g.W; q.ph = g.ph; q.pw = g.pw;
     q.div_pairs = make_fastdiv(k.pairs); q.div_q = make_fastdiv(g.Q); q.div_c = make_fastdiv(g.C); q.div_s = make_fastdiv(g.S);
 
     BandPackPair b{};

@@ -12,39 +12,20 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int PLANES = 3;
 
-// x = p0 + p1 + p2 exactly (as long as the parts stay above the smallest bf16 subnormal). Values that
-// round up past the largest bf16 are truncated instead; infinities and NaNs go into p0 alone.
-__device__ __forceinline__ void split3(float x, __bf16& p0, __bf16& p1, __bf16& p2) {
-    const uint32_t u = __float_as_uint(x);
-    p0 = (__bf16)x;
-    if ((u & 0x7fffffffu) >= 0x7f7f8000u) {                    // would round to infinity, or is not finite
-        const bool nan = (u & 0x7fffffffu) > 0x7f800000u;
-        p0 = __builtin_bit_cast(__bf16, (uint16_t)(nan ? 0x7fc0u : (u >> 16)));
-        if ((u & 0x7f800000u) == 0x7f800000u) { p1 = (__bf16)0.0f; p2 = (__bf16)0.0f; return; }
-    }
-    const float r1 = x - (float)p0;
-    p1 = (__bf16)r1;
-    p2 = (__bf16)(r1 - (float)p1);
-}
+// An operand is split as 2^16 times its value, and the joined sums are scaled back: 2^16 x = p0 + p1 + p2 exactly for
+// every fp32 x of less than 2^112, because the last bit of the smallest normal number (2^-149) is then bf16's smallest
+// subnormal. (Unscaled, the third part is lost below 2^-110 and the second below 2^-118: 2e-5 of the operand at 2^-120,
+// 1.5e-3 at 2^-126.) Scaling by powers of two leaves every rounding of ordinary numbers where it was. What does not
+// fit above, operands of 2^112 or results of 2^96 and more, comes out infinite or NaN, as infinities and NaNs do, and is
+// computed again from the fp32 operands.
+constexpr float SPLIT_SCALE = 65536.0f, JOIN_SCALE = 1.0f / (65536.0f * 65536.0f);
 
-__device__ __forceinline__ void store_split8(const float (&v)[8], unsigned char* base, size_t plane_bytes) {
-    bf16x8 q[PLANES];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        __bf16 a, b, c;
-        split3(v[e], a, b, c);
-        q[0][e] = a; q[1][e] = b; q[2][e] = c;
-    }
-#pragma unroll
-    for (int pl = 0; pl < PLANES; ++pl) *reinterpret_cast<bf16x8*>(base + pl * plane_bytes) = q[pl];
-}
-
-// The parts of two numbers, for kernels that have the fp32 numbers at hand when an output comes out
-// infinite or NaN: no special values (an infinity, or a value that rounds to one, leaves NaNs in the
-// lower parts). Eleven instructions.
+// The parts of two numbers. Thirteen instructions, two of them the scaling.
 __device__ __forceinline__ void split_pair(float x, float y, uint32_t (&part)[PLANES]) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     typedef float floatx2 __attribute__((ext_vector_type(2)));
+    x *= SPLIT_SCALE;
+    y *= SPLIT_SCALE;
 #pragma unroll
     for (int pl = 0; pl < PLANES; ++pl) {
         const floatx2 f = {x, y};
@@ -52,6 +33,20 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t (&part)[PL
         x -= __uint_as_float(part[pl] << 16);
         y -= __uint_as_float(part[pl] & 0xffff0000u);
     }
+}
+
+__device__ __forceinline__ void store_split8(const float (&v)[8], unsigned char* base, size_t plane_bytes) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 q[PLANES];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        uint32_t part[PLANES];
+        split_pair(v[2 * e], v[2 * e + 1], part);
+#pragma unroll
+        for (int pl = 0; pl < PLANES; ++pl) q[pl][e] = part[pl];
+    }
+#pragma unroll
+    for (int pl = 0; pl < PLANES; ++pl) *reinterpret_cast<u32x4*>(base + pl * plane_bytes) = q[pl];
 }
 
 template <int TM, int TN, int WM, int WN>
@@ -127,7 +122,7 @@ __device__ __forceinline__ void packets_landed() {
     asm volatile("" ::: "memory");
 }
 
-// Adds the two accumulator sets (into hi) and returns a bit per element that is infinite or NaN.
+// Adds the two accumulator sets (into hi), scales them back and returns a bit per element that is infinite or NaN.
 template <int TM, int TN>
 __device__ __forceinline__ unsigned long long join_sets(floatx16 (&hi)[TM][TN], const floatx16 (&lo)[TM][TN]) {
     static_assert(TM * TN * 16 <= 64, "");
@@ -138,8 +133,9 @@ __device__ __forceinline__ unsigned long long join_sets(floatx16 (&hi)[TM][TN], 
         for (int b = 0; b < TN; ++b)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                hi[a][b][e] += lo[a][b][e];
-                if (!(__builtin_fabsf(hi[a][b][e]) <= 3.402823466e38f)) bad |= 1ull << ((a * TN + b) * 16 + e);
+                const float v = hi[a][b][e] + lo[a][b][e];
+                if (!(__builtin_fabsf(v) <= 3.402823466e38f)) bad |= 1ull << ((a * TN + b) * 16 + e);
+                hi[a][b][e] = v * JOIN_SCALE;
             }
     return bad;
 }
@@ -152,13 +148,6 @@ __device__ __forceinline__ void replace_element(floatx16 (&hi)[TM][TN], int idx,
         for (int b = 0; b < TN; ++b)
 #pragma unroll
             for (int k = 0; k < 16; ++k) hi[a][b][k] = (a * TN + b) * 16 + k == idx ? v : hi[a][b][k];
-}
-
-// The fp32 number whose parts sit `plane` bytes apart (the small parts first: every sum is exact).
-__device__ __forceinline__ float join_parts(const unsigned char* p, size_t plane) {
-    float v = 0.0f;
-    for (int pl = PLANES - 1; pl >= 0; --pl) v += (float)*reinterpret_cast<const __bf16*>(p + pl * plane);
-    return v;
 }
 
 }  // namespace packets

@@ -97,21 +97,28 @@ def test_split_products_against_the_oracle_and_the_general_kernels(case):
             assert rel_l2(g, r) <= 1e-5, (route, name)
 
 
+def _huge_part(g, ref):
+    """The outputs of 1e30 and more that are finite on both sides, scaled into range: (got, wanted)."""
+    m = np.isfinite(g) & np.isfinite(ref) & (np.abs(ref) >= 1e30) & (np.abs(ref) < 3e38)
+    return g[m].astype(np.float64) / 2.0 ** 100, ref[m] / 2.0 ** 100
+
+
 @pytest.mark.parametrize("route", ["patch", "packets"])
-def test_infinities_nans_and_values_at_the_ends_of_the_range(route):
-    """An infinity times the zero low parts of the other operand is a NaN in the split products, and a
-    value above the largest bf16 has no rounded high part: outputs that come out infinite or NaN are
-    computed again the way the fp32 kernel would. Same infinities, same NaNs as the general kernel."""
+def test_infinities_nans_and_values_at_the_upper_end_of_the_range(route):
+    """An infinity times the zero low parts of the other operand is a NaN in the split products, and a value of 2^112
+    and more has no scaled parts: outputs that come out infinite or NaN are computed again the way the fp32 kernel
+    would. Same infinities, same NaNs as the general kernel; the finite ones right, small and huge."""
     import paper_1412_6249_amd as pa
     from gpu_util import rel_l2
     case = (2, 200, 12, 12, 208, 3, 3, 1, 1)
     x, w, b, dy, act, prev = _inputs(case)
     big = np.float32(3.4028234e38)
     x[0, 3, 2, 2], x[0, 5, 9, 9], x[1, 0, 0, 0], x[1, 7, 6, 6] = np.inf, np.nan, -np.inf, big
+    x[1, 9, 3, 9] = 3e34                        # (above what the split holds, below the largest bf16)
     dy[0, 1, 3, 3], dy[1, 2, 8, 8], dy[1, 40, 1, 10] = -np.inf, np.nan, big
     w *= np.float32(0.1)                        # so that no finite partial sum overflows, whatever the order
     w[4, 4, 0, 0] = np.inf
-    x[0, :, 5, 5] *= np.float32(1e-30)          # and small ones: exact down to the parts' smallest subnormal
+    x[0, :, 5, 5] *= np.float32(1e-30)
     try:
         _forced(pa, route)
         got, _ = _run(pa, case, x, w, b, dy, act, prev)
@@ -120,12 +127,79 @@ def test_infinities_nans_and_values_at_the_ends_of_the_range(route):
     finally:
         _forced(pa, "auto")
     assert not np.array_equal(got[1], base[1], equal_nan=True) and not np.array_equal(got[2], base[2], equal_nan=True)
-    for name, g, o in zip(("y fused", "y", "dx", "dx accumulated", "dx masked"), got, base):
+    with np.errstate(all="ignore"):
+        y, dx = oracle.conv_fwd(x, w, 1, 1), oracle.conv_bwd_data(dy, w, x.shape, 1, 1)
+    for name, g, o, r in zip(("y fused", "y", "dx", "dx accumulated", "dx masked"), got, base, (None, y, dx, None, None)):
         assert np.array_equal(np.isnan(g), np.isnan(o)), name
         inf = np.isinf(o)
         assert np.array_equal(np.isinf(g), inf) and np.array_equal(g[inf], o[inf]), name
         ok = np.isfinite(o) & (np.abs(o) < 1e30)
         assert ok.mean() > 0.4 and rel_l2(g[ok], o[ok]) <= 1e-6, name
+        if r is not None:                       # one fp32 sum that a single product dominates
+            have, want = _huge_part(g, r)
+            assert have.size > 500 and rel_l2(have, want) <= 1e-6 and (np.abs(have - want) <= 1e-5 * np.abs(want)).all(), name
+
+
+# exponents of the small operand: where the third part of an unscaled split falls below the smallest bf16 (2^-133) in
+# part and altogether, and where the second one does
+@pytest.mark.parametrize("power", [-112, -117, -121])
+@pytest.mark.parametrize("route", ["patch", "packets", "auto"])
+def test_tiny_operands_keep_their_bits(route, power):
+    """A whole operand close to the smallest normal number, the other one large: no less exact than the general kernels.
+    (An operand held in two parts is off by 4e-6 at 2^-117, in one and a bit by 6e-5 at 2^-121.)"""
+    import paper_1412_6249_amd as pa
+    from gpu_util import rel_l2
+    case = (8, 64, 14, 13, 72, 3, 3, 1, 1)
+    tiny, large = np.float32(2.0 ** power), np.float32(2.0 ** 60)
+    for small_filter in (False, True):
+        x, w, b, dy, act, prev = _inputs(case)
+        x, dy, w = (x * large, dy * large, w * tiny) if small_filter else (x * tiny, dy * tiny, w * large)
+        b, prev = b * np.float32(0), prev * np.float32(0)
+        got = {}
+        try:
+            for r in (route, "general"):
+                _forced(pa, r)
+                got[r], _ = _run(pa, case, x, w, b, dy, act, prev)
+        finally:
+            _forced(pa, "auto")
+        y, dx = oracle.conv_fwd(x, w, 1, 1), oracle.conv_bwd_data(dy, w, x.shape, 1, 1)
+        for name, g, o, ref in zip(("y", "dx"), got[route][1:3], got["general"][1:3], (y, dx)):
+            assert np.abs(ref).max() > 0 and rel_l2(g, ref) <= max(rel_l2(o, ref), 1.0e-7), (name, small_filter, rel_l2(g, ref), rel_l2(o, ref))
+
+
+@pytest.mark.parametrize("power", [-112, -117, -121])
+def test_tiny_operands_keep_their_bits_in_the_weight_gradient_and_fc(power):
+    import torch
+    import paper_1412_6249_amd as pa
+    from gpu_util import rel_l2, workspace
+    case = (9, 48, 14, 13, 72, 3, 3, 1, 1)
+    tiny, large = np.float32(2.0 ** power), np.float32(2.0 ** 60)
+    for small_x in (False, True):
+        x, w, b, dy, _, _ = _inputs(case)
+        x, dy = (x * tiny, dy * large) if small_x else (x * large, dy * tiny)
+        try:
+            _forced(pa, "packets")
+            got, _, _ = _wgrad(pa, case, x, dy, w, b, 0.0)
+            _forced(pa, "general")
+            base, _, _ = _wgrad(pa, case, x, dy, w, b, 0.0)
+        finally:
+            _forced(pa, "auto")
+        ref = oracle.conv_bwd_weight(x, dy, w.shape, 1, 1)
+        assert rel_l2(got, ref) <= max(rel_l2(base, ref), 1.0e-7), (small_x, rel_l2(got, ref), rel_l2(base, ref))
+    N, C, K = 40, 2304, 2400                 # the weight gradient as a streaming product too
+    g = torch.Generator().manual_seed(1)
+    x, w, dy = (torch.randn(s, generator=g) for s in ((N, C), (K, C), (N, K)))
+    err = lambda a, r: float((a.double().cpu() - r).norm() / r.norm())
+    for a, c in ((float(tiny), float(large)), (float(large), float(tiny))):
+        tx, tw, tdy = (x * a).cuda(), (w * c).cuda(), (dy * a).cuda()
+        y, dx, dw = torch.empty(N, K, device="cuda"), torch.empty(N, C, device="cuda"), torch.empty(K, C, device="cuda")
+        ws = [workspace(pa.purine_fc_workspace_bytes(p, N, C, K)) for p in (0, 1, 2)]
+        pa.purine_fc_fwd(tx, tw, None, y, ws=ws[0])
+        pa.purine_fc_bwd_data(tdy, tw, dx, ws=ws[1])
+        pa.purine_fc_bwd_weight(tx, (dy * c).cuda(), dw, None, ws=ws[2])
+        X, W, D, E = tx.double().cpu(), tw.double().cpu(), tdy.double().cpu(), (dy * c).double()
+        # 2.5e-7 is the fp32 kernels' own error over sums of 2300; dw sums 40
+        assert err(y, X @ W.t()) <= 3e-7 and err(dx, D @ W) <= 3e-7 and err(dw, E.t() @ X) <= 3e-7, (a, err(y, X @ W.t()), err(dx, D @ W), err(dw, E.t() @ X))
 
 
 @pytest.mark.parametrize("route", ["patch", "packets"])
@@ -204,6 +278,7 @@ def test_weight_gradient_route_and_nonfinite_values():
     x[1, 30, 3, 3] = np.float32(3.4028234e38)
     dy *= np.float32(1e-3)
     dy[4, 5, 14, 14], dy[3, 8, 0, 7], dy[0, 63, 10, 10] = np.inf, np.nan, -np.inf
+    x[1, 31, 5, 5], dy[1, 100, 6, 6] = 1e34, np.float32(2e36)
     got_w, got_b, need = _wgrad(pa, case, x, dy, w, b, 0.0)
     _general(pa, True)
     try:
@@ -211,6 +286,10 @@ def test_weight_gradient_route_and_nonfinite_values():
     finally:
         _general(pa, False)
     assert need != need0
+    with np.errstate(all="ignore"):
+        have, want = _huge_part(got_w, oracle.conv_bwd_weight(x, dy, w.shape, 1, 1))
+    # several products of that size may cancel: the bound on a sum's terms instead of on the sum
+    assert have.size > 500 and rel_l2(have, want) <= 1e-5
     for g, o in ((got_w, base_w), (got_b, base_b)):
         assert np.array_equal(np.isnan(g), np.isnan(o))
         inf = np.isinf(o)
