@@ -117,7 +117,12 @@ size_t purine_bias_bwd_workspace_bytes(const int64_t dy_dim[4], int32_t dtype);
  * pass takes depends on its shape); sums are fp32 either way. The parts hold any operand below 2^112 = 5.2e33 exactly,
  * and the error of the sum against exact arithmetic is no larger than the fp32 MFMAs' (products of two numbers that are
  * both subnormal aside). Outputs that involve operands of that size, infinities or NaNs, or that reach 2^96 = 7.9e28, are
- * computed again as a plain fp32 sum: the result is the fp32 one, at a small fraction of the speed. */
+ * computed again as a plain fp32 sum: the result is the fp32 one, at a small fraction of the speed.
+ * A call gives the same bits every time. They depend on its shape, the number of images included: the same image may
+ * come out with other last bits in another batch, because a small launch splits the sum over workgroups and adds the
+ * parts. Forward passes over more than 2048 products per output (c * r * s) whose output has 32 or more tiles of 128 channels x
+ * 256 positions are fp32 MFMA sums in one fixed order, whatever the batch (33..48 and 81..96 channels aside, which have
+ * two tile shapes). */
 
 /* Conv: y[n,k,p,q] = sum_{c,r,s} x[n,c,p*sh-ph+r,q*sw-pw+s] * w[k,c,r,s], taps outside x are 0.
  * x, w, y share one dtype (F32 or BF16). The patch matrix is never written to memory.
@@ -449,7 +454,8 @@ void purine_set_kernel_probe(void* start_event, void* stop_event);
  * forward / backward-data kernels to one of 128x128, 96x256, 96x128, 64x256, 128x64, 64x128, 32x256,
  * 64x64, 32x128; any other pair (e.g. 0, 0) restores the automatic choice. Results are bit-identical
  * for every shape: the reduction order per output element does not depend on it. (The automatic
- * choice may be another kernel, whose sums are ordered differently: F32 layers with several taps.)
+ * choice may be another kernel, whose sums are ordered differently: F32 layers with several taps,
+ * see the note on F32 arithmetic.)
  * (48|16, 256|128) does the same for the 16-row-granular tiles of GEMMs with at most 16 or 33..48
  * rows, (192, 128) selects an uncalibrated tile.
  * For 1x1 / stride-1 / unpadded layers, which run the streaming GEMM kernel instead: (32|64|96, 2),

@@ -737,15 +737,20 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
         // few microseconds. A patch in LDS (conv_patch_f32.hip) needs no copy of the activations; strided
         // gathers and launches that need a split reduction to fill the chip take packed operands
         // (conv_packets.hip).
-        // A forward pass over more than 2048 products per output stays on the fp32 kernels (unless it is a
-        // small launch, where the split reduction gains 3 - 5 times): what it computes decides ReLU signs and
-        // pooling winners, the rounding error of such long fp32 chains is 6 - 7e-7, and a kernel with another
-        // one, exact or not, decides enough near-ties differently to move the gradients of the five-layer
-        // stack by 1.5 - 2.7e-3 in norm (0 - 0.7e-3 on the inception module's shorter sums). Such a pass takes
-        // the patch kernel with fp32 products instead, which adds in the tap kernel's order.
+        // What a forward pass computes decides ReLU signs and pooling winners. Two arithmetics whose outputs differ by
+        // delta relative to their spread disagree on 0.4 * delta of the signs, and each disagreement moves a whole
+        // entry of a gradient: a change of sqrt(0.8 * delta) in its norm, whichever side is the more exact. The
+        // fp32 chain's rounding is 2.7e-8 * sqrt(products) (four 3x3 layers in a row, 16 images of 13x13: 4.2e-7 at 288
+        // products, 8.3e-7 at 864, 1.3e-6 at 2304, 2.0e-6 at 4608; the split's is a third of it), so that change reaches
+        // a thousandth at 2048 products. Past that line a pass keeps the fp32 order of additions, on the patch
+        // kernel with fp32 products. But not launches of less than 32 tiles (a million outputs): of those not one sign
+        // is expected to differ, and they gain 3 - 5 times from a split reduction. (Measured on the gradients of those four layers:
+        // 0 - 5e-4 in eleven of twelve runs below 2048 products, in the twelfth one sign of 86528 outputs differs and is
+        // worth 2.7e-3; 1.8e-3 - 3.1e-3 in five of six runs above. On an AlexNet stack of 128 images
+        // 1.5e-3 - 2.7e-3 without the rule, 1.4e-6 with it, for 5.15 instead of 4.15 ms; inception module 0 - 0.7e-3.)
         const double old_us = best * 2.0 * Ci * pl.Rt * pl.St / (157.3e6 / 256.0 * 0.78) + 6.0;
         const PixParams pp = make_pix_params(dtype, g, pl);
-        const bool small = ((long long)Co + 127) / 128 * ((M + 255) / 256) < 32;       // at most an eighth of the CUs get a tile
+        const bool small = ((long long)Co + 127) / 128 * ((M + 255) / 256) < 32;
         const bool keep_bits = pl.mode == 0 && (long long)Ci * g.R * g.S > 2048 && !small;
         pl.pf = plan_patch_f32(pp, pl.mode == 2, !(keep_bits && g_force_bm == 0) && !f32_patch_forced());
         pl.pk = plan_packets(pp, pl.mode == 2);

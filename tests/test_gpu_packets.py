@@ -97,6 +97,36 @@ def test_split_products_against_the_oracle_and_the_general_kernels(case):
             assert rel_l2(g, r) <= 1e-5, (route, name)
 
 
+# N, C, H, K, R and whether the forward pass keeps the fp32 order of additions: more than 2048 products and 32 or more tiles of
+# 128 channels x 256 positions; GEMMs of 33..48 and 81..96 rows then stay on the 16-row tiles of the tap kernel
+@pytest.mark.parametrize("case, keeps", [((20, 256, 13, 384, 3), True), ((50, 256, 13, 40, 3), True), ((50, 230, 13, 96, 3), True), ((50, 228, 13, 130, 3), True),
+                                         ((50, 227, 13, 130, 3), False), ((20, 83, 13, 384, 5), True), ((20, 81, 13, 384, 5), False),
+                                         ((16, 256, 13, 128, 3), False), ((2, 256, 13, 384, 3), False)], ids=str)
+def test_which_forward_passes_keep_the_fp32_order(case, keeps):
+    """The automatic route of long sums gives the general kernels' bits, below either line it gives others."""
+    import torch
+    import paper_1412_6249_amd as pa
+    from gpu_util import to_dev, workspace, to_host, rel_l2, DEV
+    N, C, H, K, R = case
+    g = torch.Generator().manual_seed(N + C)
+    x, w, b = (torch.randn(s, generator=g) for s in ((N, C, H, H), (K, C, R, R), (K,)))
+    desc, tx, tw, tb = pa.conv_desc(1, R // 2), x.to(DEV), w.to(DEV), b.to(DEV)
+
+    def once():
+        y = torch.full((N, K, H, H), float("nan"), device=DEV)
+        pa.purine_conv_fwd_bias_relu(desc, tx, tw, tb, y, relu=True, ws=workspace(pa.purine_conv_workspace_bytes(0, desc, x.shape, w.shape, pa.PURINE_F32)))
+        torch.cuda.synchronize()
+        return y
+    auto = once()
+    _general(pa, True)
+    try:
+        general = once()
+    finally:
+        _general(pa, False)
+    assert torch.equal(auto, general) == keeps
+    assert rel_l2(to_host(auto), to_host(general)) <= 5e-6          # two fp32 sums of up to 2304 products each
+
+
 def _huge_part(g, ref):
     """The outputs of 1e30 and more that are finite on both sides, scaled into range: (got, wanted)."""
     m = np.isfinite(g) & np.isfinite(ref) & (np.abs(ref) >= 1e30) & (np.abs(ref) < 3e38)
