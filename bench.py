@@ -25,22 +25,23 @@ sys.path.insert(0, ROOT)
 
 PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}     # MI355X dense MFMA peaks
 HBM_PEAK_GBS = 8000.0
-# Most passes of fp32 layers with several taps and at least 16 input channels multiply on the bf16 matrix
-# cores: three exact bf16 parts per operand, six bf16 products per fp32 product. Their matrix roof is the
-# bf16 peak, and what the units execute is six times the layer's flops.
-SPLIT_PRODUCTS = 6
-FORWARD_KINDS = (0, 13)
+# Operator kinds of a convolution pass -> the pass
+CONV_PASS = {0: 0, 13: 0, 2: 1, 14: 1, 3: 2, 15: 2}
 
 
 def products(L, kind):
-    if L.dtype != "f32" or L.R * L.S == 1 or L.C < 16:
-        return 1
-    return 1 if kind in FORWARD_KINDS and L.C * L.R * L.S > 2048 else SPLIT_PRODUCTS
+    """bf16 or fp32 products the matrix units execute per multiplication of this pass: 1, or 6 where an fp32
+    pass multiplies three bf16 parts per operand. The library says which kernel it would launch."""
+    import paper_1412_6249_amd as pa
+    return pa.purine_conv_matrix_products(CONV_PASS[kind], pa.conv_desc(L.stride, L.pad), L.x_shape, L.w_shape,
+                                          pa.PURINE_BF16 if L.dtype == "bf16" else pa.PURINE_F32)
 
 
 def mfma_peak(L, kind):
     """Peak of the matrix units for this pass, in TFLOP/s of the layer's own flops."""
-    return PEAK_TFLOPS["bf16"] / SPLIT_PRODUCTS if products(L, kind) > 1 else PEAK_TFLOPS[L.dtype]
+    n = products(L, kind)
+    return PEAK_TFLOPS["bf16"] / n if n > 1 else PEAK_TFLOPS[L.dtype]
+
 
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "hbm_traffic_dominant_kernels.md")
 
@@ -297,8 +298,9 @@ def run_config(cfg, args, secondary_figures):
     value = flop / (ms_per_step * 1e-3) / 1e12
     return {"workload": WORKLOAD_NAMES[cfg], "ms_per_step": round(ms_per_step, 4), "value": round(value, 3),
             "dtype": dtype, "conv_gflop_per_step": round(flop / 1e9, 2),
-            # matrix-unit time of the step at peak / its time
-            "frac_of_mfma_peak": round(sum(l.flop_per_pass / mfma_peak(l, k) for l in CONV_LAYERS[cfg] for k in (0, 2, 3)) / 1e12 / (ms_per_step * 1e-3), 4),
+            "frac_of_mfma_peak": round(value / PEAK_TFLOPS[dtype], 4),
+            # the same against the peak of the units each pass really runs on (fp32 passes on bf16 parts: 2500 / 6)
+            "frac_of_route_peak": round(sum(l.flop_per_pass / mfma_peak(l, k) for l in CONV_LAYERS[cfg] for k in (0, 2, 3)) / 1e12 / (ms_per_step * 1e-3), 4),
             "roofline": roofline, "secondary": secondary, "merge": merge, "streams": n_streams}
 
 

@@ -132,6 +132,9 @@ for _name, (_res, _args) in _SIGS.items():
     _f.restype, _f.argtypes = _res, _args
 
 EXPORTED = sorted(_SIGS)
+# include/purine_introspect.h
+_lib.purine_conv_matrix_products.restype = ctypes.c_int
+_lib.purine_conv_matrix_products.argtypes = [ctypes.c_int, _D, _i64p, _i64p, ctypes.c_int32]
 
 
 # ------------------------------------------------------------------ marshalling helpers
@@ -237,6 +240,11 @@ def purine_conv_out_shape(desc, x_shape, w_shape):
 
 def purine_conv_workspace_bytes(which, desc, x_shape, w_shape, dtype):
     return int(_lib.purine_conv_workspace_bytes(int(which), _ref(desc), _dims(x_shape),
+                                                _dims(w_shape), int(dtype)))
+
+
+def purine_conv_matrix_products(which, desc, x_shape, w_shape, dtype):
+    return int(_lib.purine_conv_matrix_products(int(which), _ref(desc), _dims(x_shape),
                                                 _dims(w_shape), int(dtype)))
 
 

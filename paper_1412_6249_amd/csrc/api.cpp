@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "purine_introspect.h"
 
 using namespace purine;
 
@@ -190,6 +191,22 @@ size_t purine_conv_workspace_bytes(int pass, const purine_conv_desc* desc, const
         return wgrad_db_offset(pl) + pl.db_ws_bytes;
     }
     return plan_conv_pix(g, pass == PURINE_CONV_BWD_DATA, dtype, false).ws_bytes;
+}
+
+int purine_conv_matrix_products(int pass, const purine_conv_desc* desc, const int64_t x_dim[4],
+                                const int64_t w_dim[4], int32_t dtype) {
+    if (pass < PURINE_CONV_FWD || pass > PURINE_CONV_BWD_WEIGHT_BIAS) return 0;
+    if (!desc || !x_dim || !w_dim || !is_float_dtype(dtype)) return 0;
+    ConvGeom g;
+    if (make_geom(desc, x_dim, w_dim, nullptr, &g) != PURINE_OK) return 0;
+    bool parts;
+    if (pass == PURINE_CONV_BWD_WEIGHT || pass == PURINE_CONV_BWD_WEIGHT_BIAS) {
+        parts = plan_wgrad(g, dtype).pk.use;
+    } else {
+        const PixPlan pl = plan_conv_pix(g, pass == PURINE_CONV_BWD_DATA, dtype, false);
+        parts = pl.pk.use || (pl.pf.use && pl.pf.split);
+    }
+    return parts ? 6 : 1;
 }
 
 size_t purine_bias_bwd_workspace_bytes(const int64_t dy_dim[4], int32_t dtype) {

@@ -1,0 +1,48 @@
+"""What a pass multiplies with: the library's answer (host code) over the workloads' layers, and bench.py's use of it."""
+import pytest
+
+import bench
+import paper_1412_6249_amd as pa
+from synth.configs import CONV_LAYERS
+
+FWD, BWD_DATA, BWD_WEIGHT, BWD_WEIGHT_BIAS = range(4)
+
+
+def _products(layer, which):
+    dt = pa.PURINE_F32 if layer.dtype == "f32" else pa.PURINE_BF16
+    return pa.purine_conv_matrix_products(which, pa.conv_desc(layer.stride, layer.pad), layer.x_shape, layer.w_shape, dt)
+
+
+@pytest.mark.parametrize("cfg, name, want", [
+    (3, "b3_5x5", (1, 1)),             # backward-data has 16 rows, the weight gradient 16 channels: fp32 kernels
+    (3, "b2_3x3", (6, 6)),
+    (4, "conv2", (6, 6)), (4, "conv4", (6, 6)),
+    (4, "conv1", (1, 1)),              # three channels
+    (2, "cccp1", (1, 1)), (5, "c3x3", (1, 1))])
+def test_gradients_of_the_workloads(cfg, name, want):
+    layer = next(l for l in CONV_LAYERS[cfg] if l.name == name)
+    assert (_products(layer, BWD_DATA), _products(layer, BWD_WEIGHT)) == want
+    assert _products(layer, BWD_WEIGHT_BIAS) == want[1]
+
+
+def test_forward_passes_of_long_sums_depend_on_the_launch():
+    """More than 2048 products per output: fp32 products, but not in a launch of few tiles."""
+    d = pa.conv_desc(1, 1)
+    f = lambda n, c: pa.purine_conv_matrix_products(FWD, d, (n, c, 13, 13), (384, c, 3, 3), pa.PURINE_F32)
+    assert (f(128, 384), f(2, 384), f(128, 227), f(128, 228)) == (1, 6, 6, 1)
+
+
+def test_illegal_shapes_and_passes_give_zero():
+    d = pa.conv_desc(1, 0)
+    assert pa.purine_conv_matrix_products(FWD, d, (1, 3, 2, 2), (4, 3, 3, 3), pa.PURINE_F32) == 0
+    assert pa.purine_conv_matrix_products(4, d, (1, 16, 8, 8), (16, 16, 3, 3), pa.PURINE_F32) == 0
+    assert pa.purine_conv_matrix_products(FWD, d, (1, 16, 8, 8), (16, 16, 3, 3), pa.PURINE_I32) == 0
+
+
+def test_bench_prices_a_pass_by_the_kernel_that_runs():
+    for cfg, layers in CONV_LAYERS.items():
+        for l in layers:
+            for kind, which in ((0, FWD), (13, FWD), (2, BWD_DATA), (14, BWD_DATA), (3, BWD_WEIGHT), (15, BWD_WEIGHT)):
+                n = _products(l, which)
+                assert bench.products(l, kind) == n, (cfg, l.name, kind)
+                assert bench.mfma_peak(l, kind) == (2500.0 / 6 if n == 6 else bench.PEAK_TFLOPS[l.dtype])
