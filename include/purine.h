@@ -430,7 +430,8 @@ int purine_graph_num_tensors(const purine_graph* g);
 
 /* Per-operator device timing. With timing on, purine_graph_run brackets the main kernel of every
  * device operator with a pair of HIP events on the operator's own stream (the small second-pass
- * kernels of the split reductions are outside the bracket). After the run,
+ * kernels of the split reductions are outside the bracket; an operator that lays its activations out
+ * first is bracketed whole). After the run,
  * purine_graph_op_elapsed_ms gives the elapsed time of that bracket in the last run.
  * PURINE_E_ARG for a bad id, a host operator, or when the last run was not timed. */
 int purine_graph_enable_timing(purine_graph* g, int on);

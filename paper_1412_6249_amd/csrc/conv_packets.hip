@@ -270,7 +270,6 @@ hipError_t launch_main(const PixParams& p, const PacketParams& q, hipStream_t st
                                            hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS);
         if (e != hipSuccess) return e;
     }
-    ProbeScope probe(st);
     (void)hipGetLastError();   // drop stale status left by earlier, unrelated runtime calls
     hipLaunchKernelGGL((igemm_packets_kernel<MINUS, D2S, FUSED, TM, TN, WM, WN>), dim3((unsigned)total), dim3(WM * WN * 64), T::LDS, st, p, q);
     return hipGetLastError();
@@ -347,6 +346,7 @@ PacketPlan plan_packets(const PixParams& p, bool d2s, bool any_taps) {
 
 hipError_t launch_packets(PixParams p, const PacketPlan& k, int mode, const void* w, int K, int C, void* ws, hipStream_t st) {
     if (!ws) return hipErrorInvalidValue;
+    ProbeScope whole_op(st);             // layout pass, products, second pass
     unsigned char* base = (unsigned char*)ws;
     PackParams a{};
     a.x = (const float*)p.in; a.xp = base + k.b_offset;

@@ -320,7 +320,6 @@ hipError_t launch_main(const WgradPacketParams& q, int splits, hipStream_t st) {
                                            hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS);
         if (e != hipSuccess) return e;
     }
-    ProbeScope probe(st);
     (void)hipGetLastError();   // drop stale status left by earlier, unrelated runtime calls
     hipLaunchKernelGGL((wgrad_packets_kernel<TM, TN, WM, WN>), dim3((unsigned)total), dim3(WM * WN * 64), T::LDS, st, q);
     return hipGetLastError();
@@ -438,6 +437,7 @@ WgradPacketPlan plan_wgrad_packets(const ConvGeom& g, size_t limit, double budge
 // many as the scratch holds the groups of.
 hipError_t launch_wgrad_packets(const ConvGeom& g, const WgradPacketPlan& k, const void* x, const void* dy, float* dw, float* db, float beta, void* ws,
                                 size_t ws_bytes, hipStream_t st) {
+    ProbeScope whole_op(st);             // layout pass, products, second pass
     unsigned char* base = (unsigned char*)ws;
     float* db_sums = db ? (float*)(base + k.db_offset) : nullptr;
     WgradPacketParams q{};

@@ -496,3 +496,32 @@ def test_fc_f32_takes_no_longer_than_the_composition(which, case):
     finally:
         _general(pa, False)
     assert auto <= 1.25 * general, (auto, general)
+
+
+@pytest.mark.parametrize("which, N, H, stride", [("forward", 64, 56, 2), ("weight gradient", 128, 28, 1)])
+def test_timing_bracket_holds_the_layout_pass(which, N, H, stride):
+    """A pass that lays its operands out first is bracketed from there to its second pass: what the bracket reads is
+    what a call takes on the device (the products alone are about two thirds of these)."""
+    import torch
+    import paper_1412_6249_amd as pa
+    from gpu_util import workspace, DEV
+    C, K, P = 96, 128, H // stride
+    desc = pa.conv_desc(stride, 1)
+    x, w, dy = (torch.randn(s, device=DEV) for s in ((N, C, H, H), (K, C, 3, 3), (N, K, P, P)))
+    y, dw = torch.empty_like(dy), torch.empty_like(w)
+    p = pa.PURINE_CONV_FWD if which == "forward" else pa.PURINE_CONV_BWD_WEIGHT
+    assert pa.purine_conv_matrix_products(p, desc, x.shape, w.shape, pa.PURINE_F32) == 6
+    ws = workspace(pa.purine_conv_workspace_bytes(p, desc, x.shape, w.shape, pa.PURINE_F32))
+    f = (lambda: pa.purine_conv_fwd(desc, x, w, y, ws=ws)) if which == "forward" else (lambda: pa.purine_conv_bwd_weight(desc, x, dy, dw, ws=ws))
+    whole = _graph_time_of(f)
+    evs = [[torch.cuda.Event(enable_timing=True) for _ in range(2)] for _ in range(20)]
+    for s, e in evs:                       # create the underlying handles
+        s.record(); e.record()
+    torch.cuda.synchronize()
+    for s, e in evs:
+        pa.purine_set_kernel_probe(s.cuda_event, e.cuda_event)
+        f()
+    pa.purine_set_kernel_probe(None, None)
+    torch.cuda.synchronize()
+    bracket = min(s.elapsed_time(e) for s, e in evs) * 1e-3
+    assert 0.9 * whole <= bracket <= 1.3 * whole + 1e-5, (bracket, whole)
