@@ -97,6 +97,90 @@ def test_split_products_against_the_oracle_and_the_general_kernels(case):
             assert rel_l2(g, r) <= 1e-5, (route, name)
 
 
+# Channel slices of wider buffers: images further apart than C*H*W. Tiles that cross images, rows cut into bands, a
+# strided forward gather with a phase-folded gradient, 33..48 rows
+VIEW_CASES = [(7, 32, 10, 9, 40, 3, 3, 1, 1), (1, 24, 12, 150, 64, 3, 3, 1, 1), (3, 52, 15, 16, 132, 5, 5, 1, 2), (4, 36, 17, 16, 24, 3, 3, 2, 1)]
+
+
+@pytest.mark.parametrize("route", ["patch", "patch_f32", "packets"])
+@pytest.mark.parametrize("case", VIEW_CASES, ids=str)
+def test_channel_slice_views_give_the_bits_of_dense_tensors(case, route):
+    """Inputs, outputs and the ReLU mask as views with a stride of their own: the same bits as dense tensors on the same
+    route, and nothing outside the slices written. The gradients of the weights through the packed kernel too."""
+    import torch
+    import paper_1412_6249_amd as pa
+    from gpu_util import to_dev, workspace, to_host, DEV
+    N, C, H, W, K, R, S, stride, pad = case
+    x, w, b, dy, act, prev = _inputs(case)
+    desc = pa.conv_desc(stride, pad)
+
+    def view(a, before=4, after=8):
+        """(slice holding a, the buffer around it, which channels are not the slice's); extents keep 16-byte alignment."""
+        n, c, h, wd = a.shape
+        after += -(before + c + after) % 4
+        buf = torch.full((n, before + c + after, h, wd), 7.5, device=DEV)
+        v = buf[:, before:before + c]
+        v.copy_(to_dev(a))
+        return v, buf, [i for i in range(before + c + after) if not before <= i < before + c]
+
+    tw, tb = to_dev(w), to_dev(b)
+    nan = lambda s: np.full(s, np.nan, np.float32)
+    try:
+        _forced(pa, route)
+        want, _ = _run(pa, case, x, w, b, dy, act, prev)
+        want_w, want_b, _ = _wgrad(pa, case, x, dy, w, b, 0.0)
+        ws = [workspace(pa.purine_conv_workspace_bytes(p, desc, x.shape, w.shape, pa.PURINE_F32)) for p in range(4)]
+        tx, tdy, tact = view(x), view(dy, 8, 4), view(act, 0, 12)
+        out = [view(nan(dy.shape)), view(nan(dy.shape), 0, 4), view(nan(x.shape), 12, 0), view(prev, 4, 4), view(nan(x.shape), 0, 12)]
+        dw, db = to_dev(w), to_dev(b)
+        pa.purine_conv_fwd_bias_relu(desc, tx[0], tw, tb, out[0][0], relu=True, ws=ws[0])
+        pa.purine_conv_fwd(desc, tx[0], tw, out[1][0], ws=ws[0])
+        pa.purine_conv_bwd_data(desc, tdy[0], tw, out[2][0], ws=ws[1])
+        pa.purine_conv_bwd_data(desc, tdy[0], tw, out[3][0], beta=1.0, ws=ws[1])
+        pa.purine_conv_bwd_data_relu(desc, tdy[0], tw, tact[0], out[4][0], ws=ws[1])
+        pa.purine_conv_bwd_weight_bias(desc, tx[0], tdy[0], dw, db, ws=ws[3])
+        torch.cuda.synchronize()
+    finally:
+        _forced(pa, "auto")
+    for (v, buf, rest), ref in zip(out, want):
+        assert np.array_equal(to_host(v.contiguous()), ref)
+        assert bool((buf[:, rest] == 7.5).all())
+    assert np.array_equal(to_host(dw), want_w) and np.array_equal(to_host(db), want_b)
+
+
+@pytest.mark.parametrize("route", ["auto", "patch", "patch_f32", "packets"])
+def test_grouped_convolution_is_its_groups_on_every_route(route):
+    """Two groups as one call (channel slices of x, y, dx) against each group alone on dense tensors: the same bits."""
+    import torch
+    import paper_1412_6249_amd as pa
+    from gpu_util import to_dev, workspace, DEV
+    N, C, H, K, R = 24, 96, 27, 96, 5
+    g = torch.Generator().manual_seed(9)
+    x, w, b, dy = (torch.randn(s, generator=g).to(DEV) for s in ((N, C, H, H), (K, C // 2, R, R), (K,), (N, K, H, H)))
+    desc = pa.conv_desc(1, 2)
+    full = lambda t: torch.full_like(t, float("nan"))
+    y, dx, dw, db, ya, dxa, dwa, dba = (full(t) for t in (dy, x, w, b, dy, x, w, b))
+    try:
+        _forced(pa, route)
+        ws = [workspace(pa.purine_grouped_conv_workspace_bytes(p, desc, 2, x.shape, w.shape, pa.PURINE_F32)) for p in (0, 1, 3)]
+        pa.purine_grouped_conv_fwd(desc, 2, x, w, b, y, relu=True, ws=ws[0])
+        pa.purine_grouped_conv_bwd_data(desc, 2, dy, w, dx, ws=ws[1])
+        pa.purine_grouped_conv_bwd_weight(desc, 2, x, dy, dw, db, ws=ws[2])
+        for i in range(2):
+            cs, ks = slice(i * C // 2, (i + 1) * C // 2), slice(i * K // 2, (i + 1) * K // 2)
+            xi, wi, bi, di = (t.contiguous() for t in (x[:, cs], w[ks], b[ks], dy[:, ks]))
+            yi, dxi, dwi, dbi = full(di), full(xi), full(wi), full(bi)
+            wsi = [workspace(pa.purine_conv_workspace_bytes(p, desc, xi.shape, wi.shape, pa.PURINE_F32)) for p in (0, 1, 3)]
+            pa.purine_conv_fwd_bias_relu(desc, xi, wi, bi, yi, relu=True, ws=wsi[0])
+            pa.purine_conv_bwd_data(desc, di, wi, dxi, ws=wsi[1])
+            pa.purine_conv_bwd_weight_bias(desc, xi, di, dwi, dbi, ws=wsi[2])
+            ya[:, ks], dxa[:, cs], dwa[ks], dba[ks] = yi, dxi, dwi, dbi
+        torch.cuda.synchronize()
+    finally:
+        _forced(pa, "auto")
+    assert torch.equal(y, ya) and torch.equal(dx, dxa) and torch.equal(dw, dwa) and torch.equal(db, dba)
+
+
 # N, C, H, K, R and whether the forward pass keeps the fp32 order of additions: more than 2048 products and 32 or more tiles of
 # 128 channels x 256 positions; GEMMs of 33..48 and 81..96 rows then stay on the 16-row tiles of the tap kernel
 @pytest.mark.parametrize("case, keeps", [((20, 256, 13, 384, 3), True), ((50, 256, 13, 40, 3), True), ((50, 230, 13, 96, 3), True), ((50, 228, 13, 130, 3), True),
