@@ -260,9 +260,9 @@ StreamPlan plan_stream(long long rows, long long cols, long long K, bool a_in, b
     for (const RowTile& t : kTilesS) {
         const long long ti = (rows + t.bm - 1) / t.bm, tp = (cols + COLS - 1) / COLS, tiles = ti * tp;
         if (tiles > 0x7fffffffLL || !has_tile(a_in, b_in, t.bm)) continue;
-        // B along its outer axis, read again by every row tile: 9216 x 4096, 131 images on three tiles of 64 rows 153 us,
-        // 200 images on two of 128 rows 115
-        const double eff = a_in && !b_in && t.bm == 64 && ti > 2 ? 0.40 : t.eff;
+        // B along its outer axis and too large for the caches, read again by every row tile: 9216 x 4096, 131 images on three
+        // tiles of 64 rows 153 us, on five of 32 rows 135 - 155, 200 images on two of 128 rows 115
+        const double eff = a_in && !b_in && t.bm <= 64 && ti > 2 && (double)cols * K * 4.0 > 60e6 ? 0.77 * t.eff : t.eff;
         long long last = -1;
         for (int half_fill = 0; half_fill <= 8; ++half_fill) {
             long long sp = half_fill * 128 / tiles;
