@@ -869,7 +869,7 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
     // MFMA-bound ones gain what the forward pass gains. A layer that the static-scratch entry point
     // takes has to go through its scratch on the same splits (the results are the same bits).
     const WgradPacketPlan pk = plan_wgrad_packets(g, pl.ws_bytes <= kStaticScratchBytes ? kStaticScratchBytes : 0,
-                                                  split_packets_forced() ? 1e30 : us / 1.05);
+                                                  split_packets_forced() ? 1e30 : us / 1.05 + 2.0);
     if (!pk.use) return pl;
     pl.pk = pk;
     pl.ws_bytes = pk.copies * (size_t)g.K * g.C * g.R * g.S * sizeof(float);

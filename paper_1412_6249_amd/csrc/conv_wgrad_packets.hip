@@ -333,18 +333,19 @@ hipError_t by_tile(const WgradPacketParams& q, int bm, int bn, int splits, hipSt
 
 size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Expected times (us) of the two second passes. reduce_taps_kernel reads whole lines only where there are channels
-// enough, and a thread walks ceil(taps / 4) * splits dependent-free but serial loads; wgrad_reduce_kernel (splits
-// over lanes, elements in the partials' order) scatters single floats into dw. Measured, us, taps / lanes: 55 x 3 x
-// 11x11 with 64 splits 155 / 5, 256 x 48 x 5x5 with 64 40 / 16, 128 x 96 x 3x3 with 16 4.1 / 5.4, 384 x 256 x 3x3
-// with 1 4.5 / 13.4 and with 64 34 / 45.
+// Expected times (us) of the two second passes, less the 2.6 us that either takes at least. reduce_taps_kernel reads
+// whole lines only where there are channels enough, and a thread walks ceil(taps / 4) * splits loads one after the other,
+// 0.036 us each while the partial sums stay in the L2s and 0.078 beyond; wgrad_reduce_kernel (splits over lanes,
+// elements in the partials' order) scatters single floats into dw. Measured, us, taps / lanes: 55 x 3 x 11x11 with 64
+// splits 155 / 5, 256 x 48 x 5x5 with 64 40 / 16, 128 x 96 x 3x3 with 16 4.1 / 5.4, 384 x 256 x 3x3 with 1 4.5 / 13.4
+// and with 64 34 / 45.
 double reduce_taps_us(double dw_bytes, long long splits, int taps) {
-    const double chain = 0.07 * ((taps + 3) / 4) * (double)splits, mem = (double)splits * dw_bytes / 6e6;
-    return 2.6 + (chain > mem ? chain : mem);
+    const double bytes = (double)splits * dw_bytes, chain = (bytes < 16e6 ? 0.036 : 0.078) * ((taps + 3) / 4) * (double)splits, mem = bytes / 6e6;
+    return chain > mem ? chain : mem;
 }
 double reduce_lanes_us(double dw_bytes, long long splits) {
     const double scatter = dw_bytes / 4.0 * 1e-5, mem = (double)splits * dw_bytes / ((long long)(dw_bytes / 4.0) % 4 == 0 ? 6e6 : 2.5e6);
-    return 4.8 + (scatter > mem ? scatter : mem);
+    return 2.2 + (scatter > mem ? scatter : mem);
 }
 
 }  // namespace
@@ -376,7 +377,10 @@ WgradPacketPlan plan_wgrad_packets(const ConvGeom& g, size_t limit, double budge
         const long long steps = (long long)k.pairs * k.groups;
         if (steps > (1 << 28)) continue;
         k.steps = (int)steps;
-        const double packed = (double)(dy_group + x_group) * k.groups * PLANES;
+        // (the layout pass works through CT channels at a time, there or not: an image of three costs about three times
+        // its bytes)
+        const auto dead_lanes = [](int ch) { return 0.5 + 0.5 * (double)((ch + CT - 1) / CT * CT) / (double)ch; };
+        const double packed = ((double)dy_group * dead_lanes(g.K) + (double)x_group * dead_lanes(g.C)) * k.groups * PLANES;
         const double pack_us = 5.0 + packed / 6.0 * 10.0 / 4.0e6;
         const double dw_bytes = (double)g.K * J * 4.0;
         const double least_us = pack_us + 10.0 + 2.0 * dw_bytes / 5e6;       // whatever the tile and the splits
