@@ -43,20 +43,6 @@ struct PackParams {
     FastDiv div_bm, div_steps, div_taps, div_st, div_phases, div_sw;
 };
 
-// Where the filter values of GEMM row i and tap (tr, tc) lie: channel ci's at w[fixed + ci * stride], for ci < lim.
-// mode: 0 forward (row = output channel), 1 backward-data with unit stride (row = input channel), 2 phase-folded
-// (row = (c, a, b), taps a + sh * r', b + sw * s'). Ci: reduction channels.
-struct FilterRun { int fixed, stride, lim; };
-__device__ __forceinline__ FilterRun filter_run(int mode, int i, int tr, int tc, int C, int R, int S, int sh, int sw, int Ci, const FastDiv& div_phases,
-                                                const FastDiv& div_sw) {
-    if (mode == 0) return {(i * C * R + tr) * S + tc, R * S, Ci};
-    if (mode == 1) return {(i * R + tr) * S + tc, C * R * S, Ci};
-    const int c = fastdiv(i, div_phases), ab = i - c * sh * sw;
-    const int pa = fastdiv(ab, div_sw), pb = ab - pa * sw;
-    const int r = pa + sh * tr, s = pb + sw * tc;
-    return {(c * R + r) * S + s, C * R * S, r < R && s < S ? Ci : 0};
-}
-
 __global__ __launch_bounds__(256) void pack_operands_kernel(const PackParams q) {
     float v[8];
     if ((int)blockIdx.x < q.x_blocks) {

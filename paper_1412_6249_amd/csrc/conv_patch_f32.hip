@@ -41,7 +41,7 @@ constexpr int positions_of(bool split) { return split ? 704 : 504; }
 struct PatchF32Params {
     const float* a;             // repacked filter
     unsigned a_bytes;
-    int taps, cgs;
+    int taps, cgs, mode;
     int bands, Wb, PW, Mv;      // Mv: pixels counted over bands of Wb columns
     int h_base, w_base;         // input row / column of patch row / column 0, relative to the output row / column
     int img_rows;               // patch rows of a whole image: Ho + Rt - 1
@@ -49,10 +49,11 @@ struct PatchF32Params {
 };
 
 // Filter repack, one thread per four channels: [row tile][group][tap][row][16], zero past the last row
-// or channel; modes as in the filter repack of the tap kernels.
+// or channel, times the factor of the split (here, where it costs nothing: a step splits its filter tile again).
 struct FilterPack {
     const float* w; float* a;
     int mode, K, C, R, S, sh, sw, St, Co, bm, taps, cgs, total;
+    float scale;
     FastDiv div_bm, div_taps, div_cgs, div_st, div_phases, div_sw;
 };
 __global__ __launch_bounds__(256) void pack_filter_f32_kernel(const FilterPack q) {
@@ -68,21 +69,19 @@ __global__ __launch_bounds__(256) void pack_filter_f32_kernel(const FilterPack q
     const int rt = fastdiv(u, q.div_cgs), cg = u - rt * q.cgs;
     const int tr = fastdiv(tap, q.div_st), tc = tap - tr * q.St;
     const int i = rt * q.bm + row, ci0 = cg * 16 + quad * 4;
-    int fixed = 0, stride = 0, lim = 0;          // channel ci sits at w[fixed + ci * stride], ci < lim
-    if (i < q.Co) {
-        if (q.mode == 0) { fixed = (i * q.C * q.R + tr) * q.S + tc; stride = q.R * q.S; lim = q.C; }
-        else if (q.mode == 1) { fixed = (i * q.R + tr) * q.S + tc; stride = q.C * q.R * q.S; lim = q.K; }
-        else {
-            const int c = fastdiv(i, q.div_phases), ab = i - c * q.sh * q.sw;
-            const int pa = fastdiv(ab, q.div_sw), pb = ab - pa * q.sw;
-            const int r = pa + q.sh * tr, s = pb + q.sw * tc;
-            fixed = (c * q.R + r) * q.S + s; stride = q.C * q.R * q.S;
-            lim = (r < q.R && s < q.S) ? q.K : 0;
-        }
-    }
+    FilterRun f{0, 0, 0};
+    if (i < q.Co) f = filter_run(q.mode, i, tr, tc, q.C, q.R, q.S, q.sh, q.sw, q.mode == 0 ? q.C : q.K, q.div_phases, q.div_sw);
     floatx4 v;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = ci0 + e < lim ? q.w[(size_t)fixed + (size_t)(ci0 + e) * stride] : 0.0f;
+    for (int e = 0; e < 4; ++e) {
+        v[e] = ci0 + e < f.lim ? q.w[(size_t)f.fixed + (size_t)(ci0 + e) * f.stride] : 0.0f;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float x = v[e];
+        asm volatile("" : "+v"(x));      // as in store_split8
+        v[e] = x * q.scale;
+    }
     *reinterpret_cast<floatx4*>(q.a + (size_t)t * 4) = v;
 }
 
@@ -224,8 +223,8 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, 2) void igemm_patch_f32_kernel(c
                 *reinterpret_cast<floatx2*>(base + (mine ? T::BM * 16 : 0)) = floatx2{r.f[j][1], r.f[j][3]};
             } else {
                 uint32_t p01[PLANES], p23[PLANES];
-                split_pair(r.f[j][0], r.f[j][1], p01);
-                split_pair(r.f[j][2], r.f[j][3], p23);
+                split_pair<true>(r.f[j][0], r.f[j][1], p01);
+                split_pair<true>(r.f[j][2], r.f[j][3], p23);
 #pragma unroll
                 for (int pl = 0; pl < PLANES; ++pl)
                     *reinterpret_cast<u32x2*>(base + (mine ? pl * 2 * T::BM * 16 : 0)) = u32x2{p01[pl], p23[pl]};
@@ -327,7 +326,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, 2) void igemm_patch_f32_kernel(c
         if (cg + 1 < q.cgs) store_patch(buf ^ 1);
     }
 
-    // infinities and NaNs: again, as plain fp32 sums (conv_packets.hip)
+    // infinities and NaNs: again, as plain fp32 sums of the fp32 operands
     unsigned long long bad = SPLIT ? join_sets<TM, TN>(hi, lo) : 0ull;
     if (SPLIT && __builtin_expect(__any(bad != 0), 0)) {
         while (bad) {
@@ -347,10 +346,11 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, 2) void igemm_patch_f32_kernel(c
                     const int r = fastdiv(tap, q.div_st), t = tap - r * p.St;
                     const int h = MINUS ? ho + p.g_add_h - r : ho + p.g_add_h + r, w = MINUS ? wo + p.g_add_w - t : wo + p.g_add_w + t;
                     const bool inside = (unsigned)h < (unsigned)p.Hi && (unsigned)w < (unsigned)p.Wi;
-                    const float* pa = q.a + ((size_t)(rt * n_steps + s) * T::BM + row) * 16;
-                    const float* pb = (const float*)p.in + (size_t)n * p.in_ns + (size_t)g * 16 * p.HiWi + (inside ? h * p.Wi + w : 0);
-                    for (int c = 0; c < 16 && g * 16 + c < p.Ci; ++c)
-                        sum = __builtin_fmaf(pa[c], inside ? pb[(size_t)c * p.HiWi] : 0.0f, sum);
+                    const FilterRun f = filter_run(q.mode, i0 + row, r, t, p.C, p.R, p.S, p.sh, p.sw, p.Ci, p.div_phases, p.div_sw);
+                    const float* pb = (const float*)p.in + (size_t)n * p.in_ns + (inside ? h * p.Wi + w : 0);
+                    for (int ci = g * 16; ci < g * 16 + 16 && ci < p.Ci; ++ci)
+                        sum = __builtin_fmaf(ci < f.lim ? ((const float*)p.wt)[(size_t)f.fixed + (size_t)ci * f.stride] : 0.0f,
+                                             inside ? pb[(size_t)ci * p.HiWi] : 0.0f, sum);
                 }
             }
             replace_element<TM, TN>(hi, idx, sum);
@@ -436,6 +436,7 @@ hipError_t launch_patch_f32(PixParams p, const PatchF32Plan& k, int mode, const 
     FilterPack f{};
     f.w = (const float*)w; f.a = (float*)ws;
     f.mode = mode; f.K = K; f.C = C; f.R = p.R; f.S = p.S; f.sh = p.sh; f.sw = p.sw; f.St = p.St; f.Co = p.Co;
+    f.scale = k.split ? SPLIT_SCALE : 1.0f;
     f.bm = k.bm; f.taps = p.Rt * p.St; f.cgs = k.cgs;
     f.total = (int)(k.a_bytes / 16);
     f.div_bm = make_fastdiv(k.bm); f.div_taps = make_fastdiv(f.taps); f.div_cgs = make_fastdiv(k.cgs); f.div_st = make_fastdiv(p.St);
@@ -446,7 +447,8 @@ hipError_t launch_patch_f32(PixParams p, const PatchF32Plan& k, int mode, const 
     if (e != hipSuccess) return e;
 
     PatchF32Params q{};
-    q.a = (const float*)ws; q.a_bytes = (unsigned)k.a_bytes;
+    q.a = (const float*)ws; q.a_bytes = (unsigned)k.a_bytes; q.mode = mode;
+    p.wt = w; p.C = C;
     q.taps = f.taps; q.cgs = k.cgs;
     q.bands = k.bands; q.Wb = k.Wb; q.PW = k.PW; q.Mv = p.N * k.bands * p.Ho * k.Wb;
     q.h_base = mode == 0 ? p.g_add_h : p.g_add_h - (p.Rt - 1);
