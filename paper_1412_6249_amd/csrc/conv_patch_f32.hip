@@ -416,12 +416,16 @@ PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s, bool split) {
     for (int i = 0; i < 4; ++i) {
         const RowTile& t = split ? kSplitTiles[i] : kF32Tiles[i];
         const long long ti = (p.Co + t.bm - 1) / t.bm;
+        // 32 rows: filling the patch is most of a group's time, and longer where the patches come from HBM and not the
+        // 256 MB last-level cache (3x3, 215 -> 20 channels at 58x58, N = 125, 362 MB: 84 us per tile and 14 groups, tap kernel 504 us,
+        // this 574; 113 -> 19 at 46x46, N = 28, 27 MB: 35 us and 8 groups, 69 and 45)
+        const double eff = split && t.bm == 32 && p.in_bytes > (192u << 20) ? 0.34 : t.eff;
         const long long a_bytes = ti * k.cgs * p.Rt * p.St * t.bm * 64;
         if (a_bytes >= 0x7fffffffLL || ti * tp > 0x7fffffffLL) continue;
         const double x = (double)(ti * tp) / 256.0, ceil_x = (double)((ti * tp + 255) / 256);
         // one workgroup per CU at a time (the clock rises a little as CUs run dry), or two
         const double load = split ? 0.3 * x + 0.7 * ceil_x : x <= 1.0 ? 1.3 : 0.3 * x + 0.7 * ceil_x;
-        const double us = 10.0 + load * (k.cgs * (p.Rt * p.St * t.cycles / t.eff + 1000.0) + (d2s ? 50000.0 : 10000.0)) / (split ? 2.2e3 : 2.4e3);
+        const double us = 10.0 + load * (k.cgs * (p.Rt * p.St * t.cycles / eff + 1000.0) + (d2s ? 50000.0 : 10000.0)) / (split ? 2.2e3 : 2.4e3);
         if (!k.use || us < k.us) {
             k.use = true; k.us = us;
             k.bm = t.bm; k.tiles_i = (int)ti; k.tiles_pix = (int)tp;
