@@ -688,42 +688,43 @@ StreamPlan fc_stream_plan(int pass, int64_t N, int64_t C, int64_t K) {
     if (buffer_loads_disabled() || N * C >= (1ll << 29) || K * C >= (1ll << 29) || N * K >= (1ll << 29)) return none;
     if (pass == PURINE_CONV_FWD) return pix::plan_stream(N, K, C, true, true);       // (no size found at which the composition is faster)
     if (pass == PURINE_CONV_BWD_DATA) {
-        // The composition walks the reduction in one workgroup, which a short one leaves soon (us, composition /
-        // streaming, 128 images: 64 x 10 3.8 / 5.9, 3384 x 46 6.8 / 7.4, 9000 x 64 9.0 / 8.7, 1000 x 200 11.4 / 9, 4096 x 1000
-        // 36 / 27; 16 terms are one pass there). Its time, on the scale of the streaming kernel's
-        // expected one, which counts 3 us too many for the second pass of a sum this short.
+        // A sum of 16 terms or fewer is one launch of the composition, without a filter copy, and done sooner there (128
+        // images, us on the device, composition / streaming: 64 x 10 3.8 / 5.9). Longer ones cost it a second launch, 3 us of the
+        // host's time per call (13.6 / 10.0 for a call from Python), and take as long or longer on the device: 3384 x 46
+        // 6.8 / 7.4, 9000 x 64 9.0 / 8.7, 1000 x 200 11.4 / 9, 4096 x 1000 36 / 27.
         StreamPlan k = pix::plan_stream(N, C, K, true, false);
-        const double composition_us = K <= 16 ? 6.3 : K <= 48 ? 9.2 : K <= 96 ? 10.6 : 12.4 + 0.024 * (double)(K - 96);
-        if (K < 1000) k.use = k.use && k.us - (k.splits > 1 ? 3.0 : 0.0) < composition_us;
+        k.use = k.use && K > 16;
         return k;
     }
     // The weight gradient writes K x C sums of N products. Where that write is most of the time, the general kernel
-    // does it as well or better; what decides is how large dw is (us, general / this, at N = 33, 48, 64, 128, 250):
+    // does it as well or better on the device (us, general / this, at N = 33, 48, 64, 128, 250):
     //     9216 x 4096   48 / 46   51 / 48   60 / 53   97 / 77   170 / 124
     //     3140 x 1780   17 / 16   17 / 15   19 / 17   28 / 22
     //     4096 x 1000   13 / 13   12 / 13   13 / 13   18 / 18   30 / 28
     //     1185 x 1168    9 / 10    9 / 10   10 / 10   14 / 14   21 / 22
     //     1000 x 200     7 / 8     9 / 8    10 / 8    15 / 11   13 / 18
-    // (N <= 32: 37 / 153 at 9216 x 4096 and N = 1). On small ones the general kernel is the slower one only where the
-    // batch is whole steps of 16 and the rows whole packets, for which it takes wider tiles than there is work for
+    // (N <= 32: 37 / 153 at 9216 x 4096 and N = 1), but with one launch more, 17.4 / 14.2 us per call with db from Python.
+    // So it takes over where this needs longer than that on the device: dw below 5 M sums and more than 128 images (160
+    // for the smallest), but for batches of whole steps of 16 over whole packets, for which the general kernel takes
+    // wider tiles than there is work for, and for 32 or fewer rows (250 images, 64 x 10, 13 / 9).
     const int64_t area = K * C;
-    // (and where 32 or fewer rows leave it one row tile: 250 images, 64 x 10, 13 / 9).
     const bool packets = C % 4 == 0;
-    const bool take = area >= 5ll << 20 ? N > 32 : area >= 2ll << 20 ? N >= 128 && packets
-                    : area <= 1ll << 20 && ((N >= 48 && N % 16 == 0 && packets) || (N >= 192 && K <= 32));
+    const bool take = N > 32 && (area >= 5ll << 20 || N <= 128 || (area >= 2ll << 20 && packets) ||
+                                 (area <= 1ll << 20 && (N <= 160 || K <= 32 || (N % 16 == 0 && packets))));
     return take ? pix::plan_stream(K, C, N, false, false) : none;
 }
 // The weight gradient's operands are small against its result, and every one of their elements is needed by
 // dozens of tiles: laid out as bf16 parts first, the kernel that copies packets straight into LDS takes 79 us
 // (+ 6 for the layout) where the streaming one splits the same elements again and again in 90 (9216 x 4096, N = 128).
 size_t fc_general_workspace_bytes(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype);
-// One plan per call, which also says what scratch the call asks for: at least the composition's.
+// One plan per call, which also says what scratch a streaming pass asks for (at least what the composition does); without
+// one the composition's kernels plan for themselves.
 struct FcPlan { StreamPlan k; PacketPlan pk; size_t need; };
 FcPlan fc_plan(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype) {
     FcPlan f{};
     if (dtype == PURINE_F32) f.k = fc_stream_plan(pass, N, C, K);
-    f.need = fc_general_workspace_bytes(pass, N, C, K, dtype);
     if (!f.k.use) return f;
+    f.need = fc_general_workspace_bytes(pass, N, C, K, dtype);
     if (f.k.part_bytes > f.need) f.need = f.k.part_bytes;
     if (pass >= PURINE_CONV_BWD_WEIGHT) {
         f.pk = pix::plan_packets_matrix(K, C, N);
@@ -802,7 +803,8 @@ int purine_grouped_conv_bwd_weight(const purine_conv_desc* desc, int groups, con
 size_t purine_fc_workspace_bytes(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype) {
     if (N < 1 || C < 1 || K < 1 || N >= (1ll << 31) || C >= (1ll << 31) || K >= (1ll << 31) || pass < PURINE_CONV_FWD || pass > PURINE_CONV_BWD_WEIGHT_BIAS)
         return fc_general_workspace_bytes(pass, N, C, K, dtype);
-    return fc_plan(pass, N, C, K, dtype).need;
+    const FcPlan f = fc_plan(pass, N, C, K, dtype);
+    return f.k.use ? f.need : fc_general_workspace_bytes(pass, N, C, K, dtype);
 }
 
 namespace {

@@ -284,7 +284,7 @@ StreamPlan plan_stream(long long rows, long long cols, long long K, bool a_in, b
             // B along its outer axis, one workgroup for the whole sum: a step takes its time however little there is to
             // multiply, 16 loads, their split and a barrier (247 x 169, 128 images, backward-data: 16 steps 16.2 us, split
             // one by one 8.6 with the second pass; weight gradient 64 x 10 of 128: 8 steps of 32 rows 10 us, of 64 12)
-            const double chain_us = b_in || sp > 1 ? 0.0 : (t.bm == 32 ? 0.8 : 1.05) * (double)per;
+            const double chain_us = b_in || sp > 1 ? 0.0 : (t.bm == 32 ? 0.7 : 0.95) * (double)per;
             double mma_us = load * ((double)per * t.cycles / eff + 3000.0) / 2.2e3;
             if (mma_us < chain_us) mma_us = chain_us;
             // fewer than two workgroups per CU (of the smallest tile three) do not keep enough loads in flight
