@@ -106,7 +106,10 @@ int purine_conv_out_shape(const purine_conv_desc* desc, const int64_t x_dim[4],
  * bytes per element, channels rounded up to a multiple of 16) and the partial outputs of a split
  * reduction. Backward-weight keeps its split-reduction partial sums there, F32 layers bound by the
  * matrix cores also copies of x and dy (6 bytes per element; the size is a whole number of copies of
- * dw, and of K sums for the fused bias gradient). */
+ * dw, and of K sums for the fused bias gradient). Those copies make the scratch several times the operands': 5x5 96 -> 256
+ * at 27x27, N = 128 265 MB of backward-weight for 131 MB of x and dy, 3x3 64 -> 128 at 112x112, N = 64 1.0 GB for
+ * 617 MB; a copy that would reach 2 GiB, 128 MiB of forward / backward-data partials or 256 MiB of dw's are not asked for
+ * (the pass then runs on fp32 products). */
 size_t purine_conv_workspace_bytes(int pass, const purine_conv_desc* desc, const int64_t x_dim[4],
                                    const int64_t w_dim[4], int32_t dtype);
 size_t purine_bias_bwd_workspace_bytes(const int64_t dy_dim[4], int32_t dtype);
@@ -270,9 +273,8 @@ int purine_grouped_conv_bwd_weight(const purine_conv_desc* desc, int groups, con
  *   fwd:        y = x w^T (+ b)          dx = dy w          dw = beta*dw + dy^T x,  db = beta*db + column sums of dy
  * F32 (matrices below 2 GiB): a streaming matrix product on the bf16 matrix cores, three exact bf16 parts per
  * operand and fp32 sums (as for convolutions, see purine_conv_fwd), the reduction split over workgroups where tiles alone would leave most of the chip idle
- * (partial outputs in ws, added in a fixed order): every forward pass, backward-data but for short sums, and the weight
- * gradient where dw is large (or the batch is whole steps of 16), which may lay its operands out as such parts in ws
- * first. Every other pass is one of the convolution
+ * (partial outputs in ws, added in a fixed order): every forward pass, backward-data over more than 16 outputs, and the weight
+ * gradient of more than 32 images at most sizes, which may lay its operands out as such parts in ws first. Every other pass is one of the convolution
  * GEMM kernels on reinterpreted descriptors (a matrix [rows, features] is one image of `rows` channels whose pixel
  * plane is the feature axis, or a 1x1 filter bank): forward runs the weight-gradient kernel (split reduction over
  * C, fixed-order second pass; BF16: its fp32 result gets the bias added and is rounded once), backward-data the

@@ -3,9 +3,11 @@
 // conv_packets.hip (three exact bf16 parts, six products, two accumulator sets), with the parts made
 // in LDS instead of in scratch memory.
 //
-// Bound: MFMA, in practice the power limit (bf16 MFMAs on random data run at 1.9 - 2.0 GHz; the same
-// launch on zeros is a quarter faster). A workgroup of eight wavefronts owns BM rows x 256 consecutive
-// pixels, one workgroup per CU. All positions that the taps of those pixels touch form a patch of a few
+// Bound: MFMA at the clock that power allows (bf16 MFMAs on random data run at 1.9 - 2.0 GHz; the same
+// launch on zeros is a quarter faster), with the matrix pipes busy 66 % of a CU's cycles on 96 <- 256 channels 5x5
+// at 27x27, 62 % on the 384-channel 3x3 at 13x13 and 45 - 59 % on the shorter sums of the 96 / 128-channel 3x3 at 28x28,
+// N = 128; a quarter to a third of the LDS cycles are bank conflicts (the taps' shifted reads). With fp32 products
+// 87 - 89 %. A workgroup of eight wavefronts owns BM rows x 256 consecutive pixels, one workgroup per CU. All positions that the taps of those pixels touch form a patch of a few
 // haloed rows (possibly of several images); per group of 16 gathered channels the patch is loaded
 // once from NCHW (a lane takes 8 channels of one position: coalesced 4-byte loads), split in registers
 // and stored to LDS as packets [part][channel half][position][8], and every tap reads its B fragments
