@@ -81,6 +81,21 @@ struct PatchF32Plan {
     double us;
 };
 
+// ... and bf16 layers whose patch is staged in LDS whatever the width of its rows (conv_patch_any_bf16.hip).
+struct PatchAnyPlan {
+    bool use;
+    int bm, bn, tiles_i, tiles_pix;
+    int taps, cgs;                   // groups of 16 gathered channels
+    int stage_taps, stages;          // taps per filter stage, stages per group
+    int pw, h_base, w_base;          // patch columns; input row / column of patch position 0
+    int c0, ncol, quads, rounds;     // input columns loaded, in fours; loads per thread
+    int plane_bytes, lds;
+    int rt;                          // square filter with a kernel of its own: its side, else 0
+    bool ahead;                      // ... whose filter and patch are requested several groups ahead
+    size_t a_bytes;
+    double us;
+};
+
 // Plan of the streaming fp32 GEMM on bf16 parts (gemm_stream_f32.hip): rows x columns of the output over a
 // reduction, split over workgroups where scratch for partial outputs is at hand.
 struct StreamPlan {
@@ -120,9 +135,11 @@ struct PixPlan {
     size_t gemm_part_offset;   // byte offset of the fp32 partial tiles inside the scratch
     PacketPlan pk;
     PatchF32Plan pf;
+    PatchAnyPlan pa;
 };
 PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, bool accumulate = false);
 void force_pix_tile(int bm, int bn);
+bool patch_any_forced();             // test hook: (-9, tile): bf16 layers run the patch kernel for rows of any width, with that tile (bm * 1000 + bn) or its own
 bool split_patch_forced();           // test hook: (-6, anything): fp32 layers run the kernel that splits a patch in LDS wherever it applies
 bool split_packets_forced();         // test hook: (-7, anything): ... the kernels on packed bf16 parts (forward, backward-data, weight gradient)
 bool patch_split_roles_forced();     // test hook: (-5, anything) gives it layers of few tiles too

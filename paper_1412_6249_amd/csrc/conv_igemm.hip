@@ -559,6 +559,7 @@ bool buffer_loads_disabled() { return g_no_buffer_loads != 0; }
 bool patch_split_roles_disabled() { return g_force_bm == -4; }   // tuning hook: force_pix_tile(-4, x)
 bool split_patch_forced() { return g_force_bm == -6; }           // test hooks: fp32 layers run the kernel that splits in LDS
 bool f32_patch_forced() { return g_force_bm == -8; }             // / forward passes the fp32 patch kernel
+bool patch_any_forced() { return g_force_bm == -9; }             // / bf16 layers the patch kernel for rows of any width
 bool split_packets_forced() { return g_force_bm == -7; }         // / the ones on packed parts wherever they apply
 bool patch_split_roles_forced() { return g_force_bm == -5; }     // test hook: force_pix_tile(-5, x), also for layers of few tiles
 void force_pix_tile(int bm, int bn) {
@@ -718,6 +719,18 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
         PatchGeom q;
         pl.patch = plan_patch_bf16(probe, pl.mode, &q);
         if (pl.patch) pl.ws_bytes = patch_filter_bytes(Co, Ci, pl.Rt * pl.St);
+        // The two-role kernel where it applies (a thousand tiles of whole four-pixel groups or more: 64 -> 192 channels 3x3
+        // at 56x56, N = 256 forward 198 us, 235 on the kernel for rows of any width); else that one, which the
+        // one-role kernel was behind on every layer of whole packets timed (128 -> 128 at 16x16, N = 64: 25.5 against 16.5 us;
+        // 48 -> 96 5x5 at 40x40, N = 32 backward-data: 38 against 28.5) and is left the rows too wide for its patch.
+        if (((g_force_bm == 0 || patch_split_roles_forced()) && !(pl.patch && q.roles)) || patch_any_forced()) {
+            pl.pa = plan_patch_any(make_pix_params(dtype, g, pl), pl.mode, patch_any_forced() ? g_force_bn : 0);
+            if (pl.pa.use) {
+                pl.patch = false;
+                pl.ws_bytes = pl.pa.a_bytes;
+                return pl;
+            }
+        }
     }
     if (dtype == PURINE_BF16 && !pl.flat && pl.Rt * pl.St > 1 && !pl.patch) {
         // channels-blocked copy of the gathered tensor behind the filter copy (single-tap layers
@@ -833,6 +846,10 @@ hipError_t launch_conv_pix(int dtype, const ConvGeom& g, const PixPlan& pl, cons
 
     if (pl.pf.use) return launch_patch_f32(p, pl.pf, pl.mode, wt, g.K, g.C, ws, st);
     if (pl.pk.use) return launch_packets(p, pl.pk, pl.mode, wt, g.K, g.C, ws, st);
+    if (pl.pa.use) {
+        ProbeScope whole_op(st, true);
+        return launch_patch_any(p, pl.pa, pl.mode, wt, g.K, g.C, ws, st);
+    }
     if (pl.gemm1x1) {
         const uintptr_t align = (uintptr_t)pl.gemm_tn * (dtype == PURINE_BF16 ? 2 : 4) - 1;
         if ((((uintptr_t)in | (uintptr_t)out | (uintptr_t)epi.mask) & align) == 0) {

@@ -601,6 +601,10 @@ bool plan_patch_bf16(PixParams& p, int mode, PatchGeom* q);
 size_t patch_filter_bytes(int Co, int Ci, int n_taps);
 hipError_t repack_patch_filter(const PixParams& p, int mode, const void* w, void* a, int K, int C, hipStream_t st);
 hipError_t launch_patch_bf16(const PixParams& p, const PatchGeom& q, int mode, hipStream_t st);
+// bf16 layers with several taps, rows of any width (conv_patch_any_bf16.hip); mode as above, w: the KCRS filter, repacked
+// into ws. force: a tile (bm * 1000 + bn) for tests and sweeps, or 0.
+PatchAnyPlan plan_patch_any(const PixParams& p, int mode, int force);
+hipError_t launch_patch_any(PixParams p, const PatchAnyPlan& k, int mode, const void* w, int K, int C, void* ws, hipStream_t st);
 // bf16 forward for layers with fewer than 16 input channels whose input rows are whole 16-byte
 // packets (conv_rows_bf16.hip): input rows staged in LDS in their natural layout, the reduction runs
 // over (c, r, block of 8 filter columns), persistent workgroups. plan_rows_bf16 answers whether the

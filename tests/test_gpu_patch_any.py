@@ -1,0 +1,89 @@
+"""The bf16 patch kernel for rows of any width: every tile and both request schemes at the edges of tiles, channel
+groups, rows and images, against the oracle, and bit for bit against each other (all of them add a channel
+group's taps in the same order). The tensors are channel slices whose neighbours hold NaN: what a kernel reads past a
+slice's last channel must not reach a result."""
+import numpy as np
+import pytest
+
+import oracle
+from synth import gen
+
+pytestmark = pytest.mark.gpu
+
+# N, C, H, W, K, R, S, stride, pad. The smallest width and patch, odd planes (every other channel at an odd element), last
+# loads that overlap, one row past a tile, channels on either side of a group of 16 and of 8, many images per tile, filters
+# with a kernel of their own (2x2 folded, 3x3, 5x5) and without, strides that gather and that fold, rows wider than a tile
+CASES = [(2, 16, 4, 4, 33, 3, 3, 1, 1), (3, 17, 7, 7, 32, 3, 3, 1, 1), (70, 24, 5, 5, 16, 3, 3, 1, 0), (2, 31, 13, 13, 97, 3, 3, 1, 1),
+         (1, 33, 28, 28, 129, 3, 3, 1, 1), (2, 40, 14, 9, 20, 5, 5, 1, 2), (3, 16, 11, 13, 40, 3, 3, 2, 1), (2, 24, 12, 15, 33, 5, 5, 2, 2),
+         (2, 19, 10, 11, 24, 2, 3, 1, (1, 0)), (1, 48, 9, 17, 17, 1, 5, 1, (0, 2)), (2, 16, 14, 19, 30, 4, 4, (3, 2), (2, 1)),
+         (2, 20, 6, 131, 18, 3, 3, 1, 1), (1, 64, 33, 37, 65, 3, 3, 1, 1), (4, 23, 9, 8, 41, 3, 2, (1, 2), (1, 0))]
+TILES = (0, 128256, 96256, 96128, 64256, 64128, 32256, 32128, 1032128)
+
+
+def _slice(a, lead, tail):
+    """The values of `a` as the middle channels of a tensor that holds NaN everywhere else."""
+    import torch
+    from gpu_util import to_dev, DEV
+    n, c, h, w = a.shape
+    big = torch.full((n, c + lead + tail, h, w), float("nan"), dtype=torch.bfloat16, device=DEV)
+    view = big[:, lead:lead + c]
+    view.copy_(to_dev(a, "bf16"))
+    return view
+
+
+@pytest.mark.parametrize("case", CASES, ids=str)
+def test_every_tile_against_the_oracle(case):
+    import torch
+    import paper_1412_6249_amd as pa
+    from gpu_util import rel_l2, to_dev, to_host, workspace, TOL
+    N, C, H, W, K, R, S, stride, pad = case
+    rs = np.random.default_rng(3)
+    f = lambda *s: gen.quantize_bf16(rs.uniform(-1, 1, s).astype(np.float32))
+    P, Q = oracle.out_shape((N, C, H, W), (K, C, R, S), stride, pad)[2:]
+    x, w, b, dy, act, prev = f(N, C, H, W), f(K, C, R, S), f(K), f(N, K, P, Q), f(N, C, H, W), f(N, C, H, W)
+    y = np.maximum(oracle.bias_fwd(oracle.conv_fwd(x, w, stride, pad), b), 0)
+    dx = oracle.conv_bwd_data(dy, w, x.shape, stride, pad)
+    refs = (y, dx, dx + prev, np.where(act > 0, dx, 0.0))
+    desc, first = pa.conv_desc(stride, pad), None
+    # slices start at whole 16-byte packets
+    pad_x, pad_y = (8 if H * W % 8 else 1), (8 if P * Q % 8 else 1)
+    up = lambda c, m: c + (-c) % m
+    for tile in TILES:
+        # (a forced tile that does not apply leaves the call on another kernel; 0 is the kernel's own choice)
+        pa.purine_debug_force_tile(-9, tile)
+        try:
+            tx, tdy, tact = _slice(x, pad_x, up(C, pad_x) - C), _slice(dy, pad_y, up(K, pad_y) - K), _slice(act, pad_x, up(C, pad_x) - C)
+            ty = _slice(np.zeros_like(dy), pad_y, up(K, pad_y) - K)
+            td, ta, tm = (_slice(v, pad_x, up(C, pad_x) - C) for v in (np.zeros_like(x), prev, np.zeros_like(x)))
+            tw, tb = to_dev(w, "bf16"), to_dev(b, "bf16")
+            ws = [workspace(pa.purine_conv_workspace_bytes(k, desc, x.shape, w.shape, pa.PURINE_BF16)) for k in (0, 1)]
+            pa.purine_conv_fwd_bias_relu(desc, tx, tw, tb, ty, relu=True, ws=ws[0])
+            pa.purine_conv_bwd_data(desc, tdy, tw, td, ws=ws[1])
+            pa.purine_conv_bwd_data(desc, tdy, tw, ta, beta=1.0, ws=ws[1])
+            pa.purine_conv_bwd_data_relu(desc, tdy, tw, tact, tm, ws=ws[1])
+            torch.cuda.synchronize()
+        finally:
+            pa.purine_debug_force_tile(0, 0)
+        got = [to_host(t) for t in (ty, td, ta, tm)]
+        for name, g, r in zip(("y", "dx", "dx accumulated", "dx masked"), got, refs):
+            assert rel_l2(g, r) <= TOL["bf16"], (tile, name, rel_l2(g, r))
+        if first is None:
+            first = got
+        elif tile in (32128, 32256, 64128) or (tile == 1032128 and stride == 1 and R == S and W < 100):
+            # (these apply to every layer above; the last needs a filter with a kernel of its own and a patch of 256 loads)
+            for name, g, r in zip(("y", "dx", "dx accumulated", "dx masked"), got, first):
+                assert np.array_equal(g, r), (tile, name)
+        for t, ch in ((ty, K), (td, C), (ta, C), (tm, C)):
+            assert int(torch.isnan(t._base).sum()) == t._base.numel() - t.numel(), "stored outside the slice"
+
+
+def test_rows_too_wide_for_a_patch():
+    """264 columns: the one-image kernel."""
+    import paper_1412_6249_amd as pa
+    from gpu_util import run_layer, rel_l2, TOL
+    rs = np.random.default_rng(1)
+    f = lambda *s: gen.quantize_bf16(rs.uniform(-1, 1, s).astype(np.float32))
+    x, w, b, dy = f(1, 16, 5, 264), f(20, 16, 3, 3), f(20), f(1, 20, 5, 264)
+    y, dx, _, _ = run_layer(x, w, b, dy, 1, 1, "bf16")
+    assert rel_l2(y, oracle.bias_fwd(oracle.conv_fwd(x, w, 1, 1), b)) <= TOL["bf16"]
+    assert rel_l2(dx, oracle.conv_bwd_data(dy, w, x.shape, 1, 1)) <= TOL["bf16"]
