@@ -1,4 +1,6 @@
-"""Thin ctypes binding over libpurine_conv.so: argument marshalling only.
+"""Thin binding over libpurine_conv.so: argument marshalling only. Operator calls on torch tensors go through the native
+module _marshal (a ctypes descriptor costs 1.6 us each, more than a launch); everything else, and whatever _marshal
+hands back as not the plain case (None), through ctypes.
 
 Every function has the name of the C entry point it calls (see include/purine.h). Tensors are
 torch tensors that live on the GPU (PyTorch supplies device memory and streams, nothing else);
@@ -64,6 +66,7 @@ if not os.path.exists(LIB_PATH):
     raise ImportError("libpurine_conv.so is not built: run `python -c 'import __graft_entry__ as g; "
                       "g.build()'` (or paper_1412_6249_amd/build.py) first")
 _lib = ctypes.CDLL(LIB_PATH)
+from . import _marshal  # noqa: E402  (links against the libraries loaded above)
 
 _P = ctypes.POINTER
 _T, _D, _PD = _P(purine_tensor), _P(purine_conv_desc), _P(purine_pool_desc)
@@ -262,44 +265,57 @@ def purine_debug_fastdiv(n, d):
 
 # ------------------------------------------------------------------ operators
 def purine_conv_fwd(desc, x, w, y, ws=None, stream=None):
-    p, n = _ws(ws)
-    _check(_lib.purine_conv_fwd(_ref(desc), _ref(tensor_desc(x)), _ref(tensor_desc(w)),
-                                _ref(tensor_desc(y)), p, n, _stream(stream)), "purine_conv_fwd")
+    rc = _marshal.purine_conv_fwd(desc, x, w, y, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        rc = _lib.purine_conv_fwd(_ref(desc), _ref(tensor_desc(x)), _ref(tensor_desc(w)),
+            _ref(tensor_desc(y)), p, n, _stream(stream))
+    _check(rc, "purine_conv_fwd")
 
 
 def purine_conv_bwd_data(desc, dy, w, dx, beta=0.0, ws=None, stream=None):
-    p, n = _ws(ws)
-    _check(_lib.purine_conv_bwd_data(_ref(desc), _ref(tensor_desc(dy)), _ref(tensor_desc(w)),
-                                     _ref(tensor_desc(dx)), float(beta), p, n, _stream(stream)),
-           "purine_conv_bwd_data")
+    rc = _marshal.purine_conv_bwd_data(desc, dy, w, dx, beta, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        rc = _lib.purine_conv_bwd_data(_ref(desc), _ref(tensor_desc(dy)), _ref(tensor_desc(w)),
+            _ref(tensor_desc(dx)), float(beta), p, n, _stream(stream))
+    _check(rc, "purine_conv_bwd_data")
 
 
 def purine_conv_fwd_bias_relu(desc, x, w, b, y, relu=True, ws=None, stream=None):
-    p, n = _ws(ws)
-    bd = _ref(tensor_desc(b)) if b is not None else None
-    _check(_lib.purine_conv_fwd_bias_relu(_ref(desc), _ref(tensor_desc(x)), _ref(tensor_desc(w)), bd,
-                                          _ref(tensor_desc(y)), 1 if relu else 0, p, n, _stream(stream)),
-           "purine_conv_fwd_bias_relu")
+    rc = _marshal.purine_conv_fwd_bias_relu(desc, x, w, b, y, 1 if relu else 0, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        bd = _ref(tensor_desc(b)) if b is not None else None
+        rc = _lib.purine_conv_fwd_bias_relu(_ref(desc), _ref(tensor_desc(x)), _ref(tensor_desc(w)), bd,
+            _ref(tensor_desc(y)), 1 if relu else 0, p, n, _stream(stream))
+    _check(rc, "purine_conv_fwd_bias_relu")
 
 
 def purine_conv_bwd_data_relu(desc, dy, w, act, dx, beta=0.0, ws=None, stream=None):
-    p, n = _ws(ws)
-    _check(_lib.purine_conv_bwd_data_relu(_ref(desc), _ref(tensor_desc(dy)), _ref(tensor_desc(w)),
-                                          _ref(tensor_desc(act)), _ref(tensor_desc(dx)), float(beta), p, n,
-                                          _stream(stream)), "purine_conv_bwd_data_relu")
+    rc = _marshal.purine_conv_bwd_data_relu(desc, dy, w, act, dx, beta, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        rc = _lib.purine_conv_bwd_data_relu(_ref(desc), _ref(tensor_desc(dy)), _ref(tensor_desc(w)),
+            _ref(tensor_desc(act)), _ref(tensor_desc(dx)), float(beta), p, n, _stream(stream))
+    _check(rc, "purine_conv_bwd_data_relu")
 
 
 def purine_conv_bwd_weight(desc, x, dy, dw, beta=0.0, ws=None, stream=None):
-    p, n = _ws(ws)
-    _check(_lib.purine_conv_bwd_weight(_ref(desc), _ref(tensor_desc(x)), _ref(tensor_desc(dy)),
-                                       _ref(tensor_desc(dw)), float(beta), p, n, _stream(stream)),
-           "purine_conv_bwd_weight")
+    rc = _marshal.purine_conv_bwd_weight(desc, x, dy, dw, beta, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        rc = _lib.purine_conv_bwd_weight(_ref(desc), _ref(tensor_desc(x)), _ref(tensor_desc(dy)),
+            _ref(tensor_desc(dw)), float(beta), p, n, _stream(stream))
+    _check(rc, "purine_conv_bwd_weight")
 
 
 def purine_conv_bwd_weight_static(desc, x, dy, dw, beta=0.0, stream=None):
-    _check(_lib.purine_conv_bwd_weight_static(_ref(desc), _ref(tensor_desc(x)), _ref(tensor_desc(dy)),
-                                              _ref(tensor_desc(dw)), float(beta), _stream(stream)),
-           "purine_conv_bwd_weight_static")
+    rc = _marshal.purine_conv_bwd_weight_static(desc, x, dy, dw, beta, stream)
+    if rc is None:
+        rc = _lib.purine_conv_bwd_weight_static(_ref(desc), _ref(tensor_desc(x)), _ref(tensor_desc(dy)),
+            _ref(tensor_desc(dw)), float(beta), _stream(stream))
+    _check(rc, "purine_conv_bwd_weight_static")
 
 
 def purine_static_scratch_bytes():
@@ -307,10 +323,12 @@ def purine_static_scratch_bytes():
 
 
 def purine_conv_bwd_weight_bias(desc, x, dy, dw, db, beta=0.0, ws=None, stream=None):
-    p, n = _ws(ws)
-    _check(_lib.purine_conv_bwd_weight_bias(_ref(desc), _ref(tensor_desc(x)), _ref(tensor_desc(dy)),
-                                            _ref(tensor_desc(dw)), _ref(tensor_desc(db)), float(beta), p, n,
-                                            _stream(stream)), "purine_conv_bwd_weight_bias")
+    rc = _marshal.purine_conv_bwd_weight_bias(desc, x, dy, dw, db, beta, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        rc = _lib.purine_conv_bwd_weight_bias(_ref(desc), _ref(tensor_desc(x)), _ref(tensor_desc(dy)),
+            _ref(tensor_desc(dw)), _ref(tensor_desc(db)), float(beta), p, n, _stream(stream))
+    _check(rc, "purine_conv_bwd_weight_bias")
 
 
 def _opt(t):
@@ -323,24 +341,30 @@ def purine_grouped_conv_workspace_bytes(which, desc, groups, x_shape, w_shape, d
 
 
 def purine_grouped_conv_fwd(desc, groups, x, w, b, y, relu=False, ws=None, stream=None):
-    p, n = _ws(ws)
-    _check(_lib.purine_grouped_conv_fwd(_ref(desc), int(groups), _ref(tensor_desc(x)), _ref(tensor_desc(w)), _opt(b),
-                                        _ref(tensor_desc(y)), 1 if relu else 0, p, n, _stream(stream)),
-           "purine_grouped_conv_fwd")
+    rc = _marshal.purine_grouped_conv_fwd(desc, groups, x, w, b, y, 1 if relu else 0, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        rc = _lib.purine_grouped_conv_fwd(_ref(desc), int(groups), _ref(tensor_desc(x)), _ref(tensor_desc(w)),
+            _opt(b), _ref(tensor_desc(y)), 1 if relu else 0, p, n, _stream(stream))
+    _check(rc, "purine_grouped_conv_fwd")
 
 
 def purine_grouped_conv_bwd_data(desc, groups, dy, w, dx, beta=0.0, ws=None, stream=None):
-    p, n = _ws(ws)
-    _check(_lib.purine_grouped_conv_bwd_data(_ref(desc), int(groups), _ref(tensor_desc(dy)), _ref(tensor_desc(w)),
-                                             _ref(tensor_desc(dx)), float(beta), p, n, _stream(stream)),
-           "purine_grouped_conv_bwd_data")
+    rc = _marshal.purine_grouped_conv_bwd_data(desc, groups, dy, w, dx, beta, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        rc = _lib.purine_grouped_conv_bwd_data(_ref(desc), int(groups), _ref(tensor_desc(dy)),
+            _ref(tensor_desc(w)), _ref(tensor_desc(dx)), float(beta), p, n, _stream(stream))
+    _check(rc, "purine_grouped_conv_bwd_data")
 
 
 def purine_grouped_conv_bwd_weight(desc, groups, x, dy, dw, db=None, beta=0.0, ws=None, stream=None):
-    p, n = _ws(ws)
-    _check(_lib.purine_grouped_conv_bwd_weight(_ref(desc), int(groups), _ref(tensor_desc(x)), _ref(tensor_desc(dy)),
-                                               _ref(tensor_desc(dw)), _opt(db), float(beta), p, n, _stream(stream)),
-           "purine_grouped_conv_bwd_weight")
+    rc = _marshal.purine_grouped_conv_bwd_weight(desc, groups, x, dy, dw, db, beta, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        rc = _lib.purine_grouped_conv_bwd_weight(_ref(desc), int(groups), _ref(tensor_desc(x)),
+            _ref(tensor_desc(dy)), _ref(tensor_desc(dw)), _opt(db), float(beta), p, n, _stream(stream))
+    _check(rc, "purine_grouped_conv_bwd_weight")
 
 
 def purine_fc_workspace_bytes(which, N, C, K, dtype=PURINE_F32):
@@ -348,64 +372,93 @@ def purine_fc_workspace_bytes(which, N, C, K, dtype=PURINE_F32):
 
 
 def purine_fc_fwd(x, w, b, y, ws=None, stream=None):
-    p, n = _ws(ws)
-    _check(_lib.purine_fc_fwd(_ref(tensor_desc(x)), _ref(tensor_desc(w)), _opt(b), _ref(tensor_desc(y)), p, n,
-                              _stream(stream)), "purine_fc_fwd")
+    rc = _marshal.purine_fc_fwd(x, w, b, y, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        rc = _lib.purine_fc_fwd(_ref(tensor_desc(x)), _ref(tensor_desc(w)), _opt(b), _ref(tensor_desc(y)), p,
+            n, _stream(stream))
+    _check(rc, "purine_fc_fwd")
 
 
 def purine_fc_bwd_data(dy, w, dx, ws=None, stream=None):
-    p, n = _ws(ws)
-    _check(_lib.purine_fc_bwd_data(_ref(tensor_desc(dy)), _ref(tensor_desc(w)), _ref(tensor_desc(dx)), p, n,
-                                   _stream(stream)), "purine_fc_bwd_data")
+    rc = _marshal.purine_fc_bwd_data(dy, w, dx, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        rc = _lib.purine_fc_bwd_data(_ref(tensor_desc(dy)), _ref(tensor_desc(w)), _ref(tensor_desc(dx)), p, n,
+            _stream(stream))
+    _check(rc, "purine_fc_bwd_data")
 
 
 def purine_fc_bwd_weight(x, dy, dw, db=None, beta=0.0, ws=None, stream=None):
-    p, n = _ws(ws)
-    _check(_lib.purine_fc_bwd_weight(_ref(tensor_desc(x)), _ref(tensor_desc(dy)), _ref(tensor_desc(dw)), _opt(db),
-                                     float(beta), p, n, _stream(stream)), "purine_fc_bwd_weight")
+    rc = _marshal.purine_fc_bwd_weight(x, dy, dw, db, beta, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        rc = _lib.purine_fc_bwd_weight(_ref(tensor_desc(x)), _ref(tensor_desc(dy)), _ref(tensor_desc(dw)),
+            _opt(db), float(beta), p, n, _stream(stream))
+    _check(rc, "purine_fc_bwd_weight")
 
 
 def purine_sgd_update(w, dw, new_w, lr, stream=None):
-    _check(_lib.purine_sgd_update(_ref(tensor_desc(w)), _ref(tensor_desc(dw)), _ref(tensor_desc(new_w)),
-                                  float(lr), _stream(stream)), "purine_sgd_update")
+    rc = _marshal.purine_sgd_update(w, dw, new_w, lr, stream)
+    if rc is None:
+        rc = _lib.purine_sgd_update(_ref(tensor_desc(w)), _ref(tensor_desc(dw)), _ref(tensor_desc(new_w)),
+            float(lr), _stream(stream))
+    _check(rc, "purine_sgd_update")
 
 
 def purine_bias_fwd(b, y, stream=None):
-    _check(_lib.purine_bias_fwd(_ref(tensor_desc(b)), _ref(tensor_desc(y)), _stream(stream)),
-           "purine_bias_fwd")
+    rc = _marshal.purine_bias_fwd(b, y, stream)
+    if rc is None:
+        rc = _lib.purine_bias_fwd(_ref(tensor_desc(b)), _ref(tensor_desc(y)), _stream(stream))
+    _check(rc, "purine_bias_fwd")
 
 
 def purine_bias_bwd(dy, db, beta=0.0, ws=None, stream=None):
-    p, n = _ws(ws)
-    _check(_lib.purine_bias_bwd(_ref(tensor_desc(dy)), _ref(tensor_desc(db)), float(beta), p, n,
-                                _stream(stream)), "purine_bias_bwd")
+    rc = _marshal.purine_bias_bwd(dy, db, beta, ws, stream)
+    if rc is None:
+        p, n = _ws(ws)
+        rc = _lib.purine_bias_bwd(_ref(tensor_desc(dy)), _ref(tensor_desc(db)), float(beta), p, n,
+            _stream(stream))
+    _check(rc, "purine_bias_bwd")
 
 
 def purine_relu_fwd(x, y, stream=None):
-    _check(_lib.purine_relu_fwd(_ref(tensor_desc(x)), _ref(tensor_desc(y)), _stream(stream)),
-           "purine_relu_fwd")
+    rc = _marshal.purine_relu_fwd(x, y, stream)
+    if rc is None:
+        rc = _lib.purine_relu_fwd(_ref(tensor_desc(x)), _ref(tensor_desc(y)), _stream(stream))
+    _check(rc, "purine_relu_fwd")
 
 
 def purine_relu_bwd(x, dy, dx, stream=None):
-    _check(_lib.purine_relu_bwd(_ref(tensor_desc(x)), _ref(tensor_desc(dy)), _ref(tensor_desc(dx)),
-                                _stream(stream)), "purine_relu_bwd")
+    rc = _marshal.purine_relu_bwd(x, dy, dx, stream)
+    if rc is None:
+        rc = _lib.purine_relu_bwd(_ref(tensor_desc(x)), _ref(tensor_desc(dy)), _ref(tensor_desc(dx)),
+            _stream(stream))
+    _check(rc, "purine_relu_bwd")
 
 
 def purine_maxpool_fwd(desc, x, y, arg, stream=None):
-    _check(_lib.purine_maxpool_fwd(_ref(desc), _ref(tensor_desc(x)), _ref(tensor_desc(y)),
-                                   _ref(tensor_desc(arg)), _stream(stream)), "purine_maxpool_fwd")
+    rc = _marshal.purine_maxpool_fwd(desc, x, y, arg, stream)
+    if rc is None:
+        rc = _lib.purine_maxpool_fwd(_ref(desc), _ref(tensor_desc(x)), _ref(tensor_desc(y)),
+            _ref(tensor_desc(arg)), _stream(stream))
+    _check(rc, "purine_maxpool_fwd")
 
 
 def purine_maxpool_bwd(desc, dy, arg, dx, beta=0.0, stream=None):
-    _check(_lib.purine_maxpool_bwd(_ref(desc), _ref(tensor_desc(dy)), _ref(tensor_desc(arg)),
-                                   _ref(tensor_desc(dx)), float(beta), _stream(stream)),
-           "purine_maxpool_bwd")
+    rc = _marshal.purine_maxpool_bwd(desc, dy, arg, dx, beta, stream)
+    if rc is None:
+        rc = _lib.purine_maxpool_bwd(_ref(desc), _ref(tensor_desc(dy)), _ref(tensor_desc(arg)),
+            _ref(tensor_desc(dx)), float(beta), _stream(stream))
+    _check(rc, "purine_maxpool_bwd")
 
 
 def purine_maxpool_bwd_relu(desc, dy, arg, y, dx, beta=0.0, stream=None):
-    _check(_lib.purine_maxpool_bwd_relu(_ref(desc), _ref(tensor_desc(dy)), _ref(tensor_desc(arg)),
-                                        _ref(tensor_desc(y)), _ref(tensor_desc(dx)), float(beta), _stream(stream)),
-           "purine_maxpool_bwd_relu")
+    rc = _marshal.purine_maxpool_bwd_relu(desc, dy, arg, y, dx, beta, stream)
+    if rc is None:
+        rc = _lib.purine_maxpool_bwd_relu(_ref(desc), _ref(tensor_desc(dy)), _ref(tensor_desc(arg)),
+            _ref(tensor_desc(y)), _ref(tensor_desc(dx)), float(beta), _stream(stream))
+    _check(rc, "purine_maxpool_bwd_relu")
 
 
 def _tensor_ptr_array(tensors):

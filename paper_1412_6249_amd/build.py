@@ -32,12 +32,29 @@ def _compile(src):
     return obj
 
 
+def build_marshal():
+    """The native argument marshalling of the Python binding (host code only)."""
+    import sysconfig
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    out = os.path.join(PKG, "_marshal.so")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+                           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+                           "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"],
+                           "-isystem", os.path.join(tdir, "include"), "-isystem", "/opt/rocm/include",
+                           os.path.join(PKG, "native", "marshal.cpp"), "-o", out,
+                           "-L" + PKG, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN",
+                           "-L" + os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"])
+    return out
+
+
 def build_library(jobs=4):
-    """Compiles every source (always: no up-to-date shortcut) and links the shared library."""
+    """Compiles every source (always: no up-to-date shortcut) and links the shared library and the binding's module."""
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         objs = list(ex.map(_compile, sources()))
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
+    build_marshal()
     return LIB
 
 

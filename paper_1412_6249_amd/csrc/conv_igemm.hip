@@ -723,7 +723,9 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
         // at 56x56, N = 256 forward 198 us, 235 on the kernel for rows of any width); else that one, which the
         // one-role kernel was behind on every layer of whole packets timed (128 -> 128 at 16x16, N = 64: 25.5 against 16.5 us;
         // 48 -> 96 5x5 at 40x40, N = 32 backward-data: 38 against 28.5) and is left the rows too wide for its patch.
-        if (((g_force_bm == 0 || patch_split_roles_forced()) && !(pl.patch && q.roles)) || patch_any_forced()) {
+        // (A layer whose copy for the kernel below would have 2^31 bytes or more is refused, whatever would run.)
+        const bool copy_fits = (size_t)g.N * pl.Ci_pad * (bwd_data ? (size_t)g.P * g.Q : (size_t)g.H * g.W) * elem < 0x7fffffffull;
+        if ((pl.patch || copy_fits) && (((g_force_bm == 0 || patch_split_roles_forced()) && !(pl.patch && q.roles)) || patch_any_forced())) {
             pl.pa = plan_patch_any(make_pix_params(dtype, g, pl), pl.mode, patch_any_forced() ? g_force_bn : 0);
             if (pl.pa.use) {
                 pl.patch = false;

@@ -1,0 +1,63 @@
+"""The native argument marshalling: what it hands back to the general path (None), which then raises as it always did."""
+import numpy as np
+import pytest
+import torch
+
+
+def test_hands_back_what_is_not_a_plain_gpu_tensor():
+    import paper_1412_6249_amd as pa
+    from paper_1412_6249_amd import _marshal
+    x, y = torch.zeros(1, 4, 4, 4), torch.zeros(1, 4, 4, 4)
+    raw = pa.raw_desc(0, pa.PURINE_F32, (1, 4, 4, 4))
+    for a, b, s in ((x, y, 0), (raw, raw, 0), (None, y, 0), (object(), y, 0), (x, np.zeros(4), 0), (x, y, "stream")):
+        assert _marshal.purine_relu_fwd(a, b, s) is None
+    assert _marshal.purine_relu_fwd(x, y) is None and _marshal.purine_relu_fwd(x, y, 0, 0) is None
+    assert _marshal.purine_conv_fwd(object(), x, x, y, None, 0) is None
+    with pytest.raises(ValueError):
+        pa.purine_relu_fwd(x, y, stream=0)
+    with pytest.raises(pa.PurineError) as e:
+        pa.purine_relu_fwd(raw, raw, stream=0)
+    assert e.value.status == -1
+    with pytest.raises(AttributeError):
+        pa.purine_relu_fwd(None, y, stream=0)
+
+
+@pytest.mark.gpu
+def test_same_call_and_same_refusals_as_the_general_path():
+    import ctypes
+    import paper_1412_6249_amd as pa
+    from paper_1412_6249_amd import _marshal
+    dev = "cuda:0"
+    big = torch.randn(3, 24, 5, 6, device=dev)
+    x, side = big[:, 8:16], torch.cuda.Stream()
+    y = torch.zeros(3, 8, 5, 6, device=dev)
+    pa.purine_relu_fwd(x, y)
+    assert torch.equal(y, x.clamp(min=0))
+    y.zero_()
+    torch.cuda.synchronize()
+    for stream in (side, side.cuda_stream):
+        pa.purine_relu_fwd(x, y, stream=stream)
+        side.synchronize()
+        assert torch.equal(y, x.clamp(min=0))
+        y.zero_()
+        torch.cuda.synchronize()
+    with torch.cuda.stream(side):                       # the current stream
+        pa.purine_relu_fwd(x, y)
+        side.synchronize()
+    assert torch.equal(y, x.clamp(min=0))
+    # a descriptor beside a tensor; errors of the entry point; forms that are refused before it
+    pa.purine_relu_fwd(pa.tensor_desc(x), y)
+    with pytest.raises(pa.PurineError) as e:
+        pa.purine_relu_fwd(x, y[:, :4].contiguous())
+    assert e.value.status == -2
+    for bad in (x.transpose(2, 3), big[:, ::2], x.double(), torch.zeros(1, 1, 1, 1, 1, device=dev)):
+        assert _marshal.purine_relu_fwd(bad, y, None) is None
+        with pytest.raises((ValueError, TypeError)):
+            pa.purine_relu_fwd(bad, y)
+    desc = pa.conv_desc(1, 1)
+    w, out = torch.randn(8, 24, 3, 3, device=dev), torch.empty(3, 8, 5, 6, device=dev)
+    with pytest.raises(pa.PurineError) as e:
+        pa.purine_conv_fwd(desc, big, w, out)            # no scratch
+    assert e.value.status == -5
+    with pytest.raises(ctypes.ArgumentError):
+        pa.purine_conv_fwd(pa.pool_desc(2, 2), big, w, out)
