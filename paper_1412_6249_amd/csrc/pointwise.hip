@@ -299,7 +299,7 @@ __global__ __launch_bounds__(TPB) void relu_bwd_kernel(const T* __restrict__ x, 
 // group of `ppw` planes (grid.x: group, grid.y: chunk) (small planes are batched so that every workgroup has a few thousand
 // elements; large planes are split). Outputs are written in memory order (coalesced); the window
 // reads overlap between neighbours and are served by L1. Index arithmetic uses the reciprocal
-// division; window size and stride are template constants for the common shapes (K = 0: runtime).
+// division. These kernels take any window and stride; the common shapes have their own below.
 constexpr int POOL_CHUNK = 2048;
 
 struct PoolParams {
@@ -308,10 +308,9 @@ struct PoolParams {
     float beta;
 };
 
-template <typename T, int K, int S>
+template <typename T>
 __global__ __launch_bounds__(TPB) void maxpool_fwd_kernel(const T* __restrict__ x, T* __restrict__ y,
                                                           int32_t* __restrict__ arg, const PoolParams pp) {
-    const int k = K ? K : pp.k, st = K ? S : pp.stride;
     const int lim = min(pp.ppw * pp.PQ, ((int)blockIdx.y + 1) * POOL_CHUNK);
     for (int l = blockIdx.y * POOL_CHUNK + threadIdx.x; l < lim; l += TPB) {
         const int pl = fastdiv(l, pp.div_pq);
@@ -319,33 +318,18 @@ __global__ __launch_bounds__(TPB) void maxpool_fwd_kernel(const T* __restrict__ 
         const int nc = blockIdx.x * pp.ppw + pl;
         if (nc >= pp.NC) break;
         const int p = fastdiv(o, pp.div_q), q = o - p * pp.Q;
-        const int h0 = p * st - pp.pad, w0 = q * st - pp.pad;
+        const int h0 = p * pp.stride - pp.pad, w0 = q * pp.stride - pp.pad;
         const T* plane = x + (size_t)nc * pp.HW;
         int best = -1;
         float bv = 0.0f;
-        if (K) {
-#pragma unroll
-            for (int r = 0; r < (K ? K : 1); ++r)
-#pragma unroll
-                for (int c = 0; c < (K ? K : 1); ++c) {
-                    const int h = h0 + r, w = w0 + c;
-                    const bool ok = ((unsigned)h < (unsigned)pp.H) & ((unsigned)w < (unsigned)pp.W);
-                    const int at = ok ? h * pp.W + w : 0;          // clamped, branch-free
-                    const float v = ldf<T>(plane, at);
-                    const bool take = ok & ((best < 0) | (v > bv));
-                    best = take ? at : best;
-                    bv = take ? v : bv;
-                }
-        } else {
-            for (int r = 0; r < k; ++r) {
-                const int h = h0 + r;
-                if ((unsigned)h >= (unsigned)pp.H) continue;
-                for (int c = 0; c < k; ++c) {
-                    const int w = w0 + c;
-                    if ((unsigned)w >= (unsigned)pp.W) continue;
-                    const float v = ldf<T>(plane, (size_t)h * pp.W + w);
-                    if (best < 0 || v > bv) { best = h * pp.W + w; bv = v; }
-                }
+        for (int r = 0; r < pp.k; ++r) {
+            const int h = h0 + r;
+            if ((unsigned)h >= (unsigned)pp.H) continue;
+            for (int c = 0; c < pp.k; ++c) {
+                const int w = w0 + c;
+                if ((unsigned)w >= (unsigned)pp.W) continue;
+                const float v = ldf<T>(plane, (size_t)h * pp.W + w);
+                if (best < 0 || v > bv) { best = h * pp.W + w; bv = v; }
             }
         }
         const size_t out = (size_t)nc * pp.PQ + o;
@@ -359,12 +343,11 @@ __global__ __launch_bounds__(TPB) void maxpool_fwd_kernel(const T* __restrict__ 
 // null): the pooling output of the forward pass; windows whose winner was not positive pass no
 // gradient. When the pooled tensor is a ReLU output that is its ReLU gradient (a position that won
 // a window holds that window's y), which would otherwise be a pass of its own over dx.
-template <typename T, int K, int S>
+template <typename T>
 __global__ __launch_bounds__(TPB) void maxpool_bwd_kernel(const T* __restrict__ dy,
                                                           const int32_t* __restrict__ arg,
                                                           T* dx, const T* __restrict__ y, const PoolParams pp) {
-    const int k = K ? K : pp.k, st = K ? S : pp.stride;
-    constexpr int NW = K ? (K + S - 1) / (S ? S : 1) : 1;   // windows per axis that can cover a position
+    const int k = pp.k, st = pp.stride;
     const int lim = min(pp.ppw * pp.HW, ((int)blockIdx.y + 1) * POOL_CHUNK);
     for (int l = blockIdx.y * POOL_CHUNK + threadIdx.x; l < lim; l += TPB) {
         const int pl = fastdiv(l, pp.div_hw);
@@ -381,27 +364,12 @@ __global__ __launch_bounds__(TPB) void maxpool_bwd_kernel(const T* __restrict__ 
         q_lo = q_lo <= 0 ? 0 : (q_lo + st - 1) / st;
         const size_t obase = (size_t)nc * pp.PQ;
         const size_t at = (size_t)nc * pp.HW + e;
-        const float old = pp.beta != 0.0f ? ldf<T>(dx, at) : 0.0f;
-        float acc = old;
-        if (K) {
-#pragma unroll
-            for (int a = 0; a < NW; ++a)
-#pragma unroll
-                for (int b = 0; b < NW; ++b) {
-                    const int p = p_lo + a, q = q_lo + b;
-                    const bool in = (p <= p_hi) & (q <= q_hi);
-                    const int o = in ? p * pp.Q + q : 0;           // clamped, branch-free
-                    const bool hit = in & (arg[obase + o] == e) & (!y || ldf<T>(y, obase + o) > 0.0f);
-                    const float g = ldf<T>(dy, obase + o);
-                    acc += hit ? g : 0.0f;
-                }
-        } else {
-            for (int p = p_lo; p <= p_hi; ++p)
-                for (int q = q_lo; q <= q_hi; ++q) {
-                    const size_t o = obase + p * pp.Q + q;
-                    if (arg[o] == e && (!y || ldf<T>(y, o) > 0.0f)) acc += ldf<T>(dy, o);
-                }
-        }
+        float acc = pp.beta != 0.0f ? ldf<T>(dx, at) : 0.0f;
+        for (int p = p_lo; p <= p_hi; ++p)
+            for (int q = q_lo; q <= q_hi; ++q) {
+                const size_t o = obase + p * pp.Q + q;
+                if (arg[o] == e && (!y || ldf<T>(y, o) > 0.0f)) acc += ldf<T>(dy, o);
+            }
         stf<T>(dx, at, acc);
     }
 }
@@ -415,15 +383,14 @@ __global__ __launch_bounds__(TPB) void maxpool_bwd_kernel(const T* __restrict__ 
 // bit-identical results. quads != 0 (a workgroup's first position is a multiple of four positions
 // from an aligned dx): a thread takes four consecutive positions, decodes the first and steps to
 // the others, and dx moves as packets of four.
-template <typename T, int K, int S>
+template <typename T>
 __global__ __launch_bounds__(TPB) void maxpool_bwd_staged_kernel(const T* __restrict__ dy,
                                                                  const int32_t* __restrict__ arg,
                                                                  T* dx, const T* __restrict__ y, const PoolParams pp,
                                                                  const int quads) {
     extern __shared__ __attribute__((aligned(16))) unsigned char pool_smem[];
     int2* win_s = reinterpret_cast<int2*>(pool_smem);                 // [ppw][PQ] {winner, gradient bits}
-    const int k = K ? K : pp.k, st = K ? S : pp.stride;
-    constexpr int NW = K ? (K + S - 1) / (S ? S : 1) : 1;
+    const int k = pp.k, st = pp.stride;
     const int nc0 = blockIdx.x * pp.ppw;
     const int planes = min(pp.ppw, pp.NC - nc0);
     {
@@ -446,23 +413,11 @@ __global__ __launch_bounds__(TPB) void maxpool_bwd_staged_kernel(const T* __rest
         q_lo = q_lo <= 0 ? 0 : (q_lo + st - 1) / st;
         const int obase = pl * pp.PQ;
         float acc = old;
-        if (K) {
-#pragma unroll
-            for (int a = 0; a < NW; ++a)
-#pragma unroll
-                for (int b = 0; b < NW; ++b) {
-                    const int p = p_lo + a, q = q_lo + b;
-                    const bool in = (p <= p_hi) & (q <= q_hi);
-                    const int2 win = win_s[obase + (in ? p * pp.Q + q : 0)];   // clamped, branch-free
-                    acc += (in & (win.x == e)) ? __int_as_float(win.y) : 0.0f;
-                }
-        } else {
-            for (int p = p_lo; p <= p_hi; ++p)
-                for (int q = q_lo; q <= q_hi; ++q) {
-                    const int2 win = win_s[obase + p * pp.Q + q];
-                    if (win.x == e) acc += __int_as_float(win.y);
-                }
-        }
+        for (int p = p_lo; p <= p_hi; ++p)
+            for (int q = q_lo; q <= q_hi; ++q) {
+                const int2 win = win_s[obase + p * pp.Q + q];
+                if (win.x == e) acc += __int_as_float(win.y);
+            }
         return acc;
     };
     const int lim = planes * pp.HW;
@@ -506,96 +461,236 @@ __global__ __launch_bounds__(TPB) void maxpool_bwd_staged_kernel(const T* __rest
     }
 }
 
-// ---- 3x3 / stride 1 / pad 1 pooling on fp32 planes whose width is a multiple of 4 ----------------
-// (the pooling branch of an inception module). A lane owns four consecutive positions of one row:
-// per window row it needs the aligned packet of those four columns plus the column on either side,
-// so 3 packets + 6 scalars replace 36 scalar loads, and the outputs leave as packets. Winners and
-// sums are taken in the same order as in the general kernels (bit-identical results).
-struct Pool3Params {
-    int NC, H, W, HW, W4;      // W4 = W / 4 packets per row
-    FastDiv div_row4, div_w4;  // by H * W4 (packets per plane) and by W4
-    long long total4;          // packets in all
+// ---- Pooling by 3x3 / stride 1, 3x3 / stride 2 and 2x2 / stride 2 windows -------------------------
+// Bound: HBM. A workgroup owns whole planes, or a band of rows of one plane: either way what it reads is ONE
+// contiguous run of each tensor, which it copies into LDS as 16-byte packets (tensors start at one), all of a
+// thread's loads of a batch in flight together; rows of any width, and windows overlapping each other, cost no
+// global access of their own. (Gathering from global memory took nine strided loads per window forward, and a
+// look-up of four windows with their index arithmetic per position backward, 60 vector instructions each.)
+// 128 x 96 planes of 55x55 fp32, 3x3 / stride 2: forward 59 -> 37 us, gradient through the ReLU 85 -> 45;
+// 128 x 192 of 28x28, 3x3 / stride 1: 46 -> 41 and 246 -> 62 (unmasked 66 -> 58).
+struct PoolTile {
+    int NC, H, W, P, Q, HW, PQ, pad;
+    int planes;                // planes per workgroup (bands == 1)
+    int bands, rows;           // else bands of a plane, of `rows` output rows (forward) or rows of cells (backward)
+    int quads;                 // runs of outputs in a row (forward), cells in a row (backward)
+    int cell_rows;             // backward: rows of cells
+    int lead, plane_s;         // backward: entries before the staged windows, entries of a staged tensor
+    FastDiv div_plane, div_row;   // by the runs or cells of a plane, of a row
     float beta;
 };
+constexpr int POOL_BATCH = 4;   // packets per thread in flight
+constexpr int pool_outputs(int stride) { return stride == 1 ? 4 : 2; }   // outputs of a row per lane, forward
 
-__global__ __launch_bounds__(TPB) void maxpool3_fwd_vec_kernel(const float* __restrict__ x, float* __restrict__ y,
-                                                               int32_t* __restrict__ arg, const Pool3Params pp) {
-    for (long long i = (long long)blockIdx.x * TPB + threadIdx.x; i < pp.total4; i += (long long)gridDim.x * TPB) {
-        // plane index and packet inside the plane (the host keeps the packet count below 2^31)
-        const int per_plane = pp.H * pp.W4;
-        const int nc = fastdiv((uint32_t)i, pp.div_row4);
-        const int r4 = (int)i - nc * per_plane;
-        const int p = fastdiv(r4, pp.div_w4);
-        const int q0 = (r4 - p * pp.W4) * 4;
-        const float* plane = x + (size_t)nc * pp.HW;
-        float bv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        int best[4] = {-1, -1, -1, -1};
+// n consecutive elements of a row, one store at whatever element it starts
+template <int n> __device__ __forceinline__ void store_run(float* p, const float (&v)[n]) {
+    typedef float run __attribute__((ext_vector_type(n), aligned(4)));
+    run r;
 #pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const int h = p - 1 + r;
-            const bool row_ok = (unsigned)h < (unsigned)pp.H;
-            const int hb = (row_ok ? h : p) * pp.W;                 // clamped row: values unused when !row_ok
-            const float4 v4 = *reinterpret_cast<const float4*>(plane + hb + q0);
-            const bool l_ok = row_ok & (q0 > 0), r_ok = row_ok & (q0 + 4 < pp.W);
-            const float vl = plane[hb + (q0 > 0 ? q0 - 1 : q0)];
-            const float vr = plane[hb + (q0 + 4 < pp.W ? q0 + 4 : q0)];
-            const float v[6] = {vl, v4.x, v4.y, v4.z, v4.w, vr};
-            const bool ok[6] = {l_ok, row_ok, row_ok, row_ok, row_ok, r_ok};
+    for (int i = 0; i < n; ++i) r[i] = v[i];
+    *reinterpret_cast<run*>(p) = r;
+}
+template <int n> __device__ __forceinline__ void store_run(uint16_t* p, const float (&v)[n]) {
+    typedef uint16_t run __attribute__((ext_vector_type(n), aligned(2)));
+    run r;
 #pragma unroll
-            for (int o = 0; o < 4; ++o)
+    for (int i = 0; i < n; ++i) r[i] = f2bf(v[i]);
+    *reinterpret_cast<run*>(p) = r;
+}
+
+// A lane takes OW outputs of a row. Positions outside the plane are clamped to its edge: the window's rows and
+// columns of that edge come twice, in order, and an element never beats itself (every window holds a position
+// of the plane; launch_maxpool_fwd sees to it).
+template <typename T, int K, int S>
+__global__ __launch_bounds__(TPB) void maxpool_fwd_tile_kernel(const T* __restrict__ x, T* __restrict__ y,
+                                                               int32_t* __restrict__ arg, const PoolTile t) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char pool_smem[];
+    const T* xs = reinterpret_cast<const T*>(pool_smem);
+    constexpr int V = Pk<T>::N;
+    int nc0 = blockIdx.x * t.planes, planes = min(t.planes, t.NC - nc0), p0 = 0, np = t.P, h_lo = 0, n = planes * t.HW;
+    if (t.bands > 1) {
+        nc0 = blockIdx.x / t.bands;
+        planes = 1;
+        p0 = (blockIdx.x - nc0 * t.bands) * t.rows;
+        np = min(t.rows, t.P - p0);
+        h_lo = min(t.H, max(0, p0 * S - t.pad));
+        n = max(0, min(t.H, (p0 + np - 1) * S - t.pad + K) - h_lo) * t.W;
+    }
+    const size_t first = (size_t)nc0 * t.HW + (size_t)h_lo * t.W;
+    const int shift = (int)(first & (V - 1));
+    {
+        const T* src = x + (first - shift);
+        const uint4* g = reinterpret_cast<const uint4*>(src);
+        uint4* s4 = reinterpret_cast<uint4*>(pool_smem);
+        const size_t left = (size_t)t.NC * t.HW - (first - shift);          // elements up to the tensor's end
+        const int whole = (int)min((size_t)((shift + n + V - 1) / V), left / V);
+        for (int i = threadIdx.x; i < whole; i += TPB * POOL_BATCH) {
+            uint4 v[POOL_BATCH];
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {                       // window column c of output o is v[o + c]
-                    const bool take = ok[o + c] & ((best[o] < 0) | (v[o + c] > bv[o]));
-                    best[o] = take ? h * pp.W + q0 + o + c - 1 : best[o];
-                    bv[o] = take ? v[o + c] : bv[o];
+            for (int b = 0; b < POOL_BATCH; ++b) v[b] = g[min(i + b * TPB, whole - 1)];
+#pragma unroll
+            for (int b = 0; b < POOL_BATCH; ++b)
+                if (i + b * TPB < whole) s4[i + b * TPB] = v[b];
+        }
+        for (int i = whole * V + threadIdx.x; i < shift + n; i += TPB) reinterpret_cast<T*>(pool_smem)[i] = src[i];
+    }
+    __syncthreads();
+    constexpr int OW = pool_outputs(S), COLS = (OW - 1) * S + K;
+    const int m = planes * np * t.quads;
+    for (int l = threadIdx.x; l < m; l += TPB) {
+        const int pl = t.bands > 1 ? 0 : fastdiv(l, t.div_plane);
+        const int o = l - pl * t.P * t.quads;
+        const int pr = fastdiv(o, t.div_row), q = (o - pr * t.quads) * OW;
+        const T* plane = xs + shift + pl * t.HW - h_lo * t.W;
+        const int h0 = (p0 + pr) * S - t.pad, w0 = q * S - t.pad;
+        int best[OW], col[COLS];
+        float bv[OW];
+#pragma unroll
+        for (int c = 0; c < COLS; ++c) col[c] = min(max(w0 + c, 0), t.W - 1);
+#pragma unroll
+        for (int r = 0; r < K; ++r) {
+            const int row = min(max(h0 + r, 0), t.H - 1) * t.W;
+            float v[COLS];
+#pragma unroll
+            for (int c = 0; c < COLS; ++c) v[c] = ldf<T>(plane, row + col[c]);
+#pragma unroll
+            for (int w = 0; w < OW; ++w)
+#pragma unroll
+                for (int c = 0; c < K; ++c) {
+                    const bool take = (r == 0 && c == 0) || v[w * S + c] > bv[w];
+                    best[w] = take ? row + col[w * S + c] : best[w];
+                    bv[w] = take ? v[w * S + c] : bv[w];
                 }
         }
-        const size_t out = (size_t)nc * pp.HW + (size_t)p * pp.W + q0;
-        *reinterpret_cast<float4*>(y + out) = make_float4(bv[0], bv[1], bv[2], bv[3]);
-        *reinterpret_cast<int4*>(arg + out) = make_int4(best[0], best[1], best[2], best[3]);
+        const size_t out = (size_t)(nc0 + pl) * t.PQ + (size_t)(p0 + pr) * t.Q + q;
+        if (q + OW <= t.Q) {
+            typedef int iw __attribute__((ext_vector_type(OW), aligned(4)));
+            iw a;
+#pragma unroll
+            for (int w = 0; w < OW; ++w) a[w] = best[w];
+            *reinterpret_cast<iw*>(arg + out) = a;
+            store_run<OW>(y + out, bv);
+        } else {
+#pragma unroll
+            for (int w = 0; w < OW; ++w)
+                if (q + w < t.Q) { arg[out + w] = best[w]; stf<T>(y, out + w, bv[w]); }
+        }
     }
 }
 
-__global__ __launch_bounds__(TPB) void maxpool3_bwd_vec_kernel(const float* __restrict__ dy,
-                                                               const int32_t* __restrict__ arg, float* dx,
-                                                               const Pool3Params pp) {
-    for (long long i = (long long)blockIdx.x * TPB + threadIdx.x; i < pp.total4; i += (long long)gridDim.x * TPB) {
-        const int per_plane = pp.H * pp.W4;
-        const int nc = fastdiv((uint32_t)i, pp.div_row4);
-        const int r4 = (int)i - nc * per_plane;
-        const int h = fastdiv(r4, pp.div_w4);
-        const int w0 = (r4 - h * pp.W4) * 4;
-        const size_t base = (size_t)nc * pp.HW;
-        const size_t at = base + (size_t)h * pp.W + w0;
-        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (pp.beta != 0.0f) {
-            const float4 o = *reinterpret_cast<const float4*>(dx + at);
-            acc[0] = o.x; acc[1] = o.y; acc[2] = o.z; acc[3] = o.w;
-        }
-        // windows (p, q) with p in h-1..h+1 and q in w-1..w+1 cover position (h, w); visited in (p, q) order
+// The gradient, gathered: a lane takes a cell of S rows x 4 columns of positions and looks at the windows that
+// cover any of them, winners and gradients in LDS; which window can reach which position is known at compile
+// time. The gradient of a window whose winner was not positive is dropped on its way into LDS (y may be null:
+// no mask). Sums in (p, q) order, as in the kernel above: the same bits.
+template <typename T, int K, int S>
+__global__ __launch_bounds__(TPB) void maxpool_bwd_tile_kernel(const T* __restrict__ dy, const int32_t* __restrict__ arg,
+                                                               T* dx, const T* __restrict__ y, const PoolTile t) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char pool_smem[];
+    int* arg_s = reinterpret_cast<int*>(pool_smem) + t.lead;            // winners; then the gradients, alike
+    float* g_s = reinterpret_cast<float*>(pool_smem) + t.plane_s + t.lead;
+    constexpr int CW = 4, NW = (K + S - 1) / S, NQ = CW / S + NW - 1;
+    typedef typename std::conditional<sizeof(T) == 4, float4, ushort4>::type Quad;
+    int nc0 = blockIdx.x * t.planes, planes = min(t.planes, t.NC - nc0), c0 = 0, rows = t.cell_rows, p_lo = 0, n = planes * t.PQ;
+    if (t.bands > 1) {
+        nc0 = blockIdx.x / t.bands;
+        planes = 1;
+        c0 = (blockIdx.x - nc0 * t.bands) * t.rows;
+        rows = min(t.rows, t.cell_rows - c0);
+        p_lo = min(t.P, max(0, c0 - NW + 1));
+        n = max(0, min(t.P, c0 + rows) - p_lo) * t.Q;
+    }
+    const size_t first = (size_t)nc0 * t.PQ + (size_t)p_lo * t.Q;
+    const int shift = (int)(first & 3);
+    {
+        const T* sdy = dy + (first - shift);
+        const T* sy = y ? y + (first - shift) : nullptr;
+        const int32_t* sarg = arg + (first - shift);
+        const size_t left = (size_t)t.NC * t.PQ - (first - shift);
+        const int whole = (int)min((size_t)((shift + n + 3) / 4), left / 4);
+        for (int i = threadIdx.x; i < whole; i += 2 * TPB) {
+            int4 a[2];
+            Quad g[2], v[2];
 #pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const int p = h - 1 + r;
-            const bool row_ok = (unsigned)p < (unsigned)pp.H;
-            const size_t rb = base + (size_t)(row_ok ? p : h) * pp.W;
-            const float4 g4 = *reinterpret_cast<const float4*>(dy + rb + w0);
-            const int4 a4 = *reinterpret_cast<const int4*>(arg + rb + w0);
-            const int li = w0 > 0 ? w0 - 1 : w0, ri = w0 + 4 < pp.W ? w0 + 4 : w0;
-            const bool l_ok = row_ok & (w0 > 0), r_ok = row_ok & (w0 + 4 < pp.W);
-            const float g[6] = {dy[rb + li], g4.x, g4.y, g4.z, g4.w, dy[rb + ri]};
-            const int a[6] = {arg[rb + li], a4.x, a4.y, a4.z, a4.w, arg[rb + ri]};
-            const bool ok[6] = {l_ok, row_ok, row_ok, row_ok, row_ok, r_ok};
+            for (int b = 0; b < 2; ++b) {
+                const int at = min(i + b * TPB, whole - 1);
+                a[b] = reinterpret_cast<const int4*>(sarg)[at];
+                g[b] = reinterpret_cast<const Quad*>(sdy)[at];
+                if (sy) v[b] = reinterpret_cast<const Quad*>(sy)[at];
+            }
 #pragma unroll
-            for (int o = 0; o < 4; ++o) {
-                const int e = h * pp.W + w0 + o;                    // this position's index in its plane
+            for (int b = 0; b < 2; ++b) {
+                float f[4], w[4];
+                if constexpr (sizeof(T) == 4) {
+                    f[0] = g[b].x; f[1] = g[b].y; f[2] = g[b].z; f[3] = g[b].w;
+                    w[0] = v[b].x; w[1] = v[b].y; w[2] = v[b].z; w[3] = v[b].w;
+                } else {
+                    f[0] = bf2f(g[b].x); f[1] = bf2f(g[b].y); f[2] = bf2f(g[b].z); f[3] = bf2f(g[b].w);
+                    w[0] = bf2f(v[b].x); w[1] = bf2f(v[b].y); w[2] = bf2f(v[b].z); w[3] = bf2f(v[b].w);
+                }
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const bool hit = ok[o + c] & (a[o + c] == e);
-                    acc[o] += hit ? g[o + c] : 0.0f;
+                for (int e = 0; e < 4; ++e) f[e] = !sy || w[e] > 0.0f ? f[e] : 0.0f;
+                if (i + b * TPB < whole) {
+                    reinterpret_cast<int4*>(arg_s)[i + b * TPB] = a[b];
+                    reinterpret_cast<float4*>(g_s)[i + b * TPB] = make_float4(f[0], f[1], f[2], f[3]);
                 }
             }
         }
-        *reinterpret_cast<float4*>(dx + at) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        for (int i = whole * 4 + threadIdx.x; i < shift + n; i += TPB) {
+            arg_s[i] = sarg[i];
+            g_s[i] = (!sy || ldf<T>(sy, i) > 0.0f) ? ldf<T>(sdy, i) : 0.0f;
+        }
+    }
+    __syncthreads();
+    const int per_plane = rows * t.quads, m = planes * per_plane;
+    for (int l = threadIdx.x; l < m; l += TPB) {
+        const int pl = t.bands > 1 ? 0 : fastdiv(l, t.div_plane);
+        const int rest = l - pl * per_plane;
+        const int cr = fastdiv(rest, t.div_row), cc = rest - cr * t.quads;
+        const int h0 = (c0 + cr) * S - t.pad, w0 = cc * CW - t.pad;       // the cell's first position
+        const int q0 = cc * (CW / S) - NW + 1;
+        int win[NW][NQ];
+        float g[NW][NQ];
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            const int p = c0 + cr - NW + 1 + i;
+            const bool row_in = (unsigned)p < (unsigned)t.P;
+            // a window outside the plane has some other entry's winner and gradient here, or what lies in LDS before
+            // or behind the staged ones: its winner is replaced by one that no position has
+            const int at = shift + pl * t.PQ + (p - p_lo) * t.Q + q0;
+#pragma unroll
+            for (int j = 0; j < NQ; ++j) {
+                const int a = arg_s[at + j];
+                g[i][j] = g_s[at + j];
+                win[i][j] = (row_in & ((unsigned)(q0 + j) < (unsigned)t.Q)) ? a : -1;
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < S; ++a) {
+            const int h = h0 + a;
+            if ((unsigned)h >= (unsigned)t.H) continue;
+            T* row = dx + (size_t)(nc0 + pl) * t.HW + (size_t)h * t.W;
+            float v[CW];
+#pragma unroll
+            for (int b = 0; b < CW; ++b) {
+                const int w = w0 + b, e = h * t.W + w;
+                v[b] = t.beta != 0.0f && (unsigned)w < (unsigned)t.W ? ldf<T>(row, w) : 0.0f;
+#pragma unroll
+                for (int i = 0; i < NW; ++i)
+#pragma unroll
+                    for (int j = 0; j < NQ; ++j) {
+                        // window row i lies NW-1-i above the cell's: it reaches row a iff S*(NW-1-i) + a < K; columns alike
+                        const int dr = S * (NW - 1 - i) + a, dc = b - S * (j - NW + 1);
+                        if (dr < K && dc >= 0 && dc < K) v[b] += win[i][j] == e ? g[i][j] : 0.0f;
+                    }
+            }
+            if (w0 >= 0 && w0 + CW <= t.W) {
+                store_run<CW>(row + w0, v);
+            } else {
+#pragma unroll
+                for (int b = 0; b < CW; ++b)
+                    if ((unsigned)(w0 + b) < (unsigned)t.W) stf<T>(row, w0 + b, v[b]);
+            }
+        }
     }
 }
 
@@ -813,52 +908,83 @@ dim3 pool_grid(const PoolParams& pp, int per_plane) {
     // x: plane groups (up to 2^31 - 1), y: chunks of one group (up to 65535)
     return dim3((unsigned)((pp.NC + pp.ppw - 1) / pp.ppw), (unsigned)((per_group + POOL_CHUNK - 1) / POOL_CHUNK));
 }
-// the packet kernels: fp32, 3x3 / stride 1 / pad 1 (output extents = input extents), rows of whole packets
-bool pool3_vec_applies(int dtype, int NC, int H, int W, int P, int Q, int k, int stride, int pad, const void* a,
-                       const void* b, const void* c) {
-    return dtype == PURINE_F32 && k == 3 && stride == 1 && pad == 1 && P == H && Q == W && W % 4 == 0 &&
-           (long long)NC * H * (W / 4) < 0x7fffffffLL &&
-           (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & 15u) == 0;
+// Splits the planes of a pooling pass over workgroups, for the tile kernels: `run` elements of `size` bytes staged
+// per plane in rows of `row`, `lines` rows of work per plane, of which r need (r - 1) * step + halo staged rows.
+// Several planes share a workgroup while at least 2048 remain (eight per CU) or while they are under 1024 elements in all;
+// a plane beyond `cap` bytes is cut into bands, and so are the planes of a call with less than two workgroups per CU,
+// down to about 512 elements each. False: not even a single row fits.
+bool pool_tile(PoolTile& t, long long run, long long row, int size, int lines, int step, int halo, int cap, size_t* lds) {
+    const long long fit = (cap / (row * size) - halo) / step + 1;          // rows of work that fit
+    if (cap / (row * size) < halo) return false;
+    long long want = (512 + t.NC - 1) / t.NC;
+    if (want > run / 512) want = run / 512;
+    if (run * size > cap && want < (lines + fit - 1) / fit) want = (lines + fit - 1) / fit;
+    t.planes = 1; t.bands = 1; t.rows = lines;
+    if (want > 1) {
+        t.rows = (int)((lines + want - 1) / want);
+        t.bands = (lines + t.rows - 1) / t.rows;
+    }
+    if (t.bands == 1) {
+        if (run * size > cap) return false;
+        long long planes = t.NC / 2048, few = (1024 + run - 1) / run;
+        if (planes < few) planes = few;
+        if (planes > cap / (run * size)) planes = cap / (run * size);
+        if (planes > t.NC) planes = t.NC;
+        t.planes = planes < 1 ? 1 : (int)planes;
+        *lds = (size_t)(t.planes * run * size);
+    } else {
+        *lds = (size_t)(((t.rows - 1) * step + halo) * row * size);
+    }
+    *lds = (*lds + 63) / 32 * 32;                                           // + a partial packet at either end
+    return (long long)(t.NC + t.planes - 1) / t.planes * t.bands <= 0x7fffffffLL;
 }
-Pool3Params pool3_params(int NC, int H, int W, float beta) {
-    Pool3Params p{};
-    p.NC = NC; p.H = H; p.W = W; p.HW = H * W; p.W4 = W / 4;
-    p.div_w4 = make_fastdiv(p.W4);
-    p.div_row4 = make_fastdiv(H * p.W4);
-    p.total4 = (long long)NC * H * p.W4;
-    p.beta = beta;
-    return p;
+PoolTile pool_tile_params(int NC, int H, int W, int P, int Q, int stride, int pad, float beta) {
+    PoolTile t{};
+    t.NC = NC; t.H = H; t.W = W; t.P = P; t.Q = Q; t.HW = H * W; t.PQ = P * Q; t.pad = pad; t.beta = beta;
+    return t;
+}
+// the shapes of the tile kernels; every window holds a position of the plane
+bool pool_tile_shape(int k, int stride, int pad, int H, int W, int P, int Q) {
+    return ((k == 3 && (stride == 1 || stride == 2)) || (k == 2 && stride == 2)) && pad < k &&
+           (long long)(P - 1) * stride - pad < H && (long long)(Q - 1) * stride - pad < W;
 }
 #define POOL_SHAPES(CALL)                                           \
     if (k == 3 && stride == 1) { CALL(3, 1); }                      \
-    else if (k == 3 && stride == 2) { CALL(3, 2); }                 \
-    else if (k == 2 && stride == 2) { CALL(2, 2); }                 \
-    else { CALL(0, 0); }
+    else if (k == 3) { CALL(3, 2); }                                \
+    else { CALL(2, 2); }
 }  // namespace
 
 hipError_t launch_maxpool_fwd(int dtype, const void* x, void* y, int32_t* arg, int NC, int H, int W,
                               int P, int Q, int k, int stride, int pad, hipStream_t st) {
     // a group of planes is indexed with 32-bit arithmetic; groups go to grid.y
     if ((long long)H * W > 0x3fffffffLL || (long long)P * Q > 0x3fffffffLL) return hipErrorInvalidValue;
-    if (pool3_vec_applies(dtype, NC, H, W, P, Q, k, stride, pad, x, y, arg)) {
-        const Pool3Params p3 = pool3_params(NC, H, W, 0.0f);
-        ProbeScope probe(st);
-        (void)hipGetLastError();
-        hipLaunchKernelGGL(maxpool3_fwd_vec_kernel, dim3(blocks_for((size_t)p3.total4)), dim3(TPB), 0, st,
-                           (const float*)x, (float*)y, arg, p3);
-        return hipGetLastError();
+    if (pool_tile_shape(k, stride, pad, H, W, P, Q)) {
+        PoolTile t = pool_tile_params(NC, H, W, P, Q, stride, pad, 0.0f);
+        size_t lds = 0;
+        // 12 KB: eight workgroups (32 wavefronts) per CU, their loads and arithmetic in each other's shadow (40 KB: 10 - 20 % slower)
+        if (pool_tile(t, t.HW, W, dtype == PURINE_BF16 ? 2 : 4, P, stride, k, 12 * 1024 - 64, &lds)) {
+            t.quads = (Q + pool_outputs(stride) - 1) / pool_outputs(stride);
+            t.div_plane = make_fastdiv(P * t.quads); t.div_row = make_fastdiv(t.quads);
+            const dim3 grid((unsigned)((NC + t.planes - 1) / t.planes * t.bands));
+            ProbeScope probe(st);
+            (void)hipGetLastError();   // drop stale status left by earlier, unrelated runtime calls
+#define CALL(K, S)                                                                                              \
+    BY_DTYPE(dtype,                                                                                             \
+             hipLaunchKernelGGL((maxpool_fwd_tile_kernel<float, K, S>), grid, dim3(TPB), lds, st, (const float*)x, (float*)y, arg, t),         \
+             hipLaunchKernelGGL((maxpool_fwd_tile_kernel<uint16_t, K, S>), grid, dim3(TPB), lds, st, (const uint16_t*)x, (uint16_t*)y, arg, t))
+            POOL_SHAPES(CALL)
+#undef CALL
+            return hipGetLastError();
+        }
     }
     const PoolParams pp = pool_params(NC, H, W, P, Q, k, stride, pad, P * Q, 0.0f);
     const dim3 grid = pool_grid(pp, P * Q);
     if (grid.y > 65535u) return hipErrorInvalidValue;
     ProbeScope probe(st);
-    (void)hipGetLastError();   // drop stale status left by earlier, unrelated runtime calls
-#define CALL(K, S)                                                                                              \
-    BY_DTYPE(dtype,                                                                                             \
-             hipLaunchKernelGGL((maxpool_fwd_kernel<float, K, S>), grid, dim3(TPB), 0, st, (const float*)x, (float*)y, arg, pp),       \
-             hipLaunchKernelGGL((maxpool_fwd_kernel<uint16_t, K, S>), grid, dim3(TPB), 0, st, (const uint16_t*)x, (uint16_t*)y, arg, pp))
-    POOL_SHAPES(CALL)
-#undef CALL
+    (void)hipGetLastError();
+    BY_DTYPE(dtype,
+             hipLaunchKernelGGL(maxpool_fwd_kernel<float>, grid, dim3(TPB), 0, st, (const float*)x, (float*)y, arg, pp),
+             hipLaunchKernelGGL(maxpool_fwd_kernel<uint16_t>, grid, dim3(TPB), 0, st, (const uint16_t*)x, (uint16_t*)y, arg, pp));
     return hipGetLastError();
 }
 
@@ -866,13 +992,33 @@ hipError_t launch_maxpool_bwd(int dtype, const void* dy, const int32_t* arg, voi
                               int NC, int H, int W, int P, int Q, int k, int stride, int pad,
                               hipStream_t st) {
     if ((long long)H * W > 0x3fffffffLL || (long long)P * Q > 0x3fffffffLL) return hipErrorInvalidValue;
-    if (!y && pool3_vec_applies(dtype, NC, H, W, P, Q, k, stride, pad, dy, dx, arg)) {
-        const Pool3Params p3 = pool3_params(NC, H, W, beta);
-        ProbeScope probe(st);
-        (void)hipGetLastError();
-        hipLaunchKernelGGL(maxpool3_bwd_vec_kernel, dim3(blocks_for((size_t)p3.total4)), dim3(TPB), 0, st,
-                           (const float*)dy, arg, (float*)dx, p3);
-        return hipGetLastError();
+    const int elem = dtype == PURINE_BF16 ? 2 : 4;
+    if (pool_tile_shape(k, stride, pad, H, W, P, Q)) {
+        PoolTile t = pool_tile_params(NC, H, W, P, Q, stride, pad, beta);
+        size_t lds = 0;
+        const int nw = (k + stride - 1) / stride;
+        t.cell_rows = (H + pad + stride - 1) / stride;
+        t.quads = (W + pad + 3) / 4;
+        t.div_plane = make_fastdiv(t.cell_rows * t.quads); t.div_row = make_fastdiv(t.quads);
+        // a cell reaches up to nw - 1 rows and columns before the staged windows, as many columns behind a row's end, and
+        // a row of cells past the last row of windows
+        t.lead = ((nw - 1) * (Q + 1) + 3) / 4 * 4;
+        const long long tail = (t.cell_rows >= P ? (long long)(t.cell_rows - P + 1) * Q : 0) + 4LL * t.quads + 8;
+        // 8 bytes per window: 12 KB, eight workgroups per CU (32 KB: 10 - 25 % slower)
+        if (t.lead + tail < 3000 && pool_tile(t, t.PQ, Q, 8, t.cell_rows, 1, nw, 12 * 1024 - 64, &lds)) {
+            t.plane_s = (int)((lds / 8 + t.lead + tail + 3) / 4 * 4);
+            lds = (size_t)t.plane_s * 8;
+            const dim3 grid((unsigned)((NC + t.planes - 1) / t.planes * t.bands));
+            ProbeScope probe(st);
+            (void)hipGetLastError();
+#define CALL(K, S)                                                                                              \
+    BY_DTYPE(dtype,                                                                                             \
+             hipLaunchKernelGGL((maxpool_bwd_tile_kernel<float, K, S>), grid, dim3(TPB), lds, st, (const float*)dy, arg, (float*)dx, (const float*)y, t),     \
+             hipLaunchKernelGGL((maxpool_bwd_tile_kernel<uint16_t, K, S>), grid, dim3(TPB), lds, st, (const uint16_t*)dy, arg, (uint16_t*)dx, (const uint16_t*)y, t))
+            POOL_SHAPES(CALL)
+#undef CALL
+            return hipGetLastError();
+        }
     }
     PoolParams pp = pool_params(NC, H, W, P, Q, k, stride, pad, H * W, beta);
     // Whole planes per workgroup with their arg and dy planes in LDS: up to about 8K positions per
@@ -890,16 +1036,12 @@ hipError_t launch_maxpool_bwd(int dtype, const void* dy, const int32_t* arg, voi
             pp.ppw = (int)ppw;
             const unsigned groups = (unsigned)((NC + pp.ppw - 1) / pp.ppw);
             const size_t lds = (size_t)pp.ppw * P * Q * 8;
-            const int elem = dtype == PURINE_BF16 ? 2 : 4;
             const int quads = ((ppw * H * W) % 4 == 0 || groups == 1) && ((uintptr_t)dx % (4 * elem)) == 0;
             ProbeScope probe(st);
             (void)hipGetLastError();
-#define CALL(K, S)                                                                                              \
-    BY_DTYPE(dtype,                                                                                             \
-             hipLaunchKernelGGL((maxpool_bwd_staged_kernel<float, K, S>), dim3(groups), dim3(TPB), lds, st, (const float*)dy, arg, (float*)dx, (const float*)y, pp, quads),     \
-             hipLaunchKernelGGL((maxpool_bwd_staged_kernel<uint16_t, K, S>), dim3(groups), dim3(TPB), lds, st, (const uint16_t*)dy, arg, (uint16_t*)dx, (const uint16_t*)y, pp, quads))
-            POOL_SHAPES(CALL)
-#undef CALL
+            BY_DTYPE(dtype,
+                     hipLaunchKernelGGL(maxpool_bwd_staged_kernel<float>, dim3(groups), dim3(TPB), lds, st, (const float*)dy, arg, (float*)dx, (const float*)y, pp, quads),
+                     hipLaunchKernelGGL(maxpool_bwd_staged_kernel<uint16_t>, dim3(groups), dim3(TPB), lds, st, (const uint16_t*)dy, arg, (uint16_t*)dx, (const uint16_t*)y, pp, quads));
             return hipGetLastError();
         }
     }
@@ -907,12 +1049,9 @@ hipError_t launch_maxpool_bwd(int dtype, const void* dy, const int32_t* arg, voi
     if (grid.y > 65535u) return hipErrorInvalidValue;
     ProbeScope probe(st);
     (void)hipGetLastError();   // drop stale status left by earlier, unrelated runtime calls
-#define CALL(K, S)                                                                                              \
-    BY_DTYPE(dtype,                                                                                             \
-             hipLaunchKernelGGL((maxpool_bwd_kernel<float, K, S>), grid, dim3(TPB), 0, st, (const float*)dy, arg, (float*)dx, (const float*)y, pp),     \
-             hipLaunchKernelGGL((maxpool_bwd_kernel<uint16_t, K, S>), grid, dim3(TPB), 0, st, (const uint16_t*)dy, arg, (uint16_t*)dx, (const uint16_t*)y, pp))
-    POOL_SHAPES(CALL)
-#undef CALL
+    BY_DTYPE(dtype,
+             hipLaunchKernelGGL(maxpool_bwd_kernel<float>, grid, dim3(TPB), 0, st, (const float*)dy, arg, (float*)dx, (const float*)y, pp),
+             hipLaunchKernelGGL(maxpool_bwd_kernel<uint16_t>, grid, dim3(TPB), 0, st, (const uint16_t*)dy, arg, (uint16_t*)dx, (const uint16_t*)y, pp));
     return hipGetLastError();
 }
 
