@@ -204,7 +204,7 @@ int purine_conv_matrix_products(int pass, const purine_conv_desc* desc, const in
         parts = plan_wgrad(g, dtype).pk.use;
     } else {
         const PixPlan pl = plan_conv_pix(g, pass == PURINE_CONV_BWD_DATA, dtype, false);
-        parts = pl.pk.use || (pl.pf.use && pl.pf.split);
+        parts = pl.pk.use || pl.ps.use || (pl.pf.use && pl.pf.split);
     }
     return parts ? 6 : 1;
 }

@@ -96,6 +96,13 @@ struct PatchAnyPlan {
     double us;
 };
 
+// ... and fp32 1x1 layers on bf16 parts split in registers (conv_gemm1x1_split.hip).
+struct Split1x1Plan {
+    bool use;
+    int tm, tiles_i, cgs;        // row tiles of 32 * tm; groups of 16 gathered channels
+    int strips, groups, waves;   // strips of 32 pixels; workgroups per row tile, wavefronts of each that take strips
+};
+
 // Plan of the streaming fp32 GEMM on bf16 parts (gemm_stream_f32.hip): rows x columns of the output over a
 // reduction, split over workgroups where scratch for partial outputs is at hand.
 struct StreamPlan {
@@ -136,10 +143,12 @@ struct PixPlan {
     PacketPlan pk;
     PatchF32Plan pf;
     PatchAnyPlan pa;
+    Split1x1Plan ps;
 };
 PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, bool accumulate = false);
 void force_pix_tile(int bm, int bn);
 bool patch_any_forced();             // test hook: (-9, tile): bf16 layers run the patch kernel for rows of any width, with that tile (bm * 1000 + bn) or its own
+bool split_1x1_forced();             // test hook: (-10, row tiles of 32, or 0): fp32 1x1 layers run the kernel on parts split in registers
 bool split_patch_forced();           // test hook: (-6, anything): fp32 layers run the kernel that splits a patch in LDS wherever it applies
 bool split_packets_forced();         // test hook: (-7, anything): ... the kernels on packed bf16 parts (forward, backward-data, weight gradient)
 bool patch_split_roles_forced();     // test hook: (-5, anything) gives it layers of few tiles too

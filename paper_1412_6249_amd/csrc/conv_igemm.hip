@@ -560,6 +560,7 @@ bool patch_split_roles_disabled() { return g_force_bm == -4; }   // tuning hook:
 bool split_patch_forced() { return g_force_bm == -6; }           // test hooks: fp32 layers run the kernel that splits in LDS
 bool f32_patch_forced() { return g_force_bm == -8; }             // / forward passes the fp32 patch kernel
 bool patch_any_forced() { return g_force_bm == -9; }             // / bf16 layers the patch kernel for rows of any width
+bool split_1x1_forced() { return g_force_bm == -10; }            // / fp32 1x1 layers the kernel on parts split in registers
 bool split_packets_forced() { return g_force_bm == -7; }         // / the ones on packed parts wherever they apply
 bool patch_split_roles_forced() { return g_force_bm == -5; }     // test hook: force_pix_tile(-5, x), also for layers of few tiles
 void force_pix_tile(int bm, int bn) {
@@ -782,6 +783,10 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
         if (pl.pk.use) { if (pl.pk.ws_bytes > pl.ws_bytes) pl.ws_bytes = pl.pk.ws_bytes; return pl; }
         if (pl.pf.use) return pl;
     }
+    if (dtype == PURINE_F32 && pl.mode != 2 && !pl.flat && g_no_buffer_loads == 0 && (g_force_bm == 0 || split_1x1_forced())) {
+        pl.ps = plan_gemm1x1_split(make_pix_params(dtype, g, pl), split_1x1_forced(), split_1x1_forced() ? g_force_bn : 0);
+        if (pl.ps.use) return pl;
+    }
     // identity gather: the streaming GEMM applies
     const long long HW = (long long)g.H * g.W;
     const bool forced = (g_force_bn == 1 || g_force_bn == 2 || g_force_bn == 4) && g_force_bm >= 32 &&
@@ -847,6 +852,7 @@ hipError_t launch_conv_pix(int dtype, const ConvGeom& g, const PixPlan& pl, cons
     p.beta = beta;
 
     if (pl.pf.use) return launch_patch_f32(p, pl.pf, pl.mode, wt, g.K, g.C, ws, st);
+    if (pl.ps.use) return launch_gemm1x1_split(p, pl.ps, pl.mode == 1, wt, st);
     if (pl.pk.use) return launch_packets(p, pl.pk, pl.mode, wt, g.K, g.C, ws, st);
     if (pl.pa.use) {
         ProbeScope whole_op(st, true);
