@@ -77,7 +77,8 @@ struct PatchF32Plan {
     int bm, tiles_i, tiles_pix;
     int bands, Wb, PW;          // images are cut into bands of Wb columns; patch rows of PW positions
     int cgs;                    // groups of 16 gathered channels
-    size_t a_bytes;
+    int full, parts, cg_part;   // tiles past the first `full` are summed by `parts` workgroups of cg_part groups each
+    size_t a_bytes, part_offset, part_bytes;
     double us;
 };
 
@@ -149,7 +150,7 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
 void force_pix_tile(int bm, int bn);
 bool patch_any_forced();             // test hook: (-9, tile): bf16 layers run the patch kernel for rows of any width, with that tile (bm * 1000 + bn) or its own
 bool split_1x1_forced();             // test hook: (-10, row tiles of 32, or 0): fp32 1x1 layers run the kernel on parts split in registers
-bool split_patch_forced();           // test hook: (-6, anything): fp32 layers run the kernel that splits a patch in LDS wherever it applies
+bool split_patch_forced();           // test hook: (-6, parts): fp32 layers run the kernel that splits a patch in LDS wherever it applies (parts > 1: each last tile's channels over as many workgroups)
 bool split_packets_forced();         // test hook: (-7, anything): ... the kernels on packed bf16 parts (forward, backward-data, weight gradient)
 bool patch_split_roles_forced();     // test hook: (-5, anything) gives it layers of few tiles too
 bool patch_split_roles_disabled();   // tuning hook: (-4, anything) keeps the bf16 patch kernel on its one-role form

@@ -768,7 +768,7 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
         const PixParams pp = make_pix_params(dtype, g, pl);
         const bool small = ((long long)Co + 127) / 128 * ((M + 255) / 256) < 32;
         const bool keep_bits = pl.mode == 0 && (long long)Ci * g.R * g.S > 2048 && !small;
-        pl.pf = plan_patch_f32(pp, pl.mode == 2, !(keep_bits && g_force_bm == 0) && !f32_patch_forced());
+        pl.pf = plan_patch_f32(pp, pl.mode == 2, !(keep_bits && g_force_bm == 0) && !f32_patch_forced(), split_patch_forced() ? g_force_bn : 0);
         pl.pk = plan_packets(pp, pl.mode == 2);
         if (pl.pf.use && pl.pf.a_bytes > pl.ws_bytes) pl.pf.use = false;
         if (f32_patch_forced() && pl.mode != 0) pl.pf.use = false;
@@ -781,7 +781,10 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
             if (split_packets_forced()) pl.pf.use = false; else pl.pk.use = false;
         }
         if (pl.pk.use) { if (pl.pk.ws_bytes > pl.ws_bytes) pl.ws_bytes = pl.pk.ws_bytes; return pl; }
-        if (pl.pf.use) return pl;
+        if (pl.pf.use) {
+            if (pl.pf.parts > 1 && pl.pf.part_offset + pl.pf.part_bytes > pl.ws_bytes) pl.ws_bytes = pl.pf.part_offset + pl.pf.part_bytes;
+            return pl;
+        }
     }
     if (dtype == PURINE_F32 && pl.mode != 2 && !pl.flat && g_no_buffer_loads == 0 && (g_force_bm == 0 || split_1x1_forced())) {
         pl.ps = plan_gemm1x1_split(make_pix_params(dtype, g, pl), split_1x1_forced(), split_1x1_forced() ? g_force_bn : 0);

@@ -24,7 +24,8 @@
 //
 // Measured at N = 128 (whole operator, fp32 MFMA kernel before): 384 <- 384 channels 3x3 at 13x13
 // backward-data 0.50 -> 0.28 ms (204 TFLOP/s; 0.31 with the operands packed in scratch), 96 -> 128 3x3 at
-// 28x28 forward 0.236 -> 0.140, 96 <- 256 5x5 at 27x27 backward-data 1.01 -> 0.69 (365 tiles on 256 CUs).
+// 28x28 forward 0.236 -> 0.140, 96 <- 256 5x5 at 27x27 backward-data 1.01 -> 0.69, with the last 109 of its 365 tiles on two
+// workgroups each 0.58.
 #include "packets.h"
 #include "pix_common.h"
 
@@ -48,6 +49,10 @@ struct PatchF32Params {
     int h_base, w_base;         // input row / column of patch row / column 0, relative to the output row / column
     int img_rows;               // patch rows of a whole image: Ho + Rt - 1
     FastDiv div_ho, div_wb, div_bands, div_pw, div_img, div_st;
+    // The tiles past the last whole round of CUs (split only): `parts` workgroups each take cg_part channel groups of one and
+    // leave raw sums in partial[tile][part][thread]; a second launch (join) adds them in order and finishes.
+    int full, parts, cg_part, join;
+    float* partial;
 };
 
 // Filter repack, one thread per four channels: [row tile][group][tap][row][16], zero past the last row
@@ -100,6 +105,24 @@ struct PatchTile {
     static constexpr int LDS = 2 * A_BYTES + 2 * P_BYTES + 512 + BM * 4;       // + spare half KB + bias
 };
 
+// The sums of a tile's parts, in order, and a bit per element that is infinite or NaN.
+template <int TM, int TN, int NT>
+__device__ __forceinline__ unsigned long long add_parts(floatx16 (&acc)[TM][TN], const float* partial, int tile, int parts, int tid) {
+    unsigned long long bad = 0;
+    const floatx4* src = reinterpret_cast<const floatx4*>(partial) + (size_t)tile * parts * TM * TN * 4 * NT + tid;
+#pragma unroll
+    for (int i = 0; i < TM * TN * 4; ++i) {
+        floatx4 v = src[(size_t)i * NT];
+        for (int s = 1; s < parts; ++s) v += src[((size_t)s * TM * TN * 4 + i) * NT];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (!(__builtin_fabsf(v[e]) <= 3.402823466e38f)) bad |= 1ull << (i * 4 + e);
+            acc[i / 4 / TN][i / 4 % TN][i % 4 * 4 + e] = v[e];
+        }
+    }
+    return bad;
+}
+
 template <bool SPLIT, bool MINUS, bool D2S, bool FUSED, int TM, int WM>
 __global__ __launch_bounds__(SPLIT ? 512 : 256, 2) void igemm_patch_f32_kernel(const PixParams p, const PatchF32Params q) {
     typedef PatchTile<SPLIT, TM, WM> T;
@@ -114,7 +137,17 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, 2) void igemm_patch_f32_kernel(c
     const int khalf = lane >> 5;
     const int wm = wave / WN, wn = wave % WN;
     // row tiles innermost: they read the same patch and share an XCD's L2
-    const int id = xcd_tile(blockIdx.x, gridDim.x);
+    int id, slot = -1, cg0 = 0, cg1 = q.cgs;
+    if (!SPLIT || (int)blockIdx.x < q.full) {
+        id = xcd_tile(blockIdx.x, SPLIT ? q.full : gridDim.x);
+    } else {
+        slot = xcd_tile(blockIdx.x - q.full, gridDim.x - q.full);
+        const int tile = slot / q.parts, part = slot - tile * q.parts;
+        id = q.full + tile;
+        cg0 = part * q.cg_part;
+        cg1 = min(cg0 + q.cg_part, q.cgs);
+    }
+    if (SPLIT && q.join) { slot = blockIdx.x; id = q.full + slot; }
     const int pt = id / p.tiles_i, rt = id - pt * p.tiles_i;
     const int i0 = rt * T::BM, p0 = pt * BN;
 
@@ -164,11 +197,11 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, 2) void igemm_patch_f32_kernel(c
     }
 
     float breg[TASKS][8];
-    auto load_patch = [&](int cg) {               // cg == cgs: every offset lies outside, nothing is fetched
+    auto load_patch = [&](int cg) {               // cg == cg1: every offset lies outside, nothing is fetched
 #pragma unroll
         for (int j = 0; j < TASKS; ++j) {
-            const int lim = p.Ci - cg * 16 - half[j] * 8;      // channels left for this task
-            const int soff = cg < q.cgs ? cg * 16 * p.HiWi * 4 : 0;
+            const int lim = cg < cg1 ? p.Ci - cg * 16 - half[j] * 8 : 0;      // channels left for this task
+            const int soff = cg < cg1 ? cg * 16 * p.HiWi * 4 : 0;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 unsigned v = src[j] >= 0 && e < lim ? (unsigned)src[j] + (unsigned)(e * p.HiWi * 4) : 0x80000000u;
@@ -297,39 +330,57 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, 2) void igemm_patch_f32_kernel(c
     };
 
     const int n_steps = q.cgs * q.taps;
-    load_patch(0);
-    store_a(load_a(0), 0);
-    store_patch(0);
-    int step = 0;
-    for (int cg = 0; cg < q.cgs; ++cg) {
-        const int buf = cg & 1;
-        int tr = 0, tc = 0;
-        auto tap_offset = [&]() { return MINUS ? ((p.Rt - 1 - tr) * q.PW + (p.St - 1 - tc)) * 16 : (tr * q.PW + tc) * 16; };
-        // first tap: the next group's patch is requested behind the next step's filter tile, so that
-        // waiting for the latter does not wait for the former
-        meet();
-        {
-            const FilterRegs f = load_a(step + 1);      // (one past the last step: still inside the buffer's range check)
-            load_patch(cg + 1);
-            __builtin_amdgcn_sched_barrier(0);       // requests first: they have the whole step to arrive
-            multiply(step, buf, tap_offset());
-            store_a(f, (step + 1) & 1);
-            ++step;
-        }
-        for (int tap = 1; tap < q.taps; ++tap) {
-            if (++tc == p.St) { tc = 0; ++tr; }
+    if (!SPLIT || !q.join) {
+        int step = cg0 * q.taps;
+        load_patch(cg0);
+        store_a(load_a(step), step & 1);
+        store_patch(cg0 & 1);
+        for (int cg = cg0; cg < cg1; ++cg) {
+            const int buf = cg & 1;
+            int tr = 0, tc = 0;
+            auto tap_offset = [&]() { return MINUS ? ((p.Rt - 1 - tr) * q.PW + (p.St - 1 - tc)) * 16 : (tr * q.PW + tc) * 16; };
+            // first tap: the next group's patch is requested behind the next step's filter tile, so that
+            // waiting for the latter does not wait for the former
             meet();
-            const FilterRegs f = load_a(step + 1);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(step, buf, tap_offset());
-            store_a(f, (step + 1) & 1);
-            ++step;
+            {
+                const FilterRegs f = load_a(step + 1);      // (one past the last step: still inside the buffer's range check)
+                load_patch(cg + 1);
+                __builtin_amdgcn_sched_barrier(0);       // requests first: they have the whole step to arrive
+                multiply(step, buf, tap_offset());
+                store_a(f, (step + 1) & 1);
+                ++step;
+            }
+            for (int tap = 1; tap < q.taps; ++tap) {
+                if (++tc == p.St) { tc = 0; ++tr; }
+                meet();
+                const FilterRegs f = load_a(step + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(step, buf, tap_offset());
+                store_a(f, (step + 1) & 1);
+                ++step;
+            }
+            if (cg + 1 < cg1) store_patch(buf ^ 1);
         }
-        if (cg + 1 < q.cgs) store_patch(buf ^ 1);
     }
 
     // infinities and NaNs: again, as plain fp32 sums of the fp32 operands
-    unsigned long long bad = SPLIT ? join_sets<TM, TN>(hi, lo) : 0ull;
+    unsigned long long bad = 0;
+    if (SPLIT && q.join) {
+        if (FUSED && !MINUS) __syncthreads();      // the bias values
+        bad = add_parts<TM, TN, NT>(hi, q.partial, slot, q.parts, tid);
+    } else if (SPLIT) {
+        bad = join_sets<TM, TN>(hi, lo);
+        if (slot >= 0) {
+            floatx4* dst = reinterpret_cast<floatx4*>(q.partial) + (size_t)slot * TM * TN * 4 * NT + tid;
+#pragma unroll
+            for (int i = 0; i < TM * TN * 4; ++i) {
+                const floatx16& v = hi[i / 4 / TN][i / 4 % TN];
+                const int e = i % 4 * 4;
+                dst[(size_t)i * NT] = floatx4{v[e], v[e + 1], v[e + 2], v[e + 3]};
+            }
+            return;
+        }
+    }
     if (SPLIT && __builtin_expect(__any(bad != 0), 0)) {
         while (bad) {
             const int idx = __ffsll((long long)bad) - 1;
@@ -372,7 +423,13 @@ hipError_t launch_main(const PixParams& p, const PatchF32Params& q, hipStream_t 
     if (e != hipSuccess) return e;
     ProbeScope probe(st);
     (void)hipGetLastError();   // drop stale status left by earlier, unrelated runtime calls
-    hipLaunchKernelGGL((igemm_patch_f32_kernel<SPLIT, MINUS, D2S, FUSED, TM, WM>), dim3((unsigned)total), dim3(T::NT), T::LDS, st, p, q);
+    const long long tail = total - q.full, grid = q.full + tail * q.parts;       // (no tail: q.full == total)
+    hipLaunchKernelGGL((igemm_patch_f32_kernel<SPLIT, MINUS, D2S, FUSED, TM, WM>), dim3((unsigned)grid), dim3(T::NT), T::LDS, st, p, q);
+    e = hipGetLastError();
+    if (e != hipSuccess || tail == 0) return e;
+    PatchF32Params j = q;
+    j.join = 1;
+    hipLaunchKernelGGL((igemm_patch_f32_kernel<SPLIT, MINUS, D2S, FUSED, TM, WM>), dim3((unsigned)tail), dim3(T::NT), T::LDS, st, p, j);
     return hipGetLastError();
 }
 
@@ -396,7 +453,7 @@ constexpr RowTile kF32Tiles[] = {{128, 2048, 0.90f}, {96, 1536, 0.88f}, {64, 102
 }  // namespace
 
 // How the layer would run here and the expected time (conv_igemm.hip compares). Pure host arithmetic.
-PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s, bool split) {
+PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s, bool split, int force_parts) {
     PatchF32Plan k{};
     k.split = split;
     if (p.Rt * p.St < 2 || p.Ci < 8 || p.in_bytes == 0 || p.g_mul_h != 1 || p.g_mul_w != 1) return k;
@@ -427,10 +484,35 @@ PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s, bool split) {
         const double x = (double)(ti * tp) / 256.0, ceil_x = (double)((ti * tp + 255) / 256);
         // one workgroup per CU at a time (the clock rises a little as CUs run dry), or two
         const double load = split ? 0.3 * x + 0.7 * ceil_x : x <= 1.0 ? 1.3 : 0.3 * x + 0.7 * ceil_x;
-        const double us = 10.0 + load * (k.cgs * (p.Rt * p.St * t.cycles / eff + 1000.0) + (d2s ? 50000.0 : 10000.0)) / (split ? 2.2e3 : 2.4e3);
+        auto workgroup_us = [&](double groups) {
+            return (groups * (p.Rt * p.St * t.cycles / eff + 1000.0) + (d2s ? 50000.0 : 10000.0)) / (split ? 2.2e3 : 2.4e3);
+        };
+        double us = 10.0 + load * workgroup_us(k.cgs);
+        // The tiles past the last whole round of 256 leave most CUs idle for as long as a round takes: their channel groups go
+        // to several workgroups each where that is expected to pay for the second launch and the sums' way through memory
+        // (256 <- 96 channels 5x5 at 27x27, N = 128 backward-data, 365 tiles of 16 groups, the last 109 halved: 691 -> 577 us; 83 <- 264
+        // 3x3 at 46x46, N = 63: 463 -> 385; 202 -> 270 3x3 at 11x11, N = 251 forward: 220 -> 190; 53 <- 417 5x5 at 15x17, N = 137,
+        // 137 tiles in all: 445 -> 319). Another tile height only for a clear gain (102 <- 84 5x5 at 56x56, N = 12, 294 tiles of 64 rows
+        // in parts 160 us, 147 of 128 in one round 155). Fewer than 128 tiles: the packed operands' splits.
+        const long long full = ti * tp / 256 * 256, tail = ti * tp - full;
+        int parts = 1, cg_part = k.cgs;
+        double best_us = force_parts > 1 ? 1e30 : us;
+        if (split && tail > 0 && (full + tail >= 128 || force_parts > 1)) {
+            for (int want = 2; want <= 8 && want <= k.cgs; ++want) {
+                const int per = (k.cgs + want - 1) / want, n = (k.cgs + per - 1) / per;
+                const double bytes = (double)tail * n * t.bm * BN * 4.0, x_tail = (double)(tail * n) / 256.0;
+                if (n != want || bytes > 70e6 || (force_parts > 1 && n != force_parts)) continue;
+                const double split_us = 10.0 + full / 256 * workgroup_us(k.cgs) + (0.3 * x_tail + 0.7 * (double)((tail * n + 255) / 256)) * workgroup_us(per) +
+                                        8.0 + 2.0 * bytes / 4e6;
+                if (split_us < best_us) { best_us = split_us; us = 1.06 * split_us; parts = n; cg_part = per; }
+            }
+        }
         if (!k.use || us < k.us) {
             k.use = true; k.us = us;
             k.bm = t.bm; k.tiles_i = (int)ti; k.tiles_pix = (int)tp;
+            k.full = (int)(parts > 1 ? full : full + tail); k.parts = parts; k.cg_part = cg_part;
+            k.part_offset = ((size_t)a_bytes + 255) / 256 * 256;
+            k.part_bytes = parts > 1 ? (size_t)tail * parts * t.bm * BN * 4 : 0;
             k.a_bytes = (size_t)a_bytes;
         }
     }
@@ -460,6 +542,8 @@ hipError_t launch_patch_f32(PixParams p, const PatchF32Plan& k, int mode, const 
     q.h_base = mode == 0 ? p.g_add_h : p.g_add_h - (p.Rt - 1);
     q.w_base = mode == 0 ? p.g_add_w : p.g_add_w - (p.St - 1);
     q.img_rows = p.Ho + p.Rt - 1;
+    q.full = k.full; q.parts = k.parts; q.cg_part = k.cg_part;
+    q.partial = (float*)((char*)ws + k.part_offset);
     q.div_ho = make_fastdiv(p.Ho); q.div_wb = make_fastdiv(k.Wb); q.div_bands = make_fastdiv(k.bands); q.div_pw = make_fastdiv(k.PW);
     q.div_img = make_fastdiv(q.img_rows); q.div_st = make_fastdiv(p.St);
     p.tiles_i = k.tiles_i; p.tiles_pix = k.tiles_pix;

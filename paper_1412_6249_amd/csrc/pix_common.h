@@ -632,7 +632,7 @@ Split1x1Plan plan_gemm1x1_split(const PixParams& p, bool forced, int force);
 hipError_t launch_gemm1x1_split(PixParams p, const Split1x1Plan& k, bool trans, const void* w, hipStream_t st);
 // fp32 layers with a unit-stride gather on bf16 parts split in LDS (conv_patch_f32.hip); mode and w as
 // below. launch_patch_f32 repacks the filter (fp32) into ws.
-PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s, bool split);
+PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s, bool split, int force_parts);
 hipError_t launch_patch_f32(PixParams p, const PatchF32Plan& k, int mode, const void* w, int K, int C, void* ws, hipStream_t st);
 
 // fp32 layers on packed bf16 parts (conv_packets.hip). mode: 0 forward, 1 backward-data with unit
