@@ -24,8 +24,7 @@
 //
 // Measured at N = 128 (whole operator, fp32 MFMA kernel before): 384 <- 384 channels 3x3 at 13x13
 // backward-data 0.50 -> 0.28 ms (204 TFLOP/s; 0.31 with the operands packed in scratch), 96 -> 128 3x3 at
-// 28x28 forward 0.236 -> 0.140, 96 <- 256 5x5 at 27x27 backward-data 1.01 -> 0.69, with the last 109 of its 365 tiles on two
-// workgroups each 0.58.
+// 28x28 forward 0.236 -> 0.140, 96 <- 256 5x5 at 27x27 backward-data 1.01 -> 0.69 (365 tiles on 256 CUs).
 #include "packets.h"
 #include "pix_common.h"
 
@@ -490,10 +489,10 @@ PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s, bool split, int force_
         double us = 10.0 + load * workgroup_us(k.cgs);
         // The tiles past the last whole round of 256 leave most CUs idle for as long as a round takes: their channel groups go
         // to several workgroups each where that is expected to pay for the second launch and the sums' way through memory
-        // (256 <- 96 channels 5x5 at 27x27, N = 128 backward-data, 365 tiles of 16 groups, the last 109 halved: 691 -> 577 us; 83 <- 264
-        // 3x3 at 46x46, N = 63: 463 -> 385; 202 -> 270 3x3 at 11x11, N = 251 forward: 220 -> 190; 53 <- 417 5x5 at 15x17, N = 137,
-        // 137 tiles in all: 445 -> 319). Another tile height only for a clear gain (102 <- 84 5x5 at 56x56, N = 12, 294 tiles of 64 rows
-        // in parts 160 us, 147 of 128 in one round 155). Fewer than 128 tiles: the packed operands' splits.
+        // (48 <- 128 channels 5x5 at 27x27, N = 128 backward-data, 365 tiles of 8 groups, the last 109 halved: 288 -> 238 us; 83 <- 264
+        // 3x3 at 46x46, N = 63: 463 -> 385). Another tile height only for a clear gain (102 <- 84 5x5 at 56x56, N = 12, 294 tiles of
+        // 64 rows in parts 160 us, 147 of 128 in one round 155). The sums are scratch that a caller holds for the layer: at most
+        // 16 MB (with 22, 96 <- 256 5x5 at 27x27, N = 128 would take 577 us instead of 691).
         const long long full = ti * tp / 256 * 256, tail = ti * tp - full;
         int parts = 1, cg_part = k.cgs;
         double best_us = force_parts > 1 ? 1e30 : us;
@@ -501,7 +500,7 @@ PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s, bool split, int force_
             for (int want = 2; want <= 8 && want <= k.cgs; ++want) {
                 const int per = (k.cgs + want - 1) / want, n = (k.cgs + per - 1) / per;
                 const double bytes = (double)tail * n * t.bm * BN * 4.0, x_tail = (double)(tail * n) / 256.0;
-                if (n != want || bytes > 70e6 || (force_parts > 1 && n != force_parts)) continue;
+                if (n != want || bytes > 16e6 || (force_parts > 1 && n != force_parts)) continue;
                 const double split_us = 10.0 + full / 256 * workgroup_us(k.cgs) + (0.3 * x_tail + 0.7 * (double)((tail * n + 255) / 256)) * workgroup_us(per) +
                                         8.0 + 2.0 * bytes / 4e6;
                 if (split_us < best_us) { best_us = split_us; us = 1.06 * split_us; parts = n; cg_part = per; }
