@@ -786,7 +786,7 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
             return pl;
         }
     }
-    if (dtype == PURINE_F32 && pl.mode != 2 && !pl.flat && g_no_buffer_loads == 0 && (g_force_bm == 0 || split_1x1_forced())) {
+    if (dtype == PURINE_F32 && pl.mode != 2 && pl.Rt * pl.St == 1 && !pl.flat && g_no_buffer_loads == 0 && (g_force_bm == 0 || split_1x1_forced())) {
         pl.ps = plan_gemm1x1_split(make_pix_params(dtype, g, pl), split_1x1_forced(), split_1x1_forced() ? g_force_bn : 0);
         if (pl.ps.use) return pl;
     }
