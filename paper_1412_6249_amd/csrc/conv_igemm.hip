@@ -726,7 +726,7 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
         // 48 -> 96 5x5 at 40x40, N = 32 backward-data: 38 against 28.5) and is left the rows too wide for its patch.
         // (A layer whose copy for the kernel below would have 2^31 bytes or more is refused, whatever would run.)
         const bool copy_fits = (size_t)g.N * pl.Ci_pad * (bwd_data ? (size_t)g.P * g.Q : (size_t)g.H * g.W) * elem < 0x7fffffffull;
-        if ((pl.patch || copy_fits) && (((g_force_bm == 0 || patch_split_roles_forced()) && !(pl.patch && q.roles)) || patch_any_forced())) {
+        if ((pl.patch || copy_fits) && (((g_force_bm == 0 || patch_split_roles_forced()) && !g_no_buffer_loads && !(pl.patch && q.roles)) || patch_any_forced())) {
             pl.pa = plan_patch_any(make_pix_params(dtype, g, pl), pl.mode, patch_any_forced() ? g_force_bn : 0);
             if (pl.pa.use) {
                 pl.patch = false;

@@ -527,6 +527,9 @@ __global__ __launch_bounds__(256, 2) void igemm_patch_any_bf16_kernel(const PixP
         if (q.dx_bytes) store_any_d2s2<TM, TN>(p, acc, i0 + wm * TM * 32, px0, lane, q.dx_bytes);
         else store_tile_at<uint16_t, true, true, TM, TN, false>(p, (uint16_t*)p.out, acc, i0 + wm * TM * 32, [&](int b) { return px0 + b; }, lane >> 5,
                                                            bias_s, i0, 0x7fffffff);
+    } else if (RT == 0 && p.out_bytes == 0) {          // views of 2^31 bytes and more: 64-bit addresses
+        store_tile_at<uint16_t, false, true, TM, TN, !MINUS>(p, (uint16_t*)p.out, acc, i0 + wm * TM * 32, [&](int b) { return px0 + b; }, lane >> 5,
+                                                             bias_s, i0, 0x7fffffff);
     } else {
         store_any<TM, TN, !MINUS>(p, acc, i0 + wm * TM * 32, px0, lane, bias_s, i0, q.pairs != 0);
     }
@@ -574,6 +577,9 @@ hipError_t by_tile(const PixParams& p, const PatchAnyParams& q, const PatchAnyPl
 template <bool MINUS, bool D2S>
 hipError_t by_taps(const PixParams& p, const PatchAnyParams& q, const PatchAnyPlan& k, hipStream_t st) {
     constexpr int OTHER = D2S ? 2 : 5;
+    // an output that spans 2^31 bytes or more: the kernel for any taps has the epilogue for it, and runs with the same tile
+    // and stages (its ring has fewer slots than theirs), so that the plan does not depend on the tensors' strides
+    if (!D2S && p.out_bytes == 0) return by_tile<MINUS, D2S, 0, false>(p, q, k, st);
     if (k.rt == 3) return k.ahead ? by_tile<MINUS, D2S, 3, false>(p, q, k, st) : by_tile<MINUS, D2S, 3, true>(p, q, k, st);
     if (k.rt == OTHER) return k.ahead ? by_tile<MINUS, D2S, OTHER, false>(p, q, k, st) : by_tile<MINUS, D2S, OTHER, true>(p, q, k, st);
     return by_tile<MINUS, D2S, 0, false>(p, q, k, st);
@@ -595,13 +601,12 @@ constexpr AnyTileCost kAnyTiles[] = {
 
 }  // namespace
 
-// How the layer would run here and the expected time. Pure host arithmetic on the pass's geometry.
+// How the layer would run here and the expected time. Pure host arithmetic on the pass's extents: never on the strides of
+// its tensors, which the scratch query does not know. (Loads have 32-bit byte offsets: every tensor spans less than 2^31 elements.)
 PatchAnyPlan plan_patch_any(const PixParams& p, int mode, int force) {
     PatchAnyPlan best{};
     if (p.Rt * p.St < 2 || p.Ci < 8 || p.Wi < 4) return best;
-    if (mode != 2 && p.out_bytes == 0) return best;              // the epilogue addresses the output as a raw buffer
-    const long long in_bytes = ((long long)(p.N - 1) * p.in_ns + (long long)p.Ci * p.HiWi) * 2;
-    if (in_bytes >= 0x7fffffffLL) return best;
+    if (mode != 2 && (long long)p.M * p.Co * 2 >= 0x7fffffffLL) return best;   // dense: the epilogue addresses it as a raw buffer
     const int gh = p.g_mul_h, gw = p.g_mul_w;
     PatchAnyPlan k{};
     k.taps = p.Rt * p.St; k.cgs = (p.Ci + 15) / 16;

@@ -800,9 +800,11 @@ bool plan_patch_bf16(PixParams& p, int mode, PatchGeom* qg) {
 }
 
 // bytes of the repacked filter for a layer with Co output rows, Ci gathered channels and n_taps taps,
-// whatever row tile ends up running
+// whatever row tile ends up running: here, or on the kernel for rows of any width, which the same layer takes with tensors
+// that this one cannot address
 size_t patch_filter_bytes(int Co, int Ci, int n_taps) {
-    const long long i_pad = ((long long)Co + 127) / 128 * 128;   // the row tile picked never pads further than 128-row tiles
+    const long long pad96 = ((long long)Co + 95) / 96 * 96, pad128 = ((long long)Co + 127) / 128 * 128;   // tiles of 32 and 64 rows pad less
+    const long long i_pad = pad96 > pad128 ? pad96 : pad128;
     return (size_t)n_taps * (size_t)i_pad * (size_t)((Ci + GC - 1) / GC * GC) * 2;
 }
 

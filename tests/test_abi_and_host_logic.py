@@ -259,6 +259,60 @@ def test_operator_argument_validation_without_launch():
     assert status(pa.purine_maxpool_fwd, pa.pool_desc(3, 2, 3), x, y, binding.raw_desc(fake + 0x500000, pa.PURINE_I32, (2, 4, 8, 8)), stream=s) == -8
 
 
+# dtype, groups, x, w, pad, elements between the images of x and of y (0: dense). Spans of less than 2^31 elements, most of
+# which reach 2^31 bytes, as a group's slice of a dense tensor or as a slice of a wider buffer.
+FAR_CASES = [
+    ("bf16", 2, (256, 256, 132, 132), (256, 128, 3, 3), 1, 0, 0),
+    ("bf16", 2, (256, 128, 132, 132), (256, 64, 3, 3), 1, 0, 0),               # only the output
+    ("bf16", 1, (128, 96, 28, 28), (128, 96, 3, 3), 1, 11000 * 784, 0),
+    ("bf16", 1, (128, 96, 28, 28), (128, 96, 3, 3), 1, 0, 11000 * 784),
+    ("bf16", 1, (64, 16, 55, 55), (32, 16, 3, 3), 1, 0, 20000000),
+    ("bf16", 1, (64, 16, 56, 56), (32, 16, 3, 3), 1, 0, 20000000),             # rows of whole packets
+    ("bf16", 1, (256, 64, 56, 56), (100, 64, 3, 3), 1, 8000000, 8000000),      # ... and the two-role kernel when dense
+]
+
+
+@pytest.mark.parametrize("case", FAR_CASES, ids=["-".join(map(str, c)).replace(" ", "") for c in FAR_CASES])
+def test_scratch_of_the_query_is_enough_whatever_the_strides(case):
+    # The scratch has exactly the queried size but a misaligned address: a call whose plan asks for more answers -5,
+    # one that is content with it -4, and none launches anything.
+    dtype, groups, xs, wsh, pad, x_ns, y_ns = case
+    code = pa.PURINE_BF16 if dtype == "bf16" else pa.PURINE_F32
+    desc = pa.conv_desc(1, pad)
+    ys = (xs[0], wsh[0], xs[2] + 2 * pad - wsh[2] + 1, xs[3] + 2 * pad - wsh[3] + 1)
+    x, y, act = (pa.raw_desc((1 << 44) + (i << 36), code, dims, ns) for i, (dims, ns) in enumerate(((xs, x_ns), (ys, y_ns), (xs, x_ns))))
+    w = pa.raw_desc((1 << 44) + (3 << 36), code, wsh)
+
+    class Scratch:
+        def __init__(self, n):
+            self.n = n
+
+        def data_ptr(self):
+            return (1 << 45) + 8
+
+        def numel(self):
+            return self.n
+
+        def element_size(self):
+            return 1
+
+    def status(call, *args):
+        with pytest.raises(pa.PurineError) as e:
+            call(*args, 0)
+        return e.value.status
+
+    if groups > 1:
+        q = [Scratch(pa.purine_grouped_conv_workspace_bytes(p, desc, groups, xs, wsh, code)) for p in (0, 1)]
+        got = [status(pa.purine_grouped_conv_fwd, desc, groups, x, w, None, y, False, q[0]),
+               status(pa.purine_grouped_conv_bwd_data, desc, groups, y, w, x, 0.0, q[1])]
+    else:
+        q = [Scratch(pa.purine_conv_workspace_bytes(p, desc, xs, wsh, code)) for p in (0, 1)]
+        got = [status(pa.purine_conv_fwd, desc, x, w, y, q[0]), status(pa.purine_conv_fwd_bias_relu, desc, x, w, None, y, True, q[0]),
+               status(pa.purine_conv_bwd_data, desc, y, w, x, 0.0, q[1]), status(pa.purine_conv_bwd_data, desc, y, w, x, 1.0, q[1]),
+               status(pa.purine_conv_bwd_data_relu, desc, y, w, act, x, 0.0, q[1])]
+    assert got == [-4] * len(got)
+
+
 def test_static_scratch_entry_point_refuses_what_does_not_fit():
     """purine_conv_bwd_weight_static validates like purine_conv_bwd_weight and refuses, before
     any launch, a layer whose partial sums need more than the library's static device array."""

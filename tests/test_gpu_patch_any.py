@@ -77,6 +77,55 @@ def test_every_tile_against_the_oracle(case):
             assert int(torch.isnan(t._base).sum()) == t._base.numel() - t.numel(), "stored outside the slice"
 
 
+# N, C, H, W, K, R, S, stride, pad: filters with a kernel of their own, whose requests run a group or several ahead, and without
+FAR_CASES = [(3, 24, 17, 19, 40, 3, 3, 1, 1), (3, 40, 14, 16, 97, 5, 5, 1, 2), (3, 17, 9, 8, 16, 3, 2, 1, (1, 0)), (3, 33, 28, 28, 130, 3, 3, 2, 1)]
+
+
+@pytest.mark.parametrize("case", FAR_CASES, ids=str)
+def test_images_far_apart(case):
+    """x, y and their gradients as slices whose images lie up to 4 GB apart (spans of almost 2^31 elements, past 2^31 bytes, which
+    no raw buffer addresses): the same bits as from dense tensors, with the scratch of the one query there is."""
+    import torch
+    import paper_1412_6249_amd as pa
+    from gpu_util import to_dev, workspace, DEV
+    N, C, H, W, K, R, S, stride, pad = case
+    P, Q = oracle.out_shape((N, C, H, W), (K, C, R, S), stride, pad)[2:]
+    rs = np.random.default_rng(5)
+    f = lambda *s: to_dev(gen.quantize_bf16(rs.uniform(-1, 1, s).astype(np.float32)), "bf16")
+    x, w, b, dy, act, prev = f(N, C, H, W), f(K, C, R, S), f(K), f(N, K, P, Q), f(N, C, H, W), f(N, C, H, W)
+    desc = pa.conv_desc(stride, pad)
+    ws = [workspace(pa.purine_conv_workspace_bytes(k, desc, x.shape, w.shape, pa.PURINE_BF16)) for k in (0, 1)]
+    flat = [torch.empty(2 ** 31, dtype=torch.bfloat16, device=DEV) for _ in range(3)]
+
+    def far(i, t):
+        ns = (2 ** 31 - t[0].numel() - 1) // (N - 1) // 8 * 8
+        return flat[i].as_strided(t.shape, (ns,) + t.stride()[1:]).copy_(t)
+
+    def run(x, dy, act, out_y, out_dx):
+        y, dx = out_y(torch.zeros_like(dy)), out_dx(torch.zeros_like(x))
+        got = []
+        for relu in (True, False):
+            pa.purine_conv_fwd_bias_relu(desc, x, w, b, y, relu=relu, ws=ws[0])
+            got.append(y.clone())
+        pa.purine_conv_bwd_data(desc, dy, w, dx, ws=ws[1])
+        got.append(dx.clone())
+        dx.copy_(prev)
+        pa.purine_conv_bwd_data(desc, dy, w, dx, beta=1.0, ws=ws[1])
+        got.append(dx.clone())
+        pa.purine_conv_bwd_data_relu(desc, dy, w, act, dx, ws=ws[1])
+        got.append(dx.clone())
+        torch.cuda.synchronize()
+        return [t.contiguous() for t in got]
+
+    same = lambda t: t
+    want = run(x, dy, act, same, same)
+    # far inputs, dense outputs; then far outputs (the ReLU mask has dx's strides)
+    got_in = run(far(0, x), far(1, dy), act, same, same)
+    got_out = run(x, dy, far(1, act), lambda t: far(0, t), lambda t: far(2, t))
+    for name, g, h, r in zip(("relu(y + b)", "y + b", "dx", "dx accumulated", "dx masked"), got_in, got_out, want):
+        assert torch.equal(g, r) and torch.equal(h, r), name
+
+
 def test_rows_too_wide_for_a_patch():
     """264 columns: the one-image kernel."""
     import paper_1412_6249_amd as pa
