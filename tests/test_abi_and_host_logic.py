@@ -269,6 +269,8 @@ FAR_CASES = [
     ("bf16", 1, (64, 16, 55, 55), (32, 16, 3, 3), 1, 0, 20000000),
     ("bf16", 1, (64, 16, 56, 56), (32, 16, 3, 3), 1, 0, 20000000),             # rows of whole packets
     ("bf16", 1, (256, 64, 56, 56), (100, 64, 3, 3), 1, 8000000, 8000000),      # ... and the two-role kernel when dense
+    ("f32", 1, (2, 512, 14, 14), (128, 512, 1, 1), 0, 600000000, 0),
+    ("f32", 1, (2, 512, 14, 14), (128, 512, 1, 1), 0, 0, 600000000),
 ]
 
 
