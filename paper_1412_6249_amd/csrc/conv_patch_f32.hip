@@ -477,7 +477,7 @@ PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s, bool split, int force_
         // 32 rows: filling the patch is most of a group's time, and longer where the patches come from HBM and not the
         // 256 MB last-level cache (3x3, 215 -> 20 channels at 58x58, N = 125, 362 MB: 84 us per tile and 14 groups, tap kernel 504 us,
         // this 574; 113 -> 19 at 46x46, N = 28, 27 MB: 35 us and 8 groups, 69 and 45)
-        const double eff = split && t.bm == 32 && p.in_bytes > (192u << 20) ? 0.34 : t.eff;
+        const double eff = split && t.bm == 32 && (long long)p.N * p.Ci * p.HiWi > (48ll << 20) ? 0.34 : t.eff;
         const long long a_bytes = ti * k.cgs * p.Rt * p.St * t.bm * 64;
         if (a_bytes >= 0x7fffffffLL || ti * tp > 0x7fffffffLL) continue;
         const double x = (double)(ti * tp) / 256.0, ceil_x = (double)((ti * tp + 255) / 256);

@@ -271,6 +271,7 @@ FAR_CASES = [
     ("bf16", 1, (256, 64, 56, 56), (100, 64, 3, 3), 1, 8000000, 8000000),      # ... and the two-role kernel when dense
     ("f32", 1, (2, 512, 14, 14), (128, 512, 1, 1), 0, 600000000, 0),
     ("f32", 1, (2, 512, 14, 14), (128, 512, 1, 1), 0, 0, 600000000),
+    ("f32", 1, (13, 224, 47, 47), (56, 224, 3, 3), 1, 4369064, 0),             # 200 MB, 75 of them the tensor's
 ]
 
 
