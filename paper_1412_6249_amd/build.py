@@ -33,12 +33,16 @@ def _compile(src):
 
 
 def build_marshal():
-    """The native argument marshalling of the Python binding (host code only)."""
+    """The native argument marshalling of the Python binding (host code only).
+
+    NDEBUG: pybind11's headers otherwise bring a thread_local counter, and with it a TLS segment. Loading a module with one
+    makes every access to the thread_locals of libraries loaded before it (this library's and the HIP runtime's, several
+    per launch) take the dynamic linker's slow path: 38.1 instead of 37.1 us for a pass of a single small layer."""
     import sysconfig
     import torch
     tdir = os.path.dirname(torch.__file__)
     out = os.path.join(PKG, "_marshal.so")
-    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-DNDEBUG", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
                            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
                            "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"],
                            "-isystem", os.path.join(tdir, "include"), "-isystem", "/opt/rocm/include",

@@ -22,6 +22,17 @@ def test_hands_back_what_is_not_a_plain_gpu_tensor():
         pa.purine_relu_fwd(None, y, stream=0)
 
 
+def test_has_no_thread_local_storage():
+    """A module with a TLS segment (program header type 7), loaded last, slows the thread_locals of every library loaded before."""
+    import struct
+    from paper_1412_6249_amd import _marshal
+    data = open(_marshal.__file__, "rb").read()
+    assert data[:6] == b"\x7fELF\x02\x01"
+    at, = struct.unpack_from("<Q", data, 32)
+    size, count = struct.unpack_from("<HH", data, 54)
+    assert 7 not in [struct.unpack_from("<I", data, at + i * size)[0] for i in range(count)]
+
+
 @pytest.mark.gpu
 def test_same_call_and_same_refusals_as_the_general_path():
     import ctypes
