@@ -17,6 +17,9 @@ __device__ __forceinline__ uint16_t f2bf(float v) {
 template <typename T> __device__ __forceinline__ float ldf(const T* p, size_t i);
 template <> __device__ __forceinline__ float ldf<float>(const float* p, size_t i) { return p[i]; }
 template <> __device__ __forceinline__ float ldf<uint16_t>(const uint16_t* p, size_t i) { return bf2f(p[i]); }
+template <typename T> __device__ __forceinline__ float val(T v) {
+    if constexpr (sizeof(T) == 2) return bf2f(v); else return v;
+}
 template <typename T> __device__ __forceinline__ void stf(T* p, size_t i, float v);
 template <> __device__ __forceinline__ void stf<float>(float* p, size_t i, float v) { p[i] = v; }
 template <> __device__ __forceinline__ void stf<uint16_t>(uint16_t* p, size_t i, float v) { p[i] = f2bf(v); }
@@ -299,7 +302,8 @@ __global__ __launch_bounds__(TPB) void relu_bwd_kernel(const T* __restrict__ x, 
 // group of `ppw` planes (grid.x: group, grid.y: chunk) (small planes are batched so that every workgroup has a few thousand
 // elements; large planes are split). Outputs are written in memory order (coalesced); the window
 // reads overlap between neighbours and are served by L1. Index arithmetic uses the reciprocal
-// division. These kernels take any window and stride; the common shapes have their own below.
+// division. These kernels take any window and stride; the common ones have kernels of their own below, which leave them the
+// planes whose rows are too wide for LDS: window size and stride are template constants for those (K = 0: runtime).
 constexpr int POOL_CHUNK = 2048;
 
 struct PoolParams {
@@ -308,9 +312,10 @@ struct PoolParams {
     float beta;
 };
 
-template <typename T>
+template <typename T, int K, int S>
 __global__ __launch_bounds__(TPB) void maxpool_fwd_kernel(const T* __restrict__ x, T* __restrict__ y,
                                                           int32_t* __restrict__ arg, const PoolParams pp) {
+    const int k = K ? K : pp.k, st = K ? S : pp.stride;
     const int lim = min(pp.ppw * pp.PQ, ((int)blockIdx.y + 1) * POOL_CHUNK);
     for (int l = blockIdx.y * POOL_CHUNK + threadIdx.x; l < lim; l += TPB) {
         const int pl = fastdiv(l, pp.div_pq);
@@ -318,18 +323,33 @@ __global__ __launch_bounds__(TPB) void maxpool_fwd_kernel(const T* __restrict__ 
         const int nc = blockIdx.x * pp.ppw + pl;
         if (nc >= pp.NC) break;
         const int p = fastdiv(o, pp.div_q), q = o - p * pp.Q;
-        const int h0 = p * pp.stride - pp.pad, w0 = q * pp.stride - pp.pad;
+        const int h0 = p * st - pp.pad, w0 = q * st - pp.pad;
         const T* plane = x + (size_t)nc * pp.HW;
         int best = -1;
         float bv = 0.0f;
-        for (int r = 0; r < pp.k; ++r) {
-            const int h = h0 + r;
-            if ((unsigned)h >= (unsigned)pp.H) continue;
-            for (int c = 0; c < pp.k; ++c) {
-                const int w = w0 + c;
-                if ((unsigned)w >= (unsigned)pp.W) continue;
-                const float v = ldf<T>(plane, (size_t)h * pp.W + w);
-                if (best < 0 || v > bv) { best = h * pp.W + w; bv = v; }
+        if (K) {
+#pragma unroll
+            for (int r = 0; r < (K ? K : 1); ++r)
+#pragma unroll
+                for (int c = 0; c < (K ? K : 1); ++c) {
+                    const int h = h0 + r, w = w0 + c;
+                    const bool ok = ((unsigned)h < (unsigned)pp.H) & ((unsigned)w < (unsigned)pp.W);
+                    const int at = ok ? h * pp.W + w : 0;          // clamped, branch-free
+                    const float v = ldf<T>(plane, at);
+                    const bool take = ok & ((best < 0) | (v > bv));
+                    best = take ? at : best;
+                    bv = take ? v : bv;
+                }
+        } else {
+            for (int r = 0; r < k; ++r) {
+                const int h = h0 + r;
+                if ((unsigned)h >= (unsigned)pp.H) continue;
+                for (int c = 0; c < k; ++c) {
+                    const int w = w0 + c;
+                    if ((unsigned)w >= (unsigned)pp.W) continue;
+                    const float v = ldf<T>(plane, (size_t)h * pp.W + w);
+                    if (best < 0 || v > bv) { best = h * pp.W + w; bv = v; }
+                }
             }
         }
         const size_t out = (size_t)nc * pp.PQ + o;
@@ -343,11 +363,12 @@ __global__ __launch_bounds__(TPB) void maxpool_fwd_kernel(const T* __restrict__ 
 // null): the pooling output of the forward pass; windows whose winner was not positive pass no
 // gradient. When the pooled tensor is a ReLU output that is its ReLU gradient (a position that won
 // a window holds that window's y), which would otherwise be a pass of its own over dx.
-template <typename T>
+template <typename T, int K, int S>
 __global__ __launch_bounds__(TPB) void maxpool_bwd_kernel(const T* __restrict__ dy,
                                                           const int32_t* __restrict__ arg,
                                                           T* dx, const T* __restrict__ y, const PoolParams pp) {
-    const int k = pp.k, st = pp.stride;
+    const int k = K ? K : pp.k, st = K ? S : pp.stride;
+    constexpr int NW = K ? (K + S - 1) / (S ? S : 1) : 1;   // windows per axis that can cover a position
     const int lim = min(pp.ppw * pp.HW, ((int)blockIdx.y + 1) * POOL_CHUNK);
     for (int l = blockIdx.y * POOL_CHUNK + threadIdx.x; l < lim; l += TPB) {
         const int pl = fastdiv(l, pp.div_hw);
@@ -364,12 +385,27 @@ __global__ __launch_bounds__(TPB) void maxpool_bwd_kernel(const T* __restrict__ 
         q_lo = q_lo <= 0 ? 0 : (q_lo + st - 1) / st;
         const size_t obase = (size_t)nc * pp.PQ;
         const size_t at = (size_t)nc * pp.HW + e;
-        float acc = pp.beta != 0.0f ? ldf<T>(dx, at) : 0.0f;
-        for (int p = p_lo; p <= p_hi; ++p)
-            for (int q = q_lo; q <= q_hi; ++q) {
-                const size_t o = obase + p * pp.Q + q;
-                if (arg[o] == e && (!y || ldf<T>(y, o) > 0.0f)) acc += ldf<T>(dy, o);
-            }
+        const float old = pp.beta != 0.0f ? ldf<T>(dx, at) : 0.0f;
+        float acc = old;
+        if (K) {
+#pragma unroll
+            for (int a = 0; a < NW; ++a)
+#pragma unroll
+                for (int b = 0; b < NW; ++b) {
+                    const int p = p_lo + a, q = q_lo + b;
+                    const bool in = (p <= p_hi) & (q <= q_hi);
+                    const int o = in ? p * pp.Q + q : 0;           // clamped, branch-free
+                    const bool hit = in & (arg[obase + o] == e) & (!y || ldf<T>(y, obase + o) > 0.0f);
+                    const float g = ldf<T>(dy, obase + o);
+                    acc += hit ? g : 0.0f;
+                }
+        } else {
+            for (int p = p_lo; p <= p_hi; ++p)
+                for (int q = q_lo; q <= q_hi; ++q) {
+                    const size_t o = obase + p * pp.Q + q;
+                    if (arg[o] == e && (!y || ldf<T>(y, o) > 0.0f)) acc += ldf<T>(dy, o);
+                }
+        }
         stf<T>(dx, at, acc);
     }
 }
@@ -461,14 +497,107 @@ __global__ __launch_bounds__(TPB) void maxpool_bwd_staged_kernel(const T* __rest
     }
 }
 
+// ---- 3x3 / stride 1 / pad 1 pooling on fp32 planes whose width is a multiple of 4 ----------------
+// and too large for the LDS tiles below. A lane owns four consecutive positions of one row:
+// per window row it needs the aligned packet of those four columns plus the column on either side,
+// so 3 packets + 6 scalars replace 36 scalar loads, and the outputs leave as packets. Winners and
+// sums are taken in the same order as in the general kernels (bit-identical results).
+struct Pool3Params {
+    int NC, H, W, HW, W4;      // W4 = W / 4 packets per row
+    FastDiv div_row4, div_w4;  // by H * W4 (packets per plane) and by W4
+    long long total4;          // packets in all
+    float beta;
+};
+
+__global__ __launch_bounds__(TPB) void maxpool3_fwd_vec_kernel(const float* __restrict__ x, float* __restrict__ y,
+                                                               int32_t* __restrict__ arg, const Pool3Params pp) {
+    for (long long i = (long long)blockIdx.x * TPB + threadIdx.x; i < pp.total4; i += (long long)gridDim.x * TPB) {
+        // plane index and packet inside the plane (the host keeps the packet count below 2^31)
+        const int per_plane = pp.H * pp.W4;
+        const int nc = fastdiv((uint32_t)i, pp.div_row4);
+        const int r4 = (int)i - nc * per_plane;
+        const int p = fastdiv(r4, pp.div_w4);
+        const int q0 = (r4 - p * pp.W4) * 4;
+        const float* plane = x + (size_t)nc * pp.HW;
+        float bv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        int best[4] = {-1, -1, -1, -1};
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int h = p - 1 + r;
+            const bool row_ok = (unsigned)h < (unsigned)pp.H;
+            const int hb = (row_ok ? h : p) * pp.W;                 // clamped row: values unused when !row_ok
+            const float4 v4 = *reinterpret_cast<const float4*>(plane + hb + q0);
+            const bool l_ok = row_ok & (q0 > 0), r_ok = row_ok & (q0 + 4 < pp.W);
+            const float vl = plane[hb + (q0 > 0 ? q0 - 1 : q0)];
+            const float vr = plane[hb + (q0 + 4 < pp.W ? q0 + 4 : q0)];
+            const float v[6] = {vl, v4.x, v4.y, v4.z, v4.w, vr};
+            const bool ok[6] = {l_ok, row_ok, row_ok, row_ok, row_ok, r_ok};
+#pragma unroll
+            for (int o = 0; o < 4; ++o)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {                       // window column c of output o is v[o + c]
+                    const bool take = ok[o + c] & ((best[o] < 0) | (v[o + c] > bv[o]));
+                    best[o] = take ? h * pp.W + q0 + o + c - 1 : best[o];
+                    bv[o] = take ? v[o + c] : bv[o];
+                }
+        }
+        const size_t out = (size_t)nc * pp.HW + (size_t)p * pp.W + q0;
+        *reinterpret_cast<float4*>(y + out) = make_float4(bv[0], bv[1], bv[2], bv[3]);
+        *reinterpret_cast<int4*>(arg + out) = make_int4(best[0], best[1], best[2], best[3]);
+    }
+}
+
+__global__ __launch_bounds__(TPB) void maxpool3_bwd_vec_kernel(const float* __restrict__ dy,
+                                                               const int32_t* __restrict__ arg, float* dx,
+                                                               const Pool3Params pp) {
+    for (long long i = (long long)blockIdx.x * TPB + threadIdx.x; i < pp.total4; i += (long long)gridDim.x * TPB) {
+        const int per_plane = pp.H * pp.W4;
+        const int nc = fastdiv((uint32_t)i, pp.div_row4);
+        const int r4 = (int)i - nc * per_plane;
+        const int h = fastdiv(r4, pp.div_w4);
+        const int w0 = (r4 - h * pp.W4) * 4;
+        const size_t base = (size_t)nc * pp.HW;
+        const size_t at = base + (size_t)h * pp.W + w0;
+        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (pp.beta != 0.0f) {
+            const float4 o = *reinterpret_cast<const float4*>(dx + at);
+            acc[0] = o.x; acc[1] = o.y; acc[2] = o.z; acc[3] = o.w;
+        }
+        // windows (p, q) with p in h-1..h+1 and q in w-1..w+1 cover position (h, w); visited in (p, q) order
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int p = h - 1 + r;
+            const bool row_ok = (unsigned)p < (unsigned)pp.H;
+            const size_t rb = base + (size_t)(row_ok ? p : h) * pp.W;
+            const float4 g4 = *reinterpret_cast<const float4*>(dy + rb + w0);
+            const int4 a4 = *reinterpret_cast<const int4*>(arg + rb + w0);
+            const int li = w0 > 0 ? w0 - 1 : w0, ri = w0 + 4 < pp.W ? w0 + 4 : w0;
+            const bool l_ok = row_ok & (w0 > 0), r_ok = row_ok & (w0 + 4 < pp.W);
+            const float g[6] = {dy[rb + li], g4.x, g4.y, g4.z, g4.w, dy[rb + ri]};
+            const int a[6] = {arg[rb + li], a4.x, a4.y, a4.z, a4.w, arg[rb + ri]};
+            const bool ok[6] = {l_ok, row_ok, row_ok, row_ok, row_ok, r_ok};
+#pragma unroll
+            for (int o = 0; o < 4; ++o) {
+                const int e = h * pp.W + w0 + o;                    // this position's index in its plane
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const bool hit = ok[o + c] & (a[o + c] == e);
+                    acc[o] += hit ? g[o + c] : 0.0f;
+                }
+            }
+        }
+        *reinterpret_cast<float4*>(dx + at) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    }
+}
+
 // ---- Pooling by 3x3 / stride 1, 3x3 / stride 2 and 2x2 / stride 2 windows -------------------------
 // Bound: HBM. A workgroup owns whole planes, or a band of rows of one plane: either way what it reads is ONE
 // contiguous run of each tensor, which it copies into LDS as 16-byte packets (tensors start at one), all of a
 // thread's loads of a batch in flight together; rows of any width, and windows overlapping each other, cost no
 // global access of their own. (Gathering from global memory took nine strided loads per window forward, and a
 // look-up of four windows with their index arithmetic per position backward, 60 vector instructions each.)
-// 128 x 96 planes of 55x55 fp32, 3x3 / stride 2: forward 59 -> 37 us, gradient through the ReLU 85 -> 45;
-// 128 x 192 of 28x28, 3x3 / stride 1: 46 -> 41 and 246 -> 62 (unmasked 66 -> 58).
+// 128 x 96 planes of 55x55 fp32 from HBM, 3x3 / stride 2: forward 71 -> 46 us, gradient through the ReLU 94 -> 49;
+// 128 x 192 of 28x28, 3x3 / stride 1: 59 -> 51 and 258 -> 63 (unmasked 78 -> 55).
 struct PoolTile {
     int NC, H, W, P, Q, HW, PQ, pad;
     int planes;                // planes per workgroup (bands == 1)
@@ -578,16 +707,62 @@ __global__ __launch_bounds__(TPB) void maxpool_fwd_tile_kernel(const T* __restri
     }
 }
 
+// 2x2 / stride 2 without padding: windows neither overlap nor leave the plane, so nothing is gained from LDS. A lane takes OW outputs
+// of a row: two 16-byte loads at whatever element they start, one run each of y and arg (64 channels of 112x112, N = 16: 12.4 us,
+// 14.6 through LDS, 13.1 with one output per lane; N = 75: 63, 65, 73).
+template <typename T, int OW>
+__global__ __launch_bounds__(TPB) void maxpool2_fwd_kernel(const T* __restrict__ x, T* __restrict__ y, int32_t* __restrict__ arg,
+                                                           const PoolTile t, const unsigned tasks) {
+    typedef T in_run __attribute__((ext_vector_type(2 * OW), aligned(sizeof(T))));
+    typedef int iw __attribute__((ext_vector_type(OW), aligned(4)));
+    const unsigned l = blockIdx.x * TPB + threadIdx.x;
+    if (l >= tasks) return;
+    const unsigned row = fastdiv(l, t.div_row);                            // of the output, over all planes
+    const int nc = fastdiv(row, t.div_plane), p = row - nc * t.P;
+    const int q0 = (int)(l - row * t.quads) * OW;
+    const T* top = x + (size_t)nc * t.HW + (size_t)(2 * p) * t.W;
+    const size_t out = (size_t)row * t.Q;
+    auto winner = [&](float a, float b, float c, float d, int at, float& v) {
+        int best = at;
+        v = a;
+        if (b > v) { v = b; best = at + 1; }
+        if (c > v) { v = c; best = at + t.W; }
+        if (d > v) { v = d; best = at + t.W + 1; }
+        return best;
+    };
+    if (t.Q >= OW) {
+        const int q = min(q0, t.Q - OW);                                   // the last run of a row starts earlier: some outputs twice
+        const in_run a = *reinterpret_cast<const in_run*>(top + 2 * q), b = *reinterpret_cast<const in_run*>(top + t.W + 2 * q);
+        float v[OW];
+        iw best;
+#pragma unroll
+        for (int w = 0; w < OW; ++w)
+            best[w] = winner(val<T>(a[2 * w]), val<T>(a[2 * w + 1]), val<T>(b[2 * w]), val<T>(b[2 * w + 1]), 2 * p * t.W + 2 * (q + w), v[w]);
+        *reinterpret_cast<iw*>(arg + out + q) = best;
+        store_run<OW>(y + out + q, v);
+    } else {
+        for (int q = 0; q < t.Q; ++q) {
+            float v;
+            arg[out + q] = winner(ldf<T>(top, 2 * q), ldf<T>(top, 2 * q + 1), ldf<T>(top, t.W + 2 * q), ldf<T>(top, t.W + 2 * q + 1), 2 * p * t.W + 2 * q, v);
+            stf<T>(y, out + q, v);
+        }
+    }
+}
+
 // The gradient, gathered: a lane takes a cell of S rows x 4 columns of positions and looks at the windows that
 // cover any of them, winners and gradients in LDS; which window can reach which position is known at compile
 // time. The gradient of a window whose winner was not positive is dropped on its way into LDS (y may be null:
-// no mask). Sums in (p, q) order, as in the kernel above: the same bits.
-template <typename T, int K, int S>
+// no mask). Sums in (p, q) order, as in the kernel above: the same bits. What a workgroup writes is one contiguous run too: PACKETS,
+// it leaves through LDS as aligned packets, because a cell's 16 bytes lie at any element and its two rows apart, and lines
+// stored from the lanes go out in parts (figures at the launch).
+template <typename T, int K, int S, bool PACKETS>
 __global__ __launch_bounds__(TPB) void maxpool_bwd_tile_kernel(const T* __restrict__ dy, const int32_t* __restrict__ arg,
                                                                T* dx, const T* __restrict__ y, const PoolTile t) {
     extern __shared__ __attribute__((aligned(16))) unsigned char pool_smem[];
     int* arg_s = reinterpret_cast<int*>(pool_smem) + t.lead;            // winners; then the gradients, alike
     float* g_s = reinterpret_cast<float*>(pool_smem) + t.plane_s + t.lead;
+    T* out_s = reinterpret_cast<T*>(pool_smem + (size_t)t.plane_s * 8);
+    constexpr int V = Pk<T>::N;
     constexpr int CW = 4, NW = (K + S - 1) / S, NQ = CW / S + NW - 1;
     typedef typename std::conditional<sizeof(T) == 4, float4, ushort4>::type Quad;
     int nc0 = blockIdx.x * t.planes, planes = min(t.planes, t.NC - nc0), c0 = 0, rows = t.cell_rows, p_lo = 0, n = planes * t.PQ;
@@ -640,6 +815,11 @@ __global__ __launch_bounds__(TPB) void maxpool_bwd_tile_kernel(const T* __restri
             g_s[i] = (!sy || ldf<T>(sy, i) > 0.0f) ? ldf<T>(sdy, i) : 0.0f;
         }
     }
+    // the run of dx: whole planes, or the band's rows [h_out, ...)
+    const int h_out = t.bands > 1 ? max(0, c0 * S - t.pad) : 0;
+    const int n_out = t.bands > 1 ? max(0, min(t.H, (c0 + rows) * S - t.pad) - h_out) * t.W : planes * t.HW;
+    const size_t first_out = (size_t)nc0 * t.HW + (size_t)h_out * t.W;
+    const int shift_out = (int)(first_out & (V - 1));
     __syncthreads();
     const int per_plane = rows * t.quads, m = planes * per_plane;
     for (int l = threadIdx.x; l < m; l += TPB) {
@@ -654,9 +834,9 @@ __global__ __launch_bounds__(TPB) void maxpool_bwd_tile_kernel(const T* __restri
         for (int i = 0; i < NW; ++i) {
             const int p = c0 + cr - NW + 1 + i;
             const bool row_in = (unsigned)p < (unsigned)t.P;
-            // a window outside the plane has some other entry's winner and gradient here, or what lies in LDS before
+            // a window outside the plane has some other entry's winner and gradient here, or what lies in LDS just before
             // or behind the staged ones: its winner is replaced by one that no position has
-            const int at = shift + pl * t.PQ + (p - p_lo) * t.Q + q0;
+            const int at = shift + pl * t.PQ + (row_in ? p - p_lo : 0) * t.Q + q0;
 #pragma unroll
             for (int j = 0; j < NQ; ++j) {
                 const int a = arg_s[at + j];
@@ -669,6 +849,7 @@ __global__ __launch_bounds__(TPB) void maxpool_bwd_tile_kernel(const T* __restri
             const int h = h0 + a;
             if ((unsigned)h >= (unsigned)t.H) continue;
             T* row = dx + (size_t)(nc0 + pl) * t.HW + (size_t)h * t.W;
+            T* out = out_s + (shift_out + pl * t.HW + (h - h_out) * t.W);
             float v[CW];
 #pragma unroll
             for (int b = 0; b < CW; ++b) {
@@ -683,15 +864,23 @@ __global__ __launch_bounds__(TPB) void maxpool_bwd_tile_kernel(const T* __restri
                         if (dr < K && dc >= 0 && dc < K) v[b] += win[i][j] == e ? g[i][j] : 0.0f;
                     }
             }
-            if (w0 >= 0 && w0 + CW <= t.W) {
+            if (!PACKETS && w0 >= 0 && w0 + CW <= t.W) {
                 store_run<CW>(row + w0, v);
             } else {
 #pragma unroll
                 for (int b = 0; b < CW; ++b)
-                    if ((unsigned)(w0 + b) < (unsigned)t.W) stf<T>(row, w0 + b, v[b]);
+                    if ((unsigned)(w0 + b) < (unsigned)t.W) stf<T>(PACKETS ? out : row, w0 + b, v[b]);
             }
         }
     }
+    if (!PACKETS) return;
+    __syncthreads();
+    T* dst = dx + (first_out - shift_out);
+    const int end = shift_out + n_out, whole = end / V, head = shift_out ? 1 : 0;
+    for (int i = head + threadIdx.x; i < whole; i += TPB) reinterpret_cast<uint4*>(dst)[i] = reinterpret_cast<const uint4*>(out_s)[i];
+    if (head)
+        for (int i = shift_out + threadIdx.x; i < min(V, end); i += TPB) dst[i] = out_s[i];
+    for (int i = max(whole, head) * V + threadIdx.x; i < end; i += TPB) dst[i] = out_s[i];
 }
 
 // ---- channel-slice copy (concat and its inverse) -------------------------------------------------
@@ -909,26 +1098,28 @@ dim3 pool_grid(const PoolParams& pp, int per_plane) {
     return dim3((unsigned)((pp.NC + pp.ppw - 1) / pp.ppw), (unsigned)((per_group + POOL_CHUNK - 1) / POOL_CHUNK));
 }
 // Splits the planes of a pooling pass over workgroups, for the tile kernels: `run` elements of `size` bytes staged
-// per plane in rows of `row`, `lines` rows of work per plane, of which r need (r - 1) * step + halo staged rows.
-// Several planes share a workgroup while at least 2048 remain (eight per CU) or while they are under 1024 elements in all;
-// a plane beyond `cap` bytes is cut into bands, and so are the planes of a call with less than two workgroups per CU,
-// down to about 512 elements each. False: not even a single row fits.
-bool pool_tile(PoolTile& t, long long run, long long row, int size, int lines, int step, int halo, int cap, size_t* lds) {
-    const long long fit = (cap / (row * size) - halo) / step + 1;          // rows of work that fit
-    if (cap / (row * size) < halo) return false;
-    long long want = (512 + t.NC - 1) / t.NC;
+// per plane in rows of `row`, `lines` rows of work per plane, of which r need (r - 1) * step + halo staged rows and `extra` bytes
+// of LDS each. Several planes share a workgroup while at least 2048 remain (eight per CU) or, while 512 do, while they are under
+// 1024 elements in all; a plane beyond `cap` bytes is cut into bands, and so are the planes of a call with less than `fill`
+// workgroups, down to about 512 elements each. False: not even a single row fits.
+bool pool_tile(PoolTile& t, long long run, long long row, int size, int lines, int step, int halo, long long extra, int fill, int cap, size_t* lds) {
+    const long long line = step * row * size + extra, fixed = (halo - step) * row * size, plane = run * size + lines * extra;
+    const long long fit = (cap - fixed) / line;                             // rows of work that fit
+    if (cap < fixed + line) return false;
+    long long want = (fill + t.NC - 1) / t.NC;
     if (want > run / 512) want = run / 512;
-    if (run * size > cap && want < (lines + fit - 1) / fit) want = (lines + fit - 1) / fit;
+    if (plane > cap && want < (lines + fit - 1) / fit) want = (lines + fit - 1) / fit;
     t.planes = 1; t.bands = 1; t.rows = lines;
     if (want > 1) {
         t.rows = (int)((lines + want - 1) / want);
         t.bands = (lines + t.rows - 1) / t.rows;
     }
     if (t.bands == 1) {
-        if (run * size > cap) return false;
+        if (plane > cap) return false;
         long long planes = t.NC / 2048, few = (1024 + run - 1) / run;
+        if (few > t.NC / 512) few = t.NC / 512;
         if (planes < few) planes = few;
-        if (planes > cap / (run * size)) planes = cap / (run * size);
+        if (planes > cap / plane) planes = cap / plane;
         if (planes > t.NC) planes = t.NC;
         t.planes = planes < 1 ? 1 : (int)planes;
         *lds = (size_t)(t.planes * run * size);
@@ -948,21 +1139,60 @@ bool pool_tile_shape(int k, int stride, int pad, int H, int W, int P, int Q) {
     return ((k == 3 && (stride == 1 || stride == 2)) || (k == 2 && stride == 2)) && pad < k &&
            (long long)(P - 1) * stride - pad < H && (long long)(Q - 1) * stride - pad < W;
 }
+// the packet kernels: fp32, 3x3 / stride 1 / pad 1 (output extents = input extents), rows of whole packets
+bool pool3_vec_applies(int dtype, int NC, int H, int W, int P, int Q, int k, int stride, int pad, const void* a,
+                       const void* b, const void* c) {
+    return dtype == PURINE_F32 && k == 3 && stride == 1 && pad == 1 && P == H && Q == W && W % 4 == 0 &&
+           (long long)NC * H * (W / 4) < 0x7fffffffLL &&
+           (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & 15u) == 0;
+}
+Pool3Params pool3_params(int NC, int H, int W, float beta) {
+    Pool3Params p{};
+    p.NC = NC; p.H = H; p.W = W; p.HW = H * W; p.W4 = W / 4;
+    p.div_w4 = make_fastdiv(p.W4);
+    p.div_row4 = make_fastdiv(H * p.W4);
+    p.total4 = (long long)NC * H * p.W4;
+    p.beta = beta;
+    return p;
+}
 #define POOL_SHAPES(CALL)                                           \
     if (k == 3 && stride == 1) { CALL(3, 1); }                      \
     else if (k == 3) { CALL(3, 2); }                                \
     else { CALL(2, 2); }
+#define POOL_SHAPES_ANY(CALL)                                       \
+    if (pool_tile_shape(k, stride, pad, H, W, P, Q)) { POOL_SHAPES(CALL) }   \
+    else { CALL(0, 0); }
 }  // namespace
 
 hipError_t launch_maxpool_fwd(int dtype, const void* x, void* y, int32_t* arg, int NC, int H, int W,
                               int P, int Q, int k, int stride, int pad, hipStream_t st) {
     // a group of planes is indexed with 32-bit arithmetic; groups go to grid.y
     if ((long long)H * W > 0x3fffffffLL || (long long)P * Q > 0x3fffffffLL) return hipErrorInvalidValue;
+    if (k == 2 && stride == 2 && pad == 0) {
+        PoolTile t = pool_tile_params(NC, H, W, P, Q, stride, pad, 0.0f);
+        const int ow = dtype == PURINE_BF16 && Q >= 4 ? 4 : 2;
+        t.quads = (Q + ow - 1) / ow;
+        t.div_plane = make_fastdiv(P); t.div_row = make_fastdiv(t.quads);
+        const unsigned tasks = (unsigned)((long long)NC * P * t.quads);    // at most one per output: below 2^31
+        const dim3 grid((tasks + TPB - 1) / TPB);
+        ProbeScope probe(st);
+        (void)hipGetLastError();   // drop stale status left by earlier, unrelated runtime calls
+        if (dtype == PURINE_F32)
+            hipLaunchKernelGGL((maxpool2_fwd_kernel<float, 2>), grid, dim3(TPB), 0, st, (const float*)x, (float*)y, arg, t, tasks);
+        else if (ow == 4)
+            hipLaunchKernelGGL((maxpool2_fwd_kernel<uint16_t, 4>), grid, dim3(TPB), 0, st, (const uint16_t*)x, (uint16_t*)y, arg, t, tasks);
+        else
+            hipLaunchKernelGGL((maxpool2_fwd_kernel<uint16_t, 2>), grid, dim3(TPB), 0, st, (const uint16_t*)x, (uint16_t*)y, arg, t, tasks);
+        return hipGetLastError();
+    }
     if (pool_tile_shape(k, stride, pad, H, W, P, Q)) {
         PoolTile t = pool_tile_params(NC, H, W, P, Q, stride, pad, 0.0f);
         size_t lds = 0;
-        // 12 KB: eight workgroups (32 wavefronts) per CU, their loads and arithmetic in each other's shadow (40 KB: 10 - 20 % slower)
-        if (pool_tile(t, t.HW, W, dtype == PURINE_BF16 ? 2 : 4, P, stride, k, 12 * 1024 - 64, &lds)) {
+        // 12 KB: eight workgroups (32 wavefronts) per CU, their loads and arithmetic in each other's shadow (40 KB: 10 - 20 % slower).
+        // Rows too wide for that: 24 KB (3x3 / stride 1 of 1200x1200, 32 planes: 130 us, 173 on the kernel for packets; at 3000
+        // columns the other way round, 21 and 17).
+        for (int cap = 12; cap <= 24; cap += 12) {
+            if (!pool_tile(t, t.HW, W, dtype == PURINE_BF16 ? 2 : 4, P, stride, k, 0, 512, cap * 1024 - 64, &lds)) continue;
             t.quads = (Q + pool_outputs(stride) - 1) / pool_outputs(stride);
             t.div_plane = make_fastdiv(P * t.quads); t.div_row = make_fastdiv(t.quads);
             const dim3 grid((unsigned)((NC + t.planes - 1) / t.planes * t.bands));
@@ -976,15 +1206,26 @@ hipError_t launch_maxpool_fwd(int dtype, const void* x, void* y, int32_t* arg, i
 #undef CALL
             return hipGetLastError();
         }
+        if (pool3_vec_applies(dtype, NC, H, W, P, Q, k, stride, pad, x, y, arg)) {
+            const Pool3Params p3 = pool3_params(NC, H, W, 0.0f);
+            ProbeScope probe(st);
+            (void)hipGetLastError();
+            hipLaunchKernelGGL(maxpool3_fwd_vec_kernel, dim3(blocks_for((size_t)p3.total4)), dim3(TPB), 0, st,
+                               (const float*)x, (float*)y, arg, p3);
+            return hipGetLastError();
+        }
     }
     const PoolParams pp = pool_params(NC, H, W, P, Q, k, stride, pad, P * Q, 0.0f);
     const dim3 grid = pool_grid(pp, P * Q);
     if (grid.y > 65535u) return hipErrorInvalidValue;
     ProbeScope probe(st);
     (void)hipGetLastError();
-    BY_DTYPE(dtype,
-             hipLaunchKernelGGL(maxpool_fwd_kernel<float>, grid, dim3(TPB), 0, st, (const float*)x, (float*)y, arg, pp),
-             hipLaunchKernelGGL(maxpool_fwd_kernel<uint16_t>, grid, dim3(TPB), 0, st, (const uint16_t*)x, (uint16_t*)y, arg, pp));
+#define CALL(K, S)                                                                                              \
+    BY_DTYPE(dtype,                                                                                             \
+             hipLaunchKernelGGL((maxpool_fwd_kernel<float, K, S>), grid, dim3(TPB), 0, st, (const float*)x, (float*)y, arg, pp),       \
+             hipLaunchKernelGGL((maxpool_fwd_kernel<uint16_t, K, S>), grid, dim3(TPB), 0, st, (const uint16_t*)x, (uint16_t*)y, arg, pp))
+    POOL_SHAPES_ANY(CALL)
+#undef CALL
     return hipGetLastError();
 }
 
@@ -1000,25 +1241,48 @@ hipError_t launch_maxpool_bwd(int dtype, const void* dy, const int32_t* arg, voi
         t.cell_rows = (H + pad + stride - 1) / stride;
         t.quads = (W + pad + 3) / 4;
         t.div_plane = make_fastdiv(t.cell_rows * t.quads); t.div_row = make_fastdiv(t.quads);
-        // a cell reaches up to nw - 1 rows and columns before the staged windows, as many columns behind a row's end, and
-        // a row of cells past the last row of windows
-        t.lead = ((nw - 1) * (Q + 1) + 3) / 4 * 4;
-        const long long tail = (t.cell_rows >= P ? (long long)(t.cell_rows - P + 1) * Q : 0) + 4LL * t.quads + 8;
-        // 8 bytes per window: 12 KB, eight workgroups per CU (32 KB: 10 - 25 % slower)
-        if (t.lead + tail < 3000 && pool_tile(t, t.PQ, Q, 8, t.cell_rows, 1, nw, 12 * 1024 - 64, &lds)) {
+        // a cell reaches up to nw - 1 columns before a row's first window and some behind its last
+        t.lead = (nw - 1 + 3) / 4 * 4;
+        const int behind = 4 * t.quads / stride - Q, tail = (behind > 0 ? behind : 0) + 4;
+        // dx leaves through LDS where a cell's two rows of four positions are not aligned, and in fp32 beyond the last-level cache
+        // (64 channels, masked, us stored from the lanes / through LDS: 3x3 fp32 14x14 179 / 67 at N = 4783, 21 / 11 at 478;
+        // 2x2 fp32 28x28 101 / 74 at 1196, 9.9 / 9.7 at 120; 112x112 79 / 75 at 75, 9.0 / 9.3 at 7; 2x2 bf16 112x112 47 / 52 at 75).
+        // Stride 1 leaves no gaps between a wavefront's rows (bf16 28x28, N = 120: 19.6 / 21.8).
+        const bool packets = stride == 2 && (((W | pad) & 3) || (dtype == PURINE_F32 && (long long)NC * t.HW >= 16 << 20));
+        const long long extra = packets ? (long long)stride * W * elem : 0;
+        // 12 KB, or 20 with dx: eight workgroups per CU (32 KB of windows: 10 - 25 % slower). Rows too wide for that take more while
+        // two workgroups per CU are left (3x3 / stride 1 of 600x600, 64 planes: 130 us, 273 on the gathering kernel), but not where
+        // the kernel for packets does as well (1200x1200, 32 planes: 227 us, 199 there).
+        const int caps[2][3] = {{12, 24, 40}, {20, 40, 60}};
+        // bands of few planes: two workgroups per CU; eight where a position looks at nine windows (448 planes of 56x56: 9.4 / 8.5 us)
+        const int fill = stride == 1 ? 2048 : 512;
+        for (int c = 0; c < 3 && !(c > 0 && !y && pool3_vec_applies(dtype, NC, H, W, P, Q, k, stride, pad, dy, dx, arg)); ++c) {
+            if (!pool_tile(t, t.PQ, Q, 8, t.cell_rows, 1, nw, extra, fill, caps[packets][c] * 1024 - 160, &lds)) continue;
+            if (c > 0 && (long long)NC * t.bands < 512) break;
             t.plane_s = (int)((lds / 8 + t.lead + tail + 3) / 4 * 4);
             lds = (size_t)t.plane_s * 8;
+            if (packets) lds += ((size_t)(t.bands > 1 ? t.rows * extra : (long long)t.planes * t.HW * elem) + 47) / 16 * 16;
             const dim3 grid((unsigned)((NC + t.planes - 1) / t.planes * t.bands));
             ProbeScope probe(st);
             (void)hipGetLastError();
-#define CALL(K, S)                                                                                              \
+#define CALL1(K, S, PACKETS)                                                                                    \
     BY_DTYPE(dtype,                                                                                             \
-             hipLaunchKernelGGL((maxpool_bwd_tile_kernel<float, K, S>), grid, dim3(TPB), lds, st, (const float*)dy, arg, (float*)dx, (const float*)y, t),     \
-             hipLaunchKernelGGL((maxpool_bwd_tile_kernel<uint16_t, K, S>), grid, dim3(TPB), lds, st, (const uint16_t*)dy, arg, (uint16_t*)dx, (const uint16_t*)y, t))
+             hipLaunchKernelGGL((maxpool_bwd_tile_kernel<float, K, S, PACKETS>), grid, dim3(TPB), lds, st, (const float*)dy, arg, (float*)dx, (const float*)y, t),     \
+             hipLaunchKernelGGL((maxpool_bwd_tile_kernel<uint16_t, K, S, PACKETS>), grid, dim3(TPB), lds, st, (const uint16_t*)dy, arg, (uint16_t*)dx, (const uint16_t*)y, t))
+#define CALL(K, S) if (S == 2 && packets) { CALL1(K, S, S == 2); } else { CALL1(K, S, false); }
             POOL_SHAPES(CALL)
 #undef CALL
+#undef CALL1
             return hipGetLastError();
         }
+    }
+    if (!y && pool3_vec_applies(dtype, NC, H, W, P, Q, k, stride, pad, dy, dx, arg)) {
+        const Pool3Params p3 = pool3_params(NC, H, W, beta);
+        ProbeScope probe(st);
+        (void)hipGetLastError();
+        hipLaunchKernelGGL(maxpool3_bwd_vec_kernel, dim3(blocks_for((size_t)p3.total4)), dim3(TPB), 0, st,
+                           (const float*)dy, arg, (float*)dx, p3);
+        return hipGetLastError();
     }
     PoolParams pp = pool_params(NC, H, W, P, Q, k, stride, pad, H * W, beta);
     // Whole planes per workgroup with their arg and dy planes in LDS: up to about 8K positions per
@@ -1049,9 +1313,12 @@ hipError_t launch_maxpool_bwd(int dtype, const void* dy, const int32_t* arg, voi
     if (grid.y > 65535u) return hipErrorInvalidValue;
     ProbeScope probe(st);
     (void)hipGetLastError();   // drop stale status left by earlier, unrelated runtime calls
-    BY_DTYPE(dtype,
-             hipLaunchKernelGGL(maxpool_bwd_kernel<float>, grid, dim3(TPB), 0, st, (const float*)dy, arg, (float*)dx, (const float*)y, pp),
-             hipLaunchKernelGGL(maxpool_bwd_kernel<uint16_t>, grid, dim3(TPB), 0, st, (const uint16_t*)dy, arg, (uint16_t*)dx, (const uint16_t*)y, pp));
+#define CALL(K, S)                                                                                              \
+    BY_DTYPE(dtype,                                                                                             \
+             hipLaunchKernelGGL((maxpool_bwd_kernel<float, K, S>), grid, dim3(TPB), 0, st, (const float*)dy, arg, (float*)dx, (const float*)y, pp),     \
+             hipLaunchKernelGGL((maxpool_bwd_kernel<uint16_t, K, S>), grid, dim3(TPB), 0, st, (const uint16_t*)dy, arg, (uint16_t*)dx, (const uint16_t*)y, pp))
+    POOL_SHAPES_ANY(CALL)
+#undef CALL
     return hipGetLastError();
 }
 

@@ -1,5 +1,6 @@
 """Max pooling staged in LDS: whole planes per workgroup, planes cut into bands of rows (too large for LDS, or too
-few to fill the chip), runs that start and end inside a packet, windows at the planes' edges, infinities and NaN. Against the oracle, bit for bit."""
+few to fill the chip), runs that start and end inside a packet, gradients stored from the lanes and through LDS, rows of any width,
+2x2 windows straight from memory, windows at the planes' edges, infinities and NaN. Against the oracle, bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -16,9 +17,19 @@ CASES = [
     (1, 150, 149, 3, 1, 1),     # bands both ways
     (3, 97, 101, 2, 2, 0),      # few planes: bands although a plane fits
     (1, 9, 2000, 3, 2, 1),      # a handful of rows, one or two per band
-    (1, 4, 9000, 3, 1, 1),      # rows that fit no workgroup: the general kernels
+    (130, 6, 700, 3, 1, 1),     # rows that need more LDS; unmasked fp32 gradient: the kernel for packets
+    (130, 6, 2001, 3, 2, 1),
+    (3, 4, 2100, 3, 1, 1),      # rows that need too much: the general kernels, and in fp32 the one for packets
+    (1, 4, 9001, 3, 1, 1),
+    (1, 5, 9001, 3, 2, 0),
+    (2, 3, 9001, 2, 2, 0),
     (2061, 7, 7, 3, 2, 1),      # several planes per workgroup, the last one not full
     (2500, 3, 5, 2, 2, 0),
+    (300, 6, 11, 2, 2, 0),      # 2x2 forward: the last run of a row starts earlier; rows of three outputs and of one; padding
+    (700, 4, 7, 2, 2, 0),
+    (700, 5, 3, 2, 2, 0),
+    (60, 9, 10, 2, 2, 1),
+    (21500, 28, 28, 2, 2, 0),   # an fp32 gradient of aligned rows that leaves through LDS for its size
     (700, 13, 1, 3, 1, 1),
     (4099, 1, 2, 3, 2, 1),
 ]
