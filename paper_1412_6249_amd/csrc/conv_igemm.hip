@@ -25,6 +25,7 @@
 // MFMA operand roles: A rows = channels i, B columns = pixels, so each accumulator register holds
 // 32 consecutive pixels of one channel and the NCHW stores are 128-byte coalesced.
 #include "pix_common.h"
+#include <cmath>
 
 namespace purine {
 namespace {
@@ -624,6 +625,16 @@ static PixParams make_pix_params(int dtype, const ConvGeom& g, const PixPlan& pl
     return p;
 }
 
+// Expected time of a bf16 layer on the blocked copy: copy, filter repack, slabs of 32 channels of a tap. Fitted to 11853 passes
+// (R and S of 1 - 7, stride 1 - 3, 7 - 256 pixels a side, 16 - 512 channels, 1 - 256 images): within 0.87 - 1.12 of
+// the measured time in nine of ten. The kernels that it is compared with have fits of their own on the same layers.
+static double blocked_us(const PixParams& p, const PixPlan& pl) {
+    const double m = (double)pl.tiles_i * pl.tiles_pix / 256.0, area = pl.bm * pl.bn / 1024.0, slabs = pl.Ci_pad / 32 * (double)(pl.Rt * pl.St);
+    const double in_mb = 2e-6 * p.N * p.HiWi * (double)(p.Ci + pl.Ci_pad), out_mb = 2e-6 * p.M * (double)p.Co;
+    const double filter_mb = 2e-6 * pl.Rt * pl.St * pl.Ci_pad * (double)pl.i_pad;
+    return 8.5 + 0.295 * slabs + 0.0143 * slabs * std::ceil(m) * area + 0.28 * in_mb + 0.333 * out_mb + 2.48 * filter_mb + (pl.mode == 2 ? 0.214 * m * area : 0.0);
+}
+
 PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, bool accumulate) {
     PixPlan pl{};
     const int elem = dtype == PURINE_BF16 ? 2 : 4;
@@ -720,19 +731,36 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
         PatchGeom q;
         pl.patch = plan_patch_bf16(probe, pl.mode, &q);
         if (pl.patch) pl.ws_bytes = patch_filter_bytes(Co, Ci, pl.Rt * pl.St);
-        // The two-role kernel where it applies (a thousand tiles of whole four-pixel groups or more: 64 -> 192 channels 3x3
-        // at 56x56, N = 256 forward 198 us, 235 on the kernel for rows of any width); else that one, which the
-        // one-role kernel was behind on every layer of whole packets timed (128 -> 128 at 16x16, N = 64: 25.5 against 16.5 us;
-        // 48 -> 96 5x5 at 40x40, N = 32 backward-data: 38 against 28.5) and is left the rows too wide for its patch.
+        // Which kernel a layer takes follows from its extents alone, as the scratch query does. (A view that the one-image kernel
+        // cannot address takes the one for rows of any width, whose filter copy the scratch holds too.)
+        ConvGeom dense = g;
+        dense.x_ns = g.C * g.H * g.W; dense.y_ns = g.K * g.P * g.Q;
+        bool patch_dense = pl.patch;
+        if (!pl.patch && (g.x_ns != dense.x_ns || g.y_ns != dense.y_ns)) {
+            probe = make_pix_params(dtype, dense, pl);
+            patch_dense = plan_patch_bf16(probe, pl.mode, &q);
+        }
         // (A layer whose copy for the kernel below would have 2^31 bytes or more is refused, whatever would run.)
         const bool copy_fits = (size_t)g.N * pl.Ci_pad * (bwd_data ? (size_t)g.P * g.Q : (size_t)g.H * g.W) * elem < 0x7fffffffull;
-        if ((pl.patch || copy_fits) && (((g_force_bm == 0 || patch_split_roles_forced()) && !g_no_buffer_loads && !(pl.patch && q.roles)) || patch_any_forced())) {
-            pl.pa = plan_patch_any(make_pix_params(dtype, g, pl), pl.mode, patch_any_forced() ? g_force_bn : 0);
-            if (pl.pa.use) {
+        const bool two_roles = pl.patch && q.roles;
+        if ((patch_dense || copy_fits) && (((g_force_bm == 0 || patch_split_roles_forced()) && !g_no_buffer_loads && !two_roles) || patch_any_forced())) {
+            const PixParams pd = make_pix_params(dtype, dense, pl);
+            pl.pa = plan_patch_any(pd, pl.mode, patch_any_forced() ? g_force_bn : 0);
+            // The two-role kernel where it applies (a thousand tiles of whole four-pixel groups or more: 64 -> 192 channels 3x3
+            // at 56x56, N = 256 forward 198 us, 235 on the kernel for rows of any width); else that one where it is expected to
+            // be faster than what would run without it, with a twentieth to spare, or more where its tile was chosen outside the
+            // sizes that its tiles were timed at (rows of more than 66 pixels, filters that it has no kernel of its own for). Slower by a
+            // tenth or more than that in 0.4 % of the fitted passes (taken wherever it applies: in 9 %, down to a quarter of
+            // the speed), and all of them together 1.32 times as fast (1.31).
+            const double margin = pl.pa.rt && pd.Wi <= 66 ? 0.95 : 0.88;
+            const bool faster = pl.pa.use && !(patch_dense && q.roles) &&
+                                pl.pa.us < margin * (patch_dense ? patch_bf16_us(probe, q, pl.mode) : blocked_us(pd, pl));
+            if (pl.pa.use && (faster || patch_any_forced() || (patch_dense && !pl.patch))) {
                 pl.patch = false;
-                pl.ws_bytes = pl.pa.a_bytes;
+                pl.ws_bytes = patch_dense && !faster && !patch_any_forced() ? patch_filter_bytes(Co, Ci, pl.Rt * pl.St) : pl.pa.a_bytes;
                 return pl;
             }
+            pl.pa.use = false;
         }
     }
     if (dtype == PURINE_BF16 && !pl.flat && pl.Rt * pl.St > 1 && !pl.patch) {

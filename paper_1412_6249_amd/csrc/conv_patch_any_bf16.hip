@@ -670,6 +670,22 @@ PatchAnyPlan plan_patch_any(const PixParams& p, int mode, int force) {
         k.use = true;
         if (!best.use || k.us < best.us) best = k;
     }
+    // The tile is chosen; what it takes in all, for the comparison with the other kernels: `waves` rounds of as many workgroups as
+    // a CU holds. Fitted to 16137 passes, half of them with other filters (their taps' loop is not unrolled), rows of up to 256
+    // pixels and launches of up to 1.2 TFLOP among them: within 0.84 - 1.11 of the measured time in nine of ten.
+    if (best.use) {
+        int resident = 1;
+        for (const AnyTileCost& t : kAnyTiles)
+            if (t.bm == best.bm && t.bn == best.bn && t.ahead == best.ahead) resident = t.resident;
+        const int by_lds = 160 * 1024 / best.lds, fit = by_lds < resident ? by_lds : resident;
+        const double m = (double)best.tiles_i * best.tiles_pix / 256.0, waves = std::ceil(m / fit), out_mb = 2e-6 * p.M * (double)p.Co;
+        const double groups = best.cgs, steps = groups * best.taps, area = best.bm * best.bn / 1024, fills = groups * std::ceil(m) * best.rounds;
+        if (best.rt)
+            best.us = 4.8 + 0.356 * best.us + waves * steps * (0.0176 + 0.00387 * area) + 0.25 * fills + (mode == 2 ? 0.506 : 0.338) * out_mb;
+        else
+            best.us = 6.5 + 0.043 * best.us + waves * (steps * (0.0517 + 0.00482 * area) + 0.341 * groups * best.stages) + 0.361 * fills +
+                      (mode == 2 ? 0.517 : 0.342) * out_mb;
+    }
     return best;
 }
 

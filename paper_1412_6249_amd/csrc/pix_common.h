@@ -599,6 +599,7 @@ struct PatchGeom {
 };
 bool plan_patch_bf16(PixParams& p, int mode, PatchGeom* q);
 size_t patch_filter_bytes(int Co, int Ci, int n_taps);
+double patch_bf16_us(const PixParams& p, const PatchGeom& q, int mode);      // of a geometry that plan_patch_bf16 has filled in
 hipError_t repack_patch_filter(const PixParams& p, int mode, const void* w, void* a, int K, int C, hipStream_t st);
 hipError_t launch_patch_bf16(const PixParams& p, const PatchGeom& q, int mode, hipStream_t st);
 // bf16 layers with several taps, rows of any width (conv_patch_any_bf16.hip); mode as above, w: the KCRS filter, repacked

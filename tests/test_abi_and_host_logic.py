@@ -269,6 +269,7 @@ FAR_CASES = [
     ("bf16", 1, (64, 16, 55, 55), (32, 16, 3, 3), 1, 0, 20000000),
     ("bf16", 1, (64, 16, 56, 56), (32, 16, 3, 3), 1, 0, 20000000),             # rows of whole packets
     ("bf16", 1, (256, 64, 56, 56), (100, 64, 3, 3), 1, 8000000, 8000000),      # ... and the two-role kernel when dense
+    ("bf16", 1, (13, 64, 152, 152), (96, 64, 3, 3), 1, 120000000, 120000000),  # ... and the one-image kernel
     ("f32", 1, (2, 512, 14, 14), (128, 512, 1, 1), 0, 600000000, 0),
     ("f32", 1, (2, 512, 14, 14), (128, 512, 1, 1), 0, 0, 600000000),
     ("f32", 1, (13, 224, 47, 47), (56, 224, 3, 3), 1, 4369064, 0),             # 200 MB, 75 of them the tensor's
@@ -314,6 +315,28 @@ def test_scratch_of_the_query_is_enough_whatever_the_strides(case):
                status(pa.purine_conv_bwd_data, desc, y, w, x, 0.0, q[1]), status(pa.purine_conv_bwd_data, desc, y, w, x, 1.0, q[1]),
                status(pa.purine_conv_bwd_data_relu, desc, y, w, act, x, 0.0, q[1])]
     assert got == [-4] * len(got)
+
+
+# x, w, stride, pad, the passes that leave the blocked copy for the patch kernel for rows of any width
+ROUTES = [
+    ((128, 96, 28, 28), (128, 96, 3, 3), 1, 1, (True, True)),
+    ((64, 128, 15, 15), (128, 128, 3, 3), 1, 1, (True, True)),
+    ((29, 75, 29, 31), (150, 75, 5, 5), 1, 2, (True, True)),
+    ((56, 19, 58, 58), (27, 19, 7, 7), 1, 3, (False, False)),         # no kernel of its own: 79 us there, 49 on the copy
+    ((13, 60, 151, 151), (96, 60, 3, 3), 1, 1, (False, False)),       # wide rows: 130 and 81 us
+    ((54, 201, 39, 41), (29, 201, 3, 3), 1, 1, (True, False)),        # backward-data 65 and 44 us
+    ((8, 492, 28, 30), (445, 492, 3, 1), 1, (1, 0), (False, False)),
+]
+
+
+@pytest.mark.parametrize("case", ROUTES, ids=[str(c[:2]).replace(" ", "") for c in ROUTES])
+def test_bf16_layers_take_the_copy_where_it_is_faster(case):
+    xs, wsh, stride, pad, direct = case
+    desc = pa.conv_desc(stride, pad)
+    ys = pa.purine_conv_out_shape(desc, xs, wsh)
+    for which, gathered in ((0, xs), (1, ys)):
+        copy = 2 * gathered[0] * gathered[1] * gathered[2] * gathered[3]
+        assert (pa.purine_conv_workspace_bytes(which, desc, xs, wsh, pa.PURINE_BF16) < copy) == direct[which], which
 
 
 def test_static_scratch_entry_point_refuses_what_does_not_fit():
