@@ -1245,7 +1245,7 @@ hipError_t launch_maxpool_bwd(int dtype, const void* dy, const int32_t* arg, voi
         t.lead = (nw - 1 + 3) / 4 * 4;
         const int behind = 4 * t.quads / stride - Q, tail = (behind > 0 ? behind : 0) + 4;
         // dx leaves through LDS where a cell's two rows of four positions are not aligned, and in fp32 beyond the last-level cache
-        // (64 channels, masked, us stored from the lanes / through LDS: 3x3 fp32 14x14 179 / 67 at N = 4783, 21 / 11 at 478;
+        // (64 channels, masked, us stored from the lanes / through LDS: 3x3 fp32 14x14 179 / 78 at N = 4783, 21 / 11 at 478;
         // 2x2 fp32 28x28 101 / 74 at 1196, 9.9 / 9.7 at 120; 112x112 79 / 75 at 75, 9.0 / 9.3 at 7; 2x2 bf16 112x112 47 / 52 at 75).
         // Stride 1 leaves no gaps between a wavefront's rows (bf16 28x28, N = 120: 19.6 / 21.8).
         const bool packets = stride == 2 && (((W | pad) & 3) || (dtype == PURINE_F32 && (long long)NC * t.HW >= 16 << 20));
