@@ -257,7 +257,7 @@ hipError_t by_tile(const PixParams& p, const Split1x1Params& q, int tm, hipStrea
 }  // namespace
 
 // Whether and how the layer runs here. Pure host arithmetic. force: test hook, row tiles (1, 2), or 0.
-Split1x1Plan plan_gemm1x1_split(const PixParams& p, bool forced, int force) {
+Split1x1Plan plan_gemm1x1_split(const PixParams& p, bool fwd, bool forced, int force) {
     Split1x1Plan k{};
     if (p.Rt * p.St != 1 || p.in_bytes == 0 || p.out_bytes == 0 || p.g_add_h != 0 || p.g_add_w != 0 || p.M > 0x7fffff00 || (long long)p.Co * p.Ci > 0x1fffffffLL) return k;
     k.cgs = (p.Ci + 15) / 16;
@@ -286,7 +286,14 @@ Split1x1Plan plan_gemm1x1_split(const PixParams& p, bool forced, int force) {
     // CUs that those hold (inception module of 128 images 1017 and 1046 us, of 50, 57 MB, 534 and 547). And not outputs that dwarf the input: a row's 128 bytes per
     // strip, at any alignment, leave two partial lines each, where gemm1x1_kernel writes 512 in one go (16 -> 300
     // at 62x62, N = 256: 332 us there, 554 here).
-    k.use = forced || in_mb + out_mb < 32.0 || (p.Ci >= 224 && out_mb < 3.0 * in_mb);
+    // Within that, not where the workgroups of a dozen or more row tiles leave a wavefront strips of over 60 steps in all, one
+    // workgroup per CU (555 -> 575 at 27x27, N = 18 forward 94 us there, 130 here; 75 such passes: 0.93 of the speed together), not
+    // forward passes of up to 32 channels (32 -> 97 at 46x46, N = 13: 8.2 and 9.7; 463 passes: 1.02), and not large strided gathers
+    // (453 -> 362, stride 2 at 60x62, N = 5: 31 and 44). The 5600 other passes that were timed: 1.2 times as fast.
+    const long long chain = (long long)(k.strips + k.groups * k.waves - 1) / (k.groups * k.waves) * k.cgs;
+    const bool strided = p.g_mul_h > 1 || p.g_mul_w > 1;
+    const bool slower = (k.groups <= 16 && chain > 60) || (fwd && k.cgs <= 2);
+    k.use = forced || (!slower && (in_mb + out_mb < 32.0 || (!strided && p.Ci >= 224 && out_mb < 3.0 * in_mb)));
     return k;
 }
 

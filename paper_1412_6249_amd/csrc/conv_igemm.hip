@@ -817,7 +817,7 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
     if (dtype == PURINE_F32 && pl.mode != 2 && pl.Rt * pl.St == 1 && !pl.flat && g_no_buffer_loads == 0 && (g_force_bm == 0 || split_1x1_forced())) {
         // (it needs no scratch; the plan goes on to what the streaming kernel needs, which tensors of 2^31 bytes and more run on:
         // the query has to answer for any strides)
-        pl.ps = plan_gemm1x1_split(make_pix_params(dtype, g, pl), split_1x1_forced(), split_1x1_forced() ? g_force_bn : 0);
+        pl.ps = plan_gemm1x1_split(make_pix_params(dtype, g, pl), pl.mode == 0, split_1x1_forced(), split_1x1_forced() ? g_force_bn : 0);
     }
     // identity gather: the streaming GEMM applies
     const long long HW = (long long)g.H * g.W;

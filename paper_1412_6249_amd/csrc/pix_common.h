@@ -629,7 +629,7 @@ hipError_t dispatch_flat_bf16(PixParams& p, int bm, int bn, hipStream_t st);
 hipError_t dispatch_gemm1x1(const PixParams& p, int dtype, bool trans, int tm, int tn, hipStream_t st);
 
 // fp32 1x1 layers on bf16 parts split in registers (conv_gemm1x1_split.hip); w: the KCRS filter. No scratch.
-Split1x1Plan plan_gemm1x1_split(const PixParams& p, bool forced, int force);
+Split1x1Plan plan_gemm1x1_split(const PixParams& p, bool fwd, bool forced, int force);
 hipError_t launch_gemm1x1_split(PixParams p, const Split1x1Plan& k, bool trans, const void* w, hipStream_t st);
 // fp32 layers with a unit-stride gather on bf16 parts split in LDS (conv_patch_f32.hip); mode and w as
 // below. launch_patch_f32 repacks the filter (fp32) into ws.

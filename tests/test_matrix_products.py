@@ -32,6 +32,16 @@ def test_forward_passes_of_long_sums_depend_on_the_launch():
     assert (f(128, 384), f(2, 384), f(128, 227), f(128, 228)) == (1, 6, 6, 1)
 
 
+@pytest.mark.parametrize("n, c, hw, k, stride, want", [
+    (8, 128, 28, 128, 1, (6, 6)), (64, 256, 27, 256, 1, (6, 6)), (64, 96, 54, 96, 1, (1, 1)),
+    (18, 555, 27, 575, 1, (1, 1)),       # many row tiles, one workgroup per CU: slower on parts
+    (13, 32, 46, 97, 1, (1, 6)),         # two groups of channels forward
+    (30, 251, 60, 189, 2, (1, 1)), (5, 60, 17, 29, 2, (6, 1))])
+def test_1x1_layers(n, c, hw, k, stride, want):
+    d = pa.conv_desc(stride, 0)
+    assert tuple(pa.purine_conv_matrix_products(p, d, (n, c, hw, hw), (k, c, 1, 1), pa.PURINE_F32) for p in (FWD, BWD_DATA)) == want
+
+
 def test_illegal_shapes_and_passes_give_zero():
     d = pa.conv_desc(1, 0)
     assert pa.purine_conv_matrix_products(FWD, d, (1, 3, 2, 2), (4, 3, 3, 3), pa.PURINE_F32) == 0
