@@ -67,6 +67,7 @@ if not os.path.exists(LIB_PATH):
                       "g.build()'` (or paper_1412_6249_amd/build.py) first")
 _lib = ctypes.CDLL(LIB_PATH)
 from . import _marshal  # noqa: E402  (links against the libraries loaded above)
+_marshal.descriptor_types(purine_conv_desc, purine_pool_desc)
 
 _P = ctypes.POINTER
 _T, _D, _PD = _P(purine_tensor), _P(purine_conv_desc), _P(purine_pool_desc)

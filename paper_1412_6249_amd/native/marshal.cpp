@@ -5,8 +5,9 @@
 // 10, more than its launches: most small layers were bound by it. Here an argument costs tens of nanoseconds.
 //
 // Every function takes its entry point's arguments in the C order (scratch and its size as one argument) and returns the
-// status, or None for any argument that is not the plain case (a descriptor made by hand, another kind of object, a
-// tensor that the operators refuse): the caller then takes the general path, which says what is wrong.
+// status, or None for any argument that is not the plain case (a tensor's descriptor made by hand, another kind of object, a
+// tensor that the operators refuse): the caller then takes the general path, which says what is wrong. Convolution and
+// pooling descriptors are instances of the two ctypes structures that descriptor_types() is given, as ctypes itself asks.
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
@@ -40,6 +41,10 @@ struct Call {
         return args[next++];
     }
 };
+
+PyTypeObject* descriptor_type[2] = {nullptr, nullptr};     // purine_conv_desc, purine_pool_desc
+
+bool is_descriptor(PyObject* o, int which) { return descriptor_type[which] && PyObject_TypeCheck(o, descriptor_type[which]); }
 
 bool fill(purine_tensor& d, PyObject* o) {
     if (!THPVariable_Check(o)) return false;
@@ -76,8 +81,9 @@ A take(Call& c) {
         return &c.t[i];
     } else if constexpr (std::is_same_v<A, const purine_conv_desc*> || std::is_same_v<A, const purine_pool_desc*>) {
         PyObject* o = c.arg();
-        if (!c.ok || PyObject_GetBuffer(o, &c.desc, PyBUF_SIMPLE) != 0) { PyErr_Clear(); c.ok = false; return nullptr; }
-        if (c.desc.len != (Py_ssize_t)sizeof(std::remove_pointer_t<A>)) c.ok = false;
+        constexpr int which = std::is_same_v<A, const purine_pool_desc*> ? 1 : 0;
+        if (!c.ok || !is_descriptor(o, which) || PyObject_GetBuffer(o, &c.desc, PyBUF_SIMPLE) != 0) { PyErr_Clear(); c.ok = false; return nullptr; }
+        if (c.desc.len < (Py_ssize_t)sizeof(std::remove_pointer_t<A>)) c.ok = false;
         return (A)c.desc.buf;
     } else if constexpr (std::is_same_v<A, float>) {
         PyObject* o = c.arg();
@@ -122,9 +128,11 @@ PyObject* invoke(int (*fn)(A...), PyObject* const* args, Py_ssize_t n, unsigned 
         c.optional = optional;
         std::tuple<A...> a{take<A, POINTERS>(c)...};                    // (braces: in order)
         if (!c.ok || c.next != n) Py_RETURN_NONE;
+        // (noexcept: an exception out of a C entry ends the program, as from ctypes; it must not be taken for "not the plain case")
+        auto call = [&]() noexcept { return std::apply(fn, a); };
         int rc;
         Py_BEGIN_ALLOW_THREADS
-        rc = std::apply(fn, a);
+        rc = call();
         Py_END_ALLOW_THREADS
         return PyLong_FromLong(rc);
     } catch (const std::exception&) {
@@ -144,8 +152,34 @@ PyObject* invoke(int (*fn)(A...), PyObject* const* args, Py_ssize_t n, unsigned 
     X(purine_maxpool_fwd, 0) X(purine_maxpool_bwd, 0) X(purine_maxpool_bwd_relu, 0)
 ENTRIES(ENTRY)
 
+PyObject* descriptor_types(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    if (n != 2 || !PyType_Check(args[0]) || !PyType_Check(args[1])) {
+        PyErr_SetString(PyExc_TypeError, "descriptor_types(purine_conv_desc, purine_pool_desc)");
+        return nullptr;
+    }
+    for (int i = 0; i < 2; ++i) {
+        Py_INCREF(args[i]);
+        Py_XDECREF((PyObject*)descriptor_type[i]);
+        descriptor_type[i] = (PyTypeObject*)args[i];
+    }
+    Py_RETURN_NONE;
+}
+
+// whether a convolution (0) or pooling (1) call would take the object as its descriptor
+PyObject* takes_descriptor(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    const long which = n == 2 ? PyLong_AsLong(args[1]) : -1;
+    if (which != 0 && which != 1) {
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "takes_descriptor(object, 0 or 1)");
+        return nullptr;
+    }
+    return PyBool_FromLong(is_descriptor(args[0], (int)which));
+}
+
 #define METHOD(NAME, OPTIONAL) {#NAME, (PyCFunction)(void (*)(void))&call_##NAME, METH_FASTCALL, nullptr},
-PyMethodDef methods[] = {ENTRIES(METHOD){nullptr, nullptr, 0, nullptr}};
+PyMethodDef methods[] = {ENTRIES(METHOD)
+    {"descriptor_types", (PyCFunction)(void (*)(void))&descriptor_types, METH_FASTCALL, nullptr},
+    {"takes_descriptor", (PyCFunction)(void (*)(void))&takes_descriptor, METH_FASTCALL, nullptr},
+    {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

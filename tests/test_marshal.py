@@ -33,6 +33,25 @@ def test_has_no_thread_local_storage():
     assert 7 not in [struct.unpack_from("<I", data, at + i * size)[0] for i in range(count)]
 
 
+def test_descriptors_are_of_their_type_not_of_their_size():
+    import ctypes
+    import paper_1412_6249_amd as pa
+    from paper_1412_6249_amd import _marshal
+
+    class Derived(pa.purine_conv_desc):
+        pass
+
+    for good in (pa.conv_desc(1, 1), Derived(1, 1, 0, 0)):
+        assert _marshal.takes_descriptor(good, 0) and not _marshal.takes_descriptor(good, 1)
+    assert _marshal.takes_descriptor(pa.pool_desc(2, 2), 1) and not _marshal.takes_descriptor(pa.pool_desc(2, 2), 0)
+    for size, which, call in ((16, 0, lambda d: pa.purine_conv_fwd(d, pa.raw_desc(0, 0, (1, 4, 4, 4)), pa.raw_desc(0, 0, (1, 4, 1, 1)), pa.raw_desc(0, 0, (1, 1, 4, 4)), stream=0)),
+                              (12, 1, lambda d: pa.purine_maxpool_fwd(d, pa.raw_desc(0, 0, (1, 4, 4, 4)), pa.raw_desc(0, 0, (1, 4, 2, 2)), pa.raw_desc(0, 2, (1, 4, 2, 2)), stream=0))):
+        for bad in (bytes(size), bytearray(size), np.zeros(size // 4, np.int32), (ctypes.c_int32 * (size // 4))()):
+            assert not _marshal.takes_descriptor(bad, which)
+            with pytest.raises((TypeError, ctypes.ArgumentError)):
+                call(bad)
+
+
 @pytest.mark.gpu
 def test_same_call_and_same_refusals_as_the_general_path():
     import ctypes
@@ -65,6 +84,14 @@ def test_same_call_and_same_refusals_as_the_general_path():
         assert _marshal.purine_relu_fwd(bad, y, None) is None
         with pytest.raises((ValueError, TypeError)):
             pa.purine_relu_fwd(bad, y)
+    # objects that only have a descriptor's size
+    w1, y1, arg = torch.randn(8, 24, 1, 1, device=dev), torch.empty(3, 8, 5, 6, device=dev), torch.empty(3, 24, 2, 3, dtype=torch.int32, device=dev)
+    for bad in (bytes(16), np.ones(4, np.int32), (ctypes.c_int32 * 4)(1, 1, 0, 0)):
+        assert _marshal.purine_conv_fwd(bad, big, w1, y1, None, None) is None
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            pa.purine_conv_fwd(bad, big, w1, y1)
+    for bad in (bytes(12), np.array([2, 2, 0], np.int32)):
+        assert _marshal.purine_maxpool_fwd(bad, big, torch.empty(3, 24, 2, 3, device=dev), arg, None) is None
     desc = pa.conv_desc(1, 1)
     w, out = torch.randn(8, 24, 3, 3, device=dev), torch.empty(3, 8, 5, 6, device=dev)
     with pytest.raises(pa.PurineError) as e:
