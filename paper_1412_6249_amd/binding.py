@@ -5,7 +5,7 @@ hands back as not the plain case (None), through ctypes.
 Every function has the name of the C entry point it calls (see include/purine.h). Tensors are
 torch tensors that live on the GPU (PyTorch supplies device memory and streams, nothing else);
 each call raises PurineError on a non-zero status. There is no fallback path: if the shared
-library is missing, importing this module fails.
+library or _marshal.so is missing, importing this module fails.
 """
 import ctypes
 import os
@@ -66,7 +66,11 @@ if not os.path.exists(LIB_PATH):
     raise ImportError("libpurine_conv.so is not built: run `python -c 'import __graft_entry__ as g; "
                       "g.build()'` (or paper_1412_6249_amd/build.py) first")
 _lib = ctypes.CDLL(LIB_PATH)
-from . import _marshal  # noqa: E402  (links against the libraries loaded above)
+try:
+    from . import _marshal  # noqa: E402  (links against the libraries loaded above)
+except ImportError as e:
+    raise ImportError("_marshal.so, the native half of this module, is not built or was built against another PyTorch: run "
+                      "`python -c 'import __graft_entry__ as g; g.build()'` (or paper_1412_6249_amd/build.py) first") from e
 _marshal.descriptor_types(purine_conv_desc, purine_pool_desc)
 
 _P = ctypes.POINTER
