@@ -19,9 +19,10 @@
  *     convolution or backward-data pass whose filter has more than one tap and at least 16
  *     channels on the gathered side, and whose gathered tensor (x, or dy for backward-data) has
  *     rows that are not whole 16-byte packets (W not a multiple of 8, or a channel count or image
- *     stride not a multiple of 8), stages a channels-blocked copy of that tensor (channels rounded
- *     up to a multiple of 32) in ws, and that copy must stay below 2^31 bytes, i.e. 2^30 elements
- *     (PURINE_E_SHAPE otherwise). Layers with whole-packet rows are read in place.
+ *     stride not a multiple of 8), is accepted only if a channels-blocked copy of that tensor
+ *     (channels rounded up to a multiple of 32) stays below 2^31 bytes, i.e. 2^30 elements
+ *     (PURINE_E_SHAPE otherwise). Most such layers are read in place, as those with whole-packet rows
+ *     are; the others stage that copy in ws, where it is expected to be faster or nothing else applies.
  *   - Channel-slice views: a 4-axis F32 or BF16 activation tensor may set `nstride`, the distance in
  *     elements between consecutive images, to more than C*H*W: the tensor is then channels
  *     c0..c0+C-1 of a larger NCHW buffer with `data` pointing at channel c0 of image 0 (inside an
@@ -30,7 +31,11 @@
  *     (N-1)*nstride + C*H*W must stay below 2^31 elements. Views are accepted where an entry
  *     point says so (the activation arguments of the convolution operators and of ReLU); every
  *     other argument must be dense (PURINE_E_LAYOUT otherwise). Two views of one buffer with the
- *     same nstride overlap only if their channel ranges do.
+ *     same nstride overlap only if their channel ranges do. The workspace queries take no nstride:
+ *     what they return holds for views too, except for a PURINE_BF16 layer with whole-packet rows
+ *     whose views span 2^31 bytes or more and whose rows or filter are too large to stage in LDS any
+ *     other way (rows of some 250 elements and more): it needs the channels-blocked copy on top, and
+ *     returns PURINE_E_WORKSPACE without.
  *   - dtype: PURINE_F32 tensors hold IEEE binary32. PURINE_BF16 tensors hold bfloat16 bit
  *     patterns (uint16); arithmetic accumulates in fp32; results stored as bf16 are rounded to
  *     nearest even. Weight and bias gradients are always PURINE_F32.
@@ -104,7 +109,9 @@ int purine_conv_out_shape(const purine_conv_desc* desc, const int64_t x_dim[4],
  * copy of the filter there (none for a forward pass with fewer than 16 input channels); F32 layers
  * with several taps and a strided gather or few output tiles also a copy of the gathered tensor (6
  * bytes per element, channels rounded up to a multiple of 16) and the partial outputs of a split
- * reduction. Backward-weight keeps its split-reduction partial sums there, F32 layers bound by the
+ * reduction, unit-stride F32 layers whose last output tiles do not fill the chip up to 16 MB of those
+ * tiles' partial sums. BF16 layers that cannot be read in place add the channels-blocked copy described
+ * above. Backward-weight keeps its split-reduction partial sums there, F32 layers bound by the
  * matrix cores also copies of x and dy (6 bytes per element; the size is a whole number of copies of
  * dw, and of K sums for the fused bias gradient). Those copies make the scratch several times the operands': 5x5 96 -> 256
  * at 27x27, N = 128 265 MB of backward-weight for 131 MB of x and dy, 3x3 64 -> 128 at 112x112, N = 64 1.0 GB for

@@ -1,9 +1,12 @@
 // bf16 MFMA implicit GEMM with the input patch staged in LDS, for rows of any width, any gather stride
-// and tiles that cross images: the layers that conv_patch_bf16.hip (rows of whole 16-byte packets, one
-// image per tile) refuses, and those too small for it. Conv / ConvBwdData of paper Figure 1(b).
+// and tiles that cross images: of the layers that conv_patch_bf16.hip (rows of whole 16-byte packets, one
+// image per tile) refuses or has too few tiles for its two roles, those where this one is expected to be
+// faster than what they would run on else (plan_conv_pix). Conv / ConvBwdData of paper Figure 1(b).
 //
-// Bound: LDS reads beside the MFMAs where the chip is full, one workgroup's serial chain (first patch,
-// channel groups one after another, stores) where it is not. A workgroup of four wavefronts owns BM
+// Bound: LDS reads beside the MFMAs where the chip is full (3x3, 96 -> 128 channels at 28x28, N = 128, 31 us, 711 TFLOP/s: 47 MB
+// to and from HBM, 1.5 TB/s, the matrix pipes 42 % busy, a quarter of the LDS cycles lost to conflicts), one workgroup's
+// serial chain (first patch, channel groups one after another, stores) where it is not (256 -> 256 at 13x13, N = 128, 85 tiles of
+// 256 pixels on three row tiles, 40 us, 34 %). A workgroup of four wavefronts owns BM
 // output rows and BN consecutive output pixels, counted over all images. Per group of 16 gathered
 // channels the input rows its taps touch are loaded once from NCHW: a thread takes four pixels of eight
 // channels as 8-byte loads at whatever alignment the row has (the last four pixels of a row are taken
@@ -591,7 +594,8 @@ hipError_t by_taps(const PixParams& p, const PatchAnyParams& q, const PatchAnyPl
 // over the sizes the library is used at (3x3 and 5x5, stride 1 and 2, 16 - 512 channels, 7 - 66 pixels a side, 1 - 256
 // images): the tile picked is on average 1.6 % behind the best of the eight, 11 % at the 95th percentile; the
 // layers together 1.59 times as fast as on the blocked copy (and the one-image patch kernel where rows were
-// whole packets), the worst of them 5 % slower.
+// whole packets), the worst of them 5 % slower. (This picks the tile. Outside those sizes some layers are faster on the other
+// kernels: which of them runs is decided by the times at the end of plan_patch_any.)
 struct AnyTileCost { int bm, bn, resident; bool ahead; float tap, stage, group, fixed, eff, wg, fill; };
 constexpr AnyTileCost kAnyTiles[] = {
     {128, 256, 2, false, 200.0f, 760.0f, 0.0f, 4.7f, 0.66f, 5.4f, 0.05f}, {96, 256, 2, false, 99.0f, 730.0f, 0.0f, 4.4f, 0.62f, 4.0f, 0.03f},

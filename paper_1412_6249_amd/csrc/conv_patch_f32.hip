@@ -504,7 +504,8 @@ PatchF32Plan plan_patch_f32(const PixParams& p, bool d2s, bool split, int force_
         // (48 <- 128 channels 5x5 at 27x27, N = 128 backward-data, 365 tiles of 8 groups, the last 109 halved: 288 -> 238 us; 83 <- 264
         // 3x3 at 46x46, N = 63: 463 -> 385). Another tile height only for a clear gain (102 <- 84 5x5 at 56x56, N = 12, 294 tiles of
         // 64 rows in parts 160 us, 147 of 128 in one round 155). The sums are scratch that a caller holds for the layer: at most
-        // 16 MB (with 22, 96 <- 256 5x5 at 27x27, N = 128 would take 577 us instead of 691).
+        // 16 MB. That is a choice: forward and backward-data of the five-layer stack ask for no more than their filter copies so,
+        // as before. It costs its one layer that gains, 96 <- 256 5x5 at 27x27, N = 128, 21.4 MB of sums: 691 us, 577 with them.
         const long long full = ti * tp / 256 * 256, tail = ti * tp - full;
         int parts = 1, cg_part = k.cgs;
         double best_us = force_parts > 1 ? 1e30 : us;
