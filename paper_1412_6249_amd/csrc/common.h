@@ -152,6 +152,8 @@ bool patch_any_forced();             // test hook: (-9, tile): bf16 layers run t
 bool split_1x1_forced();             // test hook: (-10, row tiles of 32, or 0): fp32 1x1 layers run the kernel on parts split in registers
 bool split_patch_forced();           // test hook: (-6, parts): fp32 layers run the kernel that splits a patch in LDS wherever it applies (parts > 1: each last tile's channels over as many workgroups)
 bool split_packets_forced();         // test hook: (-7, anything): ... the kernels on packed bf16 parts (forward, backward-data, weight gradient)
+bool staged_wgrad_forced();          // test hook: (-11, tile): weight gradients run the kernel that lays its operands out in LDS, with that tile (bm * 1000 + bn) or its own
+int staged_wgrad_tile();
 bool patch_split_roles_forced();     // test hook: (-5, anything) gives it layers of few tiles too
 bool patch_split_roles_disabled();   // tuning hook: (-4, anything) keeps the bf16 patch kernel on its one-role form
 bool buffer_loads_disabled();   // tuning hook: (anything, -1) given to force_pix_tile
@@ -174,15 +176,28 @@ struct WgradPacketPlan {
 WgradPacketPlan plan_wgrad_packets(const ConvGeom& g, size_t limit, double budget_us);
 hipError_t launch_wgrad_packets(const ConvGeom& g, const WgradPacketPlan& k, const void* x, const void* dy, float* dw, float* db, float beta, void* ws,
                                 size_t ws_bytes, hipStream_t st);
-// Second pass of a split weight gradient: partial sums [split][k][c][tap], or [split][tap][k][c] (tap_major), into
-// dw, and db_rows rows of K sums into db (db may be null). Reads in the partials' own order.
+// ... and the kernel that lays its operands out inside LDS (conv_wgrad_staged.hip).
+struct WgradStagedPlan {
+    bool use;
+    int bm, bn, Ct, tiles_i, tiles_j, c_tiles;   // tile; channels of a channel tile; row tiles, column tiles of a channel tile, channel tiles
+    bool flat;                             // 1x1 layers as they lie in memory: one row per image
+    int band_shift, PB, PR, QS, PW, XR;    // bands per image (log2) and their output rows; chunk of PR x QS positions, its patch
+    int chunks, splits, lds;
+    double us;                             // expected time
+};
+WgradStagedPlan plan_wgrad_staged(const ConvGeom& g, int dtype, size_t limit, double budget_us);
+hipError_t launch_wgrad_staged(int dtype, const ConvGeom& g, const WgradStagedPlan& k, const void* x, const void* dy, float* dw, float* db, float beta,
+                               void* ws, float* db_partial, hipStream_t st);
+// Second pass of a split weight gradient: partial sums [split][k][c][tap], [split][tap][k][c] (tap_major) or
+// [split][k][channel tile][tap][c] (tile > 0: its channels), into dw, and db_rows rows of K sums into db (db may be null). Reads in the partials' own order.
 hipError_t launch_wgrad_reduce(const float* partial, float* dw, int splits, float beta, bool tap_major, int K, int C, int RS,
-                               const float* db_partial, float* db, int db_rows, hipStream_t st);
+                               const float* db_partial, float* db, int db_rows, hipStream_t st, int tile = 0);
 // scratch of purine_conv_bwd_weight_static
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 
 struct WgradPlan {
     WgradPacketPlan pk;
+    WgradStagedPlan sg;
     size_t static_bytes;  // what the layer has to fit into kStaticScratchBytes with: the general kernels' partial sums
     bool rows;         // bf16 3x3 layers: the row-staging kernel (one partial tile per persistent workgroup)
     bool cols;         // bf16 layers with C*R*S <= 160: whole-filter tiles per wavefront (conv_wgrad_cols_bf16.hip)

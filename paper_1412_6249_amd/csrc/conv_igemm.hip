@@ -562,6 +562,8 @@ bool split_patch_forced() { return g_force_bm == -6; }           // test hooks: 
 bool f32_patch_forced() { return g_force_bm == -8; }             // / forward passes the fp32 patch kernel
 bool patch_any_forced() { return g_force_bm == -9; }             // / bf16 layers the patch kernel for rows of any width
 bool split_1x1_forced() { return g_force_bm == -10; }            // / fp32 1x1 layers the kernel on parts split in registers
+bool staged_wgrad_forced() { return g_force_bm == -11; }         // / weight gradients the kernel that lays operands out in LDS, with that tile
+int staged_wgrad_tile() { return g_force_bm == -11 ? g_force_bn : 0; }
 bool split_packets_forced() { return g_force_bm == -7; }         // / the ones on packed parts wherever they apply
 bool patch_split_roles_forced() { return g_force_bm == -5; }     // test hook: force_pix_tile(-5, x), also for layers of few tiles
 void force_pix_tile(int bm, int bn) {

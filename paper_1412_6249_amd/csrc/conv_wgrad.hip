@@ -597,6 +597,17 @@ hipError_t dispatch_bf16(WgradParams& p, const WgradPlan& plan, hipStream_t st) 
                  : dispatch_bf16_mode<VEC_A, false, false, true>(p, plan, st);
 }
 
+// Where element i of the partials goes in dw [k][c][tap]: they are [tap][k][c] (tap_major) or [k][channel tile][tap][c of the tile].
+__device__ __forceinline__ int place_in_dw(int i, int tap_major, int tile, int K, int C, int RS) {
+    if (tap_major) {
+        const int tap = i / (K * C);
+        return (i - tap * (K * C)) * RS + tap;
+    }
+    const int k = i / (C * RS), rest = i - k * (C * RS), ct = rest / (tile * RS), j = rest - ct * (tile * RS);
+    const int tap = j / min(tile, C - ct * tile), c = j - tap * min(tile, C - ct * tile);
+    return (k * C + ct * tile + c) * RS + tap;
+}
+
 // dw[i] = beta*dw[i] + partial[0][i] + partial[1][i] + ... summed in a fixed tree: a workgroup owns
 // 16 consecutive elements; each of its 16 "split lanes" adds the partials s = lane, lane+16, ... in
 // order (independent loads, so many are in flight), and the 16 lane sums are then added in lane
@@ -604,7 +615,7 @@ hipError_t dispatch_bf16(WgradParams& p, const WgradPlan& plan, hipStream_t st) 
 // Workgroups past dw_blocks do the same for the fused bias gradient: db_rows rows of K partials into db[K].
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restrict__ partial,
                                                            float* __restrict__ dw, int n,
-                                                           int splits, float beta, int tap_major,
+                                                           int splits, float beta, int tap_major, int tile,
                                                            int K, int C, int RS, int dw_blocks,
                                                            const float* __restrict__ db_partial,
                                                            float* __restrict__ db, int db_rows) {
@@ -613,7 +624,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
     int blk = blockIdx.x;
     if (blk >= dw_blocks) {   // uniform over the workgroup
         blk -= dw_blocks;
-        partial = db_partial; dw = db; n = K; tap_major = 0; splits = db_rows;
+        partial = db_partial; dw = db; n = K; tap_major = 0; tile = 0; splits = db_rows;
     }
     const int i = blk * 16 + e;      // index in the partials' own order (coalesced reads)
     float acc = 0.0f;
@@ -632,11 +643,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
     __syncthreads();
     if (sl == 0 && i < n) {
         int dst = i;
-        if (tap_major) {   // partials are [tap][k][c]; dw is [k][c][tap]
-            const int tap = i / (K * C);
-            const int kc = i - tap * (K * C);
-            dst = kc * RS + tap;
-        }
+        if (tap_major || tile) dst = place_in_dw(i, tap_major, tile, K, C, RS);
         float t = beta != 0.0f ? dw[dst] : 0.0f;
 #pragma unroll
         for (int l = 0; l < 16; ++l) t += red[l][e];
@@ -651,7 +658,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
 // alone, so ConvBwdWeight and the fused ConvBwdWeight+BiasBwd give the same bits for dw.
 __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float* __restrict__ partial,
                                                                float* __restrict__ dw, int n,
-                                                               int splits, float beta, int tap_major,
+                                                               int splits, float beta, int tap_major, int tile,
                                                                int K, int C, int RS, int dw_blocks,
                                                                const float* __restrict__ db_partial,
                                                                float* __restrict__ db, int db_rows) {
@@ -660,7 +667,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float* __re
     int blk = blockIdx.x;
     if (blk >= dw_blocks) {   // uniform over the workgroup: the fused bias gradient's partials
         blk -= dw_blocks;
-        partial = db_partial; dw = db; n = K; tap_major = 0; splits = db_rows;
+        partial = db_partial; dw = db; n = K; tap_major = 0; tile = 0; splits = db_rows;
     }
     if (n & 3) {
         // bias-gradient partials of a layer whose K is not a multiple of 4 (rows not 16-byte aligned):
@@ -708,11 +715,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float* __re
     const int j = blk * 32 + e;
     if (e < 32 && j < n) {
         int dst = j;
-        if (tap_major) {   // partials are [tap][k][c]; dw is [k][c][tap]
-            const int tap = j / (K * C);
-            const int kc = j - tap * (K * C);
-            dst = kc * RS + tap;
-        }
+        if (tap_major || tile) dst = place_in_dw(j, tap_major, tile, K, C, RS);
         float t = beta != 0.0f ? dw[dst] : 0.0f;
 #pragma unroll
         for (int l = 0; l < 32; ++l) t += red[l][e];
@@ -862,18 +865,40 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
     double us;
     WgradPlan pl = plan_wgrad_general(g, dtype, &us);
     pl.static_bytes = pl.ws_bytes;
-    if (dtype != PURINE_F32 || buffer_loads_disabled()) return pl;
+    if (buffer_loads_disabled() || (us == 0.0 && !staged_wgrad_forced())) return pl;      // (0: a bf16 kernel of its own, which stays)
+    // A layer that the static-scratch entry point takes has to go through its scratch on the same splits (the results are the same bits).
+    const size_t limit = pl.ws_bytes <= kStaticScratchBytes ? kStaticScratchBytes : 0;
     // fp32: the kernel on packed bf16 parts where it is expected to be faster. The layout pass costs 10
-    // bytes per element of x and dy, so 1x1 layers and layers of few channels stay on the general
+    // bytes per element of x and dy, so 1x1 layers and layers of few channels stay on the other
     // kernels (96 -> 96 channels 1x1 at 54x54, N = 64: 65 us there, 90 us for the layout pass alone);
-    // MFMA-bound ones gain what the forward pass gains. A layer that the static-scratch entry point
-    // takes has to go through its scratch on the same splits (the results are the same bits).
-    const WgradPacketPlan pk = plan_wgrad_packets(g, pl.ws_bytes <= kStaticScratchBytes ? kStaticScratchBytes : 0,
-                                                  split_packets_forced() ? 1e30 : us / 1.05 + 2.0);
-    if (!pk.use) return pl;
-    pl.pk = pk;
-    pl.ws_bytes = pk.copies * (size_t)g.K * g.C * g.R * g.S * sizeof(float);
-    pl.db_ws_bytes = pk.copies * (size_t)g.K * sizeof(float);
+    // MFMA-bound ones gain what the forward pass gains.
+    if (dtype == PURINE_F32 && !staged_wgrad_forced()) {
+        pl.pk = plan_wgrad_packets(g, limit, split_packets_forced() ? 1e30 : us / 1.05 + 2.0);
+        if (pl.pk.use) {
+            pl.ws_bytes = pl.pk.copies * (size_t)g.K * g.C * g.R * g.S * sizeof(float);
+            pl.db_ws_bytes = pl.pk.copies * (size_t)g.K * sizeof(float);
+        }
+        if (split_packets_forced()) return pl;
+    }
+    // The kernel that lays its operands out inside LDS, where it is expected to be faster than either: first layers, few channels,
+    // 1x1, small launches. The estimates of the general kernels do not know that their gathers bind them: fp32 first layers take 1.15
+    // times as long as expected, bf16 tiles of fewer than 128 rows up to twice (gathered columns per pixel are the same 128).
+    // (64 channels and more with several taps: the general kernel's tiles of one tap's channels do well, and its time is known
+    // better.) Of 160 fp32 layers drawn from the measured ranges 94 go there and are 1.27 times as fast (geometric mean; three are slower, by 13 %
+    // at most), of 51 bf16 layers 13, 1.42 times as fast.
+    double old = pl.pk.use ? pl.pk.us : us;
+    if (dtype == PURINE_F32) {
+        if (!pl.pk.use && g.C < 16) old *= 1.15;
+    } else if (!pl.tap && pl.bm < 128 && us > 10.0) {
+        old += 0.5 * (us - 10.0) * (128.0 / pl.bm - 1.0);
+    }
+    pl.sg = plan_wgrad_staged(g, dtype, limit, staged_wgrad_forced() ? 1e30 : dtype == PURINE_F32 ? (pl.tap && g.R * g.S > 1 ? 0.75 : 0.92) * old - 2.0 : old - 2.0);
+    if (pl.sg.use) {
+        pl.pk.use = pl.rows = pl.cols = pl.taps = pl.tap = false;
+        pl.splits = pl.sg.splits;
+        pl.ws_bytes = (size_t)pl.splits * g.K * g.C * g.R * g.S * sizeof(float);
+        pl.db_ws_bytes = (size_t)pl.splits * g.K * sizeof(float);
+    }
     return pl;
 }
 
@@ -905,6 +930,11 @@ hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const WgradPlan& plan
     const bool vec = p.PQ % 32 == 0 && (((uintptr_t)dy) & 15u) == 0;
     if (plan.pk.use)
         return launch_wgrad_packets(g, plan.pk, x, dy, dw, db, beta, ws, ws_bytes < plan.pk.ws_bytes ? ws_bytes : plan.pk.ws_bytes, st);
+    if (plan.sg.use) {
+        e = launch_wgrad_staged(dtype, g, plan.sg, x, dy, dw, db, beta, ws, p.db_out, st);
+        if (e != hipSuccess || plan.splits == 1) return e;
+        return launch_wgrad_reduce((const float*)ws, dw, plan.splits, beta, false, g.K, g.C, p.RS, (const float*)p.db_out, db, plan.splits, st, plan.sg.Ct);
+    }
     if (plan.rows) e = launch_wgrad_rows_bf16(g, plan.splits, x, dy, (float*)ws, p.db_out, st);
     else if (plan.taps) e = launch_wgrad_taps_bf16(g, x, dy, (float*)ws, p.db_out, st);
     else if (plan.cols) e = launch_wgrad_cols_bf16(g, x, dy, (float*)ws, p.db_out, st);
@@ -916,19 +946,19 @@ hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const WgradPlan& plan
 }
 
 hipError_t launch_wgrad_reduce(const float* partial, float* dw, int splits, float beta, bool tap_major, int K, int C, int RS,
-                               const float* db_partial, float* db, int db_rows, hipStream_t st) {
+                               const float* db_partial, float* db, int db_rows, hipStream_t st, int tile) {
     const int n = K * C * RS;
     // 16-byte packets need aligned rows in both sets of partials (the scratch itself is aligned)
     const bool vec4 = n % 4 == 0;   // (the bias-gradient partials take an element-wise path when K % 4 != 0)
     if (vec4) {
         const int dw_blocks = (n + 31) / 32, db_blocks = db ? (K + 31) / 32 : 0;
         hipLaunchKernelGGL(wgrad_reduce_vec_kernel, dim3(dw_blocks + db_blocks), dim3(256), 0, st,
-                           partial, dw, n, splits, beta, tap_major ? 1 : 0, K, C, RS, dw_blocks, db_partial, db, db_rows);
+                           partial, dw, n, splits, beta, tap_major ? 1 : 0, tile, K, C, RS, dw_blocks, db_partial, db, db_rows);
         return hipGetLastError();
     }
     const int dw_blocks = (n + 15) / 16, db_blocks = db ? (K + 15) / 16 : 0;
     hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(dw_blocks + db_blocks), dim3(256), 0, st,
-                       partial, dw, n, splits, beta, tap_major ? 1 : 0, K, C, RS, dw_blocks, db_partial, db, db_rows);
+                       partial, dw, n, splits, beta, tap_major ? 1 : 0, tile, K, C, RS, dw_blocks, db_partial, db, db_rows);
     return hipGetLastError();
 }
 
