@@ -741,6 +741,16 @@ int fc_stream_checks(const FcPlan& f, const purine_tensor* out, const purine_ten
     return PURINE_OK;
 }
 
+// Passes in one launch (fc_direct_faster) need no scratch, but what the query asks for has to be there all the same.
+int fc_direct_checks(int pass, const purine_tensor* out, const purine_tensor* a, const purine_tensor* b, int64_t N, int64_t C, int64_t K, const void* ws,
+                     size_t ws_bytes) {
+    if (overlaps(out, a) || overlaps(out, b)) return PURINE_E_LAYOUT;
+    const size_t need = purine_fc_workspace_bytes(pass, N, C, K, a->dtype);
+    if (need && (!ws || ws_bytes < need)) return PURINE_E_WORKSPACE;
+    if (need && (((uintptr_t)ws) & 15u)) return PURINE_E_LAYOUT;
+    return PURINE_OK;
+}
+
 }  // namespace
 
 size_t purine_grouped_conv_workspace_bytes(int pass, const purine_conv_desc* desc, int groups,
@@ -847,6 +857,14 @@ int purine_fc_fwd(const purine_tensor* x, const purine_tensor* w, const purine_t
         if (b->dim[0] != w->dim[0]) return PURINE_E_SHAPE;
         if (overlaps(b, y)) return PURINE_E_LAYOUT;
     }
+    {
+        const int64_t N = x->dim[0], C = x->dim[1], K = w->dim[0];
+        if (fc_direct_faster(PURINE_CONV_FWD, N, C, K, x->dtype)) {
+            if ((rc = fc_direct_checks(PURINE_CONV_FWD, y, x, w, N, C, K, ws, ws_bytes))) return rc;
+            return hip_status(launch_fc_direct(PURINE_CONV_FWD, x->dtype, x->data, w->data, y->data, b ? b->data : nullptr, nullptr, 0.0f, N, C, K,
+                                               (hipStream_t)hip_stream));
+        }
+    }
     // y[n][k] = sum_c x[n][c] w[k][c]: the weight-gradient contraction with dy := x and x := w,
     // both matrices as one image whose pixel plane is the feature axis c
     const purine_tensor wp = as_plane(w), xp = as_plane(x);
@@ -887,6 +905,14 @@ int purine_fc_bwd_data(const purine_tensor* dy, const purine_tensor* w, purine_t
                        size_t ws_bytes, void* hip_stream) {
     int rc;
     if ((rc = check_fc(dx, w, dy))) return rc;
+    {
+        const int64_t N = dy->dim[0], C = w->dim[1], K = w->dim[0];
+        if (fc_direct_faster(PURINE_CONV_BWD_DATA, N, C, K, dy->dtype)) {
+            if ((rc = fc_direct_checks(PURINE_CONV_BWD_DATA, dx, dy, w, N, C, K, ws, ws_bytes))) return rc;
+            return hip_status(launch_fc_direct(PURINE_CONV_BWD_DATA, dy->dtype, dy->data, w->data, dx->data, nullptr, nullptr, 0.0f, N, C, K,
+                                               (hipStream_t)hip_stream));
+        }
+    }
     // dx[n][c] = sum_k dy[n][k] w[k][c]: a 1x1 convolution of the plane w [K channels x C pixels] with
     // the filter bank dy [N x K]
     if (dy->dtype == PURINE_BF16) {
@@ -923,6 +949,11 @@ int purine_fc_bwd_weight(const purine_tensor* x, const purine_tensor* dy, purine
         if (db->dtype != PURINE_F32) return PURINE_E_DTYPE;
         if (db->dim[0] != dw->dim[0]) return PURINE_E_SHAPE;
         if (overlaps(db, dy) || overlaps(db, x) || overlaps(db, dw)) return PURINE_E_LAYOUT;
+    }
+    if (fc_direct_faster(PURINE_CONV_BWD_WEIGHT, N, C, K, x->dtype)) {
+        if ((rc = fc_direct_checks(PURINE_CONV_BWD_WEIGHT, dw, dy, x, N, C, K, ws, ws_bytes))) return rc;
+        return hip_status(launch_fc_direct(PURINE_CONV_BWD_WEIGHT, x->dtype, dy->data, x->data, dw->data, nullptr, db ? (float*)db->data : nullptr, beta, N, C, K,
+                                           (hipStream_t)hip_stream));
     }
     if (x->dtype == PURINE_BF16) {
         // dw[k][c] = sum_n dy[n][k] x[n][c] with an fp32 result: the weight-gradient contraction over

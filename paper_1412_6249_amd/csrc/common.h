@@ -278,6 +278,10 @@ hipError_t launch_transpose16_pair(const void* in0, void* out0, int cols0, const
 bool fc_wgrad_bf16_applies(int64_t N, int64_t C, int64_t K);
 hipError_t launch_fc_wgrad_bf16(const void* dyT, const void* xT, float* dw, int N, int K, int C, bool accumulate,
                                 hipStream_t st);
+// fully-connected passes in one launch without scratch (fc_direct.hip); db: the weight gradient's bias gradient
+bool fc_direct_faster(int pass, int64_t N, int64_t C, int64_t K, int dtype);
+hipError_t launch_fc_direct(int pass, int dtype, const void* a, const void* b, void* out, const void* bias, float* db, float beta, int64_t N, int64_t C,
+                            int64_t K, hipStream_t st);
 hipError_t launch_relu_view(int dtype, bool bwd, const void* x, const void* dy, void* out, int N, int run,
                             int64_t x_ns, int64_t dy_ns, int64_t out_ns, hipStream_t st);
 hipError_t launch_sgd_update(int dtype, const void* w, const float* dw, void* new_w, float lr,
