@@ -21,7 +21,7 @@
 // chunk to issue them instead of 3000.)
 //
 // Whole operator, general kernel before / now, us: that layer 311 / 272; 3 -> 170 7x7 / 2 at 174x175, N = 88 671 / 349; 3 -> 344 7x7 / 2 at
-// 199x199, N = 10 265 / 123; 192 -> 176 1x1 at 28x28, N = 128 97 / 77; 16 -> 32 5x5 at 28x28, N = 128 60 / 39; bf16 3 -> 139 7x7 / 2 at
+// 199x199, N = 10 265 / 123; 272 -> 126 1x1 at 26x26, N = 1 15 / 10; 16 -> 32 5x5 at 28x28, N = 128 60 / 39; bf16 3 -> 139 7x7 / 2 at
 // 184x186, N = 106 638 / 158; 3 -> 220 7x7 / 2 at 65x66, N = 140 157 / 61.
 #include <type_traits>
 #include "packets.h"
@@ -543,6 +543,10 @@ WgradStagedPlan plan_wgrad_staged(const ConvGeom& g, int dtype, size_t limit, do
     const bool flat = RS == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
     const int P = flat ? 1 : g.P, Qc = flat ? (int)(((long long)g.P * g.Q + 7) / 8) : g.Q;
     if (flat && !f32) return best;     // (the general kernel is the faster: 93 -> 62 channels at 19x20, N = 14: 12.4 us, 13.6 here)
+    // (Planes as they lie in memory, 16 MB and more of them: alone a little faster than the general kernel (96 -> 96 channels at 54x54, N = 64 57 and
+    // 51 us), but its workgroups want a CU to themselves, and beside another stream's kernels the two wait for each other: the NIN
+    // block of 43 images 593 us with it, 529 without. A plan does not know what runs beside it.)
+    if (flat && (xspan + dyspan) * 4 >= (16ll << 20)) return best;
     if (P > (1 << 20) || Qc > (1 << 20) || g.S > 64 || g.sw > 16 || g.sh > 16 || g.ph > 4096 || g.pw > 4096) return best;
     int shift = 0;                     // bands: as many as fill a group of eight, or do not cost more than they bring
     if (!flat)
