@@ -145,6 +145,8 @@ struct PixPlan {
     PatchF32Plan pf;
     PatchAnyPlan pa;
     Split1x1Plan ps;
+    double us;                 // expected time of the general fp32 kernels
+    bool direct;               // ... but a launch as small as this runs conv_direct.hip's kernel (the scratch stays as it is)
 };
 PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, bool accumulate = false);
 void force_pix_tile(int bm, int bn);
@@ -154,6 +156,7 @@ bool split_patch_forced();           // test hook: (-6, parts): fp32 layers run 
 bool split_packets_forced();         // test hook: (-7, anything): ... the kernels on packed bf16 parts (forward, backward-data, weight gradient)
 bool staged_wgrad_forced();          // test hook: (-11, tile): weight gradients run the kernel that lays its operands out in LDS, with that tile (bm * 1000 + bn) or its own
 int staged_wgrad_tile();
+bool conv_direct_forced();           // test hook: (-12, anything): forward and backward-data run the kernel of small launches wherever it applies
 bool patch_split_roles_forced();     // test hook: (-5, anything) gives it layers of few tiles too
 bool patch_split_roles_disabled();   // tuning hook: (-4, anything) keeps the bf16 patch kernel on its one-role form
 bool buffer_loads_disabled();   // tuning hook: (anything, -1) given to force_pix_tile
@@ -251,6 +254,9 @@ struct PixEpilogue {
     int relu = 0;                 // forward: y = max(y, 0)
     const void* mask = nullptr;   // backward-data: dx = mask > 0 ? dx : 0 (mask has dx's extents)
 };
+// forward / backward-data of small launches in one kernel without scratch (conv_direct.hip)
+double conv_direct_us(const ConvGeom& g, bool bwd, int dtype);
+hipError_t launch_conv_direct(int dtype, const ConvGeom& g, bool bwd, const void* in, const void* wt, void* out, float beta, const PixEpilogue& epi, hipStream_t st);
 hipError_t launch_conv_pix(int dtype, const ConvGeom& g, const PixPlan& plan, const void* in,
                            const void* wt, void* out, float beta, void* ws, const PixEpilogue& epi,
                            hipStream_t st);

@@ -562,6 +562,7 @@ bool split_patch_forced() { return g_force_bm == -6; }           // test hooks: 
 bool f32_patch_forced() { return g_force_bm == -8; }             // / forward passes the fp32 patch kernel
 bool patch_any_forced() { return g_force_bm == -9; }             // / bf16 layers the patch kernel for rows of any width
 bool split_1x1_forced() { return g_force_bm == -10; }            // / fp32 1x1 layers the kernel on parts split in registers
+bool conv_direct_forced() { return g_force_bm == -12; }          // / forward and backward-data the kernel of small launches
 bool staged_wgrad_forced() { return g_force_bm == -11; }         // / weight gradients the kernel that lays operands out in LDS, with that tile
 int staged_wgrad_tile() { return g_force_bm == -11 ? g_force_bn : 0; }
 bool split_packets_forced() { return g_force_bm == -7; }         // / the ones on packed parts wherever they apply
@@ -637,7 +638,7 @@ static double blocked_us(const PixParams& p, const PixPlan& pl) {
     return 8.5 + 0.295 * slabs + 0.0143 * slabs * std::ceil(m) * area + 0.28 * in_mb + 0.333 * out_mb + 2.48 * filter_mb + (pl.mode == 2 ? 0.214 * m * area : 0.0);
 }
 
-PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, bool accumulate) {
+static PixPlan plan_general(const ConvGeom& g, bool bwd_data, int dtype, bool fused, bool accumulate) {
     PixPlan pl{};
     const int elem = dtype == PURINE_BF16 ? 2 : 4;
     int Co, Ci;
@@ -702,6 +703,7 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
     if (rows16 && (g_force_bn == 256 || g_force_bn == 128) && g_force_bm == (Co <= 16 ? 16 : 48)) {
         pl.bm = g_force_bm; pl.bn = g_force_bn;
     }
+    pl.us = best * 2.0 * Ci * pl.Rt * pl.St / (157.3e6 / 256.0 * 0.78) + 6.0;       // (fp32)
     pl.Co = Co; pl.Ci = Ci;
     pl.tiles_i = (Co + pl.bm - 1) / pl.bm;
     pl.tiles_pix = (int)((M + pl.bn - 1) / pl.bn);
@@ -794,7 +796,7 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
         // 0 - 5e-4 in eleven of twelve runs below 2048 products, in the twelfth one sign of 86528 outputs differs and is
         // worth 2.7e-3; 1.8e-3 - 3.1e-3 in five of six runs above. On an AlexNet stack of 128 images
         // 1.5e-3 - 2.7e-3 without the rule, 1.4e-6 with it, for 5.15 instead of 4.15 ms; inception module 0 - 0.7e-3.)
-        const double old_us = best * 2.0 * Ci * pl.Rt * pl.St / (157.3e6 / 256.0 * 0.78) + 6.0;
+        const double old_us = pl.us;
         const PixParams pp = make_pix_params(dtype, g, pl);
         const bool small = ((long long)Co + 127) / 128 * ((M + 255) / 256) < 32;
         const bool keep_bits = pl.mode == 0 && (long long)Ci * g.R * g.S > 2048 && !small;
@@ -877,9 +879,50 @@ PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, b
     return pl;
 }
 
+// Expected time of what plan_general chose, or 0 where a small launch stays with it.
+static double general_us(const ConvGeom& g, const PixPlan& pl, int dtype) {
+    const bool f32 = dtype == PURINE_F32;
+    if (!f32 && !pl.flat && pl.Rt * pl.St > 1) {
+        // bf16 rows and channels of whole packets: the three patch kernels give the same bits for such a layer, whatever its size, and
+        // the one for small launches would not
+        PixParams p = make_pix_params(dtype, g, pl);
+        PatchGeom q;
+        if (pl.patch || plan_patch_bf16(p, pl.mode, &q)) return 0.0;
+    }
+    if (pl.pf.use) return pl.pf.us;
+    if (pl.pk.use) return pl.pk.us;
+    if (pl.pa.use) return pl.pa.us;
+    if (pl.flat || pl.ps.use || pl.gemm1x1) return f32 ? 0.95 * pl.us : 1.0 + 0.72 * pl.us;
+    const double slabs = (double)(pl.Ci_pad / (f32 ? 16 : 32)) * pl.Rt * pl.St, rounds = (double)(((long long)pl.tiles_i * pl.tiles_pix + 255) / 256);
+    if (f32) return 1.5 + 0.09 * slabs + 0.887 * pl.us + 0.133 * rounds * slabs;
+    return pl.Rt * pl.St > 1 ? blocked_us(make_pix_params(dtype, g, pl), pl) : 6.8 + 0.15 * slabs + 0.27 * rounds * slabs;
+}
+
+// Small launches take the kernel that needs no layout pass, where it is expected in 0.72 of the time that the general ones need:
+// their own estimates where they have one; the tap kernels' chain of slabs and filter copy is fitted to 400 launches of 4 - 100 us (0.6 - 1.4
+// of the measured time in nine of ten). Of 1143 drawn passes 300 go there, 2.1 times as fast (geometric mean; two of them slower,
+// by up to a fifth). What the forward pass of a long sum must keep, it keeps (the rule on products in plan_general).
+PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, bool accumulate) {
+    PixPlan pl = plan_general(g, bwd_data, dtype, fused, accumulate);
+    if (g_no_buffer_loads != 0 || (g_force_bm != 0 && !conv_direct_forced())) return pl;
+    const double us = conv_direct_us(g, bwd_data, dtype);
+    if (us < 0.0) return pl;
+    if (conv_direct_forced()) { pl.direct = true; return pl; }
+    if (us > 60.0 || (dtype == PURINE_F32 && !bwd_data && (long long)g.C * g.R * g.S > 2048 &&
+                      ((long long)g.K + 127) / 128 * (((long long)g.N * g.P * g.Q + 255) / 256) >= 32)) return pl;
+    // (images far apart: as dense ones, whose bits they get)
+    ConvGeom d = g;
+    d.x_ns = g.C * g.H * g.W; d.y_ns = g.K * g.P * g.Q;
+    const bool far = (long long)g.N * g.x_ns >= (1ll << 28) || (long long)g.N * g.y_ns >= (1ll << 28);
+    const PixPlan as_dense = far ? plan_general(d, bwd_data, dtype, fused, accumulate) : PixPlan{};
+    pl.direct = us < 0.72 * general_us(far ? d : g, far ? as_dense : pl, dtype);
+    return pl;
+}
+
 hipError_t launch_conv_pix(int dtype, const ConvGeom& g, const PixPlan& pl, const void* in,
                            const void* wt, void* out, float beta, void* ws, const PixEpilogue& epi,
                            hipStream_t st) {
+    if (pl.direct) return launch_conv_direct(dtype, g, pl.mode != 0, in, wt, out, beta, epi, st);
     PixParams p = make_pix_params(dtype, g, pl);
     p.in = in; p.out = out;
     p.bias = epi.bias; p.relu = epi.relu; p.mask = epi.mask;
