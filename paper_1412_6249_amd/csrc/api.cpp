@@ -341,7 +341,7 @@ int static_scratch_of_current_device(void** out) {
 // scratch array instead of a caller workspace (ws and ws_bytes are ignored).
 int conv_bwd_weight_impl(const purine_conv_desc* desc, const purine_tensor* x, const purine_tensor* dy,
                          purine_tensor* dw, purine_tensor* db, float beta, void* ws, size_t ws_bytes,
-                         void* hip_stream, bool static_ws = false) {
+                         void* hip_stream, bool static_ws = false, const WgradFinish* finish = nullptr) {
     int rc;
     if ((rc = check_desc(desc)) || (rc = check_tensor(x, 4, true)) || (rc = check_tensor(dy, 4, true)) ||
         (rc = check_tensor(dw, 4)) || (db && (rc = check_tensor(db, 1))) || (rc = check_beta(beta)))
@@ -366,7 +366,7 @@ int conv_bwd_weight_impl(const purine_conv_desc* desc, const purine_tensor* x, c
     if (!ws || ws_bytes < need) return PURINE_E_WORKSPACE;
     if (((uintptr_t)ws) & 15u) return PURINE_E_LAYOUT;
     hipError_t e = launch_conv_wgrad(x->dtype, g, plan, x->data, dy->data, (float*)dw->data,
-                                     db ? (float*)db->data : nullptr, beta, ws, ws_bytes, (hipStream_t)hip_stream);
+                                     db ? (float*)db->data : nullptr, beta, ws, ws_bytes, (hipStream_t)hip_stream, finish);
     return hip_status(e);
 }
 }  // namespace
@@ -870,18 +870,16 @@ int purine_fc_fwd(const purine_tensor* x, const purine_tensor* w, const purine_t
     const purine_tensor wp = as_plane(w), xp = as_plane(x);
     purine_tensor yf = as_filter(y);
     if (x->dtype == PURINE_BF16) {
-        // that kernel's result is fp32: it goes to the end of the workspace, and a last kernel adds
-        // the bias and rounds once
+        // that kernel's partial sums are fp32; its second pass adds them up and the bias, and rounds once
         const int64_t N = x->dim[0], K = w->dim[0];
         const size_t conv_ws = align256(purine_conv_workspace_bytes(PURINE_CONV_BWD_WEIGHT, &kUnitConv, wp.dim, yf.dim, PURINE_BF16));
         if (!ws || ws_bytes < conv_ws + (size_t)N * K * 4) return PURINE_E_WORKSPACE;
         if (((uintptr_t)ws) & 15u) return PURINE_E_LAYOUT;
-        purine_tensor acc = yf;
+        purine_tensor acc = yf;   // the fp32 product, for the kernels that have no second pass
         acc.dtype = PURINE_F32;
         acc.data = (char*)ws + conv_ws;
-        if ((rc = conv_bwd_weight_impl(&kUnitConv, &wp, &xp, &acc, nullptr, 0.0f, ws, conv_ws, hip_stream))) return rc;
-        return hip_status(launch_fc_finish_bf16((const float*)acc.data, b ? b->data : nullptr, y->data, (int)N, (int)K,
-                                                (hipStream_t)hip_stream));
+        const WgradFinish finish{b ? (const uint16_t*)b->data : nullptr, (uint16_t*)y->data};
+        return conv_bwd_weight_impl(&kUnitConv, &wp, &xp, &acc, nullptr, 0.0f, ws, conv_ws, hip_stream, false, &finish);
     }
     const FcPlan plan = fc_plan(PURINE_CONV_FWD, x->dim[0], x->dim[1], w->dim[0], x->dtype);
     const StreamPlan& k = plan.k;

@@ -193,8 +193,10 @@ hipError_t launch_wgrad_staged(int dtype, const ConvGeom& g, const WgradStagedPl
                                void* ws, float* db_partial, hipStream_t st);
 // Second pass of a split weight gradient: partial sums [split][k][c][tap], [split][tap][k][c] (tap_major) or
 // [split][k][channel tile][tap][c] (tile > 0: its channels), into dw, and db_rows rows of K sums into db (db may be null). Reads in the partials' own order.
+// finish (a layer of one tap): the product goes to a bf16 matrix y [K][C], rounded once after its column's bias (may be null) is added
+struct WgradFinish { const uint16_t* bias; uint16_t* y; };
 hipError_t launch_wgrad_reduce(const float* partial, float* dw, int splits, float beta, bool tap_major, int K, int C, int RS,
-                               const float* db_partial, float* db, int db_rows, hipStream_t st, int tile = 0);
+                               const float* db_partial, float* db, int db_rows, hipStream_t st, int tile = 0, const WgradFinish* finish = nullptr);
 // scratch of purine_conv_bwd_weight_static
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 
@@ -262,7 +264,7 @@ hipError_t launch_conv_pix(int dtype, const ConvGeom& g, const PixPlan& plan, co
                            hipStream_t st);
 // db != null: also db = beta*db + sum of dy over pixels (fused BiasBwd), scratch behind dw's partials
 hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const WgradPlan& plan, const void* x,
-                             const void* dy, float* dw, float* db, float beta, void* ws, size_t ws_bytes, hipStream_t st);
+                             const void* dy, float* dw, float* db, float beta, void* ws, size_t ws_bytes, hipStream_t st, const WgradFinish* finish = nullptr);
 hipError_t launch_bias_fwd(int dtype, const void* b, void* y, int N, int K, int PQ, hipStream_t st);
 hipError_t launch_bias_bwd(int dtype, const void* dy, float* db, float beta, int N, int K, int PQ,
                            const BiasBwdPlan& plan, void* ws, hipStream_t st);
@@ -270,7 +272,6 @@ hipError_t launch_relu_fwd(int dtype, const void* x, void* y, int64_t n, hipStre
 hipError_t launch_relu_bwd(int dtype, const void* x, const void* dy, void* dx, int64_t n,
                            hipStream_t st);
 hipError_t launch_bias_rows(const float* b, float* y, int N, int K, hipStream_t st);
-hipError_t launch_fc_finish_bf16(const float* acc, const void* b, void* y, int N, int K, hipStream_t st);
 // bf16 fully-connected data gradient: scratch bytes and slicing (SIZE_MAX: rows are not whole
 // 16-byte packets, the kernel does not apply)
 size_t fc_dgrad_bf16_plan(int64_t N, int64_t C, int64_t K, int* slices, int* k_per_slice);

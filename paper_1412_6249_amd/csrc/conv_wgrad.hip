@@ -9,6 +9,7 @@
 // single fp32 accumulation chain, which the 1e-5 accuracy target needs for 10^5..10^6 pixels.
 // Neither operand is materialised: both slabs are built in LDS from the NCHW tensors with lanes
 // running along pixels.
+#include "bf16.h"
 #include "common.h"
 
 namespace purine {
@@ -608,17 +609,24 @@ __device__ __forceinline__ int place_in_dw(int i, int tap_major, int tile, int K
     return (k * C + ct * tile + c) * RS + tap;
 }
 
+// Element i of the bf16 fully-connected forward product: the bias is added in fp32, then one rounding, to nearest even. The second pass
+// does it while it has the sum; as a pass of its own over an fp32 matrix it was 4.7 us more of fc_fwd's 42 (256 x 4096 x 4096).
+__device__ __forceinline__ uint16_t finished(float sum, const WgradFinish& fin, int i, int C) {
+    return f2bf(sum + (fin.bias ? bf2f(fin.bias[i % C]) : 0.0f));
+}
+
 // dw[i] = beta*dw[i] + partial[0][i] + partial[1][i] + ... summed in a fixed tree: a workgroup owns
 // 16 consecutive elements; each of its 16 "split lanes" adds the partials s = lane, lane+16, ... in
 // order (independent loads, so many are in flight), and the 16 lane sums are then added in lane
 // order through LDS. The order never depends on timing, so the result is bit-identical run to run.
 // Workgroups past dw_blocks do the same for the fused bias gradient: db_rows rows of K partials into db[K].
+template <bool FIN>
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restrict__ partial,
                                                            float* __restrict__ dw, int n,
                                                            int splits, float beta, int tap_major, int tile,
                                                            int K, int C, int RS, int dw_blocks,
                                                            const float* __restrict__ db_partial,
-                                                           float* __restrict__ db, int db_rows) {
+                                                           float* __restrict__ db, int db_rows, WgradFinish fin) {
     __shared__ float red[16][17];
     const int e = threadIdx.x & 15, sl = threadIdx.x >> 4;
     int blk = blockIdx.x;
@@ -647,7 +655,8 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
         float t = beta != 0.0f ? dw[dst] : 0.0f;
 #pragma unroll
         for (int l = 0; l < 16; ++l) t += red[l][e];
-        dw[dst] = t;
+        if constexpr (FIN) fin.y[i] = finished(t, fin, i, C);
+        else dw[dst] = t;
     }
 }
 
@@ -656,12 +665,13 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
 // different L2s), 8 lanes x 16 bytes wide, and 32 split lanes deep; the 32 lane sums are added in
 // lane order. Also a fixed order; which of the two kernels adds dw's partials depends on K*C*R*S
 // alone, so ConvBwdWeight and the fused ConvBwdWeight+BiasBwd give the same bits for dw.
+template <bool FIN>
 __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float* __restrict__ partial,
                                                                float* __restrict__ dw, int n,
                                                                int splits, float beta, int tap_major, int tile,
                                                                int K, int C, int RS, int dw_blocks,
                                                                const float* __restrict__ db_partial,
-                                                               float* __restrict__ db, int db_rows) {
+                                                               float* __restrict__ db, int db_rows, WgradFinish fin) {
     __shared__ float red[32][33];
     const int e4 = threadIdx.x & 7, sl = threadIdx.x >> 3;
     int blk = blockIdx.x;
@@ -719,7 +729,43 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float* __re
         float t = beta != 0.0f ? dw[dst] : 0.0f;
 #pragma unroll
         for (int l = 0; l < 32; ++l) t += red[l][e];
-        dw[dst] = t;
+        if constexpr (FIN) fin.y[j] = finished(t, fin, j, C);
+        else dw[dst] = t;
+    }
+}
+
+// The same sums in the same order (the same bits) for many elements, in their order in dw, of few splits: no more than the split lanes of
+// the two kernels above, which therefore add one partial each. A thread adds all the splits of V elements: there, lanes without a
+// split have nothing to read and each sum goes through LDS. Bound: HBM. us, there / here: 16 splits of 256 x 4096 10.0 / 7.6, 8 of
+// 500 x 1000 9.2 / 5.1.
+constexpr int kFewElements = 1 << 17;   // from here on there are enough threads without the split lanes (4 x 32 x 4096: 4.9 / 4.7 us)
+template <int V, bool FIN>
+__global__ __launch_bounds__(256) void wgrad_reduce_few_kernel(const float* __restrict__ partial, float* __restrict__ dw, int n, int splits, float beta,
+                                                               int C, int dw_blocks, const float* __restrict__ db_partial, float* __restrict__ db, int K,
+                                                               WgradFinish fin) {
+    int blk = blockIdx.x;
+    if (blk >= dw_blocks) {   // uniform over the workgroup: the fused bias gradient's partials
+        blk -= dw_blocks;
+        partial = db_partial; dw = db; n = K;
+    }
+    const unsigned i = ((unsigned)blk * 256 + threadIdx.x) * V;
+    if (i >= (unsigned)n) return;   // n is a multiple of V
+    float t[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) t[e] = beta != 0.0f ? dw[i + e] : 0.0f;
+#pragma unroll 8
+    for (int s = 0; s < splits; ++s) {
+        if constexpr (V == 4) {
+            const float4 v = *reinterpret_cast<const float4*>(partial + (size_t)s * n + i);
+            t[0] += v.x; t[1] += v.y; t[2] += v.z; t[3] += v.w;
+        } else {
+            t[0] += partial[(size_t)s * n + i];
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+        if constexpr (FIN) fin.y[i + e] = finished(t[e], fin, (int)i + e, C);
+        else dw[i + e] = t[e];
     }
 }
 
@@ -903,7 +949,7 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
 }
 
 hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const WgradPlan& plan, const void* x,
-                             const void* dy, float* dw, float* db, float beta, void* ws, size_t ws_bytes, hipStream_t st) {
+                             const void* dy, float* dw, float* db, float beta, void* ws, size_t ws_bytes, hipStream_t st, const WgradFinish* finish) {
     WgradParams p{};
     p.x = x; p.dy = dy;
     // bias-gradient partials [split][K] sit behind the weight-gradient partials
@@ -928,6 +974,11 @@ hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const WgradPlan& plan
     }
     hipError_t e;
     const bool vec = p.PQ % 32 == 0 && (((uintptr_t)dy) & 15u) == 0;
+    if (finish && (p.RS != 1 || db)) return hipErrorInvalidValue;
+    if (finish && (plan.pk.use || plan.sg.use)) {   // these write dw themselves
+        e = launch_conv_wgrad(dtype, g, plan, x, dy, dw, nullptr, 0.0f, ws, ws_bytes, st);
+        return e != hipSuccess ? e : launch_wgrad_reduce(dw, nullptr, 1, 0.0f, false, g.K, g.C, 1, nullptr, nullptr, 0, st, 0, finish);
+    }
     if (plan.pk.use)
         return launch_wgrad_packets(g, plan.pk, x, dy, dw, db, beta, ws, ws_bytes < plan.pk.ws_bytes ? ws_bytes : plan.pk.ws_bytes, st);
     if (plan.sg.use) {
@@ -942,23 +993,34 @@ hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const WgradPlan& plan
     else if (plan.tap) e = vec ? dispatch_bf16<true, true>(p, plan, st) : dispatch_bf16<false, true>(p, plan, st);
     else e = vec ? dispatch_bf16<true, false>(p, plan, st) : dispatch_bf16<false, false>(p, plan, st);
     if (e != hipSuccess) return e;
-    return launch_wgrad_reduce((const float*)ws, dw, plan.splits, beta, plan.tap, g.K, g.C, p.RS, (const float*)p.db_out, db, plan.splits, st);
+    return launch_wgrad_reduce((const float*)ws, dw, plan.splits, beta, plan.tap, g.K, g.C, p.RS, (const float*)p.db_out, db, plan.splits, st, 0, finish);
 }
 
 hipError_t launch_wgrad_reduce(const float* partial, float* dw, int splits, float beta, bool tap_major, int K, int C, int RS,
-                               const float* db_partial, float* db, int db_rows, hipStream_t st, int tile) {
+                               const float* db_partial, float* db, int db_rows, hipStream_t st, int tile, const WgradFinish* finish) {
     const int n = K * C * RS;
+    const WgradFinish fin = finish ? *finish : WgradFinish{};
     // 16-byte packets need aligned rows in both sets of partials (the scratch itself is aligned)
     const bool vec4 = n % 4 == 0;   // (the bias-gradient partials take an element-wise path when K % 4 != 0)
+    if ((RS == 1 || (!tap_major && !tile)) && splits <= (vec4 ? 32 : 16) && n >= kFewElements &&
+        (!db || (db_rows == splits && (!vec4 || K % 4 == 0)))) {
+        const int each = vec4 ? 1024 : 256;
+        const int dw_blocks = (int)((n + (long long)each - 1) / each), db_blocks = db ? (K + each - 1) / each : 0;
+        const auto kernel = vec4 ? (finish ? wgrad_reduce_few_kernel<4, true> : wgrad_reduce_few_kernel<4, false>)
+                                 : (finish ? wgrad_reduce_few_kernel<1, true> : wgrad_reduce_few_kernel<1, false>);
+        hipLaunchKernelGGL(kernel, dim3(dw_blocks + db_blocks), dim3(256), 0, st,
+                           partial, dw, n, splits, beta, C, dw_blocks, db_partial, db, K, fin);
+        return hipGetLastError();
+    }
     if (vec4) {
         const int dw_blocks = (n + 31) / 32, db_blocks = db ? (K + 31) / 32 : 0;
-        hipLaunchKernelGGL(wgrad_reduce_vec_kernel, dim3(dw_blocks + db_blocks), dim3(256), 0, st,
-                           partial, dw, n, splits, beta, tap_major ? 1 : 0, tile, K, C, RS, dw_blocks, db_partial, db, db_rows);
+        hipLaunchKernelGGL((finish ? wgrad_reduce_vec_kernel<true> : wgrad_reduce_vec_kernel<false>), dim3(dw_blocks + db_blocks), dim3(256), 0, st,
+                           partial, dw, n, splits, beta, tap_major ? 1 : 0, tile, K, C, RS, dw_blocks, db_partial, db, db_rows, fin);
         return hipGetLastError();
     }
     const int dw_blocks = (n + 15) / 16, db_blocks = db ? (K + 15) / 16 : 0;
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(dw_blocks + db_blocks), dim3(256), 0, st,
-                       partial, dw, n, splits, beta, tap_major ? 1 : 0, tile, K, C, RS, dw_blocks, db_partial, db, db_rows);
+    hipLaunchKernelGGL((finish ? wgrad_reduce_kernel<true> : wgrad_reduce_kernel<false>), dim3(dw_blocks + db_blocks), dim3(256), 0, st,
+                       partial, dw, n, splits, beta, tap_major ? 1 : 0, tile, K, C, RS, dw_blocks, db_partial, db, db_rows, fin);
     return hipGetLastError();
 }
 

@@ -216,7 +216,7 @@ hipError_t launch(const FcDirectParams& q, hipStream_t st) {
 // Whether a pass goes here: its time (fitted to 260 layers drawn from 1 - 256 images, 64 - 9216 inputs, 10 - 4096 outputs: 0.6 - 1.5 of
 // the measured ones) against that of the kernels it would take otherwise (their launches, operands at 4.5 TB/s, and the arithmetic they reach).
 // us, otherwise / here: y fp32 185 x 499 x 1333 (images, inputs, outputs) 14.6 / 7.2, 64 x 4096 x 1000 17.6 / 34 (stays); dx bf16 34 x 2243 x 2795
-// 66 / 18, 128 x 9216 x 4096 38 / 125 (stays); dw bf16 20 x 5327 x 1781 217 / 28, 16 x 4096 x 4096 21 / 40 (stays).
+// 66 / 18, 128 x 9216 x 4096 38 / 125 (stays); dw bf16 3 x 3273 x 2559 35 / 24, 281 x 2011 x 2591 43 / 55 and 16 x 4096 x 4096 21 / 40 (stay).
 bool fc_direct_faster(int pass, int64_t N, int64_t C, int64_t K, int dtype) {
     const bool f32 = dtype == PURINE_F32;
     const int64_t es = f32 ? 4 : 2, most = (1ll << 30) / es;
@@ -228,15 +228,16 @@ bool fc_direct_faster(int pass, int64_t N, int64_t C, int64_t K, int dtype) {
     const double bytes = (grad ? 4.0 : (double)es) * K * C, flops = 2e-6 * (double)N * C * K;
     if (pass == PURINE_CONV_FWD)
         return f32 ? 1.1 * (3.5 + 1.17 * chain + 1.4e-3 * tiles + 0.44 * work) < 9.0 + bytes / 4.5e6 + flops / 150.0
-                   : 1.15 * (2.5 + 0.88 * chain + 0.27 * work) < 11.0 + bytes / 4.5e6 + flops / 400.0;
+                   : 1.15 * (2.5 + 0.88 * chain + 0.35 * work) < 9.4 + 0.02 * (double)(N < 80 ? N : 80) + bytes / 4.5e6 + flops / 400.0;
     if (!grad) {
         if (f32) return K > 16 && 1.1 * (3.5 + 0.86 * chain + 2.25e-3 * tiles + 0.42 * work) < 9.5 + bytes / 4.5e6 + flops / 120.0;
         // (rows of w that are no whole packets have no kernel of their own otherwise)
         return C % 8 == 0 ? 1.1 * (3.4 + 0.55 * chain + 0.73e-3 * tiles + 0.31 * work) < 6.3 + bytes / 4.5e6 + flops / 400.0 : 0.31 * work < 60.0;
     }
-    if (!f32 && N % 8 != 0) return true;      // (nor have these)
-    const double here = f32 ? 5.5 + 1.3 * (1.97e-3 * tiles + 0.69 * work) : 4.7 + 1.3 * (1.41e-3 * tiles + 0.72 * work);
-    return here < (f32 ? N <= 32 ? 7.0 : 10.0 : 11.5) + bytes / 4.5e6 + flops / (f32 ? 120.0 : 400.0);
+    if (f32) return 5.5 + 1.3 * (1.97e-3 * tiles + 0.69 * work) < (N <= 32 ? 7.0 : 10.0) + bytes / 4.5e6 + flops / 120.0;
+    // (whose operands there are transposed first, and read in pieces if their rows then are no whole packets)
+    const double pieces = N % 8 != 0 ? 1.5 + 2.1e-6 * (double)K * C : 0.0;
+    return 1.1 * (4.7 + 1.41e-3 * tiles + 0.72 * work) < 11.0 + 0.022 * (double)N + bytes / 4.5e6 + flops / 400.0 + pieces;
 }
 
 hipError_t launch_fc_direct(int pass, int dtype, const void* a, const void* b, void* out, const void* bias, float* db, float beta, int64_t N, int64_t C,

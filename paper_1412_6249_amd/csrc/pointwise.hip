@@ -1,19 +1,13 @@
 // HBM-bound operators: Bias / BiasBwd of the convolution layer (paper Figure 1(b)) and the exact
 // support operators (ReLU, max-pool, channel copy, fan-in sum) that chain layers together.
 // All of them stream each tensor once with coalesced accesses; none uses atomics.
+#include "bf16.h"
 #include "common.h"
 #include <type_traits>
 
 namespace purine {
 namespace {
 
-__device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
-__device__ __forceinline__ uint16_t f2bf(float v) {
-    uint32_t u = __float_as_uint(v);
-    uint32_t r = u + 0x7FFFu + ((u >> 16) & 1u);
-    if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x007FFFFFu)) r = 0x7FC00000u;
-    return (uint16_t)(r >> 16);
-}
 template <typename T> __device__ __forceinline__ float ldf(const T* p, size_t i);
 template <> __device__ __forceinline__ float ldf<float>(const float* p, size_t i) { return p[i]; }
 template <> __device__ __forceinline__ float ldf<uint16_t>(const uint16_t* p, size_t i) { return bf2f(p[i]); }
@@ -211,15 +205,6 @@ __global__ __launch_bounds__(256) void fc_bias_bwd_kernel(const T* __restrict__ 
         const float t = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
         db[k] = beta != 0.0f ? db[k] + t : t;
     }
-}
-
-// bf16 fully-connected forward, last step: y[n][k] = bf16(acc[n][k] + b[k]) from the fp32 product
-// matrix (one rounding, to nearest even, after the bias is added in fp32). b may be null.
-__global__ __launch_bounds__(TPB) void fc_finish_bf16_kernel(const float* __restrict__ acc, const uint16_t* __restrict__ b,
-                                                             uint16_t* __restrict__ y, int K, size_t n) {
-    const size_t stride = (size_t)gridDim.x * TPB;
-    for (size_t i = (size_t)blockIdx.x * TPB + threadIdx.x; i < n; i += stride)
-        y[i] = f2bf(acc[i] + (b ? bf2f(b[i % (size_t)K]) : 0.0f));
 }
 
 // out[c][r] = in[r][c] for two dense 2-byte matrices of `rows` x cols0 and `rows` x cols1 elements in
@@ -1007,14 +992,6 @@ hipError_t launch_bias_rows(const float* b, float* y, int N, int K, hipStream_t 
     const size_t n = (size_t)N * K;
     (void)hipGetLastError();
     hipLaunchKernelGGL(bias_rows_kernel, dim3(blocks_for(n)), dim3(TPB), 0, st, b, y, K, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_fc_finish_bf16(const float* acc, const void* b, void* y, int N, int K, hipStream_t st) {
-    const size_t n = (size_t)N * K;
-    (void)hipGetLastError();
-    hipLaunchKernelGGL(fc_finish_bf16_kernel, dim3(blocks_for(n)), dim3(TPB), 0, st, acc, (const uint16_t*)b,
-                       (uint16_t*)y, K, n);
     return hipGetLastError();
 }
 
