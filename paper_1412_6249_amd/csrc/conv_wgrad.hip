@@ -610,7 +610,7 @@ __device__ __forceinline__ int place_in_dw(int i, int tap_major, int tile, int K
 }
 
 // Element i of the bf16 fully-connected forward product: the bias is added in fp32, then one rounding, to nearest even. The second pass
-// does it while it has the sum; as a pass of its own over an fp32 matrix it was 4.7 us more of fc_fwd's 42 (256 x 4096 x 4096).
+// does it while it has the sum; as a pass of its own over an fp32 matrix it was 4.8 of fc_fwd's 44 us (128 images, 9216 -> 4096).
 __device__ __forceinline__ uint16_t finished(float sum, const WgradFinish& fin, int i, int C) {
     return f2bf(sum + (fin.bias ? bf2f(fin.bias[i % C]) : 0.0f));
 }
@@ -736,9 +736,9 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float* __re
 
 // The same sums in the same order (the same bits) for many elements, in their order in dw, of few splits: no more than the split lanes of
 // the two kernels above, which therefore add one partial each. A thread adds all the splits of V elements: there, lanes without a
-// split have nothing to read and each sum goes through LDS. Bound: HBM. us, there / here: 16 splits of 256 x 4096 10.0 / 7.6, 8 of
+// split have nothing to read and each sum goes through LDS. Bound: HBM. us, there / here: 16 splits of 128 x 4096 10.0 / 7.6, 8 of
 // 500 x 1000 9.2 / 5.1.
-constexpr int kFewElements = 1 << 17;   // from here on there are enough threads without the split lanes (4 x 32 x 4096: 4.9 / 4.7 us)
+constexpr int kFewElements = 1 << 17;   // from here on there are enough threads without the split lanes (16 splits of 32 x 4096: 4.9 / 4.7 us)
 template <int V, bool FIN>
 __global__ __launch_bounds__(256) void wgrad_reduce_few_kernel(const float* __restrict__ partial, float* __restrict__ dw, int n, int splits, float beta,
                                                                int C, int dw_blocks, const float* __restrict__ db_partial, float* __restrict__ db, int K,
@@ -942,8 +942,10 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
     if (pl.sg.use) {
         pl.pk.use = pl.rows = pl.cols = pl.taps = pl.tap = false;
         pl.splits = pl.sg.splits;
-        pl.ws_bytes = (size_t)pl.splits * g.K * g.C * g.R * g.S * sizeof(float);
-        pl.db_ws_bytes = (size_t)pl.splits * g.K * sizeof(float);
+        // (A view whose images lie too far apart for it takes one of the others, out of scratch that was sized for dense tensors.)
+        const size_t own = (size_t)pl.splits * g.K * g.C * g.R * g.S * sizeof(float), own_db = (size_t)pl.splits * g.K * sizeof(float);
+        if (own > pl.ws_bytes) pl.ws_bytes = own;
+        if (own_db > pl.db_ws_bytes) pl.db_ws_bytes = own_db;
     }
     return pl;
 }

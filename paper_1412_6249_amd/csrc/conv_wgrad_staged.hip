@@ -546,7 +546,7 @@ WgradStagedPlan plan_wgrad_staged(const ConvGeom& g, int dtype, size_t limit, do
     // (Planes as they lie in memory, 16 MB and more of them: alone a little faster than the general kernel (96 -> 96 channels at 54x54, N = 64 57 and
     // 51 us), but its workgroups want a CU to themselves, and beside another stream's kernels the two wait for each other: the NIN
     // block of 43 images 593 us with it, 529 without. A plan does not know what runs beside it.)
-    if (flat && (xspan + dyspan) * 4 >= (16ll << 20)) return best;
+    if (flat && (long long)g.N * ((long long)g.C * g.H * g.W + (long long)g.K * g.P * g.Q) * 4 >= (16ll << 20)) return best;   // (of views as of dense tensors)
     if (P > (1 << 20) || Qc > (1 << 20) || g.S > 64 || g.sw > 16 || g.sh > 16 || g.ph > 4096 || g.pw > 4096) return best;
     int shift = 0;                     // bands: as many as fill a group of eight, or do not cost more than they bring
     if (!flat)

@@ -125,3 +125,22 @@ def test_infinities(case, dtype):
         assert torch.equal(got[inf], want[inf]) and inf.any()
         ok = torch.isfinite(want)
         np.testing.assert_allclose(got[ok], want[ok], rtol=1e-5)
+
+
+@pytest.mark.parametrize("case", [(12, 192, 28, 28, 16, 1, 1, 1, 0, 256 * 784), (2, 3, 40, 41, 40, 7, 7, 2, 3, 1 << 29), (3, 50, 13, 11, 33, 1, 1, 1, 0, 1 << 28)],
+                         ids=["wide-concat", "first-layer-far", "1x1-far"])
+def test_scratch_of_dense_tensors_is_enough_for_views(case):
+    """The scratch query knows no strides: a slice of a wide tensor, and one whose images lie 1 and 2 GiB apart, run out of it."""
+    import paper_1412_6249_amd as pa
+    N, C, H, W, K, R, S, s, p, ns = case
+    g = torch.Generator().manual_seed(N + K)
+    P, Q = (H + 2 * p - R) // s + 1, (W + 2 * p - S) // s + 1
+    x, dy = torch.randn((N, C, H, W), generator=g), torch.randn((N, K, P, Q), generator=g)
+    wide = torch.empty((N - 1) * ns + K * P * Q + 64, device="cuda")
+    v = torch.as_strided(wide, dy.shape, (ns, P * Q, Q, 1), 0)
+    v.copy_(dy)
+    rw, rb = _ref(x, dy, R, S, s, p)
+    dw, db = _run(pa, pa.conv_desc(s, p), x.cuda(), v, (K, C, R, S), pa.PURINE_F32)
+    # (the general kernels add plain fp32 products)
+    _close(dw, rw, N * P * Q, "dw", "bf16")
+    _close(db, rb, 4 * N * P * Q, "db", "bf16")
