@@ -927,18 +927,14 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
         if (split_packets_forced()) return pl;
     }
     // The kernel that lays its operands out inside LDS, where it is expected to be faster than either: first layers, few channels,
-    // 1x1, small launches. The estimates of the general kernels do not know that their gathers bind them: fp32 first layers take 1.15
-    // times as long as expected, bf16 tiles of fewer than 128 rows up to twice (gathered columns per pixel are the same 128).
-    // (64 channels and more with several taps: the general kernel's tiles of one tap's channels do well, and its time is known
-    // better.) Of 160 fp32 layers drawn from the measured ranges 94 go there and are 1.27 times as fast (geometric mean; three are slower, by 13 %
-    // at most), of 51 bf16 layers 13, 1.42 times as fast.
+    // 1x1, small launches. The estimates of the general kernels do not know that their gathers bind them: fp32 ones with columns of several
+    // taps take 1.2 times as long as expected (16 -> 32 5x5 at 28x28, N = 128: 62 us there, 41 here), bf16 tiles of fewer than 128 rows up to
+    // twice (gathered columns per pixel are the same 128); that of the packed parts is a quarter too high. Of 160 fp32 layers drawn from the measured
+    // ranges 98 go there and are 1.30 times as fast (geometric mean; three are slower, by 6 % at most), of 60 bf16 layers 13, 1.42 times.
     double old = pl.pk.use ? pl.pk.us : us;
-    if (dtype == PURINE_F32) {
-        if (!pl.pk.use && g.C < 16) old *= 1.15;
-    } else if (!pl.tap && pl.bm < 128 && us > 10.0) {
-        old += 0.5 * (us - 10.0) * (128.0 / pl.bm - 1.0);
-    }
-    pl.sg = plan_wgrad_staged(g, dtype, limit, staged_wgrad_forced() ? 1e30 : dtype == PURINE_F32 ? (pl.tap && g.R * g.S > 1 ? 0.75 : 0.92) * old - 2.0 : old - 2.0);
+    if (dtype == PURINE_F32) old *= pl.pk.use ? 0.75 : !pl.tap ? 1.2 : g.R * g.S > 1 ? 1.0 : 0.92;
+    else if (!pl.tap && pl.bm < 128 && us > 10.0) old += 0.5 * (us - 10.0) * (128.0 / pl.bm - 1.0);
+    pl.sg = plan_wgrad_staged(g, dtype, limit, staged_wgrad_forced() ? 1e30 : old - 2.0);
     if (pl.sg.use) {
         pl.pk.use = pl.rows = pl.cols = pl.taps = pl.tap = false;
         pl.splits = pl.sg.splits;
