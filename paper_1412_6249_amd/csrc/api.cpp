@@ -201,10 +201,12 @@ int purine_conv_matrix_products(int pass, const purine_conv_desc* desc, const in
     if (make_geom(desc, x_dim, w_dim, nullptr, &g) != PURINE_OK) return 0;
     bool parts;
     if (pass == PURINE_CONV_BWD_WEIGHT || pass == PURINE_CONV_BWD_WEIGHT_BIAS) {
-        parts = plan_wgrad(g, dtype).pk.use;
+        const WgradPlan pl = plan_wgrad(g, dtype);
+        parts = pl.pk.use || (pl.sg.use && dtype == PURINE_F32);
     } else {
+        // (direct first: the other flags are those of the kernel that a larger launch would run)
         const PixPlan pl = plan_conv_pix(g, pass == PURINE_CONV_BWD_DATA, dtype, false);
-        parts = pl.pk.use || pl.ps.use || (pl.pf.use && pl.pf.split);
+        parts = pl.direct ? dtype == PURINE_F32 : pl.pk.use || pl.ps.use || (pl.pf.use && pl.pf.split);
     }
     return parts ? 6 : 1;
 }

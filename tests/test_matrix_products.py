@@ -14,10 +14,10 @@ def _products(layer, which):
 
 
 @pytest.mark.parametrize("cfg, name, want", [
-    (3, "b3_5x5", (1, 1)),             # backward-data has 16 rows, the weight gradient 16 channels: fp32 kernels
+    (3, "b3_5x5", (1, 6)),             # backward-data has 16 rows: fp32 kernels; the weight gradient's operands are laid out in LDS as parts
     (3, "b2_3x3", (6, 6)),
     (4, "conv2", (6, 6)), (4, "conv4", (6, 6)),
-    (4, "conv1", (1, 1)),              # three channels
+    (4, "conv1", (1, 6)),              # three channels: likewise
     (2, "cccp1", (1, 1)), (5, "c3x3", (1, 1))])
 def test_gradients_of_the_workloads(cfg, name, want):
     layer = next(l for l in CONV_LAYERS[cfg] if l.name == name)
@@ -36,10 +36,20 @@ def test_forward_passes_of_long_sums_depend_on_the_launch():
     (8, 128, 28, 128, 1, (6, 6)), (64, 256, 27, 256, 1, (6, 6)), (64, 96, 54, 96, 1, (1, 1)),
     (18, 555, 27, 575, 1, (1, 1)),       # many row tiles, one workgroup per CU: slower on parts
     (13, 32, 46, 97, 1, (1, 6)),         # two groups of channels forward
-    (30, 251, 60, 189, 2, (1, 1)), (5, 60, 17, 29, 2, (6, 1))])
+    (30, 251, 60, 189, 2, (1, 1)),
+    (5, 60, 17, 29, 2, (6, 6))])         # backward: a small launch
 def test_1x1_layers(n, c, hw, k, stride, want):
     d = pa.conv_desc(stride, 0)
     assert tuple(pa.purine_conv_matrix_products(p, d, (n, c, hw, hw), (k, c, 1, 1), pa.PURINE_F32) for p in (FWD, BWD_DATA)) == want
+
+
+@pytest.mark.parametrize("n, c, h, w, k, r, pad, want", [
+    (2, 38, 8, 9, 42, 3, 1, [6, 6, 6, 6]),       # forward and backward-data in the kernel of small launches, the weight gradient's operands laid out in LDS
+    (1, 272, 26, 26, 126, 1, 0, [6, 6, 6, 6]),
+    (1, 64, 56, 56, 64, 3, 1, [6, 6, 1, 1])])    # the general weight gradient
+def test_small_launches_multiply_parts_in_fp32_alone(n, c, h, w, k, r, pad, want):
+    f = lambda dt: [pa.purine_conv_matrix_products(p, pa.conv_desc(1, pad), (n, c, h, w), (k, c, r, r), dt) for p in range(4)]
+    assert f(pa.PURINE_F32) == want and f(pa.PURINE_BF16) == [1] * 4
 
 
 def test_illegal_shapes_and_passes_give_zero():
