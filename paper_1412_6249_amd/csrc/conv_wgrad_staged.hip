@@ -20,7 +20,8 @@
 // load, neighbouring lanes on neighbouring columns: 247. Loads with lanes along channels ask for each line once per lane: 8800 cycles a
 // chunk to issue them instead of 3000.)
 //
-// Whole operator, general kernel before / now, us: that layer 311 / 272; 3 -> 170 7x7 / 2 at 174x175, N = 88 671 / 349; 3 -> 344 7x7 / 2 at
+// Whole operator, general kernel before / here, us: that layer 311 / 272 (with sums copied after every chunk and a quarter of them through
+// memory; 254 then and 214 now over three sets of tensors in turn); 3 -> 170 7x7 / 2 at 174x175, N = 88 671 / 349; 3 -> 344 7x7 / 2 at
 // 199x199, N = 10 265 / 123; 272 -> 126 1x1 at 26x26, N = 1 15 / 10; 16 -> 32 5x5 at 28x28, N = 128 60 / 39; bf16 3 -> 139 7x7 / 2 at
 // 184x186, N = 106 638 / 158; 3 -> 220 7x7 / 2 at 65x66, N = 140 157 / 61.
 #include <type_traits>
@@ -413,6 +414,15 @@ __global__ __launch_bounds__(WM * WN * 64 + 2 * LOADERS, 2) void wgrad_staged_ke
                     for (int b = 0; b < TN; ++b) hi[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av2[a], bv2[b], hi[a][b], 0, 0, 0);
             }
         }
+        // (The sums stay where they are from chunk to chunk: used element by element after the loop, they were copied element by element at the
+        // end of every chunk, and 27 of 96 went through memory: 182 MB written beside conv1's 12 MB of partial sums.)
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+            for (int b = 0; b < TN; ++b) {
+                asm volatile("" : "+v"(hi[a][b]));
+                if constexpr (PL == 3) asm volatile("" : "+v"(lo[a][b]));
+            }
     }
     meet();
 
