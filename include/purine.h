@@ -477,7 +477,9 @@ void purine_set_kernel_probe(void* start_event, void* stop_event);
  * the automatic choice.
  * (-11, tile) sends weight gradients through the kernel that lays its operands out inside LDS, with that tile
  * (rows * 1000 + columns: 128128, 96128, 64256, 64128, 32256, 32128) or the one it would take (0).
- * (-12, anything) sends forward and backward-data through the kernel of small launches wherever it applies.
+ * (-12, anything) sends forward, backward-data and fully-connected passes through the kernels of small launches wherever they
+ * apply; (-13, anything) sends nothing through those, the weight gradient inside LDS or the second pass of few splits: every call
+ * runs what larger launches run.
  * (anything, -1) makes every kernel take ordinary global loads with explicit zero fill instead of
  * range-checked raw buffer loads (the path tensors of 2 GiB and more take anyway). */
 void purine_debug_force_tile(int bm, int bn);

@@ -14,6 +14,12 @@ extern "C" {
 int purine_conv_matrix_products(int pass, const purine_conv_desc* desc, const int64_t x_dim[4],
                                 const int64_t w_dim[4], int32_t dtype);
 
+/* Which of the kernels that the test hooks (-11) to (-13) of purine_debug_force_tile name a pass runs, or 0 for any other (and for
+ * an illegal shape). The launch's own plan for dense tensors, hooks included. */
+enum { PURINE_ROUTE_OTHER = 0, PURINE_ROUTE_SMALL_LAUNCH = 1, PURINE_ROUTE_INSIDE_LDS = 2 };
+int purine_conv_route(int pass, const purine_conv_desc* desc, const int64_t x_dim[4], const int64_t w_dim[4], int32_t dtype);
+int purine_fc_route(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype);
+
 #ifdef __cplusplus
 }
 #endif

@@ -143,6 +143,10 @@ EXPORTED = sorted(_SIGS)
 # include/purine_introspect.h
 _lib.purine_conv_matrix_products.restype = ctypes.c_int
 _lib.purine_conv_matrix_products.argtypes = [ctypes.c_int, _D, _i64p, _i64p, ctypes.c_int32]
+_lib.purine_conv_route.restype = ctypes.c_int
+_lib.purine_conv_route.argtypes = [ctypes.c_int, _D, _i64p, _i64p, ctypes.c_int32]
+_lib.purine_fc_route.restype = ctypes.c_int
+_lib.purine_fc_route.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int32]
 
 
 # ------------------------------------------------------------------ marshalling helpers
@@ -254,6 +258,17 @@ def purine_conv_workspace_bytes(which, desc, x_shape, w_shape, dtype):
 def purine_conv_matrix_products(which, desc, x_shape, w_shape, dtype):
     return int(_lib.purine_conv_matrix_products(int(which), _ref(desc), _dims(x_shape),
                                                 _dims(w_shape), int(dtype)))
+
+
+PURINE_ROUTE_OTHER, PURINE_ROUTE_SMALL_LAUNCH, PURINE_ROUTE_INSIDE_LDS = 0, 1, 2
+
+
+def purine_conv_route(which, desc, x_shape, w_shape, dtype):
+    return int(_lib.purine_conv_route(int(which), _ref(desc), _dims(x_shape), _dims(w_shape), int(dtype)))
+
+
+def purine_fc_route(which, N, C, K, dtype):
+    return int(_lib.purine_fc_route(int(which), int(N), int(C), int(K), int(dtype)))
 
 
 def purine_bias_bwd_workspace_bytes(dy_shape, dtype):

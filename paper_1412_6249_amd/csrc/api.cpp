@@ -211,6 +211,15 @@ int purine_conv_matrix_products(int pass, const purine_conv_desc* desc, const in
     return parts ? 6 : 1;
 }
 
+int purine_conv_route(int pass, const purine_conv_desc* desc, const int64_t x_dim[4], const int64_t w_dim[4], int32_t dtype) {
+    if (pass < PURINE_CONV_FWD || pass > PURINE_CONV_BWD_WEIGHT_BIAS) return PURINE_ROUTE_OTHER;
+    if (!desc || !x_dim || !w_dim || !is_float_dtype(dtype)) return PURINE_ROUTE_OTHER;
+    ConvGeom g;
+    if (make_geom(desc, x_dim, w_dim, nullptr, &g) != PURINE_OK) return PURINE_ROUTE_OTHER;
+    if (pass >= PURINE_CONV_BWD_WEIGHT) return plan_wgrad(g, dtype).sg.use ? PURINE_ROUTE_INSIDE_LDS : PURINE_ROUTE_OTHER;
+    return plan_conv_pix(g, pass == PURINE_CONV_BWD_DATA, dtype, false).direct ? PURINE_ROUTE_SMALL_LAUNCH : PURINE_ROUTE_OTHER;
+}
+
 size_t purine_bias_bwd_workspace_bytes(const int64_t dy_dim[4], int32_t dtype) {
     if (!dy_dim || !is_float_dtype(dtype)) return 0;
     for (int i = 0; i < 4; ++i)
@@ -817,6 +826,11 @@ size_t purine_fc_workspace_bytes(int pass, int64_t N, int64_t C, int64_t K, int3
         return fc_general_workspace_bytes(pass, N, C, K, dtype);
     const FcPlan f = fc_plan(pass, N, C, K, dtype);
     return f.k.use ? f.need : fc_general_workspace_bytes(pass, N, C, K, dtype);
+}
+
+int purine_fc_route(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype) {
+    if (pass < PURINE_CONV_FWD || pass > PURINE_CONV_BWD_WEIGHT_BIAS || N < 1 || C < 1 || K < 1 || !is_float_dtype(dtype)) return PURINE_ROUTE_OTHER;
+    return fc_direct_faster(pass, N, C, K, dtype) ? PURINE_ROUTE_SMALL_LAUNCH : PURINE_ROUTE_OTHER;
 }
 
 namespace {

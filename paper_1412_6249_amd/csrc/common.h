@@ -156,7 +156,8 @@ bool split_patch_forced();           // test hook: (-6, parts): fp32 layers run 
 bool split_packets_forced();         // test hook: (-7, anything): ... the kernels on packed bf16 parts (forward, backward-data, weight gradient)
 bool staged_wgrad_forced();          // test hook: (-11, tile): weight gradients run the kernel that lays its operands out in LDS, with that tile (bm * 1000 + bn) or its own
 int staged_wgrad_tile();
-bool conv_direct_forced();           // test hook: (-12, anything): forward and backward-data run the kernel of small launches wherever it applies
+bool direct_forced();                // test hook: (-12, anything): forward, backward-data and fully-connected passes run the kernels of small launches wherever they apply
+bool small_kernels_disabled();       // test hook: (-13, anything): nothing runs them, the weight gradient inside LDS or the second pass of few splits
 bool patch_split_roles_forced();     // test hook: (-5, anything) gives it layers of few tiles too
 bool patch_split_roles_disabled();   // tuning hook: (-4, anything) keeps the bf16 patch kernel on its one-role form
 bool buffer_loads_disabled();   // tuning hook: (anything, -1) given to force_pix_tile

@@ -931,6 +931,7 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
     // taps take 1.2 times as long as expected (16 -> 32 5x5 at 28x28, N = 128: 62 us there, 41 here), bf16 tiles of fewer than 128 rows up to
     // twice (gathered columns per pixel are the same 128); that of the packed parts is a quarter too high. Of 160 fp32 layers drawn from the measured
     // ranges 98 go there and are 1.30 times as fast (geometric mean; three are slower, by 6 % at most), of 60 bf16 layers 13, 1.42 times.
+    if (small_kernels_disabled()) return pl;
     double old = pl.pk.use ? pl.pk.us : us;
     if (dtype == PURINE_F32) old *= pl.pk.use ? 0.75 : !pl.tap ? 1.2 : g.R * g.S > 1 ? 1.0 : 0.92;
     else if (!pl.tap && pl.bm < 128 && us > 10.0) old += 0.5 * (us - 10.0) * (128.0 / pl.bm - 1.0);
@@ -1000,7 +1001,7 @@ hipError_t launch_wgrad_reduce(const float* partial, float* dw, int splits, floa
     const WgradFinish fin = finish ? *finish : WgradFinish{};
     // 16-byte packets need aligned rows in both sets of partials (the scratch itself is aligned)
     const bool vec4 = n % 4 == 0;   // (the bias-gradient partials take an element-wise path when K % 4 != 0)
-    if ((RS == 1 || (!tap_major && !tile)) && splits <= (vec4 ? 32 : 16) && n >= kFewElements &&
+    if ((RS == 1 || (!tap_major && !tile)) && splits <= (vec4 ? 32 : 16) && n >= kFewElements && !small_kernels_disabled() &&
         (!db || (db_rows == splits && (!vec4 || K % 4 == 0)))) {
         const int each = vec4 ? 1024 : 256;
         const int dw_blocks = (int)((n + (long long)each - 1) / each), db_blocks = db ? (K + each - 1) / each : 0;

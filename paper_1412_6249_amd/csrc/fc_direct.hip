@@ -220,7 +220,8 @@ hipError_t launch(const FcDirectParams& q, hipStream_t st) {
 bool fc_direct_faster(int pass, int64_t N, int64_t C, int64_t K, int dtype) {
     const bool f32 = dtype == PURINE_F32;
     const int64_t es = f32 ? 4 : 2, most = (1ll << 30) / es;
-    if (buffer_loads_disabled() || N >= most || C >= most || K >= most || N * C >= most || K * C >= most / 2 || N * K >= most) return false;
+    if (buffer_loads_disabled() || N >= most || C >= most || K >= most || N * C >= most || K * C >= most / 2 || N * K >= most || small_kernels_disabled()) return false;
+    if (direct_forced()) return true;
     const bool grad = pass >= PURINE_CONV_BWD_WEIGHT;
     const int64_t rows = grad ? K : N, cols = pass == PURINE_CONV_FWD ? K : C, len = pass == PURINE_CONV_FWD ? C : grad ? N : K;
     const double steps = (double)((len + 15) / 16), tiles = (double)((rows + 31) / 32) * (double)((cols + 31) / 32), work = tiles * steps * 1e-3;

@@ -1,0 +1,42 @@
+"""Which kernel a call goes to (host code): the test hooks do what they say, and the dispatch lines lie where both sides were measured."""
+import pytest
+
+import paper_1412_6249_amd as pa
+
+FWD, BWD_DATA, BWD_WEIGHT = range(3)
+F32, BF16 = pa.PURINE_F32, pa.PURINE_BF16
+SMALL = ((2, 38, 8, 9), (42, 38, 3, 3))
+
+
+def _conv(dtype, x=SMALL[0], w=SMALL[1]):
+    return [pa.purine_conv_route(p, pa.conv_desc(1, w[2] // 2), x, w, dtype) for p in range(4)]
+
+
+def _fc(dtype, *nck):
+    return [pa.purine_fc_route(p, *nck, dtype) for p in range(3)]
+
+
+@pytest.fixture
+def hook():
+    yield lambda v: pa.purine_debug_force_tile(v, 0)
+    pa.purine_debug_force_tile(0, 0)
+
+
+def test_hooks(hook):
+    large = ((128, 96, 27, 27), (256, 96, 5, 5))
+    assert _conv(F32) == [1, 1, 2, 2] and _fc(F32, 20, 300, 100) == [1] * 3 and _fc(BF16, 128, 9216, 4096) == [0] * 3
+    assert _conv(F32, *large)[:2] == [0, 0]
+    hook(-12)
+    assert _conv(BF16)[:2] == [1, 1] and _conv(F32, *large)[:2] == [1, 1] and _fc(BF16, 128, 9216, 4096) == [1] * 3
+    hook(-11)
+    assert _conv(F32, *large) == [0, 0, 2, 2]
+    hook(-13)
+    assert _conv(F32) == _conv(BF16) == [0] * 4 and _fc(F32, 20, 300, 100) == [0] * 3
+    hook(0)
+    assert _conv(F32) == [1, 1, 2, 2]
+
+
+def test_illegal_calls_have_no_route():
+    assert pa.purine_conv_route(FWD, pa.conv_desc(1, 0), (1, 3, 2, 2), (4, 3, 3, 3), F32) == 0
+    assert pa.purine_conv_route(4, pa.conv_desc(1, 1), *SMALL, F32) == 0 and pa.purine_fc_route(FWD, 0, 4, 4, F32) == 0
+    assert pa.purine_fc_route(FWD, 4, 4, 4, pa.PURINE_I32) == 0
