@@ -752,7 +752,12 @@ int fc_stream_checks(const FcPlan& f, const purine_tensor* out, const purine_ten
     return PURINE_OK;
 }
 
-// Passes in one launch (fc_direct_faster) need no scratch, but what the query asks for has to be there all the same.
+bool goes_direct(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype) {
+    const bool splits = pass >= PURINE_CONV_BWD_WEIGHT && N > 256 &&
+                        (dtype == PURINE_F32 ? fc_stream_plan(PURINE_CONV_BWD_WEIGHT, N, C, K).use : !fc_wgrad_bf16_applies(N, C, K));
+    return fc_direct_faster(pass, N, C, K, dtype, splits);
+}
+// Passes in one launch (goes_direct) need no scratch, but what the query asks for has to be there all the same.
 int fc_direct_checks(int pass, const purine_tensor* out, const purine_tensor* a, const purine_tensor* b, int64_t N, int64_t C, int64_t K, const void* ws,
                      size_t ws_bytes) {
     if (overlaps(out, a) || overlaps(out, b)) return PURINE_E_LAYOUT;
@@ -830,7 +835,7 @@ size_t purine_fc_workspace_bytes(int pass, int64_t N, int64_t C, int64_t K, int3
 
 int purine_fc_route(int pass, int64_t N, int64_t C, int64_t K, int32_t dtype) {
     if (pass < PURINE_CONV_FWD || pass > PURINE_CONV_BWD_WEIGHT_BIAS || N < 1 || C < 1 || K < 1 || !is_float_dtype(dtype)) return PURINE_ROUTE_OTHER;
-    return fc_direct_faster(pass, N, C, K, dtype) ? PURINE_ROUTE_SMALL_LAUNCH : PURINE_ROUTE_OTHER;
+    return goes_direct(pass, N, C, K, dtype) ? PURINE_ROUTE_SMALL_LAUNCH : PURINE_ROUTE_OTHER;
 }
 
 namespace {
@@ -875,7 +880,7 @@ int purine_fc_fwd(const purine_tensor* x, const purine_tensor* w, const purine_t
     }
     {
         const int64_t N = x->dim[0], C = x->dim[1], K = w->dim[0];
-        if (fc_direct_faster(PURINE_CONV_FWD, N, C, K, x->dtype)) {
+        if (goes_direct(PURINE_CONV_FWD, N, C, K, x->dtype)) {
             if ((rc = fc_direct_checks(PURINE_CONV_FWD, y, x, w, N, C, K, ws, ws_bytes))) return rc;
             return hip_status(launch_fc_direct(PURINE_CONV_FWD, x->dtype, x->data, w->data, y->data, b ? b->data : nullptr, nullptr, 0.0f, N, C, K,
                                                (hipStream_t)hip_stream));
@@ -921,7 +926,7 @@ int purine_fc_bwd_data(const purine_tensor* dy, const purine_tensor* w, purine_t
     if ((rc = check_fc(dx, w, dy))) return rc;
     {
         const int64_t N = dy->dim[0], C = w->dim[1], K = w->dim[0];
-        if (fc_direct_faster(PURINE_CONV_BWD_DATA, N, C, K, dy->dtype)) {
+        if (goes_direct(PURINE_CONV_BWD_DATA, N, C, K, dy->dtype)) {
             if ((rc = fc_direct_checks(PURINE_CONV_BWD_DATA, dx, dy, w, N, C, K, ws, ws_bytes))) return rc;
             return hip_status(launch_fc_direct(PURINE_CONV_BWD_DATA, dy->dtype, dy->data, w->data, dx->data, nullptr, nullptr, 0.0f, N, C, K,
                                                (hipStream_t)hip_stream));
@@ -964,7 +969,7 @@ int purine_fc_bwd_weight(const purine_tensor* x, const purine_tensor* dy, purine
         if (db->dim[0] != dw->dim[0]) return PURINE_E_SHAPE;
         if (overlaps(db, dy) || overlaps(db, x) || overlaps(db, dw)) return PURINE_E_LAYOUT;
     }
-    if (fc_direct_faster(PURINE_CONV_BWD_WEIGHT, N, C, K, x->dtype)) {
+    if (goes_direct(PURINE_CONV_BWD_WEIGHT, N, C, K, x->dtype)) {
         if ((rc = fc_direct_checks(PURINE_CONV_BWD_WEIGHT, dw, dy, x, N, C, K, ws, ws_bytes))) return rc;
         return hip_status(launch_fc_direct(PURINE_CONV_BWD_WEIGHT, x->dtype, dy->data, x->data, dw->data, nullptr, db ? (float*)db->data : nullptr, beta, N, C, K,
                                            (hipStream_t)hip_stream));

@@ -287,7 +287,7 @@ bool fc_wgrad_bf16_applies(int64_t N, int64_t C, int64_t K);
 hipError_t launch_fc_wgrad_bf16(const void* dyT, const void* xT, float* dw, int N, int K, int C, bool accumulate,
                                 hipStream_t st);
 // fully-connected passes in one launch without scratch (fc_direct.hip); db: the weight gradient's bias gradient
-bool fc_direct_faster(int pass, int64_t N, int64_t C, int64_t K, int dtype);
+bool fc_direct_faster(int pass, int64_t N, int64_t C, int64_t K, int dtype, bool other_splits);
 hipError_t launch_fc_direct(int pass, int dtype, const void* a, const void* b, void* out, const void* bias, float* db, float beta, int64_t N, int64_t C,
                             int64_t K, hipStream_t st);
 hipError_t launch_relu_view(int dtype, bool bwd, const void* x, const void* dy, void* out, int N, int run,

@@ -217,7 +217,13 @@ hipError_t launch(const FcDirectParams& q, hipStream_t st) {
 // the measured ones) against that of the kernels it would take otherwise (their launches, operands at 4.5 TB/s, and the arithmetic they reach).
 // us, otherwise / here: y fp32 185 x 499 x 1333 (images, inputs, outputs) 14.6 / 7.2, 64 x 4096 x 1000 17.6 / 34 (stays); dx bf16 34 x 2243 x 2795
 // 66 / 18, 128 x 9216 x 4096 38 / 125 (stays); dw bf16 3 x 3273 x 2559 35 / 24, 281 x 2011 x 2591 43 / 55 and 16 x 4096 x 4096 21 / 40 (stay).
-bool fc_direct_faster(int pass, int64_t N, int64_t C, int64_t K, int dtype) {
+// other_splits (weight gradients of more than 256 images): the kernel it would take otherwise has its reduction over workgroups. A wavefront here
+// walks N / 256 steps by itself, which more images than the layers above had make the longer way (both sides again fitted to 425
+// layers of 257 - 262144 images without db; half of db's time counts against the other kernel, which has a launch of its own for it; the bits
+// of dw must not depend on db). us without db, otherwise / here: fp32 32 x 32 at 1024 images 14.4 / 11.9, at 8192 19.6 / 49, at 65536
+// 69 / 344; bf16 43 x 33 at 225580 56 / 1062 (these but the first stay). Where the other kernel does not split, it is the slower one at any
+// length: fp32 53 x 49 at 752 25 / 11, bf16 512 x 512 at 262144 4962 / 1179.
+bool fc_direct_faster(int pass, int64_t N, int64_t C, int64_t K, int dtype, bool other_splits) {
     const bool f32 = dtype == PURINE_F32;
     const int64_t es = f32 ? 4 : 2, most = (1ll << 30) / es;
     if (buffer_loads_disabled() || N >= most || C >= most || K >= most || N * C >= most || K * C >= most / 2 || N * K >= most || small_kernels_disabled()) return false;
@@ -234,6 +240,13 @@ bool fc_direct_faster(int pass, int64_t N, int64_t C, int64_t K, int dtype) {
         if (f32) return K > 16 && 1.1 * (3.5 + 0.86 * chain + 2.25e-3 * tiles + 0.42 * work) < 9.5 + bytes / 4.5e6 + flops / 120.0;
         // (rows of w that are no whole packets have no kernel of their own otherwise)
         return C % 8 == 0 ? 1.1 * (3.4 + 0.55 * chain + 0.73e-3 * tiles + 0.31 * work) < 6.3 + bytes / 4.5e6 + flops / 400.0 : 0.31 * work < 60.0;
+    }
+    if (other_splits) {
+        const double big = (double)((K + 127) / 128) * (double)((C + 127) / 128), db = 0.6e-6 * (double)N * K;
+        const double here = 2.4 + (f32 ? 1.2 : 0.98) * chain + 5.9e-3 * tiles + (f32 ? 0.3 : 0.2) * work;
+        const double split = f32 ? 11.7 + 0.57e-3 * (double)N + 2.5e-6 * (double)K * C + 0.23e-3 * big * (double)N
+                                 : 15.9 + 1.2e-6 * (double)N * (double)(C + K) + 17.5e-6 * (double)K * C + 0.091e-3 * big * (double)N;
+        if (here > split + db) return false;
     }
     if (f32) return 5.5 + 1.3 * (1.97e-3 * tiles + 0.69 * work) < (N <= 32 ? 7.0 : 10.0) + bytes / 4.5e6 + flops / 120.0;
     // (whose operands there are transposed first, and read in pieces if their rows then are no whole packets)

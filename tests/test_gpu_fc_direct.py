@@ -59,6 +59,25 @@ def test_fc_direct(case, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,K", [(256, 17), (257, 16), (511, 1), (512, 40), (513, 65), (961, 15), (5000, 33)])
+def test_bias_gradient_of_many_images(N, K, dtype):
+    """On both sides of the row count from which a workgroup takes 16 columns, rows that do not fill its last round; never read past the end."""
+    import paper_1412_6249_amd as pa
+    t, d, ws, td = _data(pa, (N, 24, K), dtype)
+    rb = t["dy"].double().sum(0)
+    dw, db = torch.empty(K, 24, device="cuda"), torch.full((K,), float("nan"), device="cuda")
+    pa.purine_debug_force_tile(-13, 0)
+    try:
+        pa.purine_fc_bwd_weight(d["x"], d["dy"], dw, db, ws=ws(pa.PURINE_CONV_BWD_WEIGHT))
+        first = db.clone()
+        pa.purine_fc_bwd_weight(d["x"], d["dy"], dw, db, beta=1.0, ws=ws(pa.PURINE_CONV_BWD_WEIGHT))
+    finally:
+        pa.purine_debug_force_tile(0, 0)
+    assert float((first.double().cpu() - rb).norm()) <= 1e-7 * float(t["dy"].double().norm()) * N ** 0.5
+    assert torch.equal(db, first + first)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_infinities(dtype):
     """At the ends of rows, where the next row's elements are loaded along with them."""
     import paper_1412_6249_amd as pa

@@ -40,3 +40,12 @@ def test_illegal_calls_have_no_route():
     assert pa.purine_conv_route(FWD, pa.conv_desc(1, 0), (1, 3, 2, 2), (4, 3, 3, 3), F32) == 0
     assert pa.purine_conv_route(4, pa.conv_desc(1, 1), *SMALL, F32) == 0 and pa.purine_fc_route(FWD, 0, 4, 4, F32) == 0
     assert pa.purine_fc_route(FWD, 4, 4, 4, pa.PURINE_I32) == 0
+
+
+@pytest.mark.parametrize("dtype, n, c, k, want", [
+    (F32, 20, 300, 100, 1), (F32, 1024, 32, 32, 1),
+    (F32, 8192, 32, 32, 0), (F32, 65536, 32, 32, 0), (BF16, 225580, 43, 33, 0),      # a chain of n / 256 steps; split over workgroups otherwise
+    (F32, 752, 53, 49, 1), (BF16, 65536, 96, 32, 1), (BF16, 262144, 512, 512, 1)])   # not split otherwise: a longer chain
+def test_fully_connected_weight_gradients_of_many_images(dtype, n, c, k, want):
+    assert pa.purine_fc_route(BWD_WEIGHT, n, c, k, dtype) == want
+    assert pa.purine_fc_route(BWD_WEIGHT + 1, n, c, k, dtype) == want                # the bits of dw do not depend on db
