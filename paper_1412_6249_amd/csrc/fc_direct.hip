@@ -10,6 +10,7 @@
 //
 // Bound: the chain of a few loads, and one launch's 3 us. All three passes together, us, before / now: bf16 3 x 222 x 37 (images,
 // inputs, outputs) 30 / 13, 4 x 957 x 93 33 / 15; fp32 3 x 222 x 37 25 / 14, 226 x 853 x 271 42 / 23.
+#include <cmath>
 #include "packets.h"
 #include "pix_common.h"
 
@@ -238,8 +239,13 @@ bool fc_direct_faster(int pass, int64_t N, int64_t C, int64_t K, int dtype, bool
                    : 1.15 * (2.5 + 0.88 * chain + 0.35 * work) < 9.4 + 0.02 * (double)(N < 80 ? N : 80) + bytes / 4.5e6 + flops / 400.0;
     if (!grad) {
         if (f32) return K > 16 && 1.1 * (3.5 + 0.86 * chain + 2.25e-3 * tiles + 0.42 * work) < 9.5 + bytes / 4.5e6 + flops / 120.0;
-        // (rows of w that are no whole packets have no kernel of their own otherwise)
-        return C % 8 == 0 ? 1.1 * (3.4 + 0.55 * chain + 0.73e-3 * tiles + 0.31 * work) < 6.3 + bytes / 4.5e6 + flops / 400.0 : 0.31 * work < 60.0;
+        if (C % 8 == 0) return 1.1 * (3.4 + 0.55 * chain + 0.73e-3 * tiles + 0.31 * work) < 6.3 + bytes / 4.5e6 + flops / 400.0;
+        // Rows of w that are no whole packets run the general forward convolution otherwise: a chain of slabs of 32 outputs over tiles of 128 x 128, dy
+        // copied as its filter bank. Both sides fitted to 301 layers of 1 - 262144 images (0.64 - 1.4 of the measured times). us, otherwise / here:
+        // 142 x 30 x 3186 51 / 19, 211369 x 30 x 310 192 / 57; 7405 x 2645 x 108 36 / 123, 8975 x 3409 x 91 41 / 167 (stay).
+        const double slabs = (double)((K + 31) / 32), big = (double)((N + 127) / 128) * (double)((C + 127) / 128), rounds = std::ceil(big / 256.0);
+        const double here = 3.0 + 0.7 * chain + tiles * (steps > 32 ? 13.3e-3 : steps > 4 ? 4.0e-3 : 1.7e-3) + 0.186 * work;
+        return here < 5.2 + 0.5 * slabs + 7.7e-3 * rounds * slabs + 12.1e-3 * big + 2.2e-3 * big * slabs + 2.06e-6 * (double)N * K;
     }
     if (other_splits) {
         const double big = (double)((K + 127) / 128) * (double)((C + 127) / 128), db = 0.6e-6 * (double)N * K;

@@ -49,3 +49,10 @@ def test_illegal_calls_have_no_route():
 def test_fully_connected_weight_gradients_of_many_images(dtype, n, c, k, want):
     assert pa.purine_fc_route(BWD_WEIGHT, n, c, k, dtype) == want
     assert pa.purine_fc_route(BWD_WEIGHT + 1, n, c, k, dtype) == want                # the bits of dw do not depend on db
+
+
+@pytest.mark.parametrize("n, c, k, want", [
+    (142, 30, 3186, 1), (211369, 30, 310, 1), (19, 2770, 1599, 1), (64, 333, 100, 1),
+    (7405, 2645, 108, 0), (8975, 3409, 91, 0), (5368, 2700, 203, 0), (6902, 1738, 76, 0), (1027, 4042, 207, 0)])
+def test_bf16_data_gradients_whose_rows_are_no_whole_packets(n, c, k, want):
+    assert pa.purine_fc_route(BWD_DATA, n, c, k, BF16) == want
