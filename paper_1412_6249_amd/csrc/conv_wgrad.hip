@@ -912,6 +912,14 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
     WgradPlan pl = plan_wgrad_general(g, dtype, &us);
     pl.static_bytes = pl.ws_bytes;
     if (buffer_loads_disabled() || (us == 0.0 && !staged_wgrad_forced())) return pl;      // (0: a bf16 kernel of its own, which stays)
+    if (dtype == PURINE_BF16 && !staged_wgrad_forced()) {
+        // (neither do views of them whose images lie too far apart for that kernel: they take the general one)
+        ConvGeom d = g;
+        d.x_ns = g.C * g.H * g.W; d.y_ns = g.K * g.P * g.Q;
+        double dense_us = us;
+        if ((long long)g.N * g.x_ns >= (1LL << 28) || (long long)g.N * g.y_ns >= (1LL << 28)) plan_wgrad_general(d, dtype, &dense_us);
+        if (dense_us == 0.0) return pl;
+    }
     // A layer that the static-scratch entry point takes has to go through its scratch on the same splits (the results are the same bits).
     const size_t limit = pl.ws_bytes <= kStaticScratchBytes ? kStaticScratchBytes : 0;
     // fp32: the kernel on packed bf16 parts where it is expected to be faster. The layout pass costs 10
@@ -939,10 +947,8 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
     if (pl.sg.use) {
         pl.pk.use = pl.rows = pl.cols = pl.taps = pl.tap = false;
         pl.splits = pl.sg.splits;
-        // (A view whose images lie too far apart for it takes one of the others, out of scratch that was sized for dense tensors.)
-        const size_t own = (size_t)pl.splits * g.K * g.C * g.R * g.S * sizeof(float), own_db = (size_t)pl.splits * g.K * sizeof(float);
-        if (own > pl.ws_bytes) pl.ws_bytes = own;
-        if (own_db > pl.db_ws_bytes) pl.db_ws_bytes = own_db;
+        pl.ws_bytes = (size_t)pl.splits * g.K * g.C * g.R * g.S * sizeof(float);
+        pl.db_ws_bytes = (size_t)pl.splits * g.K * sizeof(float);
     }
     return pl;
 }

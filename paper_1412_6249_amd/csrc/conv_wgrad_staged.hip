@@ -80,10 +80,13 @@ __device__ __forceinline__ void meet() {
 
 // The wavefronts that load dy (X = false) or x: chunk after chunk into the two buffers in turn, its loads requested one chunk ahead of
 // their packing. Rows of a tile: BM channels of dy from k0, cw channels of x from c0.
-template <int PL, bool X, bool FLAT, int BM>
+// FAR: images so far apart that a tensor spans 2^31 bytes or more. x_bytes and dy_bytes are an image's, and each image is read through a
+// descriptor of its own (of whole dwords: images of a dense bf16 tensor beside a far one may begin in the middle of one).
+template <int PL, bool X, bool FLAT, bool FAR, int BM>
 __device__ __forceinline__ void load_chunks(const StagedParams& q, unsigned char* smem, int lt, int k0, int c0, int cw, int r_first, int nr, int split, int n, bool do_db) {
     constexpr int ES = PL == 1 ? 2 : 4, U = units_of(PL), DW = PL == 1 ? 3 : 4, DP = BM + 1;
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(X ? q.x : q.dy), (short)0, (int)(X ? q.x_bytes : q.dy_bytes), 0x00020000);
+    unsigned char* const from = static_cast<unsigned char*>(const_cast<void*>(X ? q.x : q.dy));
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(from, (short)0, (int)(X ? q.x_bytes : q.dy_bytes), 0x00020000);
     const int Ws = X ? q.W : q.Q, Hs = X ? q.H : q.P, ns = X ? q.x_ns : q.dy_ns, bands = 1 << q.band_shift;
     const int stride = (X ? q.CtP : DP) * 16, plane = X ? q.x_plane : q.d_plane;
 
@@ -120,9 +123,12 @@ __device__ __forceinline__ void load_chunks(const StagedParams& q, unsigned char
     auto request = [&](int ch, Units& t) {
         const Chunk c = chunk_at(q, ch);
         unsigned vo[U][8];
+        size_t image[8] = {};                              // FAR: where the image begins
         if (FLAT) {
             const int first = c.q0 * 8;
-            const unsigned off = (unsigned)(c.grp * ns + first) * ES;
+            const unsigned off = (unsigned)((FAR ? 0 : c.grp * ns) + first) * ES;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) image[e] = FAR && c.pr_n ? (size_t)c.grp * ns * ES : 0;
             t.c0 = 0; t.c1 = c.pr_n ? min(c.qn * 8, Ws - first) : 0;
             t.cut = t.c1 & 7;
             t.odd = PL == 1 && off & 2 ? 0xffu : 0u;
@@ -143,7 +149,7 @@ __device__ __forceinline__ void load_chunks(const StagedParams& q, unsigned char
             t.cut = X ? t.c0 > q.lead || t.c1 < q.lead + (c.qn - 1) * q.sw + q.S : c.qn & 3;
             t.odd = 0;
             // (The loads themselves stay out of the branch: a register loaded on one side only would be waited for where the sides meet.)
-            if (q.band_shift == 0 && c.grp * 8 + 8 <= q.N) {
+            if (!FAR && q.band_shift == 0 && c.grp * 8 + 8 <= q.N) {
                 // eight whole images: the same rows exist in all of them
                 const int h0 = X ? c.p0 * q.sh - q.ph + r_first : c.p0, b0 = X ? max(0, -h0) : 0, b1 = min(rows, Hs - h0);
                 const unsigned lo = (unsigned)b0 << 24, len = (unsigned)max(0, b1 - b0) << 24;
@@ -165,7 +171,9 @@ __device__ __forceinline__ void load_chunks(const StagedParams& q, unsigned char
                     const bool there = im_n < q.N && p < q.P;
                     const int h0 = X ? p * q.sh - q.ph + r_first : p, b0 = X ? max(0, -h0) : 0, b1 = there ? min(rows, Hs - h0) : 0;
                     const unsigned lo = (unsigned)b0 << 24, len = (unsigned)max(0, b1 - b0) << 24;
-                    const unsigned off = there ? (unsigned)(im_n * ns + h0 * Ws + w0) * ES : 0u;
+                    const size_t at = FAR && there ? (size_t)im_n * ns * ES : 0;
+                    image[e] = at;
+                    const unsigned off = there ? (unsigned)((FAR ? 0 : im_n * ns) + h0 * Ws + w0) * ES + (unsigned)(at & 3) : 0u;
                     if (PL == 1) t.odd |= (off >> 1 & 1) << e;
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
@@ -183,12 +191,13 @@ __device__ __forceinline__ void load_chunks(const StagedParams& q, unsigned char
             for (int e = 0; e < 8; ++e) {
                 typedef unsigned u32x3 __attribute__((ext_vector_type(3)));
                 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+                const __amdgpu_buffer_rsrc_t re = FAR ? __builtin_amdgcn_make_buffer_rsrc(from + (image[e] & ~(size_t)3), (short)0, (int)(((X ? q.x_bytes : q.dy_bytes) + (unsigned)(image[e] & 3) + 3) & ~3u), 0x00020000) : r;
                 if constexpr (PL == 1) {
-                    const u32x3 l = __builtin_amdgcn_raw_buffer_load_b96(r, vo[u][e], 0, 0);
+                    const u32x3 l = __builtin_amdgcn_raw_buffer_load_b96(re, vo[u][e], 0, 0);
 #pragma unroll
                     for (int j = 0; j < DW; ++j) t.v[u][e][j] = l[j];
                 } else {
-                    const u32x4 l = __builtin_amdgcn_raw_buffer_load_b128(r, vo[u][e], 0, 0);
+                    const u32x4 l = __builtin_amdgcn_raw_buffer_load_b128(re, vo[u][e], 0, 0);
 #pragma unroll
                     for (int j = 0; j < DW; ++j) t.v[u][e][j] = l[j];
                 }
@@ -288,7 +297,7 @@ __device__ __forceinline__ void load_chunks(const StagedParams& q, unsigned char
     }
 }
 
-template <int PL, bool FLAT, int TM, int TN, int WM, int WN>
+template <int PL, bool FLAT, bool FAR, int TM, int TN, int WM, int WN>
 __global__ __launch_bounds__(WM * WN * 64 + 2 * LOADERS, 2) void wgrad_staged_kernel(const StagedParams q) {
     constexpr int BM = TM * WM * 32, BN = TN * WN * 32, DP = BM + 1;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -314,8 +323,8 @@ __global__ __launch_bounds__(WM * WN * 64 + 2 * LOADERS, 2) void wgrad_staged_ke
     const int n = split < q.chunks ? ((q.chunks - split + q.splits - 1) / q.splits + 1) / 2 * 2 : 0;      // (the last of an odd number: none)
     if (wave >= WM * WN) {
         const int lt = tid - WM * WN * 64, nr = r_last - r_first + 1;
-        if (lt < LOADERS) load_chunks<PL, false, FLAT, BM>(q, smem, lt, k0, c0, cw, r_first, nr, split, n, q.db_out != nullptr && jct == 0);
-        else load_chunks<PL, true, FLAT, BM>(q, smem, lt - LOADERS, k0, c0, cw, r_first, nr, split, n, false);
+        if (lt < LOADERS) load_chunks<PL, false, FLAT, FAR, BM>(q, smem, lt, k0, c0, cw, r_first, nr, split, n, q.db_out != nullptr && jct == 0);
+        else load_chunks<PL, true, FLAT, FAR, BM>(q, smem, lt - LOADERS, k0, c0, cw, r_first, nr, split, n, false);
         return;
     }
 
@@ -494,27 +503,28 @@ __global__ __launch_bounds__(WM * WN * 64 + 2 * LOADERS, 2) void wgrad_staged_ke
     }
 }
 
-template <int PL, bool FLAT, int TM, int TN, int WM, int WN>
+template <int PL, bool FLAT, bool FAR, int TM, int TN, int WM, int WN>
 hipError_t launch_one(const StagedParams& q, int lds, int splits, hipStream_t st) {
     const long long total = (long long)q.tiles_i * q.tiles_j * q.c_tiles * splits;
     if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidValue;
     if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wgrad_staged_kernel<PL, FLAT, TM, TN, WM, WN>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wgrad_staged_kernel<PL, FLAT, FAR, TM, TN, WM, WN>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
     }
     ProbeScope probe(st);
     (void)hipGetLastError();   // drop stale status left by earlier, unrelated runtime calls
-    hipLaunchKernelGGL((wgrad_staged_kernel<PL, FLAT, TM, TN, WM, WN>), dim3((unsigned)total), dim3(WM * WN * 64 + 2 * LOADERS), lds, st, q);
+    hipLaunchKernelGGL((wgrad_staged_kernel<PL, FLAT, FAR, TM, TN, WM, WN>), dim3((unsigned)total), dim3(WM * WN * 64 + 2 * LOADERS), lds, st, q);
     return hipGetLastError();
 }
 
 struct StagedTile { bool f32; int bm, bn; };
 constexpr StagedTile kStagedTiles[] = {{true, 128, 128}, {true, 96, 128}, {true, 64, 256}, {true, 64, 128}, {true, 32, 256}, {true, 32, 128},
                                        {false, 128, 128}, {false, 96, 128}, {false, 64, 256}, {false, 64, 128}, {false, 32, 256}, {false, 32, 128}};
+template <bool FAR>
 hipError_t by_tile(int dtype, bool flat, const StagedParams& q, int bm, int bn, int lds, int splits, hipStream_t st) {
-#define ONE(PL, TM, TN, WM, WN) return flat ? launch_one<PL, true, TM, TN, WM, WN>(q, lds, splits, st) : launch_one<PL, false, TM, TN, WM, WN>(q, lds, splits, st)
-#define TWO(PL, TM, TN, WM, WN) return launch_one<PL, false, TM, TN, WM, WN>(q, lds, splits, st)
+#define ONE(PL, TM, TN, WM, WN) return flat ? launch_one<PL, true, FAR, TM, TN, WM, WN>(q, lds, splits, st) : launch_one<PL, false, FAR, TM, TN, WM, WN>(q, lds, splits, st)
+#define TWO(PL, TM, TN, WM, WN) return launch_one<PL, false, FAR, TM, TN, WM, WN>(q, lds, splits, st)
     if (dtype == PURINE_F32) {
         switch (bm * 1000 + bn) {
             case 128128: ONE(3, 2, 1, 2, 4);
@@ -547,8 +557,9 @@ WgradStagedPlan plan_wgrad_staged(const ConvGeom& g, int dtype, size_t limit, do
     WgradStagedPlan best{};
     const bool f32 = dtype == PURINE_F32;
     const int es = f32 ? 4 : 2, PL = f32 ? 3 : 1, U = units_of(PL), max_units = LOADERS * U;
-    const long long xspan = (long long)(g.N - 1) * g.x_ns + (long long)g.C * g.H * g.W, dyspan = (long long)(g.N - 1) * g.y_ns + (long long)g.K * g.P * g.Q;
-    if ((xspan + 8) * es >= (1LL << 31) || (dyspan + 8) * es >= (1LL << 31) || (long long)g.K * g.C * g.R * g.S >= (1LL << 31)) return best;
+    // (by the extents alone: views get the bits of dense tensors, however far apart their images lie)
+    const long long xs = (long long)g.N * g.C * g.H * g.W, dys = (long long)g.N * g.K * g.P * g.Q;
+    if ((xs + 8) * es >= (1LL << 31) || (dys + 8) * es >= (1LL << 31) || (long long)g.K * g.C * g.R * g.S >= (1LL << 31)) return best;
     const int RS = g.R * g.S;
     const bool flat = RS == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0;
     const int P = flat ? 1 : g.P, Qc = flat ? (int)(((long long)g.P * g.Q + 7) / 8) : g.Q;
@@ -639,8 +650,11 @@ hipError_t launch_wgrad_staged(int dtype, const ConvGeom& g, const WgradStagedPl
     q.x_ns = g.x_ns; q.dy_ns = g.y_ns;
     q.H = k.flat ? 1 : g.H; q.W = k.flat ? g.H * g.W : g.W; q.P = k.flat ? 1 : g.P; q.Q = k.flat ? g.P * g.Q : g.Q;
     const int Q = k.flat ? (q.Q + 7) / 8 : q.Q;
-    q.x_bytes = (unsigned)((((long long)(g.N - 1) * g.x_ns) + (long long)g.C * g.H * g.W) * es);
-    q.dy_bytes = (unsigned)((((long long)(g.N - 1) * g.y_ns) + (long long)g.K * g.P * g.Q) * es);
+    const long long xi = (long long)g.C * g.H * g.W, dyi = (long long)g.K * g.P * g.Q;
+    const long long xspan = (g.N - 1) * (long long)g.x_ns + xi, dyspan = (g.N - 1) * (long long)g.y_ns + dyi;
+    const bool far = (xspan + 8) * es >= (1LL << 31) || (dyspan + 8) * es >= (1LL << 31);
+    q.x_bytes = (unsigned)((far ? xi : xspan) * es); q.dy_bytes = (unsigned)((far ? dyi : dyspan) * es);
+    if (!far) { q.x_bytes = (q.x_bytes + 3) & ~3u; q.dy_bytes = (q.dy_bytes + 3) & ~3u; }      // whole dwords (the tensors begin at one)
     q.RS = g.R * g.S; q.J = q.RS * g.C;
     q.Ct = k.Ct; q.CtP = k.Ct | 1;
     q.tiles_i = k.tiles_i; q.tiles_j = k.tiles_j; q.c_tiles = k.c_tiles;
@@ -650,11 +664,10 @@ hipError_t launch_wgrad_staged(int dtype, const ConvGeom& g, const WgradStagedPl
     q.d_plane = k.PR * k.QS * (k.bm + 1) * 16; q.x_off = PL * q.d_plane; q.x_plane = k.XR * k.PW * q.CtP * 16; q.buf_bytes = k.lds / 2;
     const int cl = g.C % k.Ct ? g.C % k.Ct : k.Ct;
     q.lead = (4 - g.pw % 4) % 4; q.dquads = k.QS / 4; q.xquads = k.PW / 4;
-    q.x_bytes = (q.x_bytes + 3) & ~3u; q.dy_bytes = (q.dy_bytes + 3) & ~3u;      // whole dwords (the tensors begin at one)
     q.div_dquads = make_fastdiv(q.dquads); q.div_pr = make_fastdiv(k.PR); q.div_xquads = make_fastdiv(q.xquads); q.div_xr = make_fastdiv(k.XR);
     q.div_qsegs = make_fastdiv(q.qsegs); q.div_pchunks = make_fastdiv(q.pchunks); q.div_s = make_fastdiv(g.S);
     q.div_ct = make_fastdiv(k.Ct); q.div_cl = make_fastdiv(cl);
-    return by_tile(dtype, k.flat, q, k.bm, k.bn, k.lds, k.splits, st);
+    return far ? by_tile<true>(dtype, k.flat, q, k.bm, k.bn, k.lds, k.splits, st) : by_tile<false>(dtype, k.flat, q, k.bm, k.bn, k.lds, k.splits, st);
 }
 
 }  // namespace purine

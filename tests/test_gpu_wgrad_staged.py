@@ -127,20 +127,39 @@ def test_infinities(case, dtype):
         np.testing.assert_allclose(got[ok], want[ok], rtol=1e-5)
 
 
-@pytest.mark.parametrize("case", [(12, 192, 28, 28, 16, 1, 1, 1, 0, 256 * 784), (2, 3, 40, 41, 40, 7, 7, 2, 3, 1 << 29), (3, 50, 13, 11, 33, 1, 1, 1, 0, 1 << 28)],
-                         ids=["wide-concat", "first-layer-far", "1x1-far"])
-def test_scratch_of_dense_tensors_is_enough_for_views(case):
-    """The scratch query knows no strides: a slice of a wide tensor, and one whose images lie 1 and 2 GiB apart, run out of it."""
+@pytest.mark.parametrize("which", ["x", "dy", "both"])
+@pytest.mark.parametrize("case,dtype", [((12, 192, 28, 28, 16, 1, 1, 1, 0, 256 * 784), "f32"), ((2, 3, 40, 41, 40, 7, 7, 2, 3, 1 << 29), "f32"),
+                                        ((9, 3, 21, 23, 40, 7, 7, 2, 3, 1 << 26), "f32"), ((3, 50, 13, 11, 33, 1, 1, 1, 0, 1 << 28), "f32"),
+                                        ((2, 3, 41, 41, 40, 7, 7, 2, 3, 1 << 30), "bf16"), ((9, 3, 21, 23, 40, 3, 3, 1, 1, 1 << 27), "bf16")],
+                         ids=["wide-concat", "first-layer", "eight-and-one-images", "1x1", "bf16", "bf16-eight-and-one-images"])
+def test_views_get_the_bits_of_dense_tensors(case, dtype, which):
+    """... also slices of tensors whose images lie 0.25 to 2 GiB apart (2^31 bytes and more in all), beside dense ones whose images begin in
+    the middle of a dword; out of the scratch of dense tensors (the query knows no strides)."""
     import paper_1412_6249_amd as pa
     N, C, H, W, K, R, S, s, p, ns = case
     g = torch.Generator().manual_seed(N + K)
+    td, code = (torch.float32, pa.PURINE_F32) if dtype == "f32" else (torch.bfloat16, pa.PURINE_BF16)
     P, Q = (H + 2 * p - R) // s + 1, (W + 2 * p - S) // s + 1
-    x, dy = torch.randn((N, C, H, W), generator=g), torch.randn((N, K, P, Q), generator=g)
-    wide = torch.empty((N - 1) * ns + K * P * Q + 64, device="cuda")
-    v = torch.as_strided(wide, dy.shape, (ns, P * Q, Q, 1), 0)
-    v.copy_(dy)
+    x, dy = torch.randn((N, C, H, W), generator=g).to(td), torch.randn((N, K, P, Q), generator=g).to(td)
+    desc = pa.conv_desc(s, p)
+
+    def far(t):
+        wide = torch.empty((N - 1) * ns + t[0].numel() + 64, dtype=td, device="cuda")
+        v = torch.as_strided(wide, t.shape, (ns,) + t.stride()[1:], 0)
+        v.copy_(t)
+        return v
+
+    dx, ddy = x.cuda(), dy.cuda()
+    vx, vdy = far(x) if which != "dy" else dx, far(dy) if which != "x" else ddy
+    hook = 0 if dtype == "f32" else -11
+    pa.purine_debug_force_tile(hook, 0)
+    try:
+        assert pa.purine_conv_route(pa.PURINE_CONV_BWD_WEIGHT, desc, x.shape, (K, C, R, S), code) == pa.PURINE_ROUTE_INSIDE_LDS
+        dw, db = _run(pa, desc, vx, vdy, (K, C, R, S), code)
+        dw0, db0 = _run(pa, desc, dx, ddy, (K, C, R, S), code)
+    finally:
+        pa.purine_debug_force_tile(0, 0)
+    assert torch.equal(dw, dw0) and torch.equal(db, db0)
     rw, rb = _ref(x, dy, R, S, s, p)
-    dw, db = _run(pa, pa.conv_desc(s, p), x.cuda(), v, (K, C, R, S), pa.PURINE_F32)
-    # (the general kernels add plain fp32 products)
-    _close(dw, rw, N * P * Q, "dw", "bf16")
+    _close(dw, rw, N * P * Q, "dw", dtype)
     _close(db, rb, 4 * N * P * Q, "db", "bf16")
