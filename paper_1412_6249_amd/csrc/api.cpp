@@ -880,7 +880,9 @@ int purine_fc_fwd(const purine_tensor* x, const purine_tensor* w, const purine_t
     }
     {
         const int64_t N = x->dim[0], C = x->dim[1], K = w->dim[0];
-        if (goes_direct(PURINE_CONV_FWD, N, C, K, x->dtype)) {
+        // (bf16: y may lie over x or w, which the kernels below have read when they write it; this one has not)
+        const bool over = x->dtype == PURINE_BF16 && (overlaps(y, x) || overlaps(y, w));
+        if (!over && goes_direct(PURINE_CONV_FWD, N, C, K, x->dtype)) {
             if ((rc = fc_direct_checks(PURINE_CONV_FWD, y, x, w, N, C, K, ws, ws_bytes))) return rc;
             return hip_status(launch_fc_direct(PURINE_CONV_FWD, x->dtype, x->data, w->data, y->data, b ? b->data : nullptr, nullptr, 0.0f, N, C, K,
                                                (hipStream_t)hip_stream));

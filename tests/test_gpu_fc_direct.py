@@ -58,6 +58,18 @@ def test_fc_direct(case, dtype):
     assert torch.equal(dw, alone + alone) and torch.equal(db, db0 + db0)
 
 
+@pytest.mark.parametrize("over", ["x", "w"])
+@pytest.mark.parametrize("N,C,K", [(9, 64, 64), (64, 40, 64), (33, 35, 35)])
+def test_bf16_forward_over_its_operands(N, C, K, over):
+    """y in the place of x or w: the product is complete before it is written."""
+    import paper_1412_6249_amd as pa
+    t, d, ws, td = _data(pa, (N, C, K), "bf16")
+    y = torch.as_strided(torch.cat([d[over].flatten(), torch.zeros(N * K, dtype=td, device="cuda")]), (N, K), (K, 1), 0)
+    d[over] = torch.as_strided(y, d[over].shape, (C, 1), 0)
+    pa.purine_fc_fwd(d["x"], d["w"], d["b"], y, ws=ws(pa.PURINE_CONV_FWD))
+    _close(y, t["x"].double() @ t["w"].double().t() + t["b"].double(), C, True, "y")
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("N,K", [(256, 17), (257, 16), (511, 1), (512, 40), (513, 65), (961, 15), (5000, 33)])
 def test_bias_gradient_of_many_images(N, K, dtype):
