@@ -574,6 +574,8 @@ WgradStagedPlan plan_wgrad_staged(const ConvGeom& g, int dtype, size_t limit, do
         while (shift < 3 && (g.N << shift) % 8 != 0 && (g.P >> (shift + 1)) >= 1) ++shift;
     const int lead = flat ? 0 : (4 - g.pw % 4) % 4;
     const double dw_bytes = (double)g.K * g.C * RS * 4.0;
+    const int PB = (P + (1 << shift) - 1) >> shift, groups = flat ? g.N : (int)((((long long)g.N << shift) + 7) / 8);
+    const double positions = (double)groups * PB * Qc;
     for (const StagedTile& t : kStagedTiles) {
         if (t.f32 != f32 || (staged_wgrad_tile() > 0 && staged_wgrad_tile() != t.bm * 1000 + t.bn)) continue;
         const int tiles_i = (g.K + t.bm - 1) / t.bm;
@@ -581,6 +583,13 @@ WgradStagedPlan plan_wgrad_staged(const ConvGeom& g, int dtype, size_t limit, do
         const int most = t.bn / RS > 0 ? t.bn / RS : 1;
         const int c_tiles0 = (long long)RS * g.C <= 4 * t.bn && g.C <= 16 ? 1 : (g.C + most - 1) / most;
         const int Ct = (g.C + c_tiles0 - 1) / c_tiles0, c_tiles = (g.C + Ct - 1) / Ct, tiles_j = (RS * Ct + t.bn - 1) / t.bn, CtP = Ct | 1;
+        const long long tiles = (long long)tiles_i * tiles_j * c_tiles;
+        if (tiles > 4096) continue;
+        // A tile is left out whose positions alone take longer, by the least of the terms below on all CUs all the time, than what is to be
+        // beaten: most calls end here, and the search is 1.1 us of the others.
+        const double least = f32 ? 0.069 + 0.00129 * (t.bm + Ct) : 0.0155 + 0.00099 * t.bm + 0.00012 * Ct;
+        if (!flat && 5.0 + (double)tiles * positions * least / 256.0 >= (best.use ? best.us : budget_us)) continue;
+        const unsigned most_splits = tiles < 256 ? 256u / (unsigned)tiles : 1u;
         int nr = 1;                    // filter rows that the columns of a tile span, at most
         if (RS > 1)
             for (int cw = Ct, last = 0; !last; cw = g.C % Ct ? g.C % Ct : Ct, last = 1)
@@ -588,16 +597,14 @@ WgradStagedPlan plan_wgrad_staged(const ConvGeom& g, int dtype, size_t limit, do
                     const int j1 = (j0 + t.bn < RS * cw ? j0 + t.bn : RS * cw) - 1, n = j1 / cw / g.S - j0 / cw / g.S + 1;
                     if (n > nr) nr = n;
                 }
-        const long long tiles = (long long)tiles_i * tiles_j * c_tiles;
-        if (tiles > 4096) continue;
-        const int PB = (P + (1 << shift) - 1) >> shift, groups = flat ? g.N : (int)((((long long)g.N << shift) + 7) / 8);
         // chunks: the widest that fits LDS and the loaders, then as many rows
-        for (int qs = flat ? 8 : 32; qs >= (flat ? 8 : 4); qs = qs > 16 ? qs - 8 : qs - 4) {
+        for (int qs = flat ? 8 : 32, last = 0; qs >= (flat ? 8 : 4); qs = qs > 16 ? qs - 8 : qs - 4) {
             int QS = qs;
             if (!flat) {
                 const int segs = (Qc + qs - 1) / qs;
                 QS = ((Qc + segs - 1) / segs + 3) / 4 * 4;
-                if (QS > qs) continue;
+                if (QS > qs || QS == last) continue;      // (short rows: the same again)
+                last = QS;
             }
             const int PW = flat ? 8 : (lead + (QS - 1) * g.sw + g.S + 3) / 4 * 4;
             int PR = 0, XR = 0, lds = 0, units = 0;
@@ -615,13 +622,13 @@ WgradStagedPlan plan_wgrad_staged(const ConvGeom& g, int dtype, size_t limit, do
             // that its loads ask for. Planes as they lie in memory: whole lines, the packing alone.
             const double lines = 8.0 * ((double)t.bm * PR * ((QS * es + 63) / 64) + (double)Ct * XR * ((PW * es + 63) / 64 + 0.5));
             const double chunk_us = flat ? 0.006 * units : f32 ? 0.0035 * units + 0.069 * PR * QS + 0.00084 * lines : 1.8 + 0.0155 * PR * QS + 0.00048 * lines;
+            if (5.0 + (double)tiles * (double)chunks * chunk_us / 256.0 * 0.999999 >= (best.use ? best.us : budget_us)) continue;
             // one workgroup per CU at a time: one round of the CUs, or one workgroup for each tile where that costs no second pass
             for (int round = 0; round < 2; ++round) {
-                long long splits = round ? 1 : 256 / tiles;
-                if (splits < 1) splits = 1;
-                if (splits > chunks) splits = chunks;
-                const long long per = (chunks + splits - 1) / splits;
-                splits = (chunks + per - 1) / per;
+                unsigned splits = round ? 1 : most_splits;
+                if (splits > (unsigned)chunks) splits = (unsigned)chunks;
+                const unsigned per = ((unsigned)chunks + splits - 1) / splits;
+                splits = ((unsigned)chunks + per - 1) / per;
                 if (limit && splits > 1 && splits * (dw_bytes + g.K * 4.0) + 512 > limit) continue;
                 double us = 5.0 + (double)((tiles * splits + 255) / 256) * per * chunk_us;
                 if (splits > 1) us += 5.0 + 2.0 * splits * dw_bytes / 4e6;
