@@ -845,8 +845,7 @@ size_t fc_general_workspace_bytes(int pass, int64_t N, int64_t C, int64_t K, int
     const int64_t xd[4] = {1, K, 1, C}, wd[4] = {N, K, 1, 1};
     switch (pass) {
         case PURINE_CONV_FWD:   // y = x w^T through the weight-gradient kernel (split reduction over C)
-            return align256(purine_conv_workspace_bytes(PURINE_CONV_BWD_WEIGHT, &kUnitConv, xd, wd, dtype)) +
-                   (dtype == PURINE_BF16 ? (size_t)N * K * 4 : 0);   // bf16: the fp32 product matrix before the bias
+            return align256(purine_conv_workspace_bytes(PURINE_CONV_BWD_WEIGHT, &kUnitConv, xd, wd, dtype));
         case PURINE_CONV_BWD_DATA: {   // dx = dy w through the forward kernel, or (bf16) a kernel of its own
             const size_t own = dtype == PURINE_BF16 ? fc_dgrad_bf16_plan(N, C, K, nullptr, nullptr) : SIZE_MAX;
             return own != SIZE_MAX ? own : purine_conv_workspace_bytes(PURINE_CONV_FWD, &kUnitConv, xd, wd, dtype);
@@ -894,13 +893,12 @@ int purine_fc_fwd(const purine_tensor* x, const purine_tensor* w, const purine_t
     purine_tensor yf = as_filter(y);
     if (x->dtype == PURINE_BF16) {
         // that kernel's partial sums are fp32; its second pass adds them up and the bias, and rounds once
-        const int64_t N = x->dim[0], K = w->dim[0];
         const size_t conv_ws = align256(purine_conv_workspace_bytes(PURINE_CONV_BWD_WEIGHT, &kUnitConv, wp.dim, yf.dim, PURINE_BF16));
-        if (!ws || ws_bytes < conv_ws + (size_t)N * K * 4) return PURINE_E_WORKSPACE;
+        if (!ws || ws_bytes < conv_ws) return PURINE_E_WORKSPACE;
         if (((uintptr_t)ws) & 15u) return PURINE_E_LAYOUT;
-        purine_tensor acc = yf;   // the fp32 product, for the kernels that have no second pass
+        purine_tensor acc = yf;   // stands for the fp32 product, which nothing writes: the partial sums begin there
         acc.dtype = PURINE_F32;
-        acc.data = (char*)ws + conv_ws;
+        acc.data = ws;
         const WgradFinish finish{b ? (const uint16_t*)b->data : nullptr, (uint16_t*)y->data};
         return conv_bwd_weight_impl(&kUnitConv, &wp, &xp, &acc, nullptr, 0.0f, ws, conv_ws, hip_stream, false, &finish);
     }

@@ -979,11 +979,8 @@ hipError_t launch_conv_wgrad(int dtype, const ConvGeom& g, const WgradPlan& plan
     }
     hipError_t e;
     const bool vec = p.PQ % 32 == 0 && (((uintptr_t)dy) & 15u) == 0;
-    if (finish && (p.RS != 1 || db)) return hipErrorInvalidValue;
-    if (finish && (plan.pk.use || plan.sg.use)) {   // these write dw themselves
-        e = launch_conv_wgrad(dtype, g, plan, x, dy, dw, nullptr, 0.0f, ws, ws_bytes, st);
-        return e != hipSuccess ? e : launch_wgrad_reduce(dw, nullptr, 1, 0.0f, false, g.K, g.C, 1, nullptr, nullptr, 0, st, 0, finish);
-    }
+    // (bf16 1x1 layers alone have one, and take neither of the kernels that write dw themselves)
+    if (finish && (p.RS != 1 || db || plan.pk.use || plan.sg.use)) return hipErrorInvalidValue;
     if (plan.pk.use)
         return launch_wgrad_packets(g, plan.pk, x, dy, dw, db, beta, ws, ws_bytes < plan.pk.ws_bytes ? ws_bytes : plan.pk.ws_bytes, st);
     if (plan.sg.use) {

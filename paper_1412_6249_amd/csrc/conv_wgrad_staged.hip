@@ -84,6 +84,7 @@ __device__ __forceinline__ void meet() {
 // descriptor of its own (of whole dwords: images of a dense bf16 tensor beside a far one may begin in the middle of one).
 template <int PL, bool X, bool FLAT, bool FAR, int BM>
 __device__ __forceinline__ void load_chunks(const StagedParams& q, unsigned char* smem, int lt, int k0, int c0, int cw, int r_first, int nr, int split, int n, bool do_db) {
+    static_assert(!FLAT || PL == 3, "bf16 planes as they lie in memory: the general kernel");
     constexpr int ES = PL == 1 ? 2 : 4, U = units_of(PL), DW = PL == 1 ? 3 : 4, DP = BM + 1;
     unsigned char* const from = static_cast<unsigned char*>(const_cast<void*>(X ? q.x : q.dy));
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(from, (short)0, (int)(X ? q.x_bytes : q.dy_bytes), 0x00020000);
@@ -131,14 +132,14 @@ __device__ __forceinline__ void load_chunks(const StagedParams& q, unsigned char
             for (int e = 0; e < 8; ++e) image[e] = FAR && c.pr_n ? (size_t)c.grp * ns * ES : 0;
             t.c0 = 0; t.c1 = c.pr_n ? min(c.qn * 8, Ws - first) : 0;
             t.cut = t.c1 & 7;
-            t.odd = PL == 1 && off & 2 ? 0xffu : 0u;
+            t.odd = 0;
 #pragma unroll
             for (int u = 0; u < U * B; ++u) {
                 const int col = (where[u] >> 14) & 1023;
                 const unsigned o = base[u] + off;
                 const bool ok = col < t.c1 && base[u] != NOWHERE;
-                vo[u / 4][u % 4 * 2] = ok ? PL == 1 ? o & ~3u : o : NOWHERE;
-                vo[u / 4][u % 4 * 2 + 1] = ok && col + 4 < t.c1 ? (PL == 1 ? o & ~3u : o) + 4 * ES : NOWHERE;
+                vo[u / 4][u % 4 * 2] = ok ? o : NOWHERE;
+                vo[u / 4][u % 4 * 2 + 1] = ok && col + 4 < t.c1 ? o + 4 * ES : NOWHERE;
             }
         } else {
             const int w0 = X ? c.q0 * q.sw - q.pw - q.lead : c.q0;
@@ -219,7 +220,7 @@ __device__ __forceinline__ void load_chunks(const StagedParams& q, unsigned char
             if constexpr (PL == 1) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const unsigned s0 = (base[FLAT ? u * 4 + e / 2 : u] & 2) * 8, s = t.odd >> e & 1 ? 16 - s0 : s0;
+                    const unsigned s0 = (base[u] & 2) * 8, s = t.odd >> e & 1 ? 16 - s0 : s0;
                     v[e][0] = __builtin_amdgcn_alignbit(v[e][1], v[e][0], s);
                     v[e][1] = __builtin_amdgcn_alignbit(v[e][2], v[e][1], s);
                 }
@@ -252,10 +253,8 @@ __device__ __forceinline__ void load_chunks(const StagedParams& q, unsigned char
                 if (FLAT && to == 0xffffffffu) continue;
                 if constexpr (PL == 1) {
                     const unsigned pick = j & 1 ? 0x07060302u : 0x05040100u;
-                    uint4 w;
-                    if (FLAT) w = make_uint4(v[2 * j][0], v[2 * j][1], v[2 * j + 1][0], v[2 * j + 1][1]);
-                    else w = make_uint4(__builtin_amdgcn_perm(v[1][j >> 1], v[0][j >> 1], pick), __builtin_amdgcn_perm(v[3][j >> 1], v[2][j >> 1], pick),
-                                        __builtin_amdgcn_perm(v[5][j >> 1], v[4][j >> 1], pick), __builtin_amdgcn_perm(v[7][j >> 1], v[6][j >> 1], pick));
+                    const uint4 w = make_uint4(__builtin_amdgcn_perm(v[1][j >> 1], v[0][j >> 1], pick), __builtin_amdgcn_perm(v[3][j >> 1], v[2][j >> 1], pick),
+                                               __builtin_amdgcn_perm(v[5][j >> 1], v[4][j >> 1], pick), __builtin_amdgcn_perm(v[7][j >> 1], v[6][j >> 1], pick));
                     *reinterpret_cast<uint4*>(dst) = w;
                 } else {
                     float f[8];

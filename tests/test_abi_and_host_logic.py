@@ -241,6 +241,9 @@ def test_operator_argument_validation_without_launch():
     assert pa.purine_fc_workspace_bytes(0, 4, 20, 6) > 0 and pa.purine_fc_workspace_bytes(7, 4, 20, 6) == 0
     assert pa.purine_fc_workspace_bytes(0, 4, 20, 6, BF16) >= 4 * 6 * 4 and pa.purine_fc_workspace_bytes(2, 4, 20, 6, BF16) >= 2 * (4 * 20 + 4 * 6)
     assert pa.purine_fc_workspace_bytes(0, 4, 20, 6, pa.PURINE_I32) == 0
+    # bf16 forward: the partial sums alone (the pass that adds them writes y)
+    conv = pa.purine_conv_workspace_bytes(pa.PURINE_CONV_BWD_WEIGHT, pa.conv_desc(1, 0), (1, 4096, 1, 9216), (128, 4096, 1, 1), BF16)
+    assert pa.purine_fc_workspace_bytes(0, 128, 9216, 4096, BF16) == (conv + 255) // 256 * 256
     # bf16 backward-data with rows of whole 16-byte packets: fp32 tiles of the slices of the reduction
     # (whole multiples of N*C*4 bytes, none when one slice covers it); other shapes size the forward kernel's scratch
     n_, c_, k_ = 128, 9216, 4096
