@@ -124,48 +124,30 @@ __global__ __launch_bounds__(WAVES * 64) void conv_direct_kernel(const ConvDirec
         }
     };
     auto multiply = [&](int s, Frag& f) {
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
         const int t = s * 16 + khalf * 8;
-        u32x4 ap[PL], bp[PL];
         if constexpr (PL == 1) {
+            unsigned a[4], b[4];
             if constexpr (BWD) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) ap[0][e] = f.a[2 * e] | f.a[2 * e + 1] << 16;
+                for (int e = 0; e < 4; ++e) a[e] = f.a[2 * e] | f.a[2 * e + 1] << 16;
             } else {
                 const unsigned sh = ((unsigned)row * (unsigned)q.T + (unsigned)t) & 1 ? 16u : 0u;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) ap[0][e] = __builtin_amdgcn_alignbit(f.a[e + 1], f.a[e], sh);
+                for (int e = 0; e < 4; ++e) a[e] = __builtin_amdgcn_alignbit(f.a[e + 1], f.a[e], sh);
                 if (t + 8 > q.T) {                 // (past the end of the reduction lies the next row)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) ap[0][e] &= (t + 2 * e < q.T ? 0xffffu : 0u) | (t + 2 * e + 1 < q.T ? 0xffff0000u : 0u);
+                    for (int e = 0; e < 4; ++e) a[e] &= (t + 2 * e < q.T ? 0xffffu : 0u) | (t + 2 * e + 1 < q.T ? 0xffff0000u : 0u);
                 }
             }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) bp[0][e] = f.b[2 * e] | f.b[2 * e + 1] << 16;
+            for (int e = 0; e < 4; ++e) b[e] = f.b[2 * e] | f.b[2 * e + 1] << 16;
+            multiply_loaded<PL>(a, b, hi, lo);
         } else {
             if (!BWD && t + 8 > q.T) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) f.a[e] = t + e < q.T ? f.a[e] : 0u;
             }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                uint32_t pa[PLANES], pb[PLANES];
-                split_pair(__uint_as_float(f.a[2 * e]), __uint_as_float(f.a[2 * e + 1]), pa);
-                split_pair(__uint_as_float(f.b[2 * e]), __uint_as_float(f.b[2 * e + 1]), pb);
-#pragma unroll
-                for (int pl = 0; pl < PLANES; ++pl) { ap[pl][e] = pa[pl]; bp[pl][e] = pb[pl]; }
-            }
-        }
-        auto mul = [&](int i, int j, floatx16& acc) {
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ap[i]), __builtin_bit_cast(bf16x8, bp[j]), acc, 0, 0, 0);
-        };
-        mul(0, 0, hi);
-        if constexpr (PL == 3) {
-            mul(0, 1, lo);
-            mul(1, 0, lo);
-            mul(1, 1, lo);
-            mul(0, 2, lo);
-            mul(2, 0, lo);
+            multiply_loaded<PL>(f.a, f.b, hi, lo);
         }
     };
     Frag f0, f1;
@@ -177,18 +159,14 @@ __global__ __launch_bounds__(WAVES * 64) void conv_direct_kernel(const ConvDirec
         multiply(s + WAVES, f1);             // (past the last step: zeros)
     }
     __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 16; ++e) sums[wave][e][lane] = PL == 3 ? (hi[e] + lo[e]) * JOIN_SCALE : hi[e];
+    put_sums<PL>(sums[wave], lane, hi, lo);
     __syncthreads();
 
     auto value = [](const void* t, size_t i) { return PL == 1 ? __uint_as_float((unsigned)((const uint16_t*)t)[i] << 16) : ((const float*)t)[i]; };
     for (int o = tid; o < 1024; o += NT) {
         const int e = o >> 6, l = o & 63;
         const int i = it * 32 + (e >> 2) * 8 + (l >> 5) * 4 + (e & 3), j = jt * 32 + (l & 31);
-        double all = 0.0;                    // (one rounding at the end, however many wavefronts)
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) all += (double)sums[w][e][l];
-        float v = (float)all;
+        float v = all_sums<WAVES>(sums, e, l);
         if (i >= q.rows || j >= q.M) continue;
         const int n = fastdiv(j, q.div_howo), pix = j - n * q.HoWo;
         if ((PL == 3 || BWD) && !(__builtin_fabsf(v) <= 3.402823466e38f)) {

@@ -116,32 +116,7 @@ __global__ __launch_bounds__(WAVES * 64) void fc_direct_kernel(const FcDirectPar
             for (int e = 0; e < (PL == 1 ? 4 : 8); ++e)
                 dsum += PL == 1 ? __uint_as_float(f.a[e] << 16) + __uint_as_float(f.a[e] & 0xffff0000u) : __uint_as_float(f.a[e]);
         }
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        u32x4 ap[PL], bp[PL];
-        if constexpr (PL == 1) {
-            ap[0] = u32x4{f.a[0], f.a[1], f.a[2], f.a[3]};
-            bp[0] = u32x4{f.b[0], f.b[1], f.b[2], f.b[3]};
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                uint32_t pa[PLANES], pb[PLANES];
-                split_pair(__uint_as_float(f.a[2 * e]), __uint_as_float(f.a[2 * e + 1]), pa);
-                split_pair(__uint_as_float(f.b[2 * e]), __uint_as_float(f.b[2 * e + 1]), pb);
-#pragma unroll
-                for (int pl = 0; pl < PLANES; ++pl) { ap[pl][e] = pa[pl]; bp[pl][e] = pb[pl]; }
-            }
-        }
-        auto mul = [&](int i, int j, floatx16& acc) {
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ap[i]), __builtin_bit_cast(bf16x8, bp[j]), acc, 0, 0, 0);
-        };
-        mul(0, 0, hi);
-        if constexpr (PL == 3) {
-            mul(0, 1, lo);
-            mul(1, 0, lo);
-            mul(1, 1, lo);
-            mul(0, 2, lo);
-            mul(2, 0, lo);
-        }
+        multiply_loaded<PL>(f.a, f.b, hi, lo);
     };
     // (both axes inner: two or four 16-byte loads a step, so four steps are in flight; else two)
     constexpr int AHEAD = A_IN && B_IN ? 4 : 2;
@@ -156,16 +131,12 @@ __global__ __launch_bounds__(WAVES * 64) void fc_direct_kernel(const FcDirectPar
         }
     }
 
-#pragma unroll
-    for (int e = 0; e < 16; ++e) sums[wave][e][lane] = PL == 3 ? (hi[e] + lo[e]) * JOIN_SCALE : hi[e];
+    put_sums<PL>(sums[wave], lane, hi, lo);
     __syncthreads();
     for (int o = tid; o < 1024; o += WAVES * 64) {
         const int e = o >> 6, l = o & 63;
         const int i = it * 32 + (e >> 2) * 8 + (l >> 5) * 4 + (e & 3), j = jt * 32 + (l & 31);
-        double all = 0.0;                    // (one rounding at the end, however many wavefronts)
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) all += (double)sums[w][e][l];
-        float t = (float)all;
+        float t = all_sums<WAVES>(sums, e, l);
         if (i >= q.rows || j >= q.cols) continue;
         if (PL == 3 && !(__builtin_fabsf(t) <= 3.402823466e38f)) {
             // infinities and NaNs: again, as a plain fp32 sum

@@ -1,6 +1,6 @@
-// What the two kernels on packed bf16 parts share (conv_packets.hip: forward and backward-data,
-// conv_wgrad_packets.hip: weight gradient): the split of an fp32 number, the tile shapes, the
-// multiplication of one step.
+// What the kernels on bf16 parts share (conv_packets.hip: forward and backward-data, conv_wgrad_packets.hip and
+// conv_wgrad_staged.hip: weight gradient, conv_direct.hip and fc_direct.hip: small launches): the split of an fp32 number,
+// the tile shapes, the multiplication of one step.
 #pragma once
 #include "common.h"
 
@@ -113,6 +113,52 @@ __device__ __forceinline__ void multiply_step(const unsigned char* st, int a_off
     mul(1, 1, lo);
     mul(0, 2, lo);
     mul(2, 0, lo);
+}
+
+// The kernels of small launches hold a step's operands in registers: a lane's eight elements of a row (a) and of a column (b), bf16 as four
+// pairs (PL = 1, into hi) or fp32, split here.
+template <int PL>
+__device__ __forceinline__ void multiply_loaded(const unsigned* a, const unsigned* b, floatx16& hi, floatx16& lo) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 ap[PL], bp[PL];
+    if constexpr (PL == 1) {
+        ap[0] = u32x4{a[0], a[1], a[2], a[3]};
+        bp[0] = u32x4{b[0], b[1], b[2], b[3]};
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            uint32_t pa[PLANES], pb[PLANES];
+            split_pair(__uint_as_float(a[2 * e]), __uint_as_float(a[2 * e + 1]), pa);
+            split_pair(__uint_as_float(b[2 * e]), __uint_as_float(b[2 * e + 1]), pb);
+#pragma unroll
+            for (int pl = 0; pl < PLANES; ++pl) { ap[pl][e] = pa[pl]; bp[pl][e] = pb[pl]; }
+        }
+    }
+    auto mul = [&](int i, int j, floatx16& acc) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ap[i]), __builtin_bit_cast(bf16x8, bp[j]), acc, 0, 0, 0);
+    };
+    mul(0, 0, hi);
+    if constexpr (PL == 3) {
+        mul(0, 1, lo);
+        mul(1, 0, lo);
+        mul(1, 1, lo);
+        mul(0, 2, lo);
+        mul(2, 0, lo);
+    }
+}
+
+// Their wavefronts' sums of one tile in LDS, and element (e, l) of all of them: one rounding at the end, however many wavefronts.
+template <int PL>
+__device__ __forceinline__ void put_sums(float (&to)[16][64], int lane, const floatx16& hi, const floatx16& lo) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) to[e][lane] = PL == 3 ? (hi[e] + lo[e]) * JOIN_SCALE : hi[e];
+}
+template <int WAVES>
+__device__ __forceinline__ float all_sums(const float (*sums)[16][64], int e, int l) {
+    double all = 0.0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) all += (double)sums[w][e][l];
+    return (float)all;
 }
 
 // Every load of this wavefront but the `YOUNGER` youngest has written its LDS packets; then all
