@@ -752,7 +752,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_few_kernel(const float* __re
     if (i >= (unsigned)n) return;   // n is a multiple of V
     float t[V];
 #pragma unroll
-    for (int e = 0; e < V; ++e) t[e] = beta != 0.0f ? dw[i + e] : 0.0f;
+    for (int e = 0; e < V; ++e) t[e] = beta != 0.0f ? dw[i + e] + 0.0f : 0.0f;      // (minus zero: there, lanes without a split add plus zeros)
 #pragma unroll 8
     for (int s = 0; s < splits; ++s) {
         if constexpr (V == 4) {

@@ -41,6 +41,59 @@ def test_fc(N, C, K):
     assert not torch.equal(dw, prev)
 
 
+def _both(pa, call):
+    """The same call with the kernels of few splits and with the ones that they stand for."""
+    out = []
+    for hook in (0, -13):
+        pa.purine_debug_force_tile(hook, 0)
+        try:
+            out.append(call())
+        finally:
+            pa.purine_debug_force_tile(0, 0)
+    for a, b in zip(*out):
+        assert torch.equal(a.view(torch.int32 if a.dtype == torch.float32 else torch.int16), b.view(torch.int32 if b.dtype == torch.float32 else torch.int16))
+    return out[0]
+
+
+@pytest.mark.parametrize("N,C,K", [(128, 4608, 2048), (300, 4099, 1021), (512, 1024, 512)])
+def test_fc_forward_bits(N, C, K):
+    """The bias and the rounding in either second pass."""
+    import paper_1412_6249_amd as pa
+    assert pa.purine_fc_route(pa.PURINE_CONV_FWD, N, C, K, pa.PURINE_BF16) == pa.PURINE_ROUTE_OTHER
+    g = torch.Generator().manual_seed(N + C + K)
+    x, w, b = (torch.randn(s, generator=g).to(torch.bfloat16).cuda() for s in ((N, C), (K, C), (K,)))
+    ws = _ws(pa.purine_fc_workspace_bytes(pa.PURINE_CONV_FWD, N, C, K, pa.PURINE_BF16))
+
+    def call():
+        out = []
+        for bias in (b, None):
+            out.append(torch.full((N, K), float("nan"), dtype=torch.bfloat16, device="cuda"))
+            pa.purine_fc_fwd(x, w, bias, out[-1], ws=ws)
+        return out
+    _close(_both(pa, call)[0], x.double().cpu() @ w.double().cpu().t() + b.double().cpu(), C, True, "y")
+
+
+@pytest.mark.parametrize("N,C,H,K", [(12, 400, 14, 360), (12, 401, 14, 357), (9, 332, 16, 396), (5, 512, 13, 256)])
+def test_weight_gradient_bits(N, C, H, K):
+    """... also of gradients that are minus zero and stay it or not."""
+    import paper_1412_6249_amd as pa
+    g = torch.Generator().manual_seed(N + C + K)
+    x, dy = (torch.randn(N, c, H, H, generator=g).to(torch.bfloat16).cuda() for c in (C, K))
+    dy[:, ::7] = 0.0
+    desc = pa.conv_desc(1, 0)
+    assert pa.purine_conv_route(pa.PURINE_CONV_BWD_WEIGHT, desc, x.shape, (K, C, 1, 1), pa.PURINE_BF16) == pa.PURINE_ROUTE_OTHER
+    ws = _ws(pa.purine_conv_workspace_bytes(pa.PURINE_CONV_BWD_WEIGHT_BIAS, desc, x.shape, (K, C, 1, 1), pa.PURINE_BF16))
+    before = torch.randn((K, C, 1, 1), generator=g).cuda()
+    before[:, ::3] = -0.0
+
+    def call():
+        dw, db, more = torch.empty_like(before), torch.empty(K, device="cuda"), before.clone()
+        pa.purine_conv_bwd_weight_bias(desc, x, dy, dw, db, ws=ws)
+        pa.purine_conv_bwd_weight(desc, x, dy, more, beta=1.0, ws=ws)
+        return dw, db, more
+    _both(pa, call)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("N,C,H,K", [(12, 400, 14, 360), (12, 401, 14, 357), (9, 331, 17, 396), (9, 332, 16, 396), (5, 512, 13, 256)])
 def test_1x1_weight_and_bias(N, C, H, K, dtype):
