@@ -555,7 +555,7 @@ hipError_t dispatch_flat(PixParams& p, int bm, int bn, hipStream_t st) {
 // operand traffic per MFMA; the busiest of the 256 CUs gets ceil(workgroups/256) of them. Pick the
 // tile that minimises that CU's load (padding waste is part of it, through the tile counts).
 static int g_force_bm = 0, g_force_bn = 0;   // tuning hook, see purine_debug_force_tile
-static bool g_small_off = false;
+static int g_small = 0;                        // ... of small launches: 1 always, -1 never (every other choice stays automatic)
 static int g_no_buffer_loads = 0;            // tuning hook: bn == -1 in purine_debug_force_tile
 bool buffer_loads_disabled() { return g_no_buffer_loads != 0; }
 bool patch_split_roles_disabled() { return g_force_bm == -4; }   // tuning hook: force_pix_tile(-4, x)
@@ -563,16 +563,16 @@ bool split_patch_forced() { return g_force_bm == -6; }           // test hooks: 
 bool f32_patch_forced() { return g_force_bm == -8; }             // / forward passes the fp32 patch kernel
 bool patch_any_forced() { return g_force_bm == -9; }             // / bf16 layers the patch kernel for rows of any width
 bool split_1x1_forced() { return g_force_bm == -10; }            // / fp32 1x1 layers the kernel on parts split in registers
-bool direct_forced() { return g_force_bm == -12; }               // / forward, backward-data and fully-connected passes the kernels of small launches
-bool small_kernels_disabled() { return g_small_off; }            // / every call the kernels that large launches run
+bool direct_forced() { return g_small > 0; }                     // / forward, backward-data and fully-connected passes the kernels of small launches
+bool small_kernels_disabled() { return g_small < 0; }            // / every call the kernels that large launches run
 bool staged_wgrad_forced() { return g_force_bm == -11; }         // / weight gradients the kernel that lays operands out in LDS, with that tile
 int staged_wgrad_tile() { return g_force_bm == -11 ? g_force_bn : 0; }
 bool split_packets_forced() { return g_force_bm == -7; }         // / the ones on packed parts wherever they apply
 bool patch_split_roles_forced() { return g_force_bm == -5; }     // test hook: force_pix_tile(-5, x), also for layers of few tiles
 void force_pix_tile(int bm, int bn) {
     g_no_buffer_loads = (bn == -1 && bm != -2) ? 1 : 0;
-    g_small_off = bm == -13;
-    g_force_bm = g_small_off ? 0 : bm; g_force_bn = g_small_off ? 0 : bn;
+    g_small = bm == -12 ? 1 : bm == -13 ? -1 : 0;
+    g_force_bm = g_small ? 0 : bm; g_force_bn = g_small ? 0 : bn;
 }
 
 // Geometry of the implicit GEMM for one pass (everything in PixParams that does not depend on the
@@ -907,7 +907,7 @@ static double general_us(const ConvGeom& g, const PixPlan& pl, int dtype) {
 // by up to a fifth). What the forward pass of a long sum must keep, it keeps (the rule on products in plan_general).
 PixPlan plan_conv_pix(const ConvGeom& g, bool bwd_data, int dtype, bool fused, bool accumulate) {
     PixPlan pl = plan_general(g, bwd_data, dtype, fused, accumulate);
-    if (g_no_buffer_loads != 0 || small_kernels_disabled() || (g_force_bm != 0 && !direct_forced())) return pl;
+    if (g_no_buffer_loads != 0 || small_kernels_disabled() || g_force_bm != 0) return pl;
     const double us = conv_direct_us(g, bwd_data, dtype);
     if (us < 0.0) return pl;
     if (direct_forced()) { pl.direct = true; return pl; }

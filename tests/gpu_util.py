@@ -2,12 +2,24 @@
 C-ABI binding, bring results back as numpy. The only arithmetic here is `pool_bwd_in_order`, the
 fp32 restatement of the pooling gradient's summation order that lets it be compared bit for bit."""
 import numpy as np
+import pytest
 import torch
 
 import paper_1412_6249_amd as pa
 from synth import gen
 
 DEV = "cuda:0"
+
+
+@pytest.fixture(autouse=True, params=[0, -13], ids=["auto", "large"])
+def kernels_of(request):
+    """For the modules that import it: every test as the library dispatches it, and with small launches on the kernels of large ones, which
+    cases of this size are there to cover."""
+    pa.purine_debug_force_tile(request.param, 0)
+    yield
+    pa.purine_debug_force_tile(0, 0)
+
+
 TOL = {"f32": 1e-5, "bf16": 1e-2}     # relative L2 error allowed against the fp64 oracle
 
 

@@ -236,6 +236,10 @@ def test_operator_argument_validation_without_launch():
     assert status(pa.purine_fc_bwd_weight, fx, fy, binding.raw_desc(fake + 0x300000, F32, (6, 20)), None, beta=0.5, stream=s) == -8
     assert status(pa.purine_fc_fwd, binding.raw_desc(fake, BF16, (4, 20)), binding.raw_desc(fake + 0x100000, BF16, (6, 20)),
                   None, binding.raw_desc(fake + 0x200000, BF16, (4, 6)), stream=s) == -5         # bf16: accepted up to the workspace
+    assert status(pa.purine_fc_fwd, binding.raw_desc(fake, BF16, (4, 20)), binding.raw_desc(fake + 0x100000, BF16, (20, 20)),
+                  None, binding.raw_desc(fake, BF16, (4, 20)), stream=s) == -5                   # ... also with y in the place of x
+    assert status(pa.purine_fc_fwd, binding.raw_desc(fake, F32, (4, 20)), binding.raw_desc(fake + 0x100000, F32, (20, 20)),
+                  None, binding.raw_desc(fake, F32, (4, 20)), stream=s) == -4
     assert status(pa.purine_fc_bwd_weight, binding.raw_desc(fake, BF16, (4, 20)), binding.raw_desc(fake + 0x200000, BF16, (4, 6)),
                   binding.raw_desc(fake + 0x300000, BF16, (6, 20)), None, stream=s) == -3        # dw is fp32
     assert pa.purine_fc_workspace_bytes(0, 4, 20, 6) > 0 and pa.purine_fc_workspace_bytes(7, 4, 20, 6) == 0

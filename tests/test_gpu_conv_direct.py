@@ -24,6 +24,8 @@ CASES = [
     (1, 57, 5, 4, 31, 5, 5, 1, 2),
     (4, 17, 6, 7, 18, 1, 1, 2, 0),
     (1, 100, 4, 4, 70, 3, 3, 1, 1),
+    (1, 512, 7, 7, 24, 3, 3, 1, 1),        # 4608 products forward, and
+    (1, 24, 7, 7, 910, 3, 3, 1, 1),        # 8190 backward: tables of more than 64 KB
 ]
 
 
@@ -60,6 +62,7 @@ def test_conv_direct(case, dtype):
     tw, tb = w.cuda(), b.cuda()
     pa.purine_debug_force_tile(-12, 0)
     try:
+        assert [pa.purine_conv_route(q, desc, x.shape, w.shape, code) for q in (0, 1)] == [pa.PURINE_ROUTE_SMALL_LAUNCH] * 2
         for view in (lambda t: t.cuda(), _slice_of):
             tx, tdy = view(x.cuda()), view(dy.cuda())
             out, odx = view(torch.full(y.shape, float("nan"), dtype=td, device="cuda")), view(torch.full(x.shape, float("nan"), dtype=td, device="cuda"))
@@ -75,6 +78,38 @@ def test_conv_direct(case, dtype):
             _close(odx, dx * (x.double() > 0), K * R * S, dtype, "through the mask")
     finally:
         pa.purine_debug_force_tile(0, 0)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(2, 3, 8, 8, 8, 3, 3, 1, 1), (2, 5, 10, 10, 40, 5, 5, 2, 2), (2, 38, 8, 9, 42, 3, 3, 1, 1)], ids=["2", "8", "16"])
+def test_far_images(case, dtype):
+    """Images 2^31 bytes apart, for each number of wavefronts: the bits of dense tensors."""
+    import paper_1412_6249_amd as pa
+    N, C, H, W, K, R, S, s, p = case
+    g = torch.Generator().manual_seed(sum(case))
+    td, code, ns = (torch.float32, pa.PURINE_F32, 1 << 29) if dtype == "f32" else (torch.bfloat16, pa.PURINE_BF16, 1 << 30)
+    desc = pa.conv_desc(s, p)
+    x, w = (torch.randn(sh, generator=g).to(td).cuda() for sh in ((N, C, H, W), (K, C, R, S)))
+    dy = torch.randn(pa.purine_conv_out_shape(desc, x.shape, w.shape), generator=g).to(td).cuda()
+    ws = lambda which: torch.empty(max(256, pa.purine_conv_workspace_bytes(which, desc, x.shape, w.shape, code)), dtype=torch.uint8, device="cuda")
+
+    def far(t):
+        v = torch.as_strided(torch.empty((N - 1) * ns + t[0].numel() + 64, dtype=td, device="cuda"), t.shape, (ns,) + t.stride()[1:], 0)
+        v.copy_(t)
+        return v
+
+    pa.purine_debug_force_tile(-12, 0)
+    try:
+        y, dx = torch.empty_like(dy), torch.empty_like(x)
+        pa.purine_conv_fwd(desc, x, w, y, ws=ws(pa.PURINE_CONV_FWD))
+        pa.purine_conv_bwd_data(desc, dy, w, dx, ws=ws(pa.PURINE_CONV_BWD_DATA))
+        y2, dx2 = far(torch.zeros_like(dy)), far(torch.zeros_like(x))
+        pa.purine_conv_fwd(desc, far(x), w, y2, ws=ws(pa.PURINE_CONV_FWD))
+        pa.purine_conv_bwd_data(desc, far(dy), w, dx2, ws=ws(pa.PURINE_CONV_BWD_DATA))
+    finally:
+        pa.purine_debug_force_tile(0, 0)
+    assert torch.equal(y2, y) and torch.equal(dx2, dx)
+    _close(y, F.conv2d(x.cpu().double(), w.cpu().double(), stride=s, padding=p), C * R * S, dtype, "forward")
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])

@@ -6,12 +6,13 @@ import numpy as np
 import pytest
 
 import oracle
+from gpu_util import kernels_of  # noqa: F401 (every test twice: small launches on their own kernels, and on those of large ones)
 
 pytestmark = pytest.mark.gpu
 
 # N, C, K: ragged against the 128-row / 128-column tiles and the split chunks; one AlexNet-like
-# shape; batches of a multiple of 8 take the bf16 weight gradient's own kernel: a half step at the end
-# (24), several staged chunks with a ragged last one (200), ragged tiles in both directions
+# shape; batches of a multiple of 8 take the bf16 weight gradient's own kernel (where small launches run the kernels of large ones):
+# a half step at the end (24), several staged chunks with a ragged last one (200), ragged tiles in both directions
 FC_CASES = [(1, 1, 1), (3, 5, 4), (7, 300, 33), (128, 1000, 130), (32, 2304, 512), (130, 64, 1000),
             (8, 1, 1), (24, 200, 136), (200, 520, 264)]
 

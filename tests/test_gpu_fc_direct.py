@@ -1,5 +1,5 @@
 """Fully-connected passes in one launch: row and column tiles that are not full, reductions of one step, of a step that is not whole and
-of the lengths at which the number of wavefronts changes, rows of odd length (bf16 rows that begin in the middle of a
+of the lengths at which the number of wavefronts changes (4 and 32 steps of 16, in each pass and type), rows of odd length (bf16 rows that begin in the middle of a
 dword), no bias, accumulation, infinities. Against float64 sums on the CPU.
 
 Bound: fp32 three quarters of an fp32 chain's 2.7e-8 * sqrt(products) and the last rounding; bf16 results are rounded once (2^-9), its fp32
@@ -11,7 +11,16 @@ pytestmark = pytest.mark.gpu
 
 # images, inputs, outputs
 CASES = [(1, 64, 10), (3, 65, 33), (16, 16, 16), (17, 70, 31), (5, 512, 40), (9, 527, 31), (33, 300, 129), (65, 129, 64), (64, 64, 63), (80, 513, 97),
-         (2, 1000, 100)]
+         (2, 1000, 100), (600, 40, 33), (5, 40, 600)]
+
+
+@pytest.fixture
+def small():
+    """... whatever the dispatch would do with a size."""
+    import paper_1412_6249_amd as pa
+    pa.purine_debug_force_tile(-12, 0)
+    yield
+    pa.purine_debug_force_tile(0, 0)
 
 
 def _data(pa, case, dtype):
@@ -32,10 +41,11 @@ def _close(got, ref, products, rounded, what):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("case", CASES, ids=["x".join(map(str, c)) for c in CASES])
-def test_fc_direct(case, dtype):
+def test_fc_direct(case, dtype, small):
     import paper_1412_6249_amd as pa
     N, C, K = case
     t, d, ws, td = _data(pa, case, dtype)
+    assert [pa.purine_fc_route(p, N, C, K, pa.PURINE_F32 if dtype == "f32" else pa.PURINE_BF16) for p in range(3)] == [pa.PURINE_ROUTE_SMALL_LAUNCH] * 3
     r = {k: v.double() for k, v in t.items()}
     nan = lambda *s, dt=td: torch.full(s, float("nan"), dtype=dt, device="cuda")
     for b in (d["b"], None):
@@ -90,7 +100,7 @@ def test_bias_gradient_of_many_images(N, K, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_infinities(dtype):
+def test_infinities(dtype, small):
     """At the ends of rows, where the next row's elements are loaded along with them."""
     import paper_1412_6249_amd as pa
     N, C, K = 9, 67, 35

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 import oracle
+from gpu_util import kernels_of  # noqa: F401 (every test twice: small launches on their own kernels, and on those of large ones)
 
 pytestmark = pytest.mark.gpu
 

@@ -54,9 +54,16 @@ def _run(pa, desc, x, dy, shape, code, beta=0.0, prev=None):
     return dw, db
 
 
-@pytest.mark.parametrize("tile", TILES)
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("case", CASES, ids=["x".join(map(str, c)) for c in CASES])
+def _runs(case, dtype, tile):
+    """bf16 planes as they lie in memory have no such kernel, and 130 channels of a 256-column tile no room in LDS."""
+    flat = case[5:] == (1, 1, 1, 0)
+    return not (flat and (dtype == "bf16" or (case[1] > 128 and tile in (64256, 32256))))
+
+
+ALL = [(c, d, t) for c in CASES for d in ("f32", "bf16") for t in TILES if _runs(c, d, t)]
+
+
+@pytest.mark.parametrize("case,dtype,tile", ALL, ids=["x".join(map(str, c)) + "-%s-%d" % (d, t) for c, d, t in ALL])
 def test_wgrad_staged(case, dtype, tile):
     import paper_1412_6249_amd as pa
     N, C, H, W, K, R, S, s, p = case
@@ -78,6 +85,7 @@ def test_wgrad_staged(case, dtype, tile):
     desc = pa.conv_desc(s, p)
     pa.purine_debug_force_tile(-11, tile)
     try:
+        assert pa.purine_conv_route(pa.PURINE_CONV_BWD_WEIGHT, desc, x0.shape, (K, C, R, S), code) == pa.PURINE_ROUTE_INSIDE_LDS
         for x, dy in ((x0, dy0), (slice_of(x0), slice_of(dy0))):
             rw, rb = _ref(x.cpu(), dy.cpu(), R, S, s, p)
             dw, db = _run(pa, desc, x, dy, (K, C, R, S), code)
@@ -90,8 +98,8 @@ def test_wgrad_staged(case, dtype, tile):
         pa.purine_debug_force_tile(0, 0)
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("case", [(3, 5, 11, 13, 33, 3, 3, 1, 1), (9, 3, 21, 22, 20, 3, 3, 2, 0), (3, 50, 13, 11, 33, 1, 1, 1, 0)], ids=["bands", "stride", "1x1"])
+@pytest.mark.parametrize("case,dtype", [(c, d) for c in [(3, 5, 11, 13, 33, 3, 3, 1, 1), (9, 3, 21, 22, 20, 3, 3, 2, 0), (3, 50, 13, 11, 33, 1, 1, 1, 0)]
+                                        for d in ("f32", "bf16") if _runs(c, d, 0)])
 def test_infinities(case, dtype):
     """An infinity in x reaches exactly the taps that meet it (also next to rows, bands and images that do not exist), one in dy its row."""
     import paper_1412_6249_amd as pa
@@ -115,6 +123,7 @@ def test_infinities(case, dtype):
             ref[:, :, r, q] = (dy.double()[:, :, None] * t[:, None]).sum((0, 3, 4))
     pa.purine_debug_force_tile(-11, 0)
     try:
+        assert pa.purine_conv_route(pa.PURINE_CONV_BWD_WEIGHT, pa.conv_desc(s, p), x.shape, (K, C, R, S), code) == pa.PURINE_ROUTE_INSIDE_LDS
         dw, db = _run(pa, pa.conv_desc(s, p), x.cuda(), dy.cuda(), (K, C, R, S), code)
     finally:
         pa.purine_debug_force_tile(0, 0)
