@@ -936,12 +936,14 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
     }
     // The kernel that lays its operands out inside LDS, where it is expected to be faster than either: first layers, few channels,
     // 1x1, small launches. The estimates of the general kernels do not know that their gathers bind them: fp32 ones with columns of several
-    // taps take 1.2 times as long as expected (16 -> 32 5x5 at 28x28, N = 128: 62 us there, 41 here), bf16 tiles of fewer than 128 rows up to
-    // twice (gathered columns per pixel are the same 128); that of the packed parts is a quarter too high. Of 160 fp32 layers drawn from the measured
-    // ranges 98 go there and are 1.30 times as fast (geometric mean; three are slower, by 6 % at most), of 60 bf16 layers 13, 1.42 times.
+    // taps take 1.2 times as long as expected (16 -> 32 5x5 at 28x28, N = 128: 62 us there, 42 here), bf16 tiles of fewer than 128 rows up to
+    // twice (gathered columns per pixel are the same 128); that of the packed parts is a quarter too high. Strided 1x1 layers of few channels gather
+    // one column per channel and take the time expected (with 1.2 for them, 21 of 123 were slower here, by up to half: 43 -> 18 at 7x7 / 2, N = 5 9.5
+    // and 14.5 us). Of 500 fp32 layers drawn from the measured ranges 349 go there and are 1.29 times as fast (geometric mean); one in twenty is
+    // slower, by 4 - 36 %, calls of 8 - 25 us; of 60 bf16 layers 13, 1.42 times.
     if (small_kernels_disabled()) return pl;
     double old = pl.pk.use ? pl.pk.us : us;
-    if (dtype == PURINE_F32) old *= pl.pk.use ? 0.75 : !pl.tap ? 1.2 : g.R * g.S > 1 ? 1.0 : 0.92;
+    if (dtype == PURINE_F32) old *= pl.pk.use ? 0.75 : g.R * g.S > 1 ? (pl.tap ? 1.0 : 1.2) : pl.tap ? 0.92 : 1.0;
     else if (!pl.tap && pl.bm < 128 && us > 10.0) old += 0.5 * (us - 10.0) * (128.0 / pl.bm - 1.0);
     pl.sg = plan_wgrad_staged(g, dtype, limit, staged_wgrad_forced() ? 1e30 : old - 2.0);
     if (pl.sg.use) {

@@ -617,8 +617,9 @@ WgradStagedPlan plan_wgrad_staged(const ConvGeom& g, int dtype, size_t limit, do
             if (!PR) continue;
             const long long chunks = (long long)((Qc + QS - 1) / QS) * ((PB + PR - 1) / PR) * groups;
             if (chunks > (1 << 28)) continue;
-            // Time of a chunk, fitted to 50 layers of all kinds (0.7 - 1.3 of the measured ones): its packing, its MFMA steps, and the lines
-            // that its loads ask for. Planes as they lie in memory: whole lines, the packing alone.
+            // Time of a chunk: its packing, its MFMA steps, and the lines that its loads ask for. Planes as they lie in memory: whole lines,
+            // the packing alone. Fitted to 50 layers; of 950 with each fp32 tile nine in ten take 0.76 - 1.37 times the expected time (up
+            // to 1.9 below 20 us, where a chunk's chain of loads counts), and the tile chosen is 5 % from the best.
             const double lines = 8.0 * ((double)t.bm * PR * ((QS * es + 63) / 64) + (double)Ct * XR * ((PW * es + 63) / 64 + 0.5));
             const double chunk_us = flat ? 0.006 * units : f32 ? 0.0035 * units + 0.069 * PR * QS + 0.00084 * lines : 1.8 + 0.0155 * PR * QS + 0.00048 * lines;
             if (5.0 + (double)tiles * (double)chunks * chunk_us / 256.0 * 0.999999 >= (best.use ? best.us : budget_us)) continue;

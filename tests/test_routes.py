@@ -56,3 +56,10 @@ def test_fully_connected_weight_gradients_of_many_images(dtype, n, c, k, want):
     (7405, 2645, 108, 0), (8975, 3409, 91, 0), (5368, 2700, 203, 0), (6902, 1738, 76, 0), (1027, 4042, 207, 0)])
 def test_bf16_data_gradients_whose_rows_are_no_whole_packets(n, c, k, want):
     assert pa.purine_fc_route(BWD_DATA, n, c, k, BF16) == want
+
+
+@pytest.mark.parametrize("n, c, hw, k, want", [
+    (5, 43, 7, 18, 0), (215, 17, 19, 274, 0), (2, 55, 9, 21, 0),      # the estimate of the general kernel holds for one tap
+    (36, 49, 13, 17, 2), (16, 33, 60, 60, 2)])
+def test_strided_1x1_weight_gradients_of_few_channels(n, c, hw, k, want):
+    assert pa.purine_conv_route(BWD_WEIGHT, pa.conv_desc(2, 0), (n, c, hw, hw), (k, c, 1, 1), F32) == want
