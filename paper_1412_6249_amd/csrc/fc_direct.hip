@@ -205,9 +205,12 @@ bool fc_direct_faster(int pass, int64_t N, int64_t C, int64_t K, int dtype, bool
     const double steps = (double)((len + 15) / 16), tiles = (double)((rows + 31) / 32) * (double)((cols + 31) / 32), work = tiles * steps * 1e-3;
     const double chain = steps > 32 ? (steps + 15) / 16 : steps > 4 ? (steps + 7) / 8 : (steps + 1) / 2;      // steps of a wavefront
     const double bytes = (grad ? 4.0 : (double)es) * K * C, flops = 2e-6 * (double)N * C * K;
+    // (bf16 rows that are whole lines apart: the 32 rows of a load ask few channels. 64 x 1664 x 64 16 us here, 9.5 otherwise; of 47 such layers of up to
+    // 256 images and more than 700 inputs 12 went here and were slower, by up to 1.7.)
+    const double lines = C % 64 == 0 && steps > 32 ? 1.3 : 1.0;
     if (pass == PURINE_CONV_FWD)
         return f32 ? 1.1 * (3.5 + 1.17 * chain + 1.4e-3 * tiles + 0.44 * work) < 9.0 + bytes / 4.5e6 + flops / 150.0
-                   : 1.15 * (2.5 + 0.88 * chain + 0.35 * work) < 9.4 + 0.02 * (double)(N < 80 ? N : 80) + bytes / 4.5e6 + flops / 400.0;
+                   : 1.15 * (2.5 + 0.88 * lines * chain + 0.35 * work) < 9.4 + 0.02 * (double)(N < 80 ? N : 80) + bytes / 4.5e6 + flops / 400.0;
     if (!grad) {
         if (f32) return K > 16 && 1.1 * (3.5 + 0.86 * chain + 2.25e-3 * tiles + 0.42 * work) < 9.5 + bytes / 4.5e6 + flops / 120.0;
         if (C % 8 == 0) return 1.1 * (3.4 + 0.55 * chain + 0.73e-3 * tiles + 0.31 * work) < 6.3 + bytes / 4.5e6 + flops / 400.0;
