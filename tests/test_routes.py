@@ -65,6 +65,6 @@ def test_strided_1x1_weight_gradients_of_few_channels(n, c, hw, k, want):
     assert pa.purine_conv_route(BWD_WEIGHT, pa.conv_desc(2, 0), (n, c, hw, hw), (k, c, 1, 1), F32) == want
 
 
-@pytest.mark.parametrize("n, c, k, want", [(64, 1664, 64, 0), (64, 1344, 144, 0), (128, 1664, 96, 0), (20, 5327, 1781, 1), (4, 957, 93, 1)])
+@pytest.mark.parametrize("n, c, k, want", [(64, 1664, 64, 0), (64, 1344, 144, 0), (128, 1664, 96, 0), (20, 1000, 100, 1), (4, 957, 93, 1)])
 def test_bf16_forward_rows_that_are_whole_lines_apart(n, c, k, want):
     assert pa.purine_fc_route(FWD, n, c, k, BF16) == want
