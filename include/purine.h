@@ -278,13 +278,15 @@ int purine_grouped_conv_bwd_weight(const purine_conv_desc* desc, int groups, con
 /* Fully-connected layer on dense 2-axis matrices: x [N,C], w [K,C], b [K], y [N,K], all F32 or all
  * BF16; dw and db are F32.
  *   fwd:        y = x w^T (+ b)          dx = dy w          dw = beta*dw + dy^T x,  db = beta*db + column sums of dy
+ * Small matrices take one launch, in either type: 32 x 32 results per workgroup, its wavefronts share the reduction and add
+ * their sums in a fixed order, the bias and its gradient ride along. Otherwise:
  * F32 (matrices below 2 GiB): a streaming matrix product on the bf16 matrix cores, three exact bf16 parts per
  * operand and fp32 sums (as for convolutions, see purine_conv_fwd), the reduction split over workgroups where tiles alone would leave most of the chip idle
  * (partial outputs in ws, added in a fixed order): every forward pass, backward-data over more than 16 outputs, and the weight
  * gradient of more than 32 images at most sizes, which may lay its operands out as such parts in ws first. Every other pass is one of the convolution
  * GEMM kernels on reinterpreted descriptors (a matrix [rows, features] is one image of `rows` channels whose pixel
  * plane is the feature axis, or a 1x1 filter bank): forward runs the weight-gradient kernel (split reduction over
- * C, fixed-order second pass; BF16: its fp32 result gets the bias added and is rounded once), backward-data the
+ * C, fixed-order second pass, which in BF16 adds the bias and rounds once; y may lie over x or w there), backward-data the
  * forward kernel (with a split reduction over K when its tiles alone would leave most of the chip idle),
  * backward-weight the backward-data kernel (F32) or, for BF16 (the result is fp32), a
  * contraction over the batch on transposed copies of x and dy kept in ws: a kernel that owns whole

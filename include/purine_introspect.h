@@ -9,7 +9,7 @@ extern "C" {
 #endif
 
 /* Matrix-core products that a pass (PURINE_CONV_*) executes per multiplication of its layer: 1 where it multiplies in
- * the layer's own type, 6 where an F32 pass multiplies bf16 parts. 0 for an illegal shape. The launch's own plan for
+ * the layer's own type, 6 where an F32 pass multiplies bf16 parts (whichever kernel it runs on). 0 for an illegal shape. The launch's own plan for
  * dense tensors. */
 int purine_conv_matrix_products(int pass, const purine_conv_desc* desc, const int64_t x_dim[4],
                                 const int64_t w_dim[4], int32_t dtype);

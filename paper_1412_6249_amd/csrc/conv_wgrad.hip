@@ -936,7 +936,7 @@ WgradPlan plan_wgrad(const ConvGeom& g, int dtype) {
     }
     // The kernel that lays its operands out inside LDS, where it is expected to be faster than either: first layers, few channels,
     // 1x1, small launches. The estimates of the general kernels do not know that their gathers bind them: fp32 ones with columns of several
-    // taps take 1.2 times as long as expected (16 -> 32 5x5 at 28x28, N = 128: 62 us there, 42 here), bf16 tiles of fewer than 128 rows up to
+    // taps take 1.2 times as long as expected (16 -> 32 5x5 at 28x28, N = 128: 59 us there, 42 here), bf16 tiles of fewer than 128 rows up to
     // twice (gathered columns per pixel are the same 128); that of the packed parts is a quarter too high. Strided 1x1 layers of few channels gather
     // one column per channel and take the time expected (with 1.2 for them, 21 of 123 were slower here, by up to half: 43 -> 18 at 7x7 / 2, N = 5 9.5
     // and 14.5 us). Of 500 fp32 layers drawn from the measured ranges 349 go there and are 1.29 times as fast (geometric mean); one in twenty is

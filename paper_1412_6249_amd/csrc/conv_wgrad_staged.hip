@@ -12,18 +12,17 @@
 // bands to a group. 1x1 layers as they lie in memory (FLAT) need no such exchange: there a packet is eight consecutive elements
 // of a plane, and a chunk 64 of them.
 //
-// Bound: none of the roofs. conv1 of the five-layer stack (3 -> 96 channels 11x11 / 4 at 227x227, N = 128) has its matrix pipes 32 % busy, the
-// address units 65 %, VALU and LDS a third each. What sets the pace is a chunk's chain of loads, packing and multiplication
+// Bound: none of the roofs. conv1 of the five-layer stack (3 -> 96 channels 11x11 / 4 at 227x227, N = 128) has its matrix pipes 41 % busy (when it
+// took a quarter longer 32 %, the address units 65 %, VALU and LDS a third each). What sets the pace is a chunk's chain of loads, packing and multiplication
 // (2.5 - 4 us), so it is taken apart: four wavefronts request and pack dy, four x, one chunk ahead and with the loads of the next in
 // flight, into two LDS buffers in turn; the others only multiply. (The same wavefronts doing both in turn, two workgroups per CU: 290 us
 // for that layer; loads and packing on wavefronts of their own, a lane loading one position of eight images: 278; four positions, 16 bytes per
 // load, neighbouring lanes on neighbouring columns: 247. Loads with lanes along channels ask for each line once per lane: 8800 cycles a
 // chunk to issue them instead of 3000.)
 //
-// Whole operator, general kernel before / here, us: that layer 311 / 272 (with sums copied after every chunk and a quarter of them through
-// memory; 254 then and 214 now over three sets of tensors in turn); 3 -> 170 7x7 / 2 at 174x175, N = 88 671 / 349; 3 -> 344 7x7 / 2 at
-// 199x199, N = 10 265 / 123; 272 -> 126 1x1 at 26x26, N = 1 15 / 10; 16 -> 32 5x5 at 28x28, N = 128 60 / 39; bf16 3 -> 139 7x7 / 2 at
-// 184x186, N = 106 638 / 158; 3 -> 220 7x7 / 2 at 65x66, N = 140 157 / 61.
+// Whole operator with the bias gradient, general kernel / here, us (three sets of tensors in turn): that layer 294 / 218; 3 -> 170 7x7 / 2 at
+// 174x175, N = 88 672 / 321; 3 -> 344 7x7 / 2 at 199x199, N = 10 266 / 112; 272 -> 126 1x1 at 26x26, N = 1 15.6 / 10.3; 16 -> 32 5x5 at
+// 28x28, N = 128 59 / 42; bf16 3 -> 139 7x7 / 2 at 184x186, N = 106 638 / 179; 3 -> 220 7x7 / 2 at 65x66, N = 140 152 / 60.
 #include <type_traits>
 #include "packets.h"
 #include "pix_common.h"
@@ -423,7 +422,7 @@ __global__ __launch_bounds__(WM * WN * 64 + 2 * LOADERS, 2) void wgrad_staged_ke
             }
         }
         // (The sums stay where they are from chunk to chunk: used element by element after the loop, they were copied element by element at the
-        // end of every chunk, and 27 of 96 went through memory: 182 MB written beside conv1's 12 MB of partial sums.)
+        // end of every chunk, and 27 of 96 went through memory: 182 MB written beside conv1's 12 MB of partial sums, 254 us instead of 218.)
 #pragma unroll
         for (int a = 0; a < TM; ++a)
 #pragma unroll
